@@ -8,52 +8,20 @@
 //       chunk. The item that owns the first free slot takes the new token from k_new/v_new
 //       and appends it to the cache on the way. With grouped query heads the rows loaded by
 //       an item serve every head of the unit (one partial per head).
+//       This is the form for long units and grouped heads; decode_unit.hip is the other one.
 //   fg_decode_finish_kernel   one workgroup per unit: merges the chunk partials into the
 //       attention output; adds this step's attention to the cumulative scores (policies with
 //       `frequent`, or every policy when the step is probed); re-derives the kept set from the
 //       policy's components  special | punct | TopK(score, k_f(L)) | window  and releases the
 //       evicted slots in place (holes below the new length are filled with the kept rows from
 //       above it); optionally reports the step's attention mass on every policy's tokens.
-#include <type_traits>
 
 #include "fg_common.h"
 #include "fg_internal.h"
-#include "fg_select.h"
+#include "fg_rows.h"
+#include "fg_update.h"
 
 namespace {
-
-constexpr int FG_MOVE_LDS = 64;  // released slots per step whose move lists stay in shared memory
-
-template <int ESIZE>
-__device__ __forceinline__ void fg_unpack(const u32x4& v, float* f);
-template <>
-__device__ __forceinline__ void fg_unpack<2>(const u32x4& v, float* f) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[2 * i] = fg_bf16_lo(v[i]);
-    f[2 * i + 1] = fg_bf16_hi(v[i]);
-  }
-}
-template <>
-__device__ __forceinline__ void fg_unpack<4>(const u32x4& v, float* f) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f[i] = __uint_as_float(v[i]);
-}
-
-// Dot product of the 8 bf16 pairs of two 16-byte chunks with float accumulation: four
-// two-element dot instructions instead of eight unpacks and eight multiply-adds. Serves the
-// output path only (the cumulative scores use the float64 logits).
-__device__ __forceinline__ float fg_dot_bf16x8(const u32x4& a, const u32x4& b) {
-  float acc = 0.f;
-  // (pairs taken from the 8-element vectors by shuffles: handed bit-cast dwords of the 128-bit
-  // vectors, the compiler of ROCm 7.2 selects element 0 for all four instructions)
-  const bf16x8 av = __builtin_bit_cast(bf16x8, a), bv = __builtin_bit_cast(bf16x8, b);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(av, av, 0, 1), __builtin_shufflevector(bv, bv, 0, 1), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(av, av, 2, 3), __builtin_shufflevector(bv, bv, 2, 3), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(av, av, 4, 5), __builtin_shufflevector(bv, bv, 4, 5), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(av, av, 6, 7), __builtin_shufflevector(bv, bv, 6, 7), acc, false);
-  return acc;
-}
 
 // GRP: several query heads per unit (a.G > 1); without it G is the constant 1 and the code is
 // the plain multi-head path.
@@ -306,23 +274,16 @@ __global__ __launch_bounds__(256) void fg_decode_partial_kernel(fg_decode_args a
   }
 }
 
-template <int ESIZE>
-__device__ __forceinline__ void fg_store_out(void* out, size_t idx, float v);
-template <>
-__device__ __forceinline__ void fg_store_out<2>(void* out, size_t idx, float v) {
-  static_cast<uint16_t*>(out)[idx] = (uint16_t)fg_f32_to_bf16_bits(v);
-}
-template <>
-__device__ __forceinline__ void fg_store_out<4>(void* out, size_t idx, float v) {
-  static_cast<float*>(out)[idx] = v;
-}
+// Latency-bound: one workgroup's chain of loads, block reductions and moves per unit. 512 threads
+// shorten the per-thread part and hold 6144 tokens in registers without a spill (256 threads,
+// before: 640 units of 8192 tokens 47 -> 22 us with the shorter chain of fg_update.h, 2560 of them
+// 90 -> 60, 256 grouped units of 2048 30 -> 22).
+constexpr int kUpdateThreads = 512;
 
 template <int ESIZE, int D, bool GRP>
-__global__ __launch_bounds__(256, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_decode_args a) {
-  constexpr int RB = D * ESIZE, CPR = RB / 16;
-  __shared__ fg_select_smem sm;
-  __shared__ int ired[20];
-  __shared__ double dred[8];
+__global__ __launch_bounds__(kUpdateThreads, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_decode_args a) {
+  constexpr int NT = kUpdateThreads;
+  __shared__ fg_update_smem sh;
   __shared__ float s_M[16];  // per query head: merged maximum of the scaled logits
   const int u = blockIdx.x, tid = threadIdx.x;
   const int G = GRP ? a.G : 1;
@@ -354,13 +315,13 @@ __global__ __launch_bounds__(256, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_d
   // the new length goes to len[] and into every work-item record of the unit
   auto set_len = [&](int v) {
     if (tid == 0) a.len[u] = v;
-    for (int i = tid; i < ((cap + CH - 1) >> ch_shift); i += 256) a.item_unit[(size_t)(c_off + i) * 8 + 3] = v;
+    for (int i = tid; i < ((cap + CH - 1) >> ch_shift); i += NT) a.item_unit[(size_t)(c_off + i) * 8 + 3] = v;
   };
   const float* part = a.part + (size_t)c_off * G * (D + 2);
 
-  // ---- merge the chunk partials of every query head:
-  //      o = sum_c o_c 2^(M_c - M) / sum_c l_c 2^(M_c - M)
-  float M = FG_NEG_BIG;   // of head 0 (the only one without grouping)
+  // merge of the chunk partials of every query head: o = sum_c o_c 2^(M_c - M) / sum_c l_c 2^(M_c - M)
+  auto merge = [&]() -> float {
+  float M = FG_NEG_BIG;
   for (int h = 0; h < G; ++h) {
     const float* ph = part + (size_t)h * (D + 2);
     const size_t cs = (size_t)G * (D + 2);  // stride between chunks
@@ -385,12 +346,9 @@ __global__ __launch_bounds__(256, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_d
     if (h == 0) M = Mh;
     if (GRP && tid == 0) s_M[h] = Mh;
   }
-  // Score path in float64 (Sec. 3.4, cumulative attention score): this step's attention on held
-  // slot j is a_j = 2^(x_j - M) / Z with the float64 logits x_j the attention kernel kept and
-  // Z = sum_j 2^(x_j - M) summed here in float64 (M is only a shift: the merged float maximum).
-  // Grouped heads: a_j summed over the query heads replaces head 0's logit in place, so that
-  // the rest of the kernel reads one ready value per slot (each thread only touches its own slots).
-  double inv_d = 0.0;   // 1 / Z of head 0 (the only one without grouping), set below where needed
+  // Grouped heads: this step's attention a_j (float64, as in fg_update.h) summed over the query
+  // heads replaces head 0's logit in place, so that the rest of the kernel reads one ready value
+  // per slot (each thread only touches its own slots).
   if (GRP) {
     __shared__ double s_invd[16];
     __syncthreads();
@@ -398,12 +356,12 @@ __global__ __launch_bounds__(256, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_d
       for (int h = 0; h < G; ++h) {
         const double Mh = (double)s_M[h];
         double z = 0.0;
-        for (int j = tid; j < L; j += 256) z += exp2(a.clogit[(off + j) * G + h] - Mh);
-        z = fg_block_sum_f64(z, dred);
+        for (int j = tid; j < L; j += NT) z += exp2(a.clogit[(off + j) * G + h] - Mh);
+        z = fg_block_sum_f64(z, sh.dred);
         if (tid == 0) s_invd[h] = 1.0 / z;
       }
       __syncthreads();
-      for (int j = tid; j < L; j += 256) {
+      for (int j = tid; j < L; j += NT) {
         double* lgj = a.clogit + (off + j) * G;
         double sum = 0.0;
         for (int h = 0; h < G; ++h) sum += exp2(lgj[h] - (double)s_M[h]) * s_invd[h];
@@ -411,265 +369,14 @@ __global__ __launch_bounds__(256, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_d
       }
     }
   }
-
+  return M;   // of head 0 (the only one without grouping)
+  };
   if (policy >= 4 && !probing) {
+    (void)merge();
     set_len(L);
     return;
   }
-  const int p_new = a.n + a.step;
-  double* score = a.cscore + off;
-  const int32_t* pos = a.cpos + off;
-  const uint8_t* cls = a.ccls + off;
-  const int cmask = ((comp & FG_COMP_SPECIAL) ? FG_CLASS_SPECIAL : 0) | ((comp & FG_COMP_PUNCT) ? FG_CLASS_PUNCT : 0);
-  const int wlo = (comp & FG_COMP_LOCAL) ? p_new - a.w : 0x7fffffff;  // positions above wlo are inside the window
-
-  // Fast path (L <= 256 * NC): each thread keeps its slots' updated scores and a "protected"
-  // bit (special / punctuation / window) in registers, so every later phase is register-only.
-  // The code below is straight-line per slot, i.e. executed once per workgroup and bound by
-  // instruction fetch: it is instantiated for a few sizes and the smallest one that fits is taken.
-  auto update = [&](auto nc_tag) __attribute__((always_inline)) {
-  constexpr int NC = decltype(nc_tag)::value;
-  uint64_t kc[NC];
-  uint32_t prot = 0;
-  const bool small = L <= 256 * NC;
-  fg_topk tk;
-  tk.mode = 0; tk.thr = 0; tk.pthr = 0;
-  if (small) {
-    // all loads first (they are independent), then the arithmetic, then the stores
-    double lg[NC];
-    double sc[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
-      kc[i] = 0;
-      lg[i] = 0.0;
-      sc[i] = 0.0;
-      if (j < L) {
-        const int cb = cls[j];
-        const int pj = pos[j];
-        if ((cb & cmask) != 0 || pj > wlo) prot |= 1u << i;
-        if (scored) {
-          lg[i] = a.clogit[(off + j) * G];
-          sc[i] = score[j];
-        }
-      }
-    }
-    if (scored) {
-      if (!GRP) {
-        // 2^(x_j - M) in place of the logits, their float64 sum over the workgroup
-        double z = 0.0;
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-          const int j = tid + 256 * i;
-          if (j < L) {
-            lg[i] = exp2(lg[i] - (double)M);
-            z += lg[i];
-          }
-        }
-        inv_d = 1.0 / fg_block_sum_f64(z, dred);
-      }
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        const int j = tid + 256 * i;
-        if (j < L) {
-          // cumulative attention score += this step's attention (Sec. 3.4, frequency policy)
-          const double v = sc[i] + (GRP ? lg[i] : lg[i] * inv_d);
-          score[j] = v;
-          kc[i] = (uint64_t)__double_as_longlong(v);
-        }
-      }
-    }
-    if (scored) {
-      const int k_f = fg_budget(a.r_f, p_new + 1);
-      __syncthreads();  // score[] is re-read by other threads only if the boundary value is tied
-      // without the probe only the unprotected tokens' membership matters: try the lowest ones
-      bool done = false;
-      if (!probing && k_f > 0 && k_f < L && L <= 0xffff) done = fg_evict_cut_regs<NC>(kc, prot, L, k_f, dred, ired, &tk);
-      if (!done)
-        tk = fg_select_topk_regs<NC>(kc, [&](int j) { return score[j]; },
-                                     [&](int j) { return (uint32_t)pos[j]; }, L, k_f, &sm);
-    }
-  } else if (scored) {
-    if (!GRP) {
-      double z = 0.0;
-      for (int j = tid; j < L; j += 256) z += exp2(a.clogit[off + j] - (double)M);
-      inv_d = 1.0 / fg_block_sum_f64(z, dred);
-    }
-    for (int j = tid; j < L; j += 256) {
-      const double aj = GRP ? a.clogit[(off + j) * G] : exp2(a.clogit[off + j] - (double)M) * inv_d;
-      score[j] += aj;
-    }
-    __syncthreads();
-    const int k_f = fg_budget(a.r_f, p_new + 1);
-    tk = fg_select_topk([&](int j) { return score[j]; }, [&](int j) { return (uint32_t)pos[j]; }, L, k_f, &sm);
-  }
-  if (probing) {
-    // Stability probe (Sec. 4): mass of this step's attention row on every family member's
-    // tokens among the held ones (frequent = the top-k just selected, local = last w positions)
-    double r[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int j = tid; j < L; j += 256) {
-      // the mean of the G heads' rows
-      const double aj = GRP ? a.clogit[(off + j) * G] / (double)G
-                            : exp2(a.clogit[off + j] - (double)M) * inv_d;
-      const int c = cls[j];
-      const bool top = fg_in_topk(tk, score[j], (uint32_t)pos[j]), recent = pos[j] > p_new - a.w;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int m = a.family[p];
-        const bool in = ((m & FG_COMP_SPECIAL) && (c & FG_CLASS_SPECIAL)) || ((m & FG_COMP_PUNCT) && (c & FG_CLASS_PUNCT)) ||
-                        ((m & FG_COMP_FREQUENT) && top) || ((m & FG_COMP_LOCAL) && recent);
-        r[p] += in ? aj : 0.0;
-      }
-      r[4] += aj;
-    }
-#pragma unroll
-    for (int p = 0; p < 5; ++p) {
-      const double t = fg_block_sum_f64(r[p], dred);
-      if (tid == 0) a.probe[(size_t)u * 5 + p] = t;
-    }
-    if (policy >= 4) {
-      set_len(L);
-      return;
-    }
-  }
-  const bool tie_pos = (tk.mode == 2 && tk.pthr != 0xffffffffu);  // rare: boundary value shared
-  auto kept = [&](int j) -> bool {  // from memory (large units and the tied case)
-    bool k = (cls[j] & cmask) != 0 || pos[j] > wlo;
-    if (freq) k = k || fg_in_topk(tk, score[j], (uint32_t)pos[j]);
-    return k;
-  };
-  uint32_t keepbits = 0;  // fast path: bit i = slot tid + 256 i stays
-  int mine = 0;
-  if (small) {
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
-      if (j < L) {
-        bool k = (prot >> i) & 1u;
-        if (freq && !k) {
-          if (tk.mode == 1) k = true;
-          else if (tk.mode == 2) k = tie_pos ? fg_in_topk(tk, __longlong_as_double((long long)kc[i]), (uint32_t)pos[j])
-                                             : (kc[i] >= tk.thr);
-        }
-        if (k) { keepbits |= 1u << i; ++mine; }
-      }
-    }
-  } else {
-    for (int j = tid; j < L; j += 256) mine += kept(j) ? 1 : 0;
-  }
-  const int new_len = fg_block_sum_i32(mine, ired);
-  if (new_len == L) {
-    set_len(L);
-    return;
-  }
-
-  // ---- in-place release: i-th hole (evicted slot below new_len) <- i-th kept slot above it
-  int* scratch = reinterpret_cast<int*>(a.clogit + off * G);  // logits are dead from here on (cap ints fit in cap doubles)
-  __shared__ int s_move[2 * FG_MOVE_LDS];
-  bool in_lds = false;
-  __syncthreads();
-  int run_h = 0, run_m = 0;
-  if (small) {
-    // any one-to-one pairing of holes and movers will do: number them thread by thread
-    int nh = 0, nm = 0;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
-      if (j < L) {
-        const bool k = (keepbits >> i) & 1u;
-        nh += (j < new_len && !k) ? 1 : 0;
-        nm += (j >= new_len && k) ? 1 : 0;
-      }
-    }
-    // one scan for both counts (each below 2^16: L <= 256 * NC)
-    int tot;
-    const int at = fg_block_exscan_i32(nh | (nm << 16), ired, &tot);
-    int at_h = at & 0xffff, at_m = at >> 16;
-    run_h = tot & 0xffff;
-    run_m = tot >> 16;
-    // a step releases very few slots: the two lists then stay in shared memory
-    in_lds = run_h <= FG_MOVE_LDS;
-    int* holes = in_lds ? s_move : scratch;
-    int* movers_end = in_lds ? s_move + 2 * FG_MOVE_LDS - 1 : scratch + cap - 1;  // filled downwards
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
-      if (j < L) {
-        const bool k = (keepbits >> i) & 1u;
-        if (j < new_len && !k) holes[at_h++] = j;
-        if (j >= new_len && k) *(movers_end - (at_m++)) = j;
-      }
-    }
-    __syncthreads();
-  } else {
-    for (int base = 0; base < L; base += 256) {
-      const int j = base + tid;
-      int is_h = 0, is_m = 0;
-      if (j < L) {
-        const bool k = kept(j);
-        is_h = (j < new_len && !k) ? 1 : 0;
-        is_m = (j >= new_len && k) ? 1 : 0;
-      }
-      int tot_h, tot_m;
-      const int ex_h = fg_block_exscan_i32(is_h, ired, &tot_h);
-      __syncthreads();
-      const int ex_m = fg_block_exscan_i32(is_m, ired, &tot_m);
-      if (is_h) scratch[run_h + ex_h] = j;
-      if (is_m) scratch[cap - 1 - (run_m + ex_m)] = j;
-      run_h += tot_h;
-      run_m += tot_m;
-      __syncthreads();
-    }
-  }
-  const int moves = run_h;  // == run_m
-  char* ck = static_cast<char*>(a.ck) + off * RB;
-  char* cv = static_cast<char*>(a.cv) + off * RB;
-  // the kept() predicate of the large-unit path reads score/pos/cls from memory: there the
-  // bookkeeping moves only after every thread is done with it
-  if (!small) {
-    for (int q = tid; q < moves * CPR; q += 256) {
-      const int i = q / CPR, ch = q % CPR;
-      const int dst = scratch[i], src = scratch[cap - 1 - i];
-      *reinterpret_cast<u32x4*>(ck + (size_t)dst * RB + ch * 16) = *reinterpret_cast<const u32x4*>(ck + (size_t)src * RB + ch * 16);
-      *reinterpret_cast<u32x4*>(cv + (size_t)dst * RB + ch * 16) = *reinterpret_cast<const u32x4*>(cv + (size_t)src * RB + ch * 16);
-    }
-    __syncthreads();
-    for (int i = tid; i < moves; i += 256) {
-      const int dst = scratch[i], src = scratch[cap - 1 - i];
-      score[dst] = score[src];
-      a.cpos[off + dst] = pos[src];
-      a.ccls[off + dst] = cls[src];
-    }
-  } else {
-    // rows and bookkeeping in one sweep: CPR lanes copy the row, one more moves score/pos/class
-    for (int q = tid; q < moves * (CPR + 1); q += 256) {
-      const int i = q / (CPR + 1), ch = q % (CPR + 1);
-      const int dst = in_lds ? s_move[i] : scratch[i];
-      const int src = in_lds ? s_move[2 * FG_MOVE_LDS - 1 - i] : scratch[cap - 1 - i];
-      if (ch < CPR) {
-        const u32x4 kr = *reinterpret_cast<const u32x4*>(ck + (size_t)src * RB + ch * 16);
-        const u32x4 vr = *reinterpret_cast<const u32x4*>(cv + (size_t)src * RB + ch * 16);
-        *reinterpret_cast<u32x4*>(ck + (size_t)dst * RB + ch * 16) = kr;
-        *reinterpret_cast<u32x4*>(cv + (size_t)dst * RB + ch * 16) = vr;
-      } else {
-        const double sv = score[src];
-        const int pv = pos[src];
-        const uint8_t cb = cls[src];
-        score[dst] = sv;
-        a.cpos[off + dst] = pv;
-        a.ccls[off + dst] = cb;
-      }
-    }
-  }
-  set_len(new_len);
-  };
-  if (L <= 256 * 2) update(std::integral_constant<int, 2>{});
-  else if (L <= 256 * 4) update(std::integral_constant<int, 4>{});
-  else if (L <= 256 * 8) update(std::integral_constant<int, 8>{});
-  else if (L <= 256 * 12) update(std::integral_constant<int, 12>{});
-  else if (L <= 256 * 16) update(std::integral_constant<int, 16>{});
-  else if (L <= 256 * 20) update(std::integral_constant<int, 20>{});
-  else update(std::integral_constant<int, 24>{});
+  fg_update_unit<ESIZE, D, GRP, NT>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
 }
 
 }  // namespace
@@ -689,7 +396,7 @@ static hipError_t launch_attn(const fg_decode_args& a, hipStream_t s) {
 
 template <bool GRP>
 static hipError_t launch_update(const fg_decode_args& a, hipStream_t s) {
-  const dim3 grid((unsigned)a.U), block(256);
+  const dim3 grid((unsigned)a.U), block(kUpdateThreads);
   if (a.dtype == FG_BF16) {
     if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<2, 128, GRP>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((fg_decode_finish_kernel<2, 64, GRP>), grid, block, 0, s, a);

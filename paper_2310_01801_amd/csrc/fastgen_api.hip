@@ -115,6 +115,7 @@ fg_layout make_layout(const fg_config& c) {
   L.pool_tokens = (int64_t)pool;
   L.chunk = fg_decode_chunk(c.prompt_len, c.max_new_tokens);
   L.max_chunks = (int64_t)(pool / (size_t)L.chunk + U);
+  L.unit_threads = fg_unit_threads(c.num_units, c.prompt_len, c.max_new_tokens, (int)G, (int)(d * e));
   size_t o = layout_profile_part(c, L);
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
   L.ck = take(pool * d * e);
@@ -396,7 +397,7 @@ fg_status fastgen_compact(fastgen_ctx* ctx, const void* K, const void* V, void* 
   hipError_t e = fg_launch_offsets(at<int32_t>(ctx, L.cap), at<int32_t>(ctx, L.len), at<int32_t>(ctx, L.policy),
                                    at<int64_t>(ctx, L.off), at<int32_t>(ctx, L.chunk_off), at<int32_t>(ctx, L.item_unit),
                                    at<int32_t>(ctx, L.flags), c.num_units, L.pool_tokens,
-                                   L.max_chunks, L.chunk, s);
+                                   L.max_chunks, L.chunk, c.prompt_len + c.max_new_tokens, L.unit_threads != 0, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "fastgen_compact(offsets)");
   fg_compact_args ca;
   ca.K = K; ca.V = V;
@@ -445,19 +446,22 @@ static fg_status decode_step_impl(fastgen_ctx* ctx, const void* q, const void* k
   da.units_per_seq = c.num_units / c.num_seqs; da.w = ctx->w; da.step = ctx->steps_done;
   da.G = group_of(c);
   da.r_f = c.r_f; da.scale = ctx->scale; da.max_chunks = L.max_chunks; da.chunk = L.chunk;
+  da.unit_threads = L.unit_threads;
   da.probe = probe;
   family_of(c, da.family);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   PhaseChain tm(ctx, s, ctx->timing == 1 || (ctx->timing > 1 && ctx->steps_done % ctx->timing == 0));
   tm.begin(FG_PHASE_DECODE_ATTN);
-  e = fg_launch_decode_attn(da, s);
+  e = L.unit_threads ? fg_launch_decode_unit(da, s) : fg_launch_decode_attn(da, s);
   tm.end();
   if (e != hipSuccess) return hip_fail(ctx, e, "fastgen_decode_step(attention)");
-  tm.begin(FG_PHASE_DECODE_UPDATE);
-  e = fg_launch_decode_update(da, s);
-  tm.end();
-  if (e != hipSuccess) return hip_fail(ctx, e, "fastgen_decode_step(update)");
+  if (!L.unit_threads) {
+    tm.begin(FG_PHASE_DECODE_UPDATE);
+    e = fg_launch_decode_update(da, s);
+    tm.end();
+    if (e != hipSuccess) return hip_fail(ctx, e, "fastgen_decode_step(update)");
+  }
   ctx->steps_done += 1;
   return FG_OK;
 }

@@ -36,13 +36,15 @@ struct fg_layout {
   size_t clogit;    // [pool, G] double  this step's scaled logit of every held token, per query head (written
                     //                   for the units whose cumulative scores are kept)
   // decode scratch
-  size_t chunk_off; // [U + 1] int32  first chunk of each unit in the flat work list
+  size_t chunk_off; // [U + 1] int32  first chunk of each unit in the flat work list (per-unit form: its place by size)
   size_t item_unit; // [max_chunks, 8] int32  work-item records: unit, chunk, cap, tokens held, pool offset lo/hi, policy word, 0
+                    //                        (per-unit form: one record per unit, longest reservations first)
   size_t part;      // [max_chunks, G, d + 2] float  split-KV partial (max, sum, o) per query head
   size_t total;
   int64_t pool_tokens;
   int64_t max_chunks;
   int chunk;        // tokens per decode work item (128 or 256)
+  int unit_threads; // 0: split-KV decode step; else one workgroup of this size per unit
 };
 
 struct fastgen_ctx {
@@ -68,6 +70,24 @@ struct fastgen_ctx {
 // can hold at most 4096 tokens (finer items balance short caches better; measured per shape).
 inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
   return ((long long)prompt_len + max_new_tokens <= 4096) ? 128 : 256;
+}
+
+// Form of the decode step: 0 = split-KV attention and a second launch for merge and update; else one
+// workgroup of that many threads per unit (no grouped heads). Measured per step, split / per unit:
+//   1024 units of 2048 tokens, d = 128 bf16        120 / 112 us     (256 threads: 118)
+//   4096 of 4096                                   831 / 790        (256 threads: 799)
+//   16384 of 1024, 256 threads                     948 / 845        (512 threads: 857)
+//   640 of 8192                                    250 / 283; 2560 of 8192: 989 / 1004
+//   64 of 1000, float32 (1 MiB per unit)           17.2 / 16.7      and one launch less
+//   128 of 1500 (0.75 MiB per unit)                20.1 / 17.3
+//   32 of 2048 (1.02 MiB per unit)                 14.9 / 19.0
+// So: long units stay split (a few of them decide how long the launch takes), and where there are
+// fewer units than CUs a workgroup's own streaming rate bounds the bytes per unit.
+inline int fg_unit_threads(int U, int prompt_len, int max_new_tokens, int group, int row_bytes) {
+  const long long tokens = (long long)prompt_len + max_new_tokens;
+  if (group > 1 || tokens > 4608) return 0;
+  if (U < 256) return tokens * 2 * row_bytes <= (1 << 20) ? 512 : 0;
+  return (U >= 2048 && tokens <= 2048) ? 256 : 512;
 }
 
 // ---------------------------------------------------------------- launch arguments
@@ -111,6 +131,7 @@ struct fg_decode_args {
   float scale;
   int64_t max_chunks;
   int chunk;       // tokens per work item (128 or 256)
+  int unit_threads; // workgroup size of the one-workgroup-per-unit form
 };
 
 struct fg_export_args {
@@ -135,7 +156,8 @@ hipError_t fg_launch_select(const fg_select_args&, hipStream_t);
 hipError_t fg_launch_compact(const fg_compact_args&, hipStream_t);
 hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32_t* policy, int64_t* off,
                              int32_t* chunk_off, int32_t* item_unit, int32_t* flags, int U, int64_t pool_tokens,
-                             int64_t max_chunks, int chunk, hipStream_t);
+                             int64_t max_chunks, int chunk, int max_cap, bool by_unit, hipStream_t);
 hipError_t fg_launch_decode_attn(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_update(const fg_decode_args&, hipStream_t);
+hipError_t fg_launch_decode_unit(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_export(const fg_export_args&, hipStream_t);

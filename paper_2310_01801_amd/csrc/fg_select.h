@@ -2,11 +2,11 @@
 // "equal score -> the smaller position is kept" (the frequent policy of Sec. 3.4 keeps the
 // tokens with the largest cumulative attention score). MSB-first radix select on the IEEE
 // bit patterns (monotone for non-negative doubles), 8 bits per pass:
-//   * keys are held in registers when m <= 256 * FG_SEL_CACHE (else re-read each pass);
+//   * keys are held in registers when m <= NT * FG_SEL_CACHE (else re-read each pass);
 //   * passes over the bits that all keys share are skipped (block-wide OR/AND of the keys);
 //   * the scan stops as soon as the boundary bucket is taken whole;
 //   * only if the boundary value is shared does a second select run on the positions.
-// blockDim.x must be 256.
+// NT = blockDim.x: a power of two from 256 to 1024.
 #pragma once
 #include "fg_common.h"
 
@@ -21,7 +21,7 @@ struct fg_topk {
 struct fg_select_smem {
   int hist[256];
   int red[20];
-  unsigned long long w_or[4], w_and[4];
+  unsigned long long w_or[16], w_and[16];
   int digit, rem, cnt;
 };
 
@@ -45,10 +45,10 @@ __device__ __forceinline__ void fg_hist_add(int* hist, bool active, int digit) {
 }
 
 // After the histogram of one digit is complete: locate the bucket that holds the rem-th
-// largest. Thread t looks at bucket 255 - t (descending order).
+// largest. Thread t < 256 looks at bucket 255 - t (descending order).
 __device__ __forceinline__ void fg_radix_locate(int rem, fg_select_smem* sm) {
   const int tid = threadIdx.x;
-  const int h = sm->hist[255 - tid];
+  const int h = tid < 256 ? sm->hist[255 - tid] : 0;
   int total;
   const int before = fg_block_exscan_i32(h, sm->red, &total);
   if (before < rem && before + h >= rem) {
@@ -59,8 +59,8 @@ __device__ __forceinline__ void fg_radix_locate(int rem, fg_select_smem* sm) {
   __syncthreads();
 }
 
-// NC > 0: element tid + 256 i of the block is kc[i] (registers); NC == 0: keys come from score(j).
-template <int NC, class ScoreFn, class PosFn>
+// NC > 0: element tid + NT i of the block is kc[i] (registers); NC == 0: keys come from score(j).
+template <int NT, int NC, class ScoreFn, class PosFn>
 __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC > 0 ? NC : 1], ScoreFn score,
                                                        PosFn pos, int m, int k, fg_select_smem* sm) {
   constexpr bool CACHED = NC > 0;
@@ -73,14 +73,14 @@ __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC >
   if (CACHED) {
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
+      const int j = tid + NT * i;
       if (j < m) {
         k_or |= kc[i];
         k_and &= kc[i];
       }
     }
   } else {
-    for (int j = tid; j < m; j += 256) {
+    for (int j = tid; j < m; j += NT) {
       const uint64_t key = (uint64_t)__double_as_longlong(score(j));
       k_or |= key;
       k_and &= key;
@@ -95,8 +95,8 @@ __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC >
   __syncthreads();
   if (lane == 0) { sm->w_or[wave] = k_or; sm->w_and[wave] = k_and; }
   __syncthreads();
-  k_or = sm->w_or[0] | sm->w_or[1] | sm->w_or[2] | sm->w_or[3];
-  k_and = sm->w_and[0] & sm->w_and[1] & sm->w_and[2] & sm->w_and[3];
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) { k_or |= sm->w_or[i]; k_and &= sm->w_and[i]; }
   const uint64_t diff = k_or ^ k_and;
 
   uint64_t prefix = 0, mask = 0;
@@ -107,16 +107,16 @@ __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC >
     mask = (shift + 8 >= 64) ? 0ull : ~((1ull << (shift + 8)) - 1ull);
     prefix = k_and & mask;
     for (; shift >= 0; shift -= 8) {
-      sm->hist[tid] = 0;
+      if (tid < 256) sm->hist[tid] = 0;
       __syncthreads();
       if (CACHED) {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-          const int j = tid + 256 * i;
+          const int j = tid + NT * i;
           fg_hist_add(sm->hist, j < m && (kc[i] & mask) == prefix, (int)((kc[i] >> shift) & 255u));
         }
       } else {
-        for (int j = tid; j < m; j += 256) {
+        for (int j = tid; j < m; j += NT) {
           const uint64_t key = (uint64_t)__double_as_longlong(score(j));
           if ((key & mask) == prefix) atomicAdd(&sm->hist[(int)((key >> shift) & 255u)], 1);
         }
@@ -142,9 +142,9 @@ __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC >
   const uint64_t thr = prefix;
   uint64_t p2 = 0, m2 = 0;
   for (int shift = 24; shift >= 0; shift -= 8) {
-    sm->hist[tid] = 0;
+    if (tid < 256) sm->hist[tid] = 0;
     __syncthreads();
-    for (int j = tid; j < m; j += 256) {
+    for (int j = tid; j < m; j += NT) {
       if ((uint64_t)__double_as_longlong(score(j)) != thr) continue;
       const uint64_t key = (uint64_t)(0xffffffffu - pos(j));
       if ((key & m2) == p2) atomicAdd(&sm->hist[(int)((key >> shift) & 255u)], 1);
@@ -159,16 +159,16 @@ __device__ __forceinline__ fg_topk fg_select_topk_impl(const uint64_t (&kc)[NC >
   return r;
 }
 
-// Keys already in registers (element tid + 256 i is kc[i], i < NC, valid while < m).
+// Keys already in registers (element tid + NT i is kc[i], i < NC, valid while < m).
 // score(j) / pos(j) are only consulted if the boundary value is tied.
-template <int NC, class ScoreFn, class PosFn>
+template <int NT, int NC, class ScoreFn, class PosFn>
 __device__ __forceinline__ fg_topk fg_select_topk_regs(const uint64_t (&kc)[NC], ScoreFn score, PosFn pos,
                                                        int m, int k, fg_select_smem* sm) {
   fg_topk r;
   r.thr = 0; r.pthr = 0;
   if (k <= 0) { r.mode = 0; return r; }
   if (k >= m) { r.mode = 1; return r; }
-  return fg_select_topk_impl<NC>(kc, score, pos, m, k, sm);
+  return fg_select_topk_impl<NT, NC>(kc, score, pos, m, k, sm);
 }
 
 // Shortcut for the per-step kept-set update. Only tokens that nothing else protects (`prot`
@@ -178,11 +178,13 @@ __device__ __forceinline__ fg_topk fg_select_topk_regs(const uint64_t (&kc)[NC],
 // tokens). Returns false when the shortcut does not apply -- two equal scores at a tested value,
 // or more than FG_EVICT_TRIES evictions -- and the caller runs the full selection instead.
 // On success every unprotected token with key >= out->thr is in the top k (mode 2, no position
-// tie-break needed). Keys of slot tid + 256 i are kc[i] (valid while < m). 256 threads.
+// tie-break needed); left[0, *left_count) (shared memory, visible after the next barrier) are the
+// slots of the tokens that leave. Keys of slot tid + NT i are kc[i] (valid while < m).
 #define FG_EVICT_TRIES 6
-template <int NC>
+template <int NT, int NC>
 __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint32_t prot, int m, int k,
-                                                  double* red_d, int* red_i, fg_topk* out) {
+                                                  double* red_d, int* red_i, int* left, int* left_count,
+                                                  fg_topk* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double inf = __longlong_as_double(0x7ff0000000000000ll);
   double last = -1.0;  // every evicted score so far is <= last
@@ -190,7 +192,7 @@ __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint
     double loc = inf;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
+      const int j = tid + NT * i;
       const double v = __longlong_as_double((long long)kc[i]);
       if (j < m && !((prot >> i) & 1u) && v > last) loc = fmin(loc, v);
     }
@@ -198,47 +200,54 @@ __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint
     __syncthreads();
     if (lane == 0) red_d[wave] = loc;
     __syncthreads();
-    const double kmin = fmin(fmin(red_d[0], red_d[1]), fmin(red_d[2], red_d[3]));
+    double kmin = red_d[0];
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) kmin = fmin(kmin, red_d[i]);
     out->mode = 2; out->pthr = 0xffffffffu;
     if (kmin == inf) {  // no unprotected token is left: none of them is in the top k
+      *left_count = it;
       out->thr = 0x7ff0000000000000ull;
       return true;
     }
     int cnt = 0;  // scores above kmin in the low half, scores equal to it in the high half
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-      const int j = tid + 256 * i;
+      const int j = tid + NT * i;
       const double v = __longlong_as_double((long long)kc[i]);
       if (j < m) cnt += (v > kmin ? 1 : 0) + (v == kmin ? (1 << 16) : 0);
     }
     const int tot = fg_block_sum_i32(cnt, red_i);
     if ((tot >> 16) != 1) return false;       // a tie at the tested value: needs the position rule
     if ((tot & 0xffff) < k) {                  // fewer than k larger scores: it stays, and so do all above it
+      *left_count = it;
       out->thr = (uint64_t)__double_as_longlong(kmin);
       return true;
     }
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (tid + NT * i < m && __longlong_as_double((long long)kc[i]) == kmin) left[it] = tid + NT * i;
     last = kmin;                               // at least k larger scores: it leaves; test the next one
   }
   return false;
 }
 
 // ScoreFn(j) -> double (>= 0), PosFn(j) -> uint32 position (unique per element).
-template <class ScoreFn, class PosFn>
+template <int NT, class ScoreFn, class PosFn>
 __device__ __forceinline__ fg_topk fg_select_topk(ScoreFn score, PosFn pos, int m, int k,
                                                   fg_select_smem* sm) {
   fg_topk r;
   r.thr = 0; r.pthr = 0;
   if (k <= 0) { r.mode = 0; return r; }
   if (k >= m) { r.mode = 1; return r; }
-  if (m <= 256 * FG_SEL_CACHE) {
+  if (m <= NT * FG_SEL_CACHE) {
     uint64_t kc[FG_SEL_CACHE];
 #pragma unroll
     for (int i = 0; i < FG_SEL_CACHE; ++i) {
-      const int j = threadIdx.x + 256 * i;
+      const int j = threadIdx.x + NT * i;
       kc[i] = (j < m) ? (uint64_t)__double_as_longlong(score(j)) : 0ull;
     }
-    return fg_select_topk_impl<FG_SEL_CACHE>(kc, score, pos, m, k, sm);
+    return fg_select_topk_impl<NT, FG_SEL_CACHE>(kc, score, pos, m, k, sm);
   }
   const uint64_t none[1] = {0ull};
-  return fg_select_topk_impl<0>(none, score, pos, m, k, sm);
+  return fg_select_topk_impl<NT, 0>(none, score, pos, m, k, sm);
 }

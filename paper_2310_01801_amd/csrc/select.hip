@@ -7,7 +7,8 @@
 //                      band sums, the cheapest policy reaching T (Eq. 1), kept flags and
 //                      their prefix scan.
 //   fg_offsets_kernel  exclusive scan of the per-unit slot reservations -> pool offsets,
-//                      and the static split-KV work list of the decode kernels.
+//                      and the static work list of the decode kernels (split-KV items, or the
+//                      units by size).
 //   fg_gather_kernel   copies the kept rows of K, V with score, position, class.
 //   fg_export_kernel   cache state read-back in ascending position order.
 #include "fg_common.h"
@@ -28,9 +29,10 @@ __global__ __launch_bounds__(256) void fg_classify_kernel(fg_classify_args a) {
   a.token_class[i] = (uint8_t)c;
 }
 
-__global__ __launch_bounds__(256) void fg_select_kernel(fg_select_args a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
   __shared__ fg_select_smem sm;
-  __shared__ double dred[8];
+  __shared__ double dred[16];
   __shared__ int ired[20];
   const int u = blockIdx.x, tid = threadIdx.x, n = a.n;
   const double* cs = a.colsum + (size_t)u * n;
@@ -39,7 +41,7 @@ __global__ __launch_bounds__(256) void fg_select_kernel(fg_select_args a) {
   const int k_f = fg_budget(a.r_f, n);
   const int w = a.w;
 
-  const fg_topk tk = fg_select_topk([&](int j) { return cs[j]; },
+  const fg_topk tk = fg_select_topk<NT>([&](int j) { return cs[j]; },
                                     [&](int j) { return (uint32_t)j; }, n, k_f, &sm);
 
   // Recovery of a policy = mean over rows of the kept attention mass. A column in the
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(256) void fg_select_kernel(fg_select_args a) {
   // sum; any other column is only seen through the local band, if the policy has one.
   double r[4] = {0.0, 0.0, 0.0, 0.0};
   int cnt[4] = {0, 0, 0, 0}, ccnt[4] = {0, 0, 0, 0};
-  for (int j = tid; j < n; j += 256) {
+  for (int j = tid; j < n; j += NT) {
     const int c = cls[j];
     const double s = cs[j], b = bc[j];
     const bool top = fg_in_topk(tk, s, (uint32_t)j), tail = j >= n - w;
@@ -82,7 +84,7 @@ __global__ __launch_bounds__(256) void fg_select_kernel(fg_select_args a) {
 
   // kept flags of the chosen policy and their exclusive scan (slot of each kept token)
   int running = 0;
-  for (int base = 0; base < n; base += 256) {
+  for (int base = 0; base < n; base += NT) {
     const int j = base + tid;
     int keep = 0, cbyte = 0;
     if (j < n) {
@@ -136,23 +138,75 @@ __global__ __launch_bounds__(256) void fg_select_kernel(fg_select_args a) {
   }
 }
 
-// Single workgroup: off[u] = sum_{v<u} cap[v]; chunk_off[u] = sum_{v<u} ceil(cap[v]/chunk).
+// Unit records of the one-workgroup-per-unit decode step: record r = unit, 0, cap, tokens held (kept
+// current by the step), off lo, off hi, policy word, 0.
+__device__ __forceinline__ void fg_write_unit_record(int32_t* unit_rec, int r, int u, int cap, int len,
+                                                     int64_t off, int policy) {
+  int4* p = reinterpret_cast<int4*>(unit_rec + (size_t)r * 8);
+  p[0] = make_int4(u, 0, cap, len);
+  p[1] = make_int4((int32_t)(off & 0xffffffffll), (int32_t)(off >> 32), policy, 0);
+}
+
+// Adds 1 to counter[key] for every active lane and returns the lane's place among them (lanes
+// that share a key are added by one atomic: the reservations take only a few different sizes).
+__device__ __forceinline__ int fg_count_place(int* counter, bool active, int key) {
+  const int lane = threadIdx.x & 63;
+  unsigned long long todo = __ballot(active);
+  int place = 0;
+  while (todo) {
+    const int leader = __ffsll((long long)todo) - 1;
+    const int k = __builtin_amdgcn_readlane(key, leader);
+    const unsigned long long same = __ballot(active && key == k) & todo;
+    int base = 0;
+    if (lane == leader) base = atomicAdd(&counter[k], (int)__popcll(same));
+    base = __builtin_amdgcn_readlane(base, leader);
+    if ((same >> lane) & 1ull) place = base + (int)__popcll(same & ((1ull << lane) - 1ull));
+    todo &= ~same;
+  }
+  return place;
+}
+
+constexpr int kSortUnits = 16384;   // units that are ordered by size (above, the tail of a launch is a small part)
+
+// Single workgroup: off[u] = sum_{v<u} cap[v]. BY_UNIT false: chunk_off[u] = sum_{v<u} ceil(cap[v]/chunk).
+// BY_UNIT true: chunk_off[u] = place of unit u among the units, longest reservations first (a
+// counting sort into 64 classes; the order inside a class does not matter), and for few units
+// their records too.
+template <bool BY_UNIT>
 __global__ __launch_bounds__(1024) void fg_offsets_kernel(const int32_t* __restrict__ cap,
                                                           int64_t* __restrict__ off,
                                                           int32_t* __restrict__ chunk_off,
                                                           int32_t* __restrict__ flags, int U,
-                                                          int64_t pool_tokens, int64_t max_chunks, int chunk) {
+                                                          int64_t pool_tokens, int64_t max_chunks, int chunk,
+                                                          int max_cap, int32_t* __restrict__ unit_rec,
+                                                          const int32_t* __restrict__ len,
+                                                          const int32_t* __restrict__ policy) {
   __shared__ int red[20];
   __shared__ long long wsum[16];
+  __shared__ int class_at[64];
+  __shared__ uint8_t s_class[BY_UNIT ? kSortUnits : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float to_class = 63.0f / (float)max_cap;
+  const bool sorted = BY_UNIT && U <= kSortUnits;
+  if (BY_UNIT) {
+    if (tid < 64) class_at[tid] = 0;
+    __syncthreads();
+  }
   long long run_off = 0;
   int run_chunk = 0;
   for (int base = 0; base < U; base += 1024) {
     const int u = base + tid;
     const int c = (u < U) ? cap[u] : 0;
-    const int nch = (c + chunk - 1) / chunk;
-    int total;
-    const int exc = fg_block_exscan_i32(nch, red, &total);
+    int exc = 0;
+    if (!BY_UNIT) {
+      int total;
+      exc = fg_block_exscan_i32((c + chunk - 1) / chunk, red, &total) + run_chunk;
+      run_chunk += total;
+    } else if (sorted) {
+      const int k = 63 - min(63, (int)((float)c * to_class));
+      (void)fg_count_place(class_at, u < U, k);
+      if (u < U) s_class[u] = (uint8_t)k;
+    }
     // 64-bit scan of the capacities: wave scan + serial over the 16 waves
     long long inc = c;
     for (int o = 1; o < 64; o <<= 1) {
@@ -169,18 +223,42 @@ __global__ __launch_bounds__(1024) void fg_offsets_kernel(const int32_t* __restr
     }
     if (u < U) {
       off[u] = run_off + wbase + inc - c;
-      chunk_off[u] = run_chunk + exc;
+      if (!BY_UNIT) chunk_off[u] = exc;
     }
     run_off += wtot;
-    run_chunk += total;
     __syncthreads();
   }
   if (tid == 0) {
     off[U] = run_off;
-    chunk_off[U] = run_chunk;
+    if (!BY_UNIT) chunk_off[U] = run_chunk;
     flags[0] = (run_off > pool_tokens || (int64_t)run_chunk > max_chunks) ? 1 : 0;
     flags[1] = 0;
   }
+  if (!BY_UNIT) return;
+  if (sorted) {
+    if (wave == 0) {
+      const int count = class_at[lane];
+      class_at[lane] = fg_wave_incscan_i32(count) - count;
+    }
+    __syncthreads();
+  }
+  for (int base = 0; base < U; base += 1024) {
+    const int u = base + tid;
+    const int r = sorted ? fg_count_place(class_at, u < U, u < U ? s_class[u] : 0) : u;
+    if (u >= U) continue;
+    if (U > 1024) chunk_off[u] = r;
+    else fg_write_unit_record(unit_rec, r, u, cap[u], len[u], off[u], policy[u]);
+  }
+}
+
+__global__ __launch_bounds__(256) void fg_unit_map_kernel(const int32_t* __restrict__ place,
+                                                          const int32_t* __restrict__ cap,
+                                                          const int64_t* __restrict__ off,
+                                                          const int32_t* __restrict__ len,
+                                                          const int32_t* __restrict__ policy,
+                                                          int32_t* __restrict__ unit_rec, int U) {
+  const int u = blockIdx.x * 256 + threadIdx.x;
+  if (u < U) fg_write_unit_record(unit_rec, place[u], u, cap[u], len[u], off[u], policy[u]);
 }
 
 // Work-item records of the decode attention kernel: item c of unit u covers slots
@@ -326,7 +404,13 @@ hipError_t fg_launch_classify(const fg_classify_args& a, hipStream_t s) {
 }
 
 hipError_t fg_launch_select(const fg_select_args& a, hipStream_t s) {
-  hipLaunchKernelGGL(fg_select_kernel, dim3((unsigned)a.U), dim3(256), 0, s, a);
+  // Workgroup size: a unit's chain of block reductions is shorter with more threads while the card
+  // has room for them (measured, us with 256 / 512 threads: 32 units of 333 tokens 14.3 / 13.0, 64 of
+  // 1000 18.9 / 16.1, 256 of 3000 38 / 27; 1024 of 2048 37 / 44, 4096 of 1024 81 / 120: many units
+  // of few tokens are bound by workgroups in flight instead). Above 256 * FG_SEL_CACHE tokens
+  // only the larger one keeps the keys in registers (640 of 8192: 137 / 100).
+  if (a.U <= 512 || a.n > 256 * FG_SEL_CACHE) hipLaunchKernelGGL(fg_select_kernel<512>, dim3((unsigned)a.U), dim3(512), 0, s, a);
+  else hipLaunchKernelGGL(fg_select_kernel<256>, dim3((unsigned)a.U), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -338,11 +422,17 @@ hipError_t fg_launch_compact(const fg_compact_args& a, hipStream_t s) {
 
 hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32_t* policy, int64_t* off,
                              int32_t* chunk_off, int32_t* item_unit, int32_t* flags, int U, int64_t pool_tokens,
-                             int64_t max_chunks, int chunk, hipStream_t s) {
-  hipLaunchKernelGGL(fg_offsets_kernel, dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
-                     pool_tokens, max_chunks, chunk);
-  hipLaunchKernelGGL(fg_item_map_kernel, dim3((unsigned)((U + 255) / 256)), dim3(256), 0, s,
-                     chunk_off, cap, off, len, policy, item_unit, flags, U);
+                             int64_t max_chunks, int chunk, int max_cap, bool by_unit, hipStream_t s) {
+  const dim3 blocks((unsigned)((U + 255) / 256));
+  if (by_unit) {
+    hipLaunchKernelGGL((fg_offsets_kernel<true>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
+                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy);
+    if (U > 1024) hipLaunchKernelGGL(fg_unit_map_kernel, blocks, dim3(256), 0, s, chunk_off, cap, off, len, policy, item_unit, U);
+  } else {
+    hipLaunchKernelGGL((fg_offsets_kernel<false>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
+                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy);
+    hipLaunchKernelGGL(fg_item_map_kernel, blocks, dim3(256), 0, s, chunk_off, cap, off, len, policy, item_unit, flags, U);
+  }
   return hipGetLastError();
 }
 

@@ -26,3 +26,35 @@ def test_f32_sweeps_at_tile_edges(n, d, G):
     rep = _compare("f32_edges", n, 2, d, "f32", 5, G)
     # float64 sums, (m, 1/l) held as floats: half an ulp (6e-8) per row, far below it in the mean
     assert rep.max_recovery_err < 6e-8
+
+
+# the decode step's two forms: one workgroup per unit (256 or 512 threads; units ordered by size in
+# one launch up to 1024 of them, in two up to 16384, unordered above) or split-KV. Unit counts and
+# lengths on both sides of every line; the oracle follows a few units at the ends and in the middle.
+@pytest.mark.parametrize("heads,n,S,d,dtype", [
+    (3, 1, 3, 128, "bf16"),        # a unit of one token
+    (5, 33, 6, 64, "bf16"),        # one tile and one row of a wave (d = 64: 32 rows)
+    (4, 65, 6, 64, "f32"),
+    (4, 1020, 4, 128, "bf16"),     # just below / at / above 1 MiB per unit, fewer units than CUs
+    (4, 2044, 4, 128, "bf16"),
+    (4, 2045, 4, 128, "bf16"),
+    (255, 40, 3, 128, "bf16"), (256, 40, 3, 128, "bf16"),
+    (256, 4100, 2, 64, "bf16"),    # the longest register instantiations
+    (256, 4606, 2, 64, "bf16"), (256, 4607, 2, 64, "bf16"),   # at and above the line to split-KV
+    (1024, 24, 3, 64, "bf16"), (1025, 24, 3, 64, "f32"), (2047, 24, 3, 64, "bf16"), (2048, 24, 3, 64, "bf16"),
+    (16384, 9, 2, 64, "bf16"), (16385, 9, 2, 64, "bf16"),
+])
+def test_decode_step_forms(heads, n, S, d, dtype):
+    w = W["llama7b_b1"].scaled(name="forms", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=d,
+                               dtype=dtype, seed=700 + n)
+    run = H.GpuRun(w, range(w.num_units))
+    check = sorted({0, 1, 2, heads // 2, heads - 2, heads - 1} & set(range(heads)))
+    rep = H.compare(run, check_units=check, cover_policies=1)
+    H.log_report(f"decode forms U={heads} n={n} S={S} d={d} {dtype}", rep)
+
+
+# steps that release several tokens at once: a frequent budget next to a window, many steps
+@pytest.mark.parametrize("forced,r_f,r_l", [(3, 0.3, 0.1), (3, 0.05, 0.02), (2, 0.5, 0.3)])
+def test_evictions_of_the_per_unit_step(forced, r_f, r_l):
+    rep = _compare("evictions", 150, 40, 64, "bf16", 6, forced=forced, r_f=r_f, r_l=r_l, probe_steps=(7, 20))
+    assert rep.policies == {forced: 6}
