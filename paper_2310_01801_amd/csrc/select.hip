@@ -29,10 +29,14 @@ __global__ __launch_bounds__(256) void fg_classify_kernel(fg_classify_args a) {
   a.token_class[i] = (uint8_t)c;
 }
 
-template <int NT>
+// Latency-bound: one workgroup's chain of loads and block reductions per unit. With NC > 0 (n <= NT *
+// NC) every token's column sum, band sum and class stay in registers (token tid + NT i in slot i),
+// loaded once and all at once, and the prefix scan of the kept flags takes two barriers.
+template <int NT, int NC>
 __global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
   __shared__ fg_select_smem sm;
-  __shared__ double dred[16];
+  __shared__ double part_r[NT / 64][4], sum_r[4];
+  __shared__ int part_n[NT / 64][8], sum_n[8];
   __shared__ int ired[20];
   const int u = blockIdx.x, tid = threadIdx.x, n = a.n;
   const double* cs = a.colsum + (size_t)u * n;
@@ -41,17 +45,33 @@ __global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
   const int k_f = fg_budget(a.r_f, n);
   const int w = a.w;
 
-  const fg_topk tk = fg_select_topk<NT>([&](int j) { return cs[j]; },
-                                    [&](int j) { return (uint32_t)j; }, n, k_f, &sm);
+  constexpr bool REGS = NC > 0;
+  constexpr int NR = REGS ? NC : 1;
+  uint64_t key[NR];
+  double band[NR];
+  int cl[NR];
+  if (REGS) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int j = tid + NT * i;
+      key[i] = 0; band[i] = 0.0; cl[i] = 0;
+      if (j < n) {
+        key[i] = (uint64_t)__double_as_longlong(cs[j]);
+        band[i] = bc[j];
+        cl[i] = cls[j];
+      }
+    }
+  }
+  fg_topk tk;
+  if (REGS) tk = fg_select_topk_regs<NT, NR>(key, [&](int j) { return cs[j]; }, [&](int j) { return (uint32_t)j; }, n, k_f, &sm);
+  else tk = fg_select_topk<NT>([&](int j) { return cs[j]; }, [&](int j) { return (uint32_t)j; }, n, k_f, &sm);
 
   // Recovery of a policy = mean over rows of the kept attention mass. A column in the
   // policy's static set (special / punctuation / frequent) counts in every row: its column
   // sum; any other column is only seen through the local band, if the policy has one.
   double r[4] = {0.0, 0.0, 0.0, 0.0};
   int cnt[4] = {0, 0, 0, 0}, ccnt[4] = {0, 0, 0, 0};
-  for (int j = tid; j < n; j += NT) {
-    const int c = cls[j];
-    const double s = cs[j], b = bc[j];
+  auto add_token = [&](int j, double s, double b, int c) {
     const bool top = fg_in_topk(tk, s, (uint32_t)j), tail = j >= n - w;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -64,13 +84,42 @@ __global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
       if (st || (loc && tail)) cnt[p]++;
       if (byclass) ccnt[p]++;
     }
+  };
+  if (REGS) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (tid + NT * i < n) add_token(tid + NT * i, __longlong_as_double((long long)key[i]), band[i], cl[i]);
+  } else {
+    for (int j = tid; j < n; j += NT) add_token(j, cs[j], bc[j], cls[j]);
   }
+  // the twelve block sums in one round: waves first, then one thread per sum in wave order
   double R[5];
   int C[5], CC[4];
-  for (int c = 0; c < 4; ++c) {
-    R[c] = fg_block_sum_f64(r[c], dred) / ((double)n * (double)a.G);  // mean over the rows of all G query heads
-    C[c] = fg_block_sum_i32(cnt[c], ired);
-    CC[c] = fg_block_sum_i32(ccnt[c], ired);
+  {
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double rs = fg_wave_sum_f64(r[c]);
+      const int n1 = fg_wave_sum_i32(cnt[c]), n2 = fg_wave_sum_i32(ccnt[c]);
+      if (lane == 0) { part_r[wave][c] = rs; part_n[wave][c] = n1; part_n[wave][4 + c] = n2; }
+    }
+    __syncthreads();
+    if (tid < 4) {
+      double t = 0.0;
+      for (int i = 0; i < NT / 64; ++i) t += part_r[i][tid];
+      sum_r[tid] = t;
+    } else if (tid < 12) {
+      int t = 0;
+      for (int i = 0; i < NT / 64; ++i) t += part_n[i][tid - 4];
+      sum_n[tid - 4] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      R[c] = sum_r[c] / ((double)n * (double)a.G);  // mean over the rows of all G query heads
+      C[c] = sum_n[c];
+      CC[c] = sum_n[4 + c];
+    }
   }
   R[4] = 1.0;
   C[4] = n;
@@ -84,27 +133,59 @@ __global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
 
   // kept flags of the chosen policy and their exclusive scan (slot of each kept token)
   int running = 0;
-  for (int base = 0; base < n; base += NT) {
-    const int j = base + tid;
-    int keep = 0, cbyte = 0;
-    if (j < n) {
-      const int c = cls[j];
-      bool k = policy >= 4;
-      if (comp & FG_COMP_SPECIAL) k = k || (c & FG_CLASS_SPECIAL) != 0;
-      if (comp & FG_COMP_PUNCT) k = k || (c & FG_CLASS_PUNCT) != 0;
-      if (comp & FG_COMP_FREQUENT) k = k || fg_in_topk(tk, cs[j], (uint32_t)j);
-      if (comp & FG_COMP_LOCAL) k = k || (j >= n - w);
-      keep = k ? 1 : 0;
-      cbyte = k ? (4 | (c & 3)) : 0;  // kept flag plus the token's class bits
+  auto kept = [&](int j, double s, int c) {
+    bool k = policy >= 4;
+    if (comp & FG_COMP_SPECIAL) k = k || (c & FG_CLASS_SPECIAL) != 0;
+    if (comp & FG_COMP_PUNCT) k = k || (c & FG_CLASS_PUNCT) != 0;
+    if (comp & FG_COMP_FREQUENT) k = k || fg_in_topk(tk, s, (uint32_t)j);
+    if (comp & FG_COMP_LOCAL) k = k || (j >= n - w);
+    return k;
+  };
+  auto store = [&](int j, bool k, int c, int slot) {
+    a.keep[(size_t)u * n + j] = (uint8_t)(k ? (4 | (c & 3)) : 0);  // kept flag plus the token's class bits
+    a.slot[(size_t)u * n + j] = slot;
+  };
+  if (REGS) {
+    // kept tokens per (slot i, wave) = per 64 consecutive positions, their scan by wave 0
+    constexpr int NW = NT / 64;
+    const int lane = tid & 63, wave = tid >> 6;
+    __shared__ int s_count[NR * NW], s_total;
+    unsigned long long flags[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int j = tid + NT * i;
+      flags[i] = __ballot(j < n && kept(j, __longlong_as_double((long long)key[i]), cl[i]));
+      if (lane == 0) s_count[i * NW + wave] = (int)__popcll(flags[i]);
     }
-    int total;
-    const int ex = fg_block_exscan_i32(keep, ired, &total);
-    if (j < n) {
-      a.keep[(size_t)u * n + j] = (uint8_t)cbyte;
-      a.slot[(size_t)u * n + j] = running + ex;
-    }
-    running += total;
     __syncthreads();
+    if (wave == 0) {
+      int base = 0;
+      for (int q = 0; q < NR * NW; q += 64) {
+        const int v = q + lane < NR * NW ? s_count[q + lane] : 0;
+        const int inc = fg_wave_incscan_i32(v);
+        if (q + lane < NR * NW) s_count[q + lane] = base + inc - v;
+        base += fg_readlane_i32(inc, 63);
+      }
+      if (lane == 0) s_total = base;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int j = tid + NT * i;
+      if (j < n) store(j, (flags[i] >> lane) & 1ull, cl[i], s_count[i * NW + wave] + (int)__popcll(flags[i] & ((1ull << lane) - 1ull)));
+    }
+    running = s_total;
+  } else {
+    for (int base = 0; base < n; base += NT) {
+      const int j = base + tid;
+      const int c = j < n ? cls[j] : 0;
+      const bool k = j < n && kept(j, cs[j], c);
+      int total;
+      const int ex = fg_block_exscan_i32(k ? 1 : 0, ired, &total);
+      if (j < n) store(j, k, c, running + ex);
+      running += total;
+      __syncthreads();
+    }
   }
 
   if (tid == 0) {
@@ -404,13 +485,28 @@ hipError_t fg_launch_classify(const fg_classify_args& a, hipStream_t s) {
 }
 
 hipError_t fg_launch_select(const fg_select_args& a, hipStream_t s) {
-  // Workgroup size: a unit's chain of block reductions is shorter with more threads while the card
-  // has room for them (measured, us with 256 / 512 threads: 32 units of 333 tokens 14.3 / 13.0, 64 of
-  // 1000 18.9 / 16.1, 256 of 3000 38 / 27; 1024 of 2048 37 / 44, 4096 of 1024 81 / 120: many units
-  // of few tokens are bound by workgroups in flight instead). Above 256 * FG_SEL_CACHE tokens
-  // only the larger one keeps the keys in registers (640 of 8192: 137 / 100).
-  if (a.U <= 512 || a.n > 256 * FG_SEL_CACHE) hipLaunchKernelGGL(fg_select_kernel<512>, dim3((unsigned)a.U), dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(fg_select_kernel<256>, dim3((unsigned)a.U), dim3(256), 0, s, a);
+  // More threads shorten a unit's chain while the card has room for them: 512 of them for few units,
+  // 256 where many units of few tokens are bound by the workgroups in flight (512 / 256 threads
+  // before the tokens stayed in registers: 256 units of 3000 tokens 27 / 38 us, 1024 of 2048
+  // 44 / 37, 4096 of 1024 120 / 81), and as many as hold the prompt in at most 12 register slots.
+  // Measured, us, with everything re-read per pass and twelve single block sums / now: 32 units of
+  // 333 tokens 14.3 / 7.3, 1024 of 2048 37 / 29, 4096 of 1024 81 / 47, 256 of 3000 38 / 19, 1600 of
+  // 4096 111 / 80, 640 of 8192 137 / 80.
+#define FG_SELECT(NT, NC) hipLaunchKernelGGL((fg_select_kernel<NT, NC>), dim3((unsigned)a.U), dim3(NT), 0, s, a)
+  if (a.U <= 512 || a.n > 3072) {
+    if (a.n <= 512) FG_SELECT(512, 1);
+    else if (a.n <= 1024) FG_SELECT(512, 2);
+    else if (a.n <= 2048) FG_SELECT(512, 4);
+    else if (a.n <= 4096) FG_SELECT(512, 8);
+    else if (a.n <= 8192) FG_SELECT(1024, 8);
+    else FG_SELECT(512, 0);
+  } else {
+    if (a.n <= 512) FG_SELECT(256, 2);
+    else if (a.n <= 1024) FG_SELECT(256, 4);
+    else if (a.n <= 2048) FG_SELECT(256, 8);
+    else FG_SELECT(256, 12);
+  }
+#undef FG_SELECT
   return hipGetLastError();
 }
 

@@ -58,3 +58,15 @@ def test_decode_step_forms(heads, n, S, d, dtype):
 def test_evictions_of_the_per_unit_step(forced, r_f, r_l):
     rep = _compare("evictions", 150, 40, 64, "bf16", 6, forced=forced, r_f=r_f, r_l=r_l, probe_steps=(7, 20))
     assert rep.policies == {forced: 6}
+
+
+# policy selection: tokens in registers (1, 2, 4, 8 slots of 512 threads for few units, 2, 4, 8, 12 of
+# 256 for many, 8 of 1024 for long prompts) or re-read: both sides of every line
+@pytest.mark.parametrize("heads,n", [(3, 512), (3, 513), (3, 1024), (3, 1025), (2, 2049), (2, 4096), (2, 4097), (1, 8192),
+                                     (1, 8193), (513, 512), (513, 513), (513, 1025), (513, 2049), (513, 3073)])
+def test_selection_sizes(heads, n):
+    w = W["llama7b_b1"].scaled(name="selection", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=64,
+                               seed=800 + n)
+    run = H.GpuRun(w, range(w.num_units))
+    rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+    H.log_report(f"selection U={heads} n={n}", rep)
