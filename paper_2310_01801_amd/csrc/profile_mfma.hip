@@ -35,7 +35,7 @@ struct Lds {
   static constexpr int kTileBytes = kTile * kRowBytes;
 };
 
-template <int D, int PASS>
+template <int D, int PASS, bool PAIRED>
 __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
     double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int w, float c,
@@ -52,14 +52,14 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   // ---- which (unit, owner block): units of one XCD walk one unit's blocks back to back
   const int idx = blockIdx.x;
   const int xcd = idx & 7, rest = idx >> 3;
-  const int npair = (nblk + 1) / 2;
+  const int npair = PAIRED ? (nblk + 1) / 2 : nblk;
   const int pair_ord = rest % npair;
   const int unit = (rest / npair) * 8 + xcd;
   if (unit >= U) return;
   // A workgroup takes two owner blocks of the unit, the pair_ord-th heaviest and the
   // pair_ord-th lightest one: every workgroup of a unit then has the same amount of work and
-  // the start-up of a workgroup is paid once per pair.
-  for (int half = 0; half < 2; ++half) {
+  // the start-up of a workgroup is paid once per pair. (Not PAIRED: one block each.)
+  for (int half = 0; half < (PAIRED ? 2 : 1); ++half) {
   const int blk_ord = half == 0 ? pair_ord : nblk - 1 - pair_ord;
   if (half == 1 && blk_ord == pair_ord) break;  // the middle block of an odd count is alone
   const int blk = (PASS == 1) ? (nblk - 1 - blk_ord) : blk_ord;  // heaviest first
@@ -352,27 +352,217 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   }
 }
 
-template <int D>
-hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
-  const int nblk = (a.n + kOwnPerBlock - 1) / kOwnPerBlock;
-  const int units = (pass == 1) ? a.U * a.G : a.U;  // sweep 1: one unit per query head
-  const int ugroups = (units + 7) / 8;
-  const dim3 grid((unsigned)(8 * ((nblk + 1) / 2) * ugroups)), block(256);
+// Tile arithmetic of the split-stream form: one tile of 32 streamed items against the 32 owners (lanes)
+// of a fragment, ac[i] = raw dot product with streamed item sbase + (i>>2)*8 + (i&3).
+__device__ __forceinline__ void fg_row_tile(const f32x16& ac, float c, int lim, float& m_run, double& l_run) {
+  float tmax = FG_NEG_BIG;   // causal: columns with an offset <= lim are visible
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, ((i >> 2) * 8 + (i & 3)) <= lim ? ac[i] * c : FG_NEG_BIG);
+  const float m_new = fmaxf(m_run, tmax);
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float p = fg_exp2(fmaf(ac[i], c, -m_new));
+    s += ((i >> 2) * 8 + (i & 3)) <= lim ? p : 0.f;
+  }
+  l_run = l_run * (double)fg_exp2(m_run - m_new) + (double)s;
+  m_run = m_new;
+}
+
+__device__ __forceinline__ void fg_col_tile(const f32x16& ac, const float (&ms)[16], const float (&il)[16], float c,
+                                            int dbase, int rlim, int w, double& col_acc, double& band_acc) {
+  float s = 0.f, sb = 0.f;   // row - col = dbase + offset >= 0, row < n iff offset < rlim
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int o = (i >> 2) * 8 + (i & 3), dist = dbase + o;
+    const bool ok = (dist >= 0) && (o < rlim);
+    const float e = fg_exp2(fmaf(ac[i], c, -ms[i]));   // may be huge where masked: select, do not scale
+    const float p = (ok ? e : 0.f) * il[i];
+    s += p;
+    sb += dist < w ? p : 0.f;
+  }
+  col_acc += (double)s;
+  band_acc += (double)sb;
+}
+
+// The same sweeps for problems that leave CUs idle with 256-owner blocks: a workgroup owns 32 * F
+// items and its four waves take the streamed tiles in turn, each straight from global memory into
+// registers, so that one short layer still occupies the card and the longest chain is a quarter.
+template <int D, int PASS, int F>
+__global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
+    double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int w, float c,
+    int nblk, int G) {
+  constexpr int KK = D / 16;
+  __shared__ double s_a[4][F][32], s_b[4][F][32];
+
+  const int idx = blockIdx.x;
+  const int xcd = idx & 7, rest = idx >> 3;
+  const int ord = rest % nblk;
+  const int unit = (rest / nblk) * 8 + xcd;
+  if (unit >= U) return;
+  const int blk = (PASS == 1) ? (nblk - 1 - ord) : ord;  // heaviest first
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 31, lh = lane >> 5;
+  const size_t mat = (size_t)n * D;
+  const __bf16* own_mat = (PASS == 1 ? Q : K) + (size_t)unit * mat;
+  const __bf16* str_mat = (PASS == 1) ? K + (size_t)(unit / G) * mat : Q + (size_t)unit * G * mat;
+  const float2* stat_row = rowstat + (size_t)unit * (PASS == 1 ? 1 : G) * n;
+  const int heads = (PASS == 1) ? 1 : G;
+  const int O0 = blk * (32 * F);
+
+  bf16x8 own[F][KK];
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    const __bf16* src = own_mat + (size_t)min(O0 + 32 * f + ln, n - 1) * D + lh * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      own[f][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * kk));
+  }
+  const int t_begin = (PASS == 1) ? 0 : O0 / kTile;
+  const int t_end = (PASS == 1) ? (min(n, O0 + 32 * F) + kTile - 1) / kTile : (n + kTile - 1) / kTile;
+  const int nt = t_end - t_begin, n_it = nt * heads;
+  const __amdgpu_buffer_rsrc_t stat_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(stat_row), 0, heads * n * 8, 0x00020000);
+
+  float m_run[F];
+  double acc_a[F], acc_b[F];   // pass 1: l (acc_b unused); pass 2: column sum and its part in the band
+#pragma unroll
+  for (int f = 0; f < F; ++f) { m_run[f] = FG_NEG_BIG; acc_a[f] = 0.0; acc_b[f] = 0.0; }
+
+  u32x4 next[KK];
+  auto load = [&](int it) {   // rows past the end of the unit are clamped: masked wherever they are used
+    const int h = it / nt, row = min((t_begin + it - h * nt) * kTile + ln, n - 1);
+    const __bf16* src = str_mat + ((size_t)h * n + row) * D + lh * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) next[kk] = *reinterpret_cast<const u32x4*>(src + 16 * kk);
+  };
+  if (wave < n_it) load(wave);
+  for (int it = wave; it < n_it; it += 4) {
+    const int h = it / nt, t0 = (t_begin + it - h * nt) * kTile;
+    const int sbase = t0 + lh * 4;  // streamed index of acc[i] = sbase + (i>>2)*8 + (i&3)
+    float ms[16], il[16];
+    if (PASS == 2) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {   // rows past the last head's end read as zeros
+        const int at = (h * n + sbase + g * 8) * 8;
+        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at, 0, 0));
+        const f32x4 u = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at + 16, 0, 0));
+        ms[g * 4 + 0] = v[0]; ms[g * 4 + 1] = v[2]; ms[g * 4 + 2] = u[0]; ms[g * 4 + 3] = u[2];
+        il[g * 4 + 0] = v[1]; il[g * 4 + 1] = v[3]; il[g * 4 + 2] = u[1]; il[g * 4 + 3] = u[3];
+      }
+    }
+    f32x16 acc[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[f][i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, next[kk]);
+#pragma unroll
+      for (int f = 0; f < F; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, own[f][kk], acc[f], 0, 0, 0);
+    }
+    if (it + 4 < n_it) load(it + 4);   // in flight during the softmax arithmetic
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const int Of = O0 + 32 * f, own_i = Of + ln;
+      if (PASS == 1) {
+        if (Of < n && t0 <= Of + 31) fg_row_tile(acc[f], c, own_i - sbase, m_run[f], acc_a[f]);
+      } else {
+        if (Of < n && t0 + 31 >= Of) fg_col_tile(acc[f], ms, il, c, sbase - own_i, n - sbase, w, acc_a[f], acc_b[f]);
+      }
+    }
+  }
+
+  // ---- merge the half-waves, then the waves, in a fixed order
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    if (PASS == 1) {
+      const float M = fmaxf(m_run[f], __shfl_xor(m_run[f], 32, 64));
+      acc_a[f] *= (double)fg_exp2(m_run[f] - M);
+      acc_b[f] = (double)M;
+    } else acc_b[f] += fg_shfl_xor_f64(acc_b[f], 32);
+    acc_a[f] += fg_shfl_xor_f64(acc_a[f], 32);
+    if (lh == 0) { s_a[wave][f][ln] = acc_a[f]; s_b[wave][f][ln] = acc_b[f]; }
+  }
+  __syncthreads();
+  if (tid < 32 * F && O0 + tid < n) {
+    const int f = tid >> 5, o = tid & 31;
+    const size_t at = (size_t)unit * n + O0 + tid;
+    if (PASS == 1) {
+      const double M = fmax(fmax(s_b[0][f][o], s_b[1][f][o]), fmax(s_b[2][f][o], s_b[3][f][o]));
+      double L = 0.0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) L += s_a[i][f][o] * (double)fg_exp2((float)(s_b[i][f][o] - M));
+      rowstat[at] = make_float2((float)M, (float)(1.0 / L));
+    } else {
+      colsum[at] = (s_a[0][f][o] + s_a[1][f][o]) + (s_a[2][f][o] + s_a[3][f][o]);
+      bandcol[at] = (s_b[0][f][o] + s_b[1][f][o]) + (s_b[2][f][o] + s_b[3][f][o]);
+    }
+  }
+}
+
+template <int D, int F>
+hipError_t launch_small(const fg_profile_args& a, int pass, hipStream_t s) {
+  const int nblk = (a.n + 32 * F - 1) / (32 * F);
+  const int units = (pass == 1) ? a.U * a.G : a.U;
+  const dim3 grid((unsigned)(8 * nblk * ((units + 7) / 8))), block(256);
   const float c = a.scale * FG_LOG2E;
   const __bf16* Q = static_cast<const __bf16*>(a.Q);
   const __bf16* K = static_cast<const __bf16*>(a.K);
   if (pass == 1)
-    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 1>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
+    hipLaunchKernelGGL((fg_profile_small_kernel<D, 1, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
                        a.bandcol, units, a.n, a.w, c, nblk, a.G);
   else
-    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
+    hipLaunchKernelGGL((fg_profile_small_kernel<D, 2, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
                        a.bandcol, units, a.n, a.w, c, nblk, a.G);
   return hipGetLastError();
+}
+
+template <int D, bool PAIRED>
+hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
+  const int nblk = (a.n + kOwnPerBlock - 1) / kOwnPerBlock;
+  const int units = (pass == 1) ? a.U * a.G : a.U;  // sweep 1: one unit per query head
+  const int npair = PAIRED ? (nblk + 1) / 2 : nblk;
+  const dim3 grid((unsigned)(8 * npair * ((units + 7) / 8))), block(256);
+  const float c = a.scale * FG_LOG2E;
+  const __bf16* Q = static_cast<const __bf16*>(a.Q);
+  const __bf16* K = static_cast<const __bf16*>(a.K);
+  if (pass == 1)
+    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 1, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
+                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+  else
+    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
+                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+  return hipGetLastError();
+}
+
+// Form of a sweep by its size. steps = 32-item tiles against 64 owners over all units; the constants
+// (us) are fits to the sweeps measured at 8 to 4096 units of 100 to 4096 tokens:
+//   split stream (small kernel)   7 + 1.75 (d = 64: 0.85) per 1024 steps: 32 x 333 tokens 9.6 + 11.4, 32 x
+//                                 2048 60 + 70, 128 x 1024 64 + 72 (256-owner blocks: 24 + 23, 70 + 80, 45 + 51)
+//   256-owner blocks              4 + 8.4 (d = 64: 6) per block of the longest chain while the card is not full
+// Blocks are taken singly where even so at most three per CU are in flight and a unit has few of
+// them (64 x 1024: 43 -> 35, 256 x 333: 26 -> 18; 256 x 1024: 57 -> 70), else in heavy / light pairs;
+// not in the second sweep at d = 128, which does not gain (128 x 700: 39 -> 42).
+template <int D>
+hipError_t launch_sized(const fg_profile_args& a, int pass, hipStream_t s) {
+  const double units = (double)a.U * (pass == 1 ? a.G : 1), heads = pass == 1 ? 1.0 : (double)a.G;
+  const double nb64 = (a.n + 63) / 64, nblk = (a.n + kOwnPerBlock - 1) / kOwnPerBlock;
+  const double small = 7.0 + (D == 128 ? 1.75 : 0.85) * units * heads * nb64 * (nb64 + 1.0) / 1024.0;
+  const double chain = 4.0 + (D == 128 ? 8.4 : 6.0) * nblk * heads;
+  if (small < chain) {
+    if (units * ((a.n + 31) / 32) <= 256.0) return launch_small<D, 1>(a, pass, s);
+    return launch_small<D, 2>(a, pass, s);
+  }
+  if ((pass == 1 || D == 64) && nblk <= 6.0 && units * nblk <= 768.0) return launch<D, false>(a, pass, s);
+  return launch<D, true>(a, pass, s);
 }
 
 }  // namespace
 
 hipError_t fg_launch_profile_bf16(const fg_profile_args& a, int pass, hipStream_t s) {
-  if (a.d == 128) return launch<128>(a, pass, s);
-  return launch<64>(a, pass, s);
+  return a.d == 128 ? launch_sized<128>(a, pass, s) : launch_sized<64>(a, pass, s);
 }

@@ -70,3 +70,20 @@ def test_selection_sizes(heads, n):
     run = H.GpuRun(w, range(w.num_units))
     rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
     H.log_report(f"selection U={heads} n={n}", rep)
+
+
+# bf16 sweeps: the split stream with one or two fragments of 32 owners (few units), 256-owner blocks
+# taken singly (first sweep; both at d = 64) or in pairs, by unit count; prompt lengths around tiles
+# and blocks, and local windows whose edge falls inside, at and across tiles
+@pytest.mark.parametrize("heads,n,d,G", [
+    (2, 31, 128, 1), (2, 32, 64, 1), (3, 33, 128, 1), (3, 63, 64, 2), (3, 65, 128, 1), (5, 129, 128, 2), (4, 300, 128, 8),
+    (24, 333, 128, 1), (24, 257, 64, 1), (200, 400, 128, 1), (200, 400, 64, 1), (9, 2049, 64, 1),
+    (800, 255, 128, 1), (800, 257, 128, 1), (800, 513, 64, 1), (400, 400, 128, 2),
+])
+def test_bf16_sweep_forms(heads, n, d, G):
+    for window in (1, 31, 33, max(1, n // 3)):
+        w = W["llama7b_b1"].scaled(name="sweeps", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d,
+                                   r_l=min(1.0, (window + 0.5) / n), seed=600 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+        H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
