@@ -232,6 +232,7 @@ hipError_t launch(const fg_decode_args& a, hipStream_t s) {
 }  // namespace
 
 hipError_t fg_launch_decode_unit(const fg_decode_args& a, hipStream_t s) {
+  if (a.G > 1) return fg_launch_decode_group(a, s);
   if (a.unit_threads == 256) return launch<256>(a, s);
   return launch<512>(a, s);
 }

@@ -104,6 +104,29 @@ __device__ __forceinline__ double fg_group_sum_f64(double v) {
   return v;
 }
 
+// Four sums of doubles over aligned groups of 16 consecutive lanes at once, v[0..3] in, their totals
+// in every lane out as floats after scaling (`scaled` receives the scaled double of one of them: number
+// fg_sum4_index()). Two exchange steps halve the values a lane still adds, two plain ones finish
+// and four broadcasts spread the result: about half of four separate sums. Fixed order.
+__device__ __forceinline__ int fg_sum4_index() { return ((threadIdx.x >> 3) & 1) | ((threadIdx.x >> 1) & 2); }
+__device__ __forceinline__ void fg_sum4_16(const double (&v)[4], double scale, double* scaled, float (&out)[4]) {
+  const bool b3 = (threadIdx.x & 8) != 0, b2 = (threadIdx.x & 4) != 0;
+  // lanes i and 15 - i: the upper eight keep values 1 and 3, the lower eight 0 and 2
+  const double a0 = (b3 ? v[1] : v[0]) + fg_dpp_f64<FG_DPP_MIRROR>(b3 ? v[0] : v[1]);
+  const double a1 = (b3 ? v[3] : v[2]) + fg_dpp_f64<FG_DPP_MIRROR>(b3 ? v[2] : v[3]);
+  // lanes i and 7 - i of eight: the upper four keep a1
+  double r = (b2 ? a1 : a0) + fg_dpp_f64<FG_DPP_HALF_MIRROR>(b2 ? a0 : a1);
+  r += fg_dpp_f64<FG_DPP_XOR1>(r);
+  r += fg_dpp_f64<FG_DPP_XOR2>(r);
+  r *= scale;
+  *scaled = r;
+  const float f = (float)r;
+  out[0] = fg_dpp<0x150>(f);   // row_newbcast: lane 0 of the 16
+  out[1] = fg_dpp<0x158>(f);
+  out[2] = fg_dpp<0x154>(f);
+  out[3] = fg_dpp<0x15C>(f);
+}
+
 __device__ __forceinline__ double fg_wave_sum_f64(double v) {
   v += fg_dpp_f64<FG_DPP_XOR1>(v);
   v += fg_dpp_f64<FG_DPP_XOR2>(v);

@@ -73,7 +73,7 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 }
 
 // Form of the decode step: 0 = split-KV attention and a second launch for merge and update; else one
-// workgroup of that many threads per unit (no grouped heads). Measured per step, split / per unit:
+// workgroup of that many threads per unit. Measured per step, split / per unit:
 //   1024 units of 2048 tokens, d = 128 bf16        120 / 112 us     (256 threads: 118)
 //   4096 of 4096                                   831 / 790        (256 threads: 799)
 //   16384 of 1024, 256 threads                     948 / 845        (512 threads: 857)
@@ -81,11 +81,17 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 //   64 of 1000, float32 (1 MiB per unit)           17.2 / 16.7      and one launch less
 //   128 of 1500 (0.75 MiB per unit)                20.1 / 17.3
 //   32 of 2048 (1.02 MiB per unit)                 14.9 / 19.0
+// Grouped heads (G heads share a unit's rows; bound by the float64 logits of the heads):
+//   256 units of 2048 tokens, G = 4                66 / 47 us;  8 of 300, G = 4: 24 / 15
+//   1024 of 700, G = 2                             71 / 52;  600 of 4000, G = 4: 242 / 180
+//   256 of 3000, G = 8                             159 / 166;  32 of 2000, G = 2: 23 / 31
+//   64 of 3000, G = 8                              80 / 149
 // So: long units stay split (a few of them decide how long the launch takes), and where there are
-// fewer units than CUs a workgroup's own streaming rate bounds the bytes per unit.
+// fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit.
 inline int fg_unit_threads(int U, int prompt_len, int max_new_tokens, int group, int row_bytes) {
   const long long tokens = (long long)prompt_len + max_new_tokens;
-  if (group > 1 || tokens > 4608) return 0;
+  if (tokens > 4608 || group > 8) return 0;
+  if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
   if (U < 256) return tokens * 2 * row_bytes <= (1 << 20) ? 512 : 0;
   return (U >= 2048 && tokens <= 2048) ? 256 : 512;
 }
@@ -160,4 +166,5 @@ hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32
 hipError_t fg_launch_decode_attn(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_update(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_unit(const fg_decode_args&, hipStream_t);
+hipError_t fg_launch_decode_group(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_export(const fg_export_args&, hipStream_t);

@@ -87,3 +87,20 @@ def test_bf16_sweep_forms(heads, n, d, G):
         run = H.GpuRun(w, range(w.num_units), group_size=G)
         rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
         H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
+# grouped heads, per-unit step (instantiated for up to 2, 4 and 8 heads; 16-, 8- and 32-lane rows) and
+# split-KV beyond its lines (more heads, more tokens), probed steps included
+@pytest.mark.parametrize("heads,n,S,d,dtype,G", [
+    (3, 1, 3, 128, "bf16", 2), (3, 17, 5, 128, "bf16", 3), (3, 130, 9, 128, "bf16", 4), (3, 130, 9, 64, "bf16", 4),
+    (3, 250, 6, 128, "bf16", 5), (3, 250, 6, 128, "bf16", 8), (2, 251, 6, 64, "bf16", 8), (3, 100, 6, 128, "f32", 2),
+    (3, 100, 6, 64, "f32", 4), (3, 65, 6, 128, "f32", 7), (2, 100, 6, 128, "bf16", 9), (2, 508, 4, 128, "bf16", 4),
+    (2, 509, 4, 128, "bf16", 4), (256, 520, 3, 64, "bf16", 4), (260, 40, 12, 128, "bf16", 2),
+])
+def test_grouped_decode_step_forms(heads, n, S, d, dtype, G):
+    w = W["llama7b_b1"].scaled(name="grouped_forms", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=d,
+                               dtype=dtype, seed=400 + n)
+    run = H.GpuRun(w, range(w.num_units), group_size=G)
+    check = sorted({0, 1, 2, heads // 2, heads - 1} & set(range(heads)))
+    rep = H.compare(run, check_units=check, probe_steps=(1,), cover_policies=1)
+    H.log_report(f"grouped forms U={heads} n={n} S={S} d={d} {dtype} G={G}", rep)
