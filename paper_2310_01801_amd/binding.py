@@ -96,7 +96,11 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle, without the Stream object torch.cuda.current_stream() builds
+    around it (2.8 us of a 10 us call; 0.2 us this way)."""
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_config(num_units: int, num_seqs: int, head_dim: int, dtype: torch.dtype, prompt_len: int,
@@ -122,8 +126,8 @@ def fastgen_classify(token_ids: torch.Tensor, special_ids, punct_ids,
     assert token_ids.dtype == torch.int32
     if token_class is None:
         token_class = torch.empty(token_ids.shape, dtype=torch.uint8, device=token_ids.device)
-    sp = (ctypes.c_int32 * max(1, len(special_ids)))(*[int(x) for x in special_ids])
-    pu = (ctypes.c_int32 * max(1, len(punct_ids)))(*[int(x) for x in punct_ids])
+    sp = (ctypes.c_int32 * max(1, len(special_ids)))(*map(int, special_ids))
+    pu = (ctypes.c_int32 * max(1, len(punct_ids)))(*map(int, punct_ids))
     st = lib.fastgen_classify(_ptr(token_ids), token_ids.numel(), sp, len(special_ids), pu, len(punct_ids),
                               _ptr(token_class), _stream())
     if st != FG_OK:
