@@ -32,15 +32,16 @@ TIMING_SAMPLE = 8         # decode steps between two timed ones (an event record
 # a timed run. "sweeps" = both sweeps together, "decode_attn" = per launch over the first 16
 # decode steps.
 MEASURED_TRAFFIC = {
-    # (FETCH_SIZE KiB x 2 + WRITE_SIZE KiB) x 1024 of sweep 1 + sweep 2; of fg_decode_partial_kernel
-    "llama65b_b2": {"sweeps": (26371393 * 2 + 655360 + 32501777 * 2 + 2129920) * 1024.0,
-                    "decode_attn": (9837948 * 2 + 274801) * 1024.0},
-    "llama7b_b1": {"sweeps": (717242 * 2 + 16384 + 736650 * 2 + 53248) * 1024.0,
-                   "decode_attn": (263969 * 2 + 10228) * 1024.0},
-    "llama7b_b16": {"sweeps": (6642435 * 2 + 131072 + 5898438 * 2 + 425984) * 1024.0,
-                    "decode_attn": (2102048 * 2 + 87862) * 1024.0},
-    "llama13b_b4": {"sweeps": (8408802 * 2 + 204800 + 9147482 * 2 + 665600) * 1024.0,
-                    "decode_attn": (4289956 * 2 + 96794) * 1024.0},
+    # (FETCH_SIZE KiB x 2 + WRITE_SIZE KiB) x 1024 of sweep 1 + sweep 2; of the decode attention launch
+    # (fg_decode_partial_kernel at llama65b_b2, else fg_decode_unit_kernel, which holds the update too)
+    "llama65b_b2": {"sweeps": (26387765 * 2 + 655360 + 32396615 * 2 + 2129920) * 1024.0,
+                    "decode_attn": (9838007 * 2 + 274807) * 1024.0},
+    "llama7b_b1": {"sweeps": (718457 * 2 + 16384 + 734949 * 2 + 53248) * 1024.0,
+                   "decode_attn": (269828 * 2 + 11049) * 1024.0},
+    "llama7b_b16": {"sweeps": (6595921 * 2 + 131072 + 5888382 * 2 + 425984) * 1024.0,
+                    "decode_attn": (2147152 * 2 + 96773) * 1024.0},
+    "llama13b_b4": {"sweeps": (8411611 * 2 + 204800 + 9088354 * 2 + 665600) * 1024.0,
+                    "decode_attn": (4355092 * 2 + 116486) * 1024.0},
 }
 
 BASELINE_INDEX = {"tiny": 0, "llama7b_b1": 1, "llama7b_b16": 2, "llama13b_b4": 3, "llama65b_b2": 4}
@@ -183,8 +184,11 @@ def run_workload(w, args, steps, warmup, dev="cuda:0"):
         fg.close()
         attn_ms = phase["decode_attn"] / max(1, launches["decode_attn"])
         upd_ms = phase["decode_update"] / max(1, launches["decode_update"])
+        by_unit = launches["decode_update"] == 0      # one launch does the whole step
+        if by_unit:
+            attn_b = step_b
         bw = (attn_b / n_timed) / (attn_ms * 1e-3)
-        roof_decode = dict(kernel="fg_decode_partial_kernel", bound="hbm", achieved=bw / 1e9,
+        roof_decode = dict(kernel="fg_decode_unit_kernel" if by_unit else "fg_decode_partial_kernel", bound="hbm", achieved=bw / 1e9,
                            peak=PEAK_HBM / 1e9, unit="GB/s", frac=bw / PEAK_HBM,
                            traffic=traffic.get("decode_attn"),
                            avg_launch_ms=attn_ms, bytes_per_launch=attn_b / n_timed,
