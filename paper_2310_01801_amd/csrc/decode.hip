@@ -285,7 +285,8 @@ __global__ __launch_bounds__(kUpdateThreads, GRP ? 2 : 4) void fg_decode_finish_
   constexpr int NT = kUpdateThreads;
   __shared__ fg_update_smem sh;
   __shared__ float s_M[16];  // per query head: merged maximum of the scaled logits
-  const int u = blockIdx.x, tid = threadIdx.x;
+  const int u = blockIdx.y * gridDim.x + blockIdx.x, tid = threadIdx.x;
+  if (u >= a.U) return;
   const int G = GRP ? a.G : 1;
   // Every header word is fetched before the first check, through the constant address space
   // (scalar loads, all in flight together; the empty asm statements pin the order): nothing
@@ -396,7 +397,8 @@ static hipError_t launch_attn(const fg_decode_args& a, hipStream_t s) {
 
 template <bool GRP>
 static hipError_t launch_update(const fg_decode_args& a, hipStream_t s) {
-  const dim3 grid((unsigned)a.U), block(kUpdateThreads);
+  const unsigned gx = a.U < (1 << 22) ? (unsigned)a.U : 1u << 22;   // fewer than 2^32 threads per grid dimension
+  const dim3 grid(gx, ((unsigned)a.U + gx - 1) / gx), block(kUpdateThreads);
   if (a.dtype == FG_BF16) {
     if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<2, 128, GRP>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((fg_decode_finish_kernel<2, 64, GRP>), grid, block, 0, s, a);

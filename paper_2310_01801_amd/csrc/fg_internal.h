@@ -91,7 +91,7 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 inline int fg_unit_threads(int U, int prompt_len, int max_new_tokens, int group, int row_bytes) {
   const long long tokens = (long long)prompt_len + max_new_tokens;
   if (tokens > 4608 || group > 8) return 0;
-  if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
+  if (group > 1) return U <= (1 << 22) && tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;   // 512 U < 2^32 threads
   if (U < 256) return tokens * 2 * row_bytes <= (1 << 20) ? 512 : 0;
   return (U >= 2048 && tokens <= 2048) ? 256 : 512;
 }
