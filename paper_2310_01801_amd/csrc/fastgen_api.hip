@@ -115,7 +115,7 @@ fg_layout make_layout(const fg_config& c) {
   L.pool_tokens = (int64_t)pool;
   L.chunk = fg_decode_chunk(c.prompt_len, c.max_new_tokens);
   L.max_chunks = (int64_t)(pool / (size_t)L.chunk + U);
-  L.unit_threads = fg_unit_threads(c.num_units, c.prompt_len, c.max_new_tokens, (int)G, (int)(d * e));
+  L.unit_threads = fg_unit_threads(c);
   size_t o = layout_profile_part(c, L);
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
   L.ck = take(pool * d * e);

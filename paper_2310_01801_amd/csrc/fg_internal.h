@@ -87,13 +87,18 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 //   256 of 3000, G = 8                             159 / 166;  32 of 2000, G = 2: 23 / 31
 //   64 of 3000, G = 8                              80 / 149
 // So: long units stay split (a few of them decide how long the launch takes), and where there are
-// fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit.
-inline int fg_unit_threads(int U, int prompt_len, int max_new_tokens, int group, int row_bytes) {
-  const long long tokens = (long long)prompt_len + max_new_tokens;
+// fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit. The step
+// is a one-dimensional launch: 512 threads per unit only while that stays below 2^32 threads.
+inline int fg_unit_threads(const fg_config& c) {
+  const int U = c.num_units, group = c.group_size > 1 ? c.group_size : 1;
+  const long long tokens = (long long)c.prompt_len + c.max_new_tokens;
+  const int row_bytes = c.head_dim * (c.dtype == FG_BF16 ? 2 : 4);
   if (tokens > 4608 || group > 8) return 0;
-  if (group > 1) return U <= (1 << 22) && tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;   // 512 U < 2^32 threads
+  if (group == 1 && U >= 2048 && tokens <= 2048) return 256;
+  if (U > (1 << 22)) return 0;
+  if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
   if (U < 256) return tokens * 2 * row_bytes <= (1 << 20) ? 512 : 0;
-  return (U >= 2048 && tokens <= 2048) ? 256 : 512;
+  return 512;
 }
 
 // ---------------------------------------------------------------- launch arguments
