@@ -1,8 +1,11 @@
 """Shapes at the edges of the kernels' tiles and dispatch rules, against the float64 oracle."""
+import math
+
 import pytest
+import torch
 
 import fg_harness as H
-from paper_2310_01801_amd import synth
+from paper_2310_01801_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +107,29 @@ def test_grouped_decode_step_forms(heads, n, S, d, dtype, G):
     check = sorted({0, 1, 2, heads // 2, heads - 1} & set(range(heads)))
     rep = H.compare(run, check_units=check, probe_steps=(1,), cover_policies=1)
     H.log_report(f"grouped forms U={heads} n={n} S={S} d={d} {dtype} G={G}", rep)
+
+
+# float32 outputs of a grouped step: both forms of the step on the same inputs (which one runs depends
+# on the tokens reserved), against softmax(q K^T) V in float64. The one-workgroup-per-unit form walks a
+# whole unit with one accumulator per lane group, the split form 256 tokens at a time, so the first one
+# must not be the worse: 1.1 covers the different order of the sums; one chain over all tokens of a
+# lane group (n / 16 at d = 128) has 1.17 times the split form's error in the first case.
+@pytest.mark.parametrize("U,n,d,G", [(24, 1000, 128, 2), (24, 500, 64, 4), (256, 2400, 128, 2)])
+def test_grouped_float32_outputs_as_accurate_as_the_split_form(U, n, d, G):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + G)
+    Q, K, V = (torch.randn(x, n, d, generator=gen, device="cuda:0") for x in (U * G, U, U))
+    q, k, v = (torch.randn(x, d, generator=gen, device="cuda:0") for x in (U * G, U, U))
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    Kd, Vd = torch.cat([K, k[:, None]], 1).double(), torch.cat([V, v[:, None]], 1).double()
+    s = (Kd[:, None] * q.view(U, G, 1, d).double()).sum(3) * float(torch.tensor(1.0 / math.sqrt(d), dtype=torch.float32))
+    ref = (torch.softmax(s, 2)[..., None] * Vd[:, None]).sum(2).view(U * G, d)
+    err = {}
+    for form, S in (("unit", 1), ("split", 4700 - n)):
+        fg = binding.FastGen(binding.make_config(U, 1, d, torch.float32, n, S, 0.95, 0.3, 0.3, forced_policy=4, group_size=G))
+        fg.fastgen_profile(Q, K, cls)
+        fg.fastgen_compact(K, V)
+        out = fg.fastgen_decode_step(q, k, v, cls[:, 0])
+        err[form] = float((out.double() - ref).norm() / ref.norm())
+        fg.close()
+    print(f"[accuracy] grouped float32 U={U} n={n} d={d} G={G}: {err}", flush=True)
+    assert err["unit"] <= 1.1 * err["split"], err
