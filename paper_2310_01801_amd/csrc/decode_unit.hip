@@ -43,7 +43,10 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
   const int Lold = __builtin_amdgcn_readfirstlane(rec.w), L = Lold + 1;
   const int off_lo = __builtin_amdgcn_readfirstlane(rec_off.x), off_hi = __builtin_amdgcn_readfirstlane(rec_off.y);
   const int pword = __builtin_amdgcn_readfirstlane(rec_off.z);
-  if (L > cap) return;  // cannot happen while the host bounds the step count
+  if (L > cap) {  // cannot happen while the host bounds the step count
+    if (threadIdx.x == 0) a.flags[0] = 1;
+    return;
+  }
   const int64_t off = ((int64_t)off_hi << 32) | (uint32_t)off_lo;
   const int policy = pword & 0xff, comp = pword >> 8;
   const bool probing = a.probe != nullptr;

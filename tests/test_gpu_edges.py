@@ -133,3 +133,30 @@ def test_grouped_float32_outputs_as_accurate_as_the_split_form(U, n, d, G):
         fg.close()
     print(f"[accuracy] grouped float32 U={U} n={n} d={d} G={G}: {err}", flush=True)
     assert err["unit"] <= 1.1 * err["split"], err
+
+
+# A step that finds no free slot in a unit's reservation leaves the cache alone and reports it. The
+# reservations rule this out, so the test takes a unit's last free slots away in its step record
+# (unit, 0, slots reserved, tokens held, offset, policy word, 0) inside the workspace.
+@pytest.mark.parametrize("G", [1, 2])
+def test_step_without_a_free_slot_is_reported(G):
+    U, n, d = 3, 20, 64
+    gen = torch.Generator(device="cuda:0").manual_seed(11)
+    Q, K = (torch.randn(x, n, d, generator=gen, device="cuda:0") for x in (U * G, U))
+    q, k = (torch.randn(x, d, generator=gen, device="cuda:0") for x in (U * G, U))
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.float32, n, 4, 0.95, 0.3, 0.3, forced_policy=4, group_size=G))
+    fg.workspace.zero_()
+    fg.fastgen_profile(Q, K, cls)
+    fg.fastgen_compact(K, K)
+    words = fg.workspace[:fg.workspace.numel() // 32 * 32].view(torch.int32).view(-1, 8)
+    record = (words[:, 0] < U) & (words[:, 1] == 0) & (words[:, 2] == n + 4) & (words[:, 3] == n) & (words[:, 5] == 0)
+    rows = torch.nonzero(record).flatten()
+    assert rows.numel() == U and sorted(words[rows, 0].tolist()) == list(range(U)), rows
+    row = rows[words[rows, 0] == 1]
+    words[row, 2] = n
+    fg.fastgen_decode_step(q, k, k, cls[:, 0])
+    st = fg.fastgen_export_state(lengths_only=True)
+    assert int(st["status"].item()) == binding.FG_ECAP
+    lengths = st["lengths"].tolist()   # the other units' workgroups may have seen the report and stopped
+    assert lengths[1] == n and set(lengths) <= {n, n + 1}
