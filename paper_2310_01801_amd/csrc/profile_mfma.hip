@@ -376,10 +376,9 @@ __device__ __forceinline__ void fg_col_tile(const f32x16& ac, const float (&ms)[
   for (int i = 0; i < 16; ++i) {
     const int o = (i >> 2) * 8 + (i & 3), dist = dbase + o;
     const bool ok = (dist >= 0) && (o < rlim);
-    const float e = fg_exp2(fmaf(ac[i], c, -ms[i]));   // may be huge where masked: select, do not scale
-    const float p = (ok ? e : 0.f) * il[i];
-    s += p;
-    sb += dist < w ? p : 0.f;
+    const float e = ok ? fg_exp2(fmaf(ac[i], c, -ms[i])) : 0.f;   // may be huge where masked: select, do not scale
+    s = fmaf(e, il[i], s);   // both sums by one rounding per term: a band over everything is the column sum
+    sb = fmaf(dist < w ? e : 0.f, il[i], sb);
   }
   col_acc += (double)s;
   band_acc += (double)sb;

@@ -160,3 +160,20 @@ def test_step_without_a_free_slot_is_reported(G):
     assert int(st["status"].item()) == binding.FG_ECAP
     lengths = st["lengths"].tolist()   # the other units' workgroups may have seen the report and stopped
     assert lengths[1] == n and set(lengths) <= {n, n + 1}
+
+
+# A local window over the whole prompt keeps every column in every row, as special tokens everywhere do:
+# the band sums are then the column sums, term by term, and the two recoveries the same number. The
+# split-stream sweeps (few units) and the 256-owner blocks.
+@pytest.mark.parametrize("U,n,d,G", [(2, 33, 64, 1), (32, 333, 128, 1), (4, 300, 64, 4), (3, 300, 128, 2), (300, 400, 128, 1)])
+def test_band_over_the_whole_prompt_is_the_column_sum(U, n, d, G):
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    Q, K = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U))
+    cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
+    cfg = binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 1.0, 0.3, family=(8, 1, 0, 0), group_size=G)
+    fg = binding.FastGen(cfg)
+    _, recovery, _ = fg.fastgen_profile(Q, K, cls)
+    rec = recovery.cpu()
+    fg.close()
+    assert torch.equal(rec[:, 0], rec[:, 1]), (rec[:, 0] - rec[:, 1]).abs().max()
+    assert float((rec[:, 0] - 1.0).abs().max()) < 1e-6
