@@ -358,7 +358,11 @@ __device__ __forceinline__ void fg_row_tile(const f32x16& ac, float c, int lim, 
   float tmax = FG_NEG_BIG;   // causal: columns with an offset <= lim are visible
 #pragma unroll
   for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, ((i >> 2) * 8 + (i & 3)) <= lim ? ac[i] * c : FG_NEG_BIG);
-  const float m_new = fmaxf(m_run, tmax);
+  // The shift is rounded up to a whole number: rescaling a wave's sum and merging the four waves then
+  // multiply by powers of two, without error. With the maximum itself, one hardware exponential per tile
+  // and wave: column sums of 32 units of 333 tokens 2.81e-8 off 64 bits and the rows' masses 1.7e-9 too
+  // large in the mean (256-owner form: 2.81e-8, 1.5e-9); so 2.75e-8 and -4e-10, in the same time.
+  const float m_new = fmaxf(m_run, ceilf(tmax));
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {

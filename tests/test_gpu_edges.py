@@ -177,3 +177,21 @@ def test_band_over_the_whole_prompt_is_the_column_sum(U, n, d, G):
     fg.close()
     assert torch.equal(rec[:, 0], rec[:, 1]), (rec[:, 0] - rec[:, 1]).abs().max()
     assert float((rec[:, 0] - 1.0).abs().max()) < 1e-6
+
+
+# Rows of the attention map sum to 1. A float32 1/l per row is off by up to half an ulp, 1.7e-8 rms in
+# either direction: over 10^4 rows and more the mean mass is within 4 x 1.7e-8 / 100 of 1 unless merging
+# the waves of the split-stream sweep adds an error of one sign (one hardware exponential per merge: 1.7e-9).
+@pytest.mark.parametrize("U,n,d", [(32, 333, 128), (32, 333, 64), (16, 1000, 64)])
+def test_split_stream_row_masses_have_no_bias(U, n, d):
+    masses = []
+    for seed in range(8):
+        gen = torch.Generator(device="cuda:0").manual_seed(seed)
+        Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+        cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
+        fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3))
+        _, recovery, _ = fg.fastgen_profile(Q, K, cls)
+        masses.append(float(recovery[:, 0].mean()) - 1.0)
+        fg.close()
+    print(f"[accuracy] row masses U={U} n={n} d={d}: mean {sum(masses) / 8:.2e}", flush=True)
+    assert abs(sum(masses) / 8) < 7e-10, masses
