@@ -277,12 +277,12 @@ __global__ __launch_bounds__(256) void fg_decode_partial_kernel(fg_decode_args a
 // Latency-bound: one workgroup's chain of loads, block reductions and moves per unit. 512 threads
 // shorten the per-thread part and hold 6144 tokens in registers without a spill (256 threads,
 // before: 640 units of 8192 tokens 47 -> 22 us with the shorter chain of fg_update.h, 2560 of them
-// 90 -> 60, 256 grouped units of 2048 30 -> 22).
-constexpr int kUpdateThreads = 512;
-
-template <int ESIZE, int D, bool GRP>
-__global__ __launch_bounds__(kUpdateThreads, GRP ? 2 : 4) void fg_decode_finish_kernel(fg_decode_args a) {
-  constexpr int NT = kUpdateThreads;
+// 90 -> 60, 256 grouped units of 2048 30 -> 22). Four waves per SIMD keep two workgroups of 512 threads on
+// a CU: left to itself the grouped form takes 134 registers, and 257 units and more ran in two rounds (300
+// of 500 tokens, twelve heads, policy 2: 95 us per step, with 128 registers 78). fg_update_threads says
+// where 256 threads serve a grouped unit.
+template <int ESIZE, int D, bool GRP, int NT>
+__global__ __launch_bounds__(NT, 4) void fg_decode_finish_kernel(fg_decode_args a) {
   __shared__ fg_update_smem sh;
   __shared__ float s_M[16];  // per query head: merged maximum of the scaled logits
   const int u = blockIdx.y * gridDim.x + blockIdx.x, tid = threadIdx.x;
@@ -395,16 +395,16 @@ static hipError_t launch_attn(const fg_decode_args& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool GRP>
+template <bool GRP, int NT>
 static hipError_t launch_update(const fg_decode_args& a, hipStream_t s) {
   const unsigned gx = a.U < (1 << 22) ? (unsigned)a.U : 1u << 22;   // fewer than 2^32 threads per grid dimension
-  const dim3 grid(gx, ((unsigned)a.U + gx - 1) / gx), block(kUpdateThreads);
+  const dim3 grid(gx, ((unsigned)a.U + gx - 1) / gx), block(NT);
   if (a.dtype == FG_BF16) {
-    if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<2, 128, GRP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((fg_decode_finish_kernel<2, 64, GRP>), grid, block, 0, s, a);
+    if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<2, 128, GRP, NT>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((fg_decode_finish_kernel<2, 64, GRP, NT>), grid, block, 0, s, a);
   } else {
-    if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<4, 128, GRP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((fg_decode_finish_kernel<4, 64, GRP>), grid, block, 0, s, a);
+    if (a.d == 128) hipLaunchKernelGGL((fg_decode_finish_kernel<4, 128, GRP, NT>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((fg_decode_finish_kernel<4, 64, GRP, NT>), grid, block, 0, s, a);
   }
   return hipGetLastError();
 }
@@ -415,5 +415,6 @@ hipError_t fg_launch_decode_attn(const fg_decode_args& a, hipStream_t s) {
 }
 
 hipError_t fg_launch_decode_update(const fg_decode_args& a, hipStream_t s) {
-  return a.G > 1 ? launch_update<true>(a, s) : launch_update<false>(a, s);
+  if (a.G == 1) return launch_update<false, 512>(a, s);
+  return a.update_threads == 256 ? launch_update<true, 256>(a, s) : launch_update<true, 512>(a, s);
 }

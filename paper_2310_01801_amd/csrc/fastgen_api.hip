@@ -116,6 +116,7 @@ fg_layout make_layout(const fg_config& c) {
   L.chunk = fg_decode_chunk(c.prompt_len, c.max_new_tokens);
   L.max_chunks = (int64_t)(pool / (size_t)L.chunk + U);
   L.unit_threads = fg_unit_threads(c);
+  L.update_threads = fg_update_threads(c);
   size_t o = layout_profile_part(c, L);
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
   L.ck = take(pool * d * e);
@@ -447,6 +448,7 @@ static fg_status decode_step_impl(fastgen_ctx* ctx, const void* q, const void* k
   da.G = group_of(c);
   da.r_f = c.r_f; da.scale = ctx->scale; da.max_chunks = L.max_chunks; da.chunk = L.chunk;
   da.unit_threads = L.unit_threads;
+  da.update_threads = L.update_threads;
   da.probe = probe;
   family_of(c, da.family);
   hipStream_t s = static_cast<hipStream_t>(stream);

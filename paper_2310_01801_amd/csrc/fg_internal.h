@@ -45,6 +45,7 @@ struct fg_layout {
   int64_t max_chunks;
   int chunk;        // tokens per decode work item (128 or 256)
   int unit_threads; // 0: split-KV decode step; else one workgroup of this size per unit
+  int update_threads; // workgroup size of the split-KV step's update kernel
 };
 
 struct fastgen_ctx {
@@ -101,6 +102,16 @@ inline int fg_unit_threads(const fg_config& c) {
   return 512;
 }
 
+// Threads per unit of the split-KV step's update kernel. Where there are more grouped units than
+// 512-thread workgroups fit the card (two per CU), smaller ones take turns sooner, as long as they hold a
+// unit in registers (256 threads: 3072 tokens). 512 / 256 threads, us per step: 600 units of 500 tokens, G =
+// 16, 168 / 162, 2048 of 300, G = 16, 335 / 282, 1500 of 500, G = 9, 198 / 179, 700 of 1500, G = 16, 361 /
+// 354 (full caches 420 / 400, forced policy 3 574 / 603); but 600 of 5000, G = 4, 286 / 340 and 300 of 500, G =
+// 12, 83 / 85.
+inline int fg_update_threads(const fg_config& c) {
+  return c.group_size > 1 && c.num_units > 512 && c.prompt_len + c.max_new_tokens <= 3072 ? 256 : 512;
+}
+
 // ---------------------------------------------------------------- launch arguments
 struct fg_profile_args {
   const void* Q; const void* K;
@@ -143,6 +154,7 @@ struct fg_decode_args {
   int64_t max_chunks;
   int chunk;       // tokens per work item (128 or 256)
   int unit_threads; // workgroup size of the one-workgroup-per-unit form
+  int update_threads; // workgroup size of the update kernel of the split form
 };
 
 struct fg_export_args {

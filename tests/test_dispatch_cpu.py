@@ -1,8 +1,10 @@
 """The host rules that choose a kernel form by sizes, compiled for the host and asked directly."""
 import ctypes
 import os
+import struct
 import subprocess
 
+import msgpack
 import pytest
 
 from paper_2310_01801_amd import binding
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = """
 #include "paper_2310_01801_amd/csrc/fg_internal.h"
 extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
+extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
 
 
@@ -37,3 +40,37 @@ def test_decode_step_grid_stays_below_2_to_32_threads(rules, n, S, G):
         cfg = _cfg(U, n, S, cache_tokens=U * 8, group_size=G)
         assert binding.fastgen_workspace_bytes(cfg) > 0
         assert U * rules.unit_threads(ctypes.byref(cfg)) < 1 << 32, (U, n, S, G)
+
+
+def _kernel_metadata(path):
+    """Name -> metadata of every kernel in the AMDGPU code objects inside a library built here."""
+    data, out, at = open(path, "rb").read(), {}, 0
+    while (at := data.find(b"\x7fELF", at + 1)) > 0:
+        if struct.unpack_from("<H", data, at + 18)[0] != 224:   # EM_AMDGPU
+            continue
+        phoff, (phentsize, phnum) = struct.unpack_from("<Q", data, at + 32)[0], struct.unpack_from("<HH", data, at + 54)
+        for i in range(phnum):
+            kind, _, offset, _, _, size = struct.unpack_from("<IIQQQQ", data, at + phoff + i * phentsize)
+            note, end = at + offset, at + offset + size
+            while kind == 4 and note < end:   # PT_NOTE
+                name_size, desc_size, note_type = struct.unpack_from("<III", data, note)
+                desc = note + 12 + (name_size + 3) // 4 * 4
+                if note_type == 32 and data[note + 12:note + 18] == b"AMDGPU":
+                    out.update({k[".name"]: k for k in msgpack.unpackb(data[desc:desc + desc_size])["amdhsa.kernels"]})
+                note = desc + (desc_size + 3) // 4 * 4
+    return out
+
+
+# Two workgroups of 512 threads of the update kernel stay on a CU: at most 128 vector registers each
+# (512 per SIMD lane, four waves on it). The grouped one took 134.
+def test_update_kernels_keep_two_workgroups_per_cu():
+    kernels = {k: v for k, v in _kernel_metadata(binding.LIB_PATH).items() if "fg_decode_finish_kernel" in k}
+    assert len(kernels) >= 8
+    for name, meta in kernels.items():
+        assert meta[".vgpr_count"] <= 128 and meta.get(".vgpr_spill_count", 0) == 0, (name, meta[".vgpr_count"])
+
+
+def test_update_threads(rules):
+    for U, n, S, G, want in ((512, 300, 16, 16, 512), (513, 300, 16, 16, 256), (513, 3072, 0, 9, 256), (513, 3072, 1, 9, 512),
+                             (4096, 300, 16, 1, 512)):
+        assert rules.update_threads(ctypes.byref(_cfg(U, n, S, group_size=G))) == want

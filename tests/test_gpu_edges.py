@@ -195,3 +195,15 @@ def test_split_stream_row_masses_have_no_bias(U, n, d):
         fg.close()
     print(f"[accuracy] row masses U={U} n={n} d={d}: mean {sum(masses) / 8:.2e}", flush=True)
     assert abs(sum(masses) / 8) < 7e-10, masses
+
+
+# the grouped split form's update kernel: 512 threads up to 512 units, above them 256 while a unit fits
+# their registers (3072 tokens)
+@pytest.mark.parametrize("heads,n,S,G", [(257, 60, 6, 9), (512, 60, 6, 9), (513, 60, 6, 9), (513, 300, 4, 12), (513, 3068, 4, 9),
+                                         (513, 3069, 4, 9)])
+def test_grouped_update_kernel_sizes(heads, n, S, G):
+    w = W["llama7b_b1"].scaled(name="grouped_update", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=64,
+                               dtype="bf16", seed=300 + n)
+    run = H.GpuRun(w, range(w.num_units), group_size=G, forced_policy=2)
+    rep = H.compare(run, check_units=[0, heads - 1], probe_steps=(1,))
+    H.log_report(f"grouped update U={heads} n={n} S={S} G={G}", rep)
