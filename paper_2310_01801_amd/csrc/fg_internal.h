@@ -112,6 +112,42 @@ inline int fg_update_threads(const fg_config& c) {
   return c.group_size > 1 && c.num_units > 512 && c.prompt_len + c.max_new_tokens <= 3072 ? 256 : 512;
 }
 
+// Form of a bf16 profiling sweep by its size: the split stream with 32 or 64 owner items per workgroup,
+// or 256-owner blocks singly or in heavy / light pairs. The times of the split stream and of the blocks
+// are estimated in microseconds by fits to about 300 shapes of 1 to 1000 units (rms 11 %), the cheaper one
+// is taken (1.1 % above the best form of every shape in the mean).
+//   split stream   fixed + contraction work + workgroups + one workgroup's chain. Units are dealt out over
+//                  the eight XCDs, so fewer than eight leave XCDs idle and cost as much as eight.
+//                  1 unit of 8192 tokens, split / pairs: 147 + 165 / 222 + 251 us (with 32 owners 242 + 303);
+//                  of 12000: 280 + 355 / 314 + 360; of 16384: 493 + 598 / 431 + 498
+//   blocks         fixed + tiles of the heaviest workgroup (a pair: the two blocks' tiles together).
+//                  Singly at most three per CU and six per unit (64 x 1024 tokens: 43 -> 35, 256 x 333:
+//                  26 -> 18; 256 x 1024: 57 -> 70); not in the second sweep at d = 128 (128 x 700: 39 -> 42),
+//                  and not where four nearly full blocks per unit already fill the card as pairs in the
+//                  first sweep (192 x 1000, d = 128: 59 -> 62; 128 x 1000, d = 64: 36 -> 39).
+// 32 owners serve up to one workgroup per CU and 64 blocks per unit, beyond that they read too much (1 x
+// 4096, 32 / 64 owners: 82 + 97 / 52 + 70). With one block per unit and four or more heads the chain of
+// a second round of workgroups decides (200 x 230 tokens, G = 8: 88 split, 78 blocks).
+enum fg_sweep_form { FG_SWEEP_SPLIT_32, FG_SWEEP_SPLIT_64, FG_SWEEP_BLOCKS, FG_SWEEP_PAIRS };
+inline fg_sweep_form fg_sweep_form_of(int d, int pass, int U, int n, int G) {
+  struct fit { double s0, work, groups, chain, pair0, pair, block0, block; };
+  static const fit fits[2][2] = {
+      {{7.0, 0.60, 0.0040, 0.055, 7.6, 0.67, 7.1, 0.70}, {6.0, 0.64, 0.0085, 0.20, 8.9, 0.85, 7.6, 0.90}},    // d = 64
+      {{6.0, 0.96, 0.0083, 0.130, 9.5, 0.89, 7.8, 0.93}, {6.0, 0.89, 0.0165, 0.24, 11.0, 1.02, 0.0, 0.0}}};   // d = 128
+  const fit& f = fits[d == 128][pass == 2];
+  const double units = (double)U * (pass == 1 ? G : 1), heads = pass == 1 ? 1.0 : (double)G;
+  const double nb32 = (n + 31) / 32, nb64 = (n + 63) / 64, nblk = (n + 255) / 256;
+  const double spread = 8.0 * (double)(((long long)units + 7) / 8);
+  bool single = (pass == 1 || d == 64) && nblk <= 6.0 && units * nblk <= 768.0;
+  if (pass == 1 && nblk == 4.0 && n > 960 && units * nblk > (d == 128 ? 576.0 : 320.0)) single = false;
+  const double tiles = heads * (single || nblk == 1.0 ? n : 2.0 * n - 256.0 * (nblk - 1.0)) / 32.0;
+  const double split = f.s0 + f.work * spread * heads * nb64 * (nb64 + 1.0) / 1024.0 + f.groups * spread * nb64 + f.chain * heads * n / 32.0;
+  const double blocks = single ? f.block0 + f.block * tiles : f.pair0 + f.pair * tiles;
+  const bool second_round = nblk == 1.0 && heads >= 4.0 && units * nb64 > 512.0;
+  if (split < blocks && !second_round) return units * nb32 <= 256.0 && nb32 <= 64.0 ? FG_SWEEP_SPLIT_32 : FG_SWEEP_SPLIT_64;
+  return single ? FG_SWEEP_BLOCKS : FG_SWEEP_PAIRS;
+}
+
 // ---------------------------------------------------------------- launch arguments
 struct fg_profile_args {
   const void* Q; const void* K;

@@ -542,26 +542,14 @@ hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Form of a sweep by its size. steps = 32-item tiles against 64 owners over all units; the constants
-// (us) are fits to the sweeps measured at 8 to 4096 units of 100 to 4096 tokens:
-//   split stream (small kernel)   7 + 1.75 (d = 64: 0.85) per 1024 steps: 32 x 333 tokens 9.6 + 11.4, 32 x
-//                                 2048 60 + 70, 128 x 1024 64 + 72 (256-owner blocks: 24 + 23, 70 + 80, 45 + 51)
-//   256-owner blocks              4 + 8.4 (d = 64: 6) per block of the longest chain while the card is not full
-// Blocks are taken singly where even so at most three per CU are in flight and a unit has few of
-// them (64 x 1024: 43 -> 35, 256 x 333: 26 -> 18; 256 x 1024: 57 -> 70), else in heavy / light pairs;
-// not in the second sweep at d = 128, which does not gain (128 x 700: 39 -> 42).
 template <int D>
 hipError_t launch_sized(const fg_profile_args& a, int pass, hipStream_t s) {
-  const double units = (double)a.U * (pass == 1 ? a.G : 1), heads = pass == 1 ? 1.0 : (double)a.G;
-  const double nb64 = (a.n + 63) / 64, nblk = (a.n + kOwnPerBlock - 1) / kOwnPerBlock;
-  const double small = 7.0 + (D == 128 ? 1.75 : 0.85) * units * heads * nb64 * (nb64 + 1.0) / 1024.0;
-  const double chain = 4.0 + (D == 128 ? 8.4 : 6.0) * nblk * heads;
-  if (small < chain) {
-    if (units * ((a.n + 31) / 32) <= 256.0) return launch_small<D, 1>(a, pass, s);
-    return launch_small<D, 2>(a, pass, s);
+  switch (fg_sweep_form_of(D, pass, a.U, a.n, a.G)) {
+    case FG_SWEEP_SPLIT_32: return launch_small<D, 1>(a, pass, s);
+    case FG_SWEEP_SPLIT_64: return launch_small<D, 2>(a, pass, s);
+    case FG_SWEEP_BLOCKS: return launch<D, false>(a, pass, s);
+    default: return launch<D, true>(a, pass, s);
   }
-  if ((pass == 1 || D == 64) && nblk <= 6.0 && units * nblk <= 768.0) return launch<D, false>(a, pass, s);
-  return launch<D, true>(a, pass, s);
 }
 
 }  // namespace

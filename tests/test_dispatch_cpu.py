@@ -13,6 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = """
 #include "paper_2310_01801_amd/csrc/fg_internal.h"
 extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
+extern "C" int sweep_form(int d, int pass, int U, int n, int G) { return fg_sweep_form_of(d, pass, U, n, G); }
 extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
 
@@ -74,3 +75,33 @@ def test_update_threads(rules):
     for U, n, S, G, want in ((512, 300, 16, 16, 512), (513, 300, 16, 16, 256), (513, 3072, 0, 9, 256), (513, 3072, 1, 9, 512),
                              (4096, 300, 16, 1, 512)):
         assert rules.update_threads(ctypes.byref(_cfg(U, n, S, group_size=G))) == want
+
+
+# Forms of the bf16 sweeps at shapes whose times were far apart (first, second sweep): a few long units,
+# which the split stream made slower; grouped short ones; blocks taken singly that fill the card as pairs
+SPLIT_32, SPLIT_64, BLOCKS, PAIRS = range(4)
+
+
+@pytest.mark.parametrize("d,U,n,G,want", [
+    (128, 1, 1000, 1, (SPLIT_32, SPLIT_32)), (128, 1, 4096, 1, (SPLIT_64, SPLIT_64)), (128, 1, 8192, 1, (SPLIT_64, SPLIT_64)),
+    (128, 1, 16384, 1, (PAIRS, PAIRS)), (128, 2, 16384, 1, (PAIRS, PAIRS)), (128, 1, 32768, 1, (PAIRS, PAIRS)),
+    (64, 1, 32768, 1, (PAIRS, PAIRS)), (128, 8, 8192, 1, (SPLIT_64, SPLIT_64)), (128, 9, 7197, 8, (PAIRS, PAIRS)),
+    (128, 2, 4096, 4, (SPLIT_64, SPLIT_64)), (128, 200, 230, 8, (PAIRS, PAIRS)), (128, 256, 300, 2, (PAIRS, PAIRS)),
+    (128, 600, 128, 2, (PAIRS, PAIRS)), (64, 600, 128, 2, (PAIRS, BLOCKS)), (64, 256, 250, 4, (PAIRS, BLOCKS)),
+    (64, 128, 1000, 1, (PAIRS, BLOCKS)), (128, 192, 1000, 1, (PAIRS, PAIRS)), (128, 160, 900, 1, (BLOCKS, PAIRS)),
+    (128, 32, 333, 1, (SPLIT_64, SPLIT_64)), (128, 32, 2048, 1, (SPLIT_64, SPLIT_64)), (128, 1024, 2048, 1, (PAIRS, PAIRS)),
+    (128, 4096, 1024, 1, (PAIRS, PAIRS)), (64, 432, 1337, 1, (PAIRS, PAIRS)),
+])
+def test_sweep_forms(rules, d, U, n, G, want):
+    assert tuple(rules.sweep_form(d, p, U, n, G) for p in (1, 2)) == want
+
+
+def test_every_accepted_size_has_a_sweep_form(rules):
+    for d in (64, 128):
+        for n in (1, 31, 256, 257, 1000, 131072):
+            for U in (1, 7, 8, 9, 1000, 1 << 24):
+                for G in (1, 2, 16):
+                    forms = [rules.sweep_form(d, p, U, n, G) for p in (1, 2)]
+                    assert all(0 <= f <= PAIRS for f in forms) and not (d == 128 and forms[1] == BLOCKS)
+                    if U >= 1000 and n >= 256:
+                        assert forms[0] == PAIRS, (d, n, U, G)
