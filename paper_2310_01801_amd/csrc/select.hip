@@ -522,20 +522,25 @@ hipError_t fg_launch_select(const fg_select_args& a, hipStream_t s) {
   // before the tokens stayed in registers: 256 units of 3000 tokens 27 / 38 us, 1024 of 2048
   // 44 / 37, 4096 of 1024 120 / 81), and as many as hold the prompt in at most 12 register slots.
   // Measured, us, with everything re-read per pass and twelve single block sums / now: 32 units of
-  // 333 tokens 14.3 / 7.3, 1024 of 2048 37 / 29, 4096 of 1024 81 / 47, 256 of 3000 38 / 19, 1600 of
-  // 4096 111 / 80, 640 of 8192 137 / 80.
+  // 333 tokens 14.3 / 7.3, 1024 of 2048 37 / 29, 4096 of 1024 81 / 47, 256 of 3000 38 / 19, 640 of 8192
+  // 137 / 80. Few workgroups of 1024 threads fit at once and twelve slots of 256 hold three waves per SIMD,
+  // so many units take fewer slots or smaller workgroups where that is enough: 1024 x 8 / 512 x 12 slots,
+  // 513 units of 4400 52 / 41, 1600 of 4400 125 / 83 (re-read 115), 1600 of 6000 139 / 91; 256 x 12 / x 10,
+  // 1024 of 2100 39 / 28, 8192 of 2500 220 / 174 (re-read 213); 4096 of 3000 with twelve 134 (138).
 #define FG_SELECT(NT, NC) hipLaunchKernelGGL((fg_select_kernel<NT, NC>), dim3((unsigned)a.U), dim3(NT), 0, s, a)
   if (a.U <= 512 || a.n > 3072) {
     if (a.n <= 512) FG_SELECT(512, 1);
     else if (a.n <= 1024) FG_SELECT(512, 2);
     else if (a.n <= 2048) FG_SELECT(512, 4);
     else if (a.n <= 4096) FG_SELECT(512, 8);
+    else if (a.n <= 6144 && a.U > 512) FG_SELECT(512, 12);
     else if (a.n <= 8192) FG_SELECT(1024, 8);
     else FG_SELECT(512, 0);
   } else {
     if (a.n <= 512) FG_SELECT(256, 2);
     else if (a.n <= 1024) FG_SELECT(256, 4);
     else if (a.n <= 2048) FG_SELECT(256, 8);
+    else if (a.n <= 2560) FG_SELECT(256, 10);
     else FG_SELECT(256, 12);
   }
 #undef FG_SELECT

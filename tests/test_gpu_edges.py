@@ -207,3 +207,13 @@ def test_grouped_update_kernel_sizes(heads, n, S, G):
     run = H.GpuRun(w, range(w.num_units), group_size=G, forced_policy=2)
     rep = H.compare(run, check_units=[0, heads - 1], probe_steps=(1,))
     H.log_report(f"grouped update U={heads} n={n} S={S} G={G}", rep)
+
+
+# selection of many units: ten slots of 256 threads up to 2560 tokens, twelve of 512 up to 6144
+@pytest.mark.parametrize("heads,n", [(513, 2560), (513, 2561), (513, 4097), (513, 6144), (513, 6145)])
+def test_selection_sizes_of_many_units(heads, n):
+    w = W["llama7b_b1"].scaled(name="selection_many", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=64,
+                               seed=200 + n)
+    run = H.GpuRun(w, range(w.num_units))
+    rep = H.compare(run, check_units=[0, heads - 1])
+    H.log_report(f"selection U={heads} n={n}", rep)
