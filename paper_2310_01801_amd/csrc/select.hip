@@ -247,12 +247,18 @@ __device__ __forceinline__ int fg_count_place(int* counter, bool active, int key
   return place;
 }
 
-constexpr int kSortUnits = 16384;   // units that are ordered by size (above, the tail of a launch is a small part)
+// Whether the units are ordered by size. The order pays where the longest units would decide the end of
+// a launch and costs one workgroup's counting sort in fastgen_compact (inside the offsets kernel's own time
+// up to 1024 units). Unordered / ordered, compaction and decode step in us: 1024 units of 2000 tokens 221 +
+// 125 / 224 + 117, 2048 of 1024 249 + 127 / 250 + 116, 4096 of 1024 495 + 228 / 506 + 221; but 4096 of 150,
+// d = 64, 59 + 30 / 66 + 30, 6000 of 400 264 + 135 / 277 + 133, 16384 of 300 349 + 149 / 381 + 162.
+constexpr int kSortUnits = 4096;
+inline bool sorts_units(int U, int max_cap) { return U <= 1024 || (U <= kSortUnits && max_cap >= 512); }
 
 // Single workgroup: off[u] = sum_{v<u} cap[v]. BY_UNIT false: chunk_off[u] = sum_{v<u} ceil(cap[v]/chunk).
-// BY_UNIT true: chunk_off[u] = place of unit u among the units, longest reservations first (a
-// counting sort into 64 classes; the order inside a class does not matter), and for few units
-// their records too.
+// BY_UNIT true: chunk_off[u] = place of unit u among the units, with `ordered` longest reservations first
+// (a counting sort into 64 classes; the order inside a class does not matter), and for few units their
+// records too.
 template <bool BY_UNIT>
 __global__ __launch_bounds__(1024) void fg_offsets_kernel(const int32_t* __restrict__ cap,
                                                           int64_t* __restrict__ off,
@@ -261,14 +267,14 @@ __global__ __launch_bounds__(1024) void fg_offsets_kernel(const int32_t* __restr
                                                           int64_t pool_tokens, int64_t max_chunks, int chunk,
                                                           int max_cap, int32_t* __restrict__ unit_rec,
                                                           const int32_t* __restrict__ len,
-                                                          const int32_t* __restrict__ policy) {
+                                                          const int32_t* __restrict__ policy, int ordered) {
   __shared__ int red[20];
   __shared__ long long wsum[16];
   __shared__ int class_at[64];
   __shared__ uint8_t s_class[BY_UNIT ? kSortUnits : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float to_class = 63.0f / (float)max_cap;
-  const bool sorted = BY_UNIT && U <= kSortUnits;
+  const bool sorted = BY_UNIT && ordered != 0;
   if (BY_UNIT) {
     if (tid < 64) class_at[tid] = 0;
     __syncthreads();
@@ -559,11 +565,11 @@ hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32
   const dim3 blocks((unsigned)((U + 255) / 256));
   if (by_unit) {
     hipLaunchKernelGGL((fg_offsets_kernel<true>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
-                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy);
+                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy, (int)sorts_units(U, max_cap));
     if (U > 1024) hipLaunchKernelGGL(fg_unit_map_kernel, blocks, dim3(256), 0, s, chunk_off, cap, off, len, policy, item_unit, U);
   } else {
     hipLaunchKernelGGL((fg_offsets_kernel<false>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
-                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy);
+                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy, 0);
     hipLaunchKernelGGL(fg_item_map_kernel, blocks, dim3(256), 0, s, chunk_off, cap, off, len, policy, item_unit, flags, U);
   }
   return hipGetLastError();

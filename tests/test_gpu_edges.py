@@ -217,3 +217,13 @@ def test_selection_sizes_of_many_units(heads, n):
     run = H.GpuRun(w, range(w.num_units))
     rep = H.compare(run, check_units=[0, heads - 1])
     H.log_report(f"selection U={heads} n={n}", rep)
+
+
+# decode units ordered by size up to 1024 of them, and up to 4096 with 512 tokens or more
+@pytest.mark.parametrize("heads,n,S", [(1025, 508, 3), (1025, 509, 3), (4096, 509, 3), (4097, 509, 3)])
+def test_order_of_decode_units(heads, n, S):
+    w = W["llama7b_b1"].scaled(name="unit_order", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=64,
+                               seed=100 + n)
+    run = H.GpuRun(w, range(w.num_units))
+    rep = H.compare(run, check_units=[0, 1, heads // 2, heads - 1], cover_policies=1)
+    H.log_report(f"unit order U={heads} n={n} S={S}", rep)
