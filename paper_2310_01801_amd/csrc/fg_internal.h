@@ -90,15 +90,37 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 // So: long units stay split (a few of them decide how long the launch takes), and where there are
 // fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit. The step
 // is a one-dimensional launch: 512 threads per unit only while that stays below 2^32 threads.
+// Above 256 units some CUs hold two and take twice as long. Units of different lengths even that out
+// (300 of 3600 tokens, five kinds of heads: 57 split, 46 per unit; 320 of 4500: 90 / 102, 576 of 4500 143 /
+// 150; all heads of one kind, which only the device knows: 300 of 3500 72 / 87), except float32 rows of 512
+// bytes beyond 1856 tokens (400 of 2010: 84 / 93, 640 of 3500: 212 / 230; 400 of 1810: 84 / 88, 300 of 1220: 39 /
+// 29). Under one forced policy all units are nearly alike, and the bytes that they hold decide:
+//   full caches    257 of 2600 tokens 68 / 82, 300 of 2000 57 / 61, 300 of 4500 128 / 147; 400 of 2600 101 / 100,
+//                  257 of 1500 36 / 36; G = 2, 300 of 2000, 66 / 69, G = 4, 300 of 4400, 198 / 176
+//   policy 3       ratios 0.3, 257 of 2600 46 / 51, 513 of 4500 161 / 185, 900 of 4500 268 / 288; 513 of 3500 133 /
+//                  138, 257 of 2000 40 / 41; policy 2, 257 of 3000 34 / 28
+inline double fg_forced_share(const fg_config& c) {   // of the tokens, in front of special and punctuation ones
+  if (c.forced_policy == 4) return 1.0;
+  const int eq2 = (c.forced_policy >= 2 ? FG_COMP_FREQUENT : 0) | (c.forced_policy == 3 ? FG_COMP_LOCAL : 0);
+  const int comp = c.family[0] | c.family[1] | c.family[2] | c.family[3] ? c.family[c.forced_policy] : eq2;
+  return ((comp & FG_COMP_FREQUENT) ? c.r_f : 0.0) + ((comp & FG_COMP_LOCAL) ? c.r_l : 0.0);
+}
 inline int fg_unit_threads(const fg_config& c) {
   const int U = c.num_units, group = c.group_size > 1 ? c.group_size : 1;
   const long long tokens = (long long)c.prompt_len + c.max_new_tokens;
   const int row_bytes = c.head_dim * (c.dtype == FG_BF16 ? 2 : 4);
+  const long long unit_bytes = tokens * 2 * row_bytes;
   if (tokens > 4608 || group > 8) return 0;
   if (group == 1 && U >= 2048 && tokens <= 2048) return 256;
   if (U > (1 << 22)) return 0;
+  if (c.forced_policy >= 0 && U > 256) {
+    const double held = fg_forced_share(c) * (double)unit_bytes;
+    if (U <= 360 && held > 0.8e6 && tokens * group <= 16000) return 0;
+    if (c.forced_policy < 4 && group == 1 && held > 1.2e6) return 0;
+  }
   if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
-  if (U < 256) return tokens * 2 * row_bytes <= (1 << 20) ? 512 : 0;
+  if (U < 256) return unit_bytes <= (1 << 20) ? 512 : 0;
+  if (U > 256 && row_bytes > 256 && tokens > 1856) return 0;
   return 512;
 }
 

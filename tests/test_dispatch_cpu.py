@@ -105,3 +105,21 @@ def test_every_accepted_size_has_a_sweep_form(rules):
                     assert all(0 <= f <= PAIRS for f in forms) and not (d == 128 and forms[1] == BLOCKS)
                     if U >= 1000 and n >= 256:
                         assert forms[0] == PAIRS, (d, n, U, G)
+
+
+# Forms of the decode step at shapes whose times were far apart: nearly equal caches just above one unit per
+# CU, long float32 rows, and their neighbours that gain from one workgroup per unit
+F32, BF16 = binding.torch.float32, binding.torch.bfloat16
+
+
+@pytest.mark.parametrize("U,tokens,d,dtype,G,forced,want", [
+    (257, 2600, 128, BF16, 1, 4, 0), (300, 4500, 128, BF16, 1, 4, 0), (300, 2000, 128, BF16, 2, 4, 0), (300, 1500, 128, F32, 1, 4, 0),
+    (900, 4500, 128, BF16, 1, 3, 0), (300, 3600, 128, BF16, 1, -1, 512), (257, 1500, 128, BF16, 1, 4, 512), (257, 3000, 128, BF16, 1, 2, 512),
+    (300, 4400, 128, BF16, 4, 4, 512), (500, 4500, 128, BF16, 1, 4, 512),
+    (256, 4500, 128, BF16, 1, 4, 512), (400, 2600, 128, BF16, 1, 4, 512), (900, 3500, 128, BF16, 1, 3, 512),
+    (400, 2500, 128, F32, 1, -1, 0), (640, 3500, 128, F32, 1, -1, 0), (400, 1800, 128, F32, 1, -1, 512), (400, 3500, 64, F32, 1, -1, 512),
+    (256, 4400, 128, F32, 1, -1, 512), (1600, 4112, 128, BF16, 1, -1, 512), (640, 8320, 128, BF16, 1, -1, 0),
+    (4096, 1280, 128, BF16, 1, -1, 256), (256, 2112, 128, BF16, 4, -1, 512), (32, 2048, 128, BF16, 1, -1, 512), (32, 2049, 128, BF16, 1, -1, 0),
+])
+def test_decode_step_forms(rules, U, tokens, d, dtype, G, forced, want):
+    assert rules.unit_threads(ctypes.byref(_cfg(U, tokens - 8, 8, d, dtype, group_size=G, forced_policy=forced))) == want
