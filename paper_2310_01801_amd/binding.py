@@ -95,12 +95,17 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# torch keeps these two to itself; where a build of it lacks one, the public call serves
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     """The current stream's handle, without the Stream object torch.cuda.current_stream() builds
     around it (2.8 us of a 10 us call; 0.2 us this way)."""
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def make_config(num_units: int, num_seqs: int, head_dim: int, dtype: torch.dtype, prompt_len: int,

@@ -128,3 +128,16 @@ def test_microbenchmark_library_loads_and_rejects_bad_arguments(lib):
     assert ub.fg_ubench_run(1, 0, 1, 0x10000, None, None, ctypes.byref(ns), None) == -1
     assert ub.fg_ubench_run(1, 1, 1, None, None, None, ctypes.byref(ns), None) == -1
     assert ub.fg_ubench_run(1, 1, 1, 0x10000, None, None, ctypes.byref(ns), ctypes.byref(mhz)) == -1  # clock without its buffer
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_calls(monkeypatch, missing):
+    # a torch without one of them: the module loads, and the public call gives the handle
+    import importlib.util
+    monkeypatch.delattr(binding.torch._C, missing, raising=False)
+    monkeypatch.setattr(binding.torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 1234}))
+    spec = importlib.util.spec_from_file_location("binding_again", binding.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream() == 1234
