@@ -377,7 +377,7 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_finish_kernel(fg_decode_args 
     set_len(L);
     return;
   }
-  fg_update_unit<ESIZE, D, GRP, NT>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
+  fg_update_unit<ESIZE, D, GRP, NT, NT == 256 ? FG_UPDATE_TOKENS_256 : 0>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
 }
 
 }  // namespace

@@ -19,8 +19,10 @@ namespace {
 constexpr int NT = 512;
 constexpr int NW = NT / 64;
 
-template <int ESIZE, int D, int GM>   // GM: the most heads the instantiation holds
-__global__ __launch_bounds__(NT, 2) void fg_decode_group_kernel(fg_decode_args a) {
+// GM: the most heads the instantiation holds. Two float32 heads fit 128 registers, and then two workgroups
+// a CU.
+template <int ESIZE, int D, int GM>
+__global__ __launch_bounds__(NT, ESIZE == 4 && GM == 2 ? 4 : 2) void fg_decode_group_kernel(fg_decode_args a) {
   constexpr int RB = D * ESIZE;        // bytes per row
   constexpr int LPR = RB / 16;         // lanes per row
   constexpr int TPL = 64 / LPR;        // rows per wave load
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(NT, 2) void fg_decode_group_kernel(fg_decode_args a
     set_len(L);
     return;
   }
-  fg_update_unit<ESIZE, D, true, NT>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
+  fg_update_unit<ESIZE, D, true, NT, FG_UNIT_TOKENS>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
 }
 
 template <int GM>

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
     set_len(L);
     return;
   }
-  fg_update_unit<ESIZE, D, false, NT>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
+  fg_update_unit<ESIZE, D, false, NT, NT == 256 ? FG_UNIT_TOKENS_256 : FG_UNIT_TOKENS>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
 }
 
 template <int NT>

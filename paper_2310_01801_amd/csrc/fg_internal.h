@@ -73,6 +73,10 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
   return ((long long)prompt_len + max_new_tokens <= 4096) ? 128 : 256;
 }
 
+// Longest units (prompt and reserved tokens) of the kernels that hold a unit's bookkeeping in registers: the
+// one-workgroup-per-unit step with 512 and with 256 threads, the update kernel with 256.
+constexpr int FG_UNIT_TOKENS = 4608, FG_UNIT_TOKENS_256 = 2048, FG_UPDATE_TOKENS_256 = 3072;
+
 // Form of the decode step: 0 = split-KV attention and a second launch for merge and update; else one
 // workgroup of that many threads per unit. Measured per step, split / per unit:
 //   1024 units of 2048 tokens, d = 128 bf16        120 / 112 us     (256 threads: 118)
@@ -110,8 +114,8 @@ inline int fg_unit_threads(const fg_config& c) {
   const long long tokens = (long long)c.prompt_len + c.max_new_tokens;
   const int row_bytes = c.head_dim * (c.dtype == FG_BF16 ? 2 : 4);
   const long long unit_bytes = tokens * 2 * row_bytes;
-  if (tokens > 4608 || group > 8) return 0;
-  if (group == 1 && U >= 2048 && tokens <= 2048) return 256;
+  if (tokens > FG_UNIT_TOKENS || group > 8) return 0;
+  if (group == 1 && U >= 2048 && tokens <= FG_UNIT_TOKENS_256) return 256;
   if (U > (1 << 22)) return 0;
   if (c.forced_policy >= 0 && U > 256) {
     const double held = fg_forced_share(c) * (double)unit_bytes;
@@ -131,7 +135,7 @@ inline int fg_unit_threads(const fg_config& c) {
 // 354 (full caches 420 / 400, forced policy 3 574 / 603); but 600 of 5000, G = 4, 286 / 340 and 300 of 500, G =
 // 12, 83 / 85.
 inline int fg_update_threads(const fg_config& c) {
-  return c.group_size > 1 && c.num_units > 512 && c.prompt_len + c.max_new_tokens <= 3072 ? 256 : 512;
+  return c.group_size > 1 && c.num_units > 512 && c.prompt_len + c.max_new_tokens <= FG_UPDATE_TOKENS_256 ? 256 : 512;
 }
 
 // Form of a bf16 profiling sweep by its size: the split stream with 32 or 64 owner items per workgroup,

@@ -2,7 +2,8 @@
 // "equal score -> the smaller position is kept" (the frequent policy of Sec. 3.4 keeps the
 // tokens with the largest cumulative attention score). MSB-first radix select on the IEEE
 // bit patterns (monotone for non-negative doubles), 8 bits per pass:
-//   * keys are held in registers when m <= NT * FG_SEL_CACHE (else re-read each pass);
+//   * the caller hands the keys over in registers (fg_select_topk_regs) or they are re-read in each pass
+//     (fg_select_topk);
 //   * passes over the bits that all keys share are skipped (block-wide OR/AND of the keys);
 //   * the scan stops as soon as the boundary bucket is taken whole;
 //   * only if the boundary value is shared does a second select run on the positions.
@@ -10,7 +11,6 @@
 #pragma once
 #include "fg_common.h"
 
-#define FG_SEL_CACHE 12
 
 struct fg_topk {
   uint64_t thr;   // keys above thr are in; keys equal to thr are in iff pos <= pthr
@@ -231,7 +231,8 @@ __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint
   return false;
 }
 
-// ScoreFn(j) -> double (>= 0), PosFn(j) -> uint32 position (unique per element).
+// Keys from score(j), re-read in every pass. ScoreFn(j) -> double (>= 0), PosFn(j) -> uint32 position
+// (unique per element).
 template <int NT, class ScoreFn, class PosFn>
 __device__ __forceinline__ fg_topk fg_select_topk(ScoreFn score, PosFn pos, int m, int k,
                                                   fg_select_smem* sm) {
@@ -239,15 +240,6 @@ __device__ __forceinline__ fg_topk fg_select_topk(ScoreFn score, PosFn pos, int 
   r.thr = 0; r.pthr = 0;
   if (k <= 0) { r.mode = 0; return r; }
   if (k >= m) { r.mode = 1; return r; }
-  if (m <= NT * FG_SEL_CACHE) {
-    uint64_t kc[FG_SEL_CACHE];
-#pragma unroll
-    for (int i = 0; i < FG_SEL_CACHE; ++i) {
-      const int j = threadIdx.x + NT * i;
-      kc[i] = (j < m) ? (uint64_t)__double_as_longlong(score(j)) : 0ull;
-    }
-    return fg_select_topk_impl<NT, FG_SEL_CACHE>(kc, score, pos, m, k, sm);
-  }
   const uint64_t none[1] = {0ull};
   return fg_select_topk_impl<NT, 0>(none, score, pos, m, k, sm);
 }

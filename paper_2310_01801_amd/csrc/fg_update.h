@@ -1,8 +1,8 @@
 // The kept-set update of one unit after a decode step (Alg. 2: f again, with the head's policy):
 // cumulative scores += this step's attention (policies with `frequent`, or every policy when the
 // step is probed), kept = special | punct | TopK(score, k_f(L)) | window, in-place release of the
-// evicted slots, and the probe's masses. Shared by the two forms of a decode step (decode.hip and
-// decode_unit.hip). One workgroup of NT threads calls it for its unit.
+// evicted slots, and the probe's masses. Shared by the forms of a decode step (decode.hip, decode_unit.hip
+// and decode_group.hip). One workgroup of NT threads calls it for its unit.
 #pragma once
 #include "fg_common.h"
 #include "fg_internal.h"
@@ -336,8 +336,9 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
   set_len(new_len);
 }
 
-// The smallest instantiation whose register slots hold the unit.
-template <int ESIZE, int D, bool GRP, int NT, class Merge, class SetLen>
+// The smallest instantiation whose register slots hold the unit. MAX: the longest unit that the calling
+// kernel can meet (0: any length, the part above the registers from memory).
+template <int ESIZE, int D, bool GRP, int NT, int MAX, class Merge, class SetLen>
 __device__ __forceinline__ void fg_update_unit(const fg_decode_args& a, int u, int L, int cap, int64_t off,
                                                int policy, int comp, fg_update_smem& sh, Merge merge,
                                                SetLen set_len) {
@@ -345,7 +346,7 @@ __device__ __forceinline__ void fg_update_unit(const fg_decode_args& a, int u, i
   if (L <= NT * 1) FG_UPDATE(1, false);
   else if (L <= NT * 2) FG_UPDATE(2, false);
   else if (L <= NT * 4) FG_UPDATE(4, false);
-  else if (L <= NT * 8) FG_UPDATE(8, false);
-  else FG_UPDATE(12, true);
+  else if ((MAX != 0 && MAX <= NT * 8) || L <= NT * 8) FG_UPDATE(8, false);
+  else FG_UPDATE(12, (MAX == 0 || MAX > NT * 12));
 #undef FG_UPDATE
 }

@@ -536,8 +536,8 @@ hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   if (pass == 1)
     hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 1, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
                        a.bandcol, units, a.n, a.w, c, nblk, a.G);
-  else
-    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
+  else   // (single blocks do not serve the second sweep at d = 128)
+    hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2, PAIRED || D == 128>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
                        a.bandcol, units, a.n, a.w, c, nblk, a.G);
   return hipGetLastError();
 }
