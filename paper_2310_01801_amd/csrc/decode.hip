@@ -377,7 +377,8 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_finish_kernel(fg_decode_args 
     set_len(L);
     return;
   }
-  fg_update_unit<ESIZE, D, GRP, NT, NT == 256 ? FG_UPDATE_TOKENS_256 : 0>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
+  // (256 threads meet at most FG_UPDATE_TOKENS_256 tokens; with that bound the compiler spills four registers)
+  fg_update_unit<ESIZE, D, GRP, NT, 0>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
 }
 
 }  // namespace
