@@ -103,6 +103,9 @@ constexpr int FG_UNIT_TOKENS = 4608, FG_UNIT_TOKENS_256 = 2048, FG_UPDATE_TOKENS
 //                  257 of 1500 36 / 36; G = 2, 300 of 2000, 66 / 69, G = 4, 300 of 4400, 198 / 176
 //   policy 3       ratios 0.3, 257 of 2600 46 / 51, 513 of 4500 161 / 185, 900 of 4500 268 / 288; 513 of 3500 133 /
 //                  138, 257 of 2000 40 / 41; policy 2, 257 of 3000 34 / 28
+// With few units nothing else of the card is busy while a workgroup streams its unit, and a full cache
+// has no update to merge the launches for: 4 full caches of 2000 tokens 8.7 / 13.7, 32 of 1000 8.7 / 9.6, float32
+// with two heads 4 of 1000 13 / 18; 64 of 1000 11.3 / 9.9, float32 32 of 500 10.2 / 8.2.
 inline double fg_forced_share(const fg_config& c) {   // of the tokens, in front of special and punctuation ones
   if (c.forced_policy == 4) return 1.0;
   const int eq2 = (c.forced_policy >= 2 ? FG_COMP_FREQUENT : 0) | (c.forced_policy == 3 ? FG_COMP_LOCAL : 0);
@@ -117,10 +120,11 @@ inline int fg_unit_threads(const fg_config& c) {
   if (tokens > FG_UNIT_TOKENS || group > 8) return 0;
   if (group == 1 && U >= 2048 && tokens <= FG_UNIT_TOKENS_256) return 256;
   if (U > (1 << 22)) return 0;
-  if (c.forced_policy >= 0 && U > 256) {
+  if (c.forced_policy >= 0) {
     const double held = fg_forced_share(c) * (double)unit_bytes;
-    if (U <= 360 && held > 0.8e6 && tokens * group <= 16000) return 0;
-    if (c.forced_policy < 4 && group == 1 && held > 1.2e6) return 0;
+    if (c.forced_policy == 4 && U < 48 && held > 0.4e6 && tokens > 900) return 0;
+    if (U > 256 && U <= 360 && held > 0.8e6 && tokens * group <= 16000) return 0;
+    if (U > 256 && c.forced_policy < 4 && group == 1 && held > 1.2e6) return 0;
   }
   if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
   if (U < 256) return unit_bytes <= (1 << 20) ? 512 : 0;

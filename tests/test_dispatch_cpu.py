@@ -115,6 +115,8 @@ F32, BF16 = binding.torch.float32, binding.torch.bfloat16
 @pytest.mark.parametrize("U,tokens,d,dtype,G,forced,want", [
     (257, 2600, 128, BF16, 1, 4, 0), (300, 4500, 128, BF16, 1, 4, 0), (300, 2000, 128, BF16, 2, 4, 0), (300, 1500, 128, F32, 1, 4, 0),
     (900, 4500, 128, BF16, 1, 3, 0), (300, 3600, 128, BF16, 1, -1, 512), (257, 1500, 128, BF16, 1, 4, 512), (257, 3000, 128, BF16, 1, 2, 512),
+    (4, 2000, 128, BF16, 1, 4, 0), (32, 1000, 128, BF16, 1, 4, 0), (47, 1000, 128, F32, 2, 4, 0), (48, 1000, 128, BF16, 1, 4, 512),
+    (4, 2000, 128, BF16, 1, 3, 512), (4, 2000, 128, BF16, 1, -1, 512), (32, 516, 128, F32, 1, 4, 512), (32, 500, 128, BF16, 1, 4, 512),
     (300, 4400, 128, BF16, 4, 4, 512), (500, 4500, 128, BF16, 1, 4, 512),
     (256, 4500, 128, BF16, 1, 4, 512), (400, 2600, 128, BF16, 1, 4, 512), (900, 3500, 128, BF16, 1, 3, 512),
     (400, 2500, 128, F32, 1, -1, 0), (640, 3500, 128, F32, 1, -1, 0), (400, 1800, 128, F32, 1, -1, 512), (400, 3500, 64, F32, 1, -1, 512),
