@@ -38,11 +38,11 @@ def test_f32_sweeps_at_tile_edges(n, d, G):
     (3, 1, 3, 128, "bf16"),        # a unit of one token
     (5, 33, 6, 64, "bf16"),        # one tile and one row of a wave (d = 64: 32 rows)
     (4, 65, 6, 64, "f32"),
-    (4, 1020, 4, 128, "bf16"),     # just below / at / above 1 MiB per unit, fewer units than CUs
+    (4, 1020, 4, 128, "bf16"),     # half of, at and above 1 MiB per unit, fewer units than CUs
     (4, 2044, 4, 128, "bf16"),
     (4, 2045, 4, 128, "bf16"),
     (255, 40, 3, 128, "bf16"), (256, 40, 3, 128, "bf16"),
-    (256, 4100, 2, 64, "bf16"),    # the longest register instantiations
+    (256, 4100, 2, 64, "bf16"),
     (256, 4606, 2, 64, "bf16"), (256, 4607, 2, 64, "bf16"),   # at and above the line to split-KV
     (1024, 24, 3, 64, "bf16"), (1025, 24, 3, 64, "f32"), (2047, 24, 3, 64, "bf16"), (2048, 24, 3, 64, "bf16"),
     (16384, 9, 2, 64, "bf16"), (16385, 9, 2, 64, "bf16"),
@@ -227,3 +227,58 @@ def test_order_of_decode_units(heads, n, S):
     run = H.GpuRun(w, range(w.num_units))
     rep = H.compare(run, check_units=[0, 1, heads // 2, heads - 1], cover_policies=1)
     H.log_report(f"unit order U={heads} n={n} S={S}", rep)
+
+
+# The update inside the one-workgroup-per-unit step holds 1, 2, 4, 8 or 12 tokens per thread: scored units on
+# both sides of 512, 1024, 2048 and 4096 held tokens, plain and with grouped heads (256 units and more, so
+# that the length does not send them to the split form), bf16 and float32. r = 1 keeps every token of a
+# frequent + local policy, which still keeps scores; under r = 0.97 tokens leave.
+@pytest.mark.parametrize("heads,n,d,dtype,G", [
+    (256, 510, 64, "bf16", 2), (256, 1022, 64, "bf16", 2), (256, 2046, 64, "bf16", 2), (256, 2046, 64, "f32", 2),
+    (256, 4094, 64, "bf16", 4), (256, 4500, 64, "bf16", 2), (256, 2040, 64, "bf16", 8), (256, 1022, 128, "f32", 4),
+    (256, 2046, 64, "bf16", 1), (256, 4094, 64, "bf16", 1), (256, 4600, 64, "bf16", 1), (256, 4094, 64, "f32", 1),
+])
+@pytest.mark.parametrize("ratio", [1.0, 0.97])
+def test_update_slots_of_long_scored_units(heads, n, d, dtype, G, ratio):
+    w = W["llama7b_b1"].scaled(name="update_slots", layers=1, heads=heads, batch=1, prompt_len=n, steps=4, head_dim=d,
+                               dtype=dtype, seed=n + G, r_l=ratio if ratio < 1 else 0.5, r_f=ratio)
+    run = H.GpuRun(w, range(w.num_units), group_size=G, forced_policy=3)
+    rep = H.compare(run, check_units=[0, heads - 1], probe_steps=(3,))
+    lengths = run.fg.fastgen_export_state(lengths_only=True)["lengths"]
+    assert int(lengths.min()) >= 0.97 * n
+    assert ratio < 1 or int(lengths.min()) == n + 4
+    H.log_report(f"update slots U={heads} n={n} d={d} {dtype} G={G} r={ratio}", rep)
+
+
+# read-back by several workgroups per unit (few units) and by one (2048 units and more), rows included
+@pytest.mark.parametrize("heads,n", [(1, 511), (1, 512), (3, 5000), (7, 2049), (2047, 300), (2048, 600)])
+def test_read_back_by_several_workgroups(heads, n):
+    w = W["llama7b_b1"].scaled(name="read_back", layers=1, heads=heads, batch=1, prompt_len=n, steps=2, head_dim=64,
+                               seed=50 + n)
+    run = H.GpuRun(w, range(w.num_units))
+    run.profile_and_compact()
+    states, off, keys, values = run.state(rows=True)
+    lengths = run.fg.fastgen_export_state(lengths_only=True)["lengths"].tolist()
+    pos = torch.cat([torch.from_numpy(p) for p, _ in states]).long().to(keys.device)
+    unit = torch.repeat_interleave(torch.arange(heads), torch.tensor(lengths)).to(keys.device)
+    assert off[-1] == sum(lengths) == pos.numel()
+    assert bool(((pos[1:] > pos[:-1]) | (unit[1:] != unit[:-1])).all())
+    assert torch.equal(keys, run.K[unit, pos]) and torch.equal(values, run.V[unit, pos])
+
+
+# Nothing of what the workspace held before is read, rows behind the end of a unit in a partly filled tile
+# included: a workspace of NaN patterns gives what a cleared one gives
+@pytest.mark.parametrize("U,n,d,dtype,G", [(3, 5, 64, "bf16", 1), (3, 37, 128, "f32", 1), (2, 21, 64, "bf16", 3), (2, 1100, 128, "bf16", 2),
+                                           (40, 333, 128, "bf16", 1), (2, 5000, 64, "bf16", 1)])
+def test_previous_contents_of_the_workspace_are_not_read(U, n, d, dtype, G):
+    w = W["llama7b_b1"].scaled(name="stale", layers=1, heads=U, batch=1, prompt_len=n, steps=3, head_dim=d, dtype=dtype, seed=n)
+    seen = []
+    for fill in (0, 255):
+        run = H.GpuRun(w, range(U), group_size=G)
+        run.fg.workspace.fill_(fill)
+        pol, rec, cnt = run.profile_and_compact()
+        outs = [run.step(t) for t in range(3)]
+        st = run.fg.fastgen_export_state(rows=True)
+        seen.append([torch.from_numpy(rec), torch.from_numpy(cnt)] + outs + [st[k] for k in ("positions", "scores", "keys", "values")])
+        assert bool(torch.isfinite(torch.stack(outs).float()).all())
+    assert all(torch.equal(a, b) for a, b in zip(*seen))
