@@ -224,8 +224,10 @@ enum {
   FG_PHASE_SELECT = 2,      /* top-k, recoveries, policy, kept flags + scan  */
   FG_PHASE_COMPACT = 3,     /* pool offsets + gather of kept rows            */
   FG_PHASE_DECODE_ATTN = 4, /* attention over the ragged cache               */
-  FG_PHASE_DECODE_UPDATE = 5, /* merge, score update, evict in place: only where the step takes two
-                                launches (long or grouped units); else it is part of phase 4  */
+  FG_PHASE_DECODE_UPDATE = 5, /* merge, score update, evict in place, where the step takes two launches:
+                                units of more than 4608 tokens, more than eight grouped heads, and
+                                some shapes below. Elsewhere one launch does the whole step, grouped
+                                heads included: it counts as phase 4, phase 5 stays at 0            */
   FG_NUM_PHASES = 6
 };
 /* enable: 0 off; 1 every kernel group; N > 1 the prompt-time phases always and every N-th

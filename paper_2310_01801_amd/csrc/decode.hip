@@ -8,7 +8,8 @@
 //       chunk. The item that owns the first free slot takes the new token from k_new/v_new
 //       and appends it to the cache on the way. With grouped query heads the rows loaded by
 //       an item serve every head of the unit (one partial per head).
-//       This is the form for long units and grouped heads; decode_unit.hip is the other one.
+//       This is the form for long units, more than eight grouped heads, few large units and nearly equal
+//       large ones (fg_unit_threads has the rule); decode_unit.hip and decode_group.hip are the other.
 //   fg_decode_finish_kernel   one workgroup per unit: merges the chunk partials into the
 //       attention output; adds this step's attention to the cumulative scores (policies with
 //       `frequent`, or every policy when the step is probed); re-derives the kept set from the

@@ -6,7 +6,8 @@
 // Bound: the float64 logits on the vector ALU (per tile of 16 rows and head 32 multiply-adds and the
 // sums over a row's 16 lanes; four sums at once and a maximum per lane group instead of per wave
 // took 256 units of 2048 tokens, G = 4, from 56 to 47 us; split form: 45 + 21). G = 8 at head
-// dimension 64 spills 25 registers and is still faster than the split form.
+// dimension 64 spills 24 registers, two float32 heads 8, and all spill some 45 scalars; both are still
+// faster than the split form.
 #include <type_traits>
 
 #include "fg_common.h"

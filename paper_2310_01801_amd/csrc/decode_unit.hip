@@ -9,8 +9,9 @@
 // Measured against the split form (attention + update launch): 1024 units of 2048 tokens, d = 128
 // bf16: 101 + 20 -> 112 us per step; 16384 of 1024: 804 + 144 -> 845; 432 of 1337, d = 64:
 // 15 + 14 -> 20; 4 of 128, float32: 12 -> 6.6. Four loads of K and of V per lane and tile, the
-// next tile's K on its way during the sums and its V during the logits, keep 113 registers: eight
-// loads spill (199 us at the first shape), 1024 threads are slower everywhere.
+// next tile's K on its way during the sums and its V during the logits, keep 109 to 118 vector
+// registers (and spill 55 to 73 scalars into lanes of one): eight loads spill vectors (199 us at the first
+// shape), 1024 threads are slower everywhere.
 #include <type_traits>
 
 #include "fg_common.h"
