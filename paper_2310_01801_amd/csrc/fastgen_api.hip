@@ -398,7 +398,8 @@ fg_status fastgen_compact(fastgen_ctx* ctx, const void* K, const void* V, void* 
   hipError_t e = fg_launch_offsets(at<int32_t>(ctx, L.cap), at<int32_t>(ctx, L.len), at<int32_t>(ctx, L.policy),
                                    at<int64_t>(ctx, L.off), at<int32_t>(ctx, L.chunk_off), at<int32_t>(ctx, L.item_unit),
                                    at<int32_t>(ctx, L.flags), c.num_units, L.pool_tokens,
-                                   L.max_chunks, L.chunk, c.prompt_len + c.max_new_tokens, L.unit_threads != 0, s);
+                                   L.max_chunks, L.chunk, c.prompt_len + c.max_new_tokens,
+                                   c.head_dim * (c.dtype == FG_BF16 ? 2 : 4), L.unit_threads != 0, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "fastgen_compact(offsets)");
   fg_compact_args ca;
   ca.K = K; ca.V = V;

@@ -245,7 +245,7 @@ hipError_t fg_launch_select(const fg_select_args&, hipStream_t);
 hipError_t fg_launch_compact(const fg_compact_args&, hipStream_t);
 hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32_t* policy, int64_t* off,
                              int32_t* chunk_off, int32_t* item_unit, int32_t* flags, int U, int64_t pool_tokens,
-                             int64_t max_chunks, int chunk, int max_cap, bool by_unit, hipStream_t);
+                             int64_t max_chunks, int chunk, int max_cap, int row_bytes, bool by_unit, hipStream_t);
 hipError_t fg_launch_decode_attn(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_update(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_unit(const fg_decode_args&, hipStream_t);

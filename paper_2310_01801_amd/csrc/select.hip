@@ -250,10 +250,14 @@ __device__ __forceinline__ int fg_count_place(int* counter, bool active, int key
 // Whether the units are ordered by size. The order pays where the longest units would decide the end of
 // a launch and costs one workgroup's counting sort in fastgen_compact (inside the offsets kernel's own time
 // up to 1024 units). Unordered / ordered, compaction and decode step in us: 1024 units of 2000 tokens 221 +
-// 125 / 224 + 117, 2048 of 1024 249 + 127 / 250 + 116, 4096 of 1024 495 + 228 / 506 + 221; but 4096 of 150,
-// d = 64, 59 + 30 / 66 + 30, 6000 of 400 264 + 135 / 277 + 133, 16384 of 300 349 + 149 / 381 + 162.
-constexpr int kSortUnits = 4096;
-inline bool sorts_units(int U, int max_cap) { return U <= 1024 || (U <= kSortUnits && max_cap >= 512); }
+// 125 / 224 + 117, 2048 of 1024 249 + 127 / 250 + 116, 4096 of 1024 495 + 228 / 506 + 221, 16384 of 1024
+// (of 1536 reserved) 2317 + 1095 / 2310 + 1048; but 4096 of 150, d = 64, 59 + 30 / 66 + 30, 6000 of 400, d = 64,
+// 166 + 72 / 181 + 72, 16384 of 600, d = 64, 666 + 252 / 700 + 262. So above 4096 units from 256 KiB each on.
+constexpr int kSortUnits = 16384;
+inline bool sorts_units(int U, int max_cap, int row_bytes) {
+  if (U <= 4096) return U <= 1024 || max_cap >= 512;
+  return U <= kSortUnits && (long long)max_cap * 2 * row_bytes >= (1 << 18);
+}
 
 // Single workgroup: off[u] = sum_{v<u} cap[v]. BY_UNIT false: chunk_off[u] = sum_{v<u} ceil(cap[v]/chunk).
 // BY_UNIT true: chunk_off[u] = place of unit u among the units, with `ordered` longest reservations first
@@ -561,11 +565,11 @@ hipError_t fg_launch_compact(const fg_compact_args& a, hipStream_t s) {
 
 hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32_t* policy, int64_t* off,
                              int32_t* chunk_off, int32_t* item_unit, int32_t* flags, int U, int64_t pool_tokens,
-                             int64_t max_chunks, int chunk, int max_cap, bool by_unit, hipStream_t s) {
+                             int64_t max_chunks, int chunk, int max_cap, int row_bytes, bool by_unit, hipStream_t s) {
   const dim3 blocks((unsigned)((U + 255) / 256));
   if (by_unit) {
     hipLaunchKernelGGL((fg_offsets_kernel<true>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,
-                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy, (int)sorts_units(U, max_cap));
+                       pool_tokens, max_chunks, chunk, max_cap, item_unit, len, policy, (int)sorts_units(U, max_cap, row_bytes));
     if (U > 1024) hipLaunchKernelGGL(fg_unit_map_kernel, blocks, dim3(256), 0, s, chunk_off, cap, off, len, policy, item_unit, U);
   } else {
     hipLaunchKernelGGL((fg_offsets_kernel<false>), dim3(1), dim3(1024), 0, s, cap, off, chunk_off, flags, U,

@@ -219,8 +219,9 @@ def test_selection_sizes_of_many_units(heads, n):
     H.log_report(f"selection U={heads} n={n}", rep)
 
 
-# decode units ordered by size up to 1024 of them, and up to 4096 with 512 tokens or more
-@pytest.mark.parametrize("heads,n,S", [(1025, 508, 3), (1025, 509, 3), (4096, 509, 3), (4097, 509, 3)])
+# decode units ordered by size up to 1024 of them, up to 4096 with 512 tokens or more, up to 16384 with 256 KiB
+# or more (1024 tokens at d = 64)
+@pytest.mark.parametrize("heads,n,S", [(1025, 508, 3), (1025, 509, 3), (4096, 509, 3), (4097, 509, 3), (4097, 1020, 3), (4097, 1021, 3)])
 def test_order_of_decode_units(heads, n, S):
     w = W["llama7b_b1"].scaled(name="unit_order", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=64,
                                seed=100 + n)
