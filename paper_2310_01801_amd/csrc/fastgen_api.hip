@@ -203,17 +203,26 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c);
   pa.scale = scale;
   hipError_t e;
-  *where = "fastgen_profile(row log-sum-exp sweep)";
-  tm.begin(FG_PHASE_SWEEP1);
-  if (lse_opt) e = fg_launch_lse_to_rowstat(lse_opt, pa.rowstat, (size_t)c.num_units * pa.G * c.prompt_len, s);
-  else e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 1, s) : fg_launch_profile_f32(pa, 1, s);
-  tm.end();
-  if (e != hipSuccess) return e;
-  *where = "fastgen_profile(column sweep)";
-  tm.begin(FG_PHASE_SWEEP2);
-  e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 2, s) : fg_launch_profile_f32(pa, 2, s);
-  tm.end();
-  if (e != hipSuccess) return e;
+  const int once = c.dtype == FG_BF16 && !lse_opt ? fg_once_waves(pa.d, pa.U, pa.n, pa.G) : 0;
+  if (once) {
+    *where = "fastgen_profile(sweeps in one pass)";
+    tm.begin(FG_PHASE_SWEEP1);
+    e = fg_launch_profile_once(pa, once, s);
+    tm.end();
+    if (e != hipSuccess) return e;
+  } else {
+    *where = "fastgen_profile(row log-sum-exp sweep)";
+    tm.begin(FG_PHASE_SWEEP1);
+    if (lse_opt) e = fg_launch_lse_to_rowstat(lse_opt, pa.rowstat, (size_t)c.num_units * pa.G * c.prompt_len, s);
+    else e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 1, s) : fg_launch_profile_f32(pa, 1, s);
+    tm.end();
+    if (e != hipSuccess) return e;
+    *where = "fastgen_profile(column sweep)";
+    tm.begin(FG_PHASE_SWEEP2);
+    e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 2, s) : fg_launch_profile_f32(pa, 2, s);
+    tm.end();
+    if (e != hipSuccess) return e;
+  }
 
   fg_select_args sa;
   sa.colsum = pa.colsum; sa.bandcol = pa.bandcol; sa.token_class = token_class;

@@ -178,6 +178,29 @@ inline fg_sweep_form fg_sweep_form_of(int d, int pass, int U, int n, int G) {
   return single ? FG_SWEEP_BLOCKS : FG_SWEEP_PAIRS;
 }
 
+// Both bf16 sweeps in one pass (profile_once.hip): waves of a unit's workgroup, 0 where the two sweeps serve.
+// A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU; while every CU
+// holds at most one, 8 waves serve the shorter prompts too. Measured, two sweeps / one pass in us (random inputs):
+//   d = 128    4096 units of 1024 tokens 1558 / 1256, 1024 of 512 176 / 109, 256 of 512 75 / 36, 256 of 1024 116 /
+//              79, 64 of 333 28 / 21, 300 of 1024 125 / 118; 32 of 512 24 / 29
+//   d = 64     4096 of 1024 1047 / 988, 512 of 333 51 / 29, 128 of 400 26 / 18; 64 of 700 31 / 35
+//   G = 4      d = 128: 1024 of 512 475 / 321, 200 of 333 91 / 54, 64 of 512 45 / 57, 300 of 900 345 / 401; d = 64:
+//              400 of 600 196 / 156, 128 of 333 32 / 35, 600 of 900 487 / 524
+// One workgroup per unit: too few units leave CUs idle, which the split stream does not, grouped heads
+// (G passes in one workgroup) sooner than single ones; and above one round of places a last round that is mostly
+// empty costs what the pass gains at d = 64 or with several heads. Over 465 measured shapes that this rule takes, 1.44x.
+inline int fg_once_waves(int d, int U, int n, int G) {
+  if (n > 1024 || U > (1 << 22)) return 0;
+  const int waves = n > 512 || (U <= 256 && n > 128) ? 8 : 4, places = waves == 8 ? 256 : 512;
+  if (U <= 256) return U >= (G > 1 ? 192 : d == 64 ? 128 : 64) ? waves : 0;
+  const double fill = (double)U / ((double)((U + places - 1) / places) * places);   // of the rounds' places
+  double least = 0.0;
+  if (n > 512 && d == 128 && G > 1) least = 0.65;
+  if (n > 512 && d == 64) least = n > 896 ? 0.8 : G > 1 ? 0.75 : 0.0;
+  if (n <= 256 && d == 64 && G > 1) least = 0.6;
+  return fill >= least ? waves : 0;
+}
+
 // ---------------------------------------------------------------- launch arguments
 struct fg_profile_args {
   const void* Q; const void* K;
@@ -232,6 +255,7 @@ struct fg_export_args {
 };
 
 hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, hipStream_t);
+hipError_t fg_launch_profile_once(const fg_profile_args&, int waves, hipStream_t);
 hipError_t fg_launch_profile_f32(const fg_profile_args&, int pass, hipStream_t);
 hipError_t fg_launch_lse_to_rowstat(const float* lse_nat, float2* rowstat, size_t count, hipStream_t);
 constexpr int FG_MAX_CLASS_IDS = 64;  // ids per list of fastgen_classify (passed by value)

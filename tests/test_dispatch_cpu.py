@@ -14,6 +14,7 @@ SOURCE = """
 #include "paper_2310_01801_amd/csrc/fg_internal.h"
 extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
 extern "C" int sweep_form(int d, int pass, int U, int n, int G) { return fg_sweep_form_of(d, pass, U, n, G); }
+extern "C" int once_waves(int d, int U, int n, int G) { return fg_once_waves(d, U, n, G); }
 extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
 
@@ -105,6 +106,21 @@ def test_every_accepted_size_has_a_sweep_form(rules):
                     assert all(0 <= f <= PAIRS for f in forms) and not (d == 128 and forms[1] == BLOCKS)
                     if U >= 1000 and n >= 256:
                         assert forms[0] == PAIRS, (d, n, U, G)
+
+
+# Both bf16 sweeps in one pass: never longer than its columns (512 with four waves), never more workgroups than a
+# launch holds threads for, and not where the two sweeps were measured faster
+def test_one_pass_profile(rules):
+    for d in (64, 128):
+        for G in (1, 2, 16):
+            for n in (1, 128, 129, 512, 513, 1024, 1025, 131072):
+                for U in (1, 64, 256, 257, 512, 1000, 1 << 22, (1 << 22) + 1, 1 << 24):
+                    waves = rules.once_waves(d, U, n, G)
+                    assert waves in (0, 4, 8) and (waves == 0 or (n <= 128 * waves and U * waves * 64 < 1 << 32))
+    for args, want in (((128, 4096, 1024, 1), 8), ((128, 4096, 512, 1), 4), ((128, 256, 512, 1), 8), ((128, 32, 333, 1), 0),
+                       ((64, 64, 700, 1), 0), ((128, 64, 512, 4), 0), ((128, 300, 900, 4), 0), ((64, 600, 900, 4), 0),
+                       ((128, 1024, 2048, 1), 0)):
+        assert rules.once_waves(*args) == want, args
 
 
 # Forms of the decode step at shapes whose times were far apart: nearly equal caches just above one unit per

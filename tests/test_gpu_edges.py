@@ -92,6 +92,56 @@ def test_bf16_sweep_forms(heads, n, d, G):
         H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
+# Both bf16 sweeps in one pass: fragments of 32 columns, blocks of 64 rows, four and eight waves, prompt lengths
+# around each and around a wave's next fragment (128, 256), windows whose edge falls in the first, the second or both
+# row fragments of a block; grouped heads walk the columns on in the other direction
+@pytest.mark.parametrize("heads,n,d,G", [
+    (64, 1, 128, 1), (64, 31, 128, 1), (128, 33, 64, 1), (64, 63, 128, 1), (64, 65, 128, 1), (192, 97, 128, 2), (64, 129, 128, 1),
+    (192, 130, 64, 3), (300, 257, 64, 1), (300, 385, 128, 1), (300, 511, 128, 2), (513, 512, 64, 1), (64, 513, 128, 1), (192, 700, 64, 2),
+    (128, 993, 64, 1), (64, 1023, 128, 1), (257, 1024, 128, 1),
+])
+def test_bf16_one_pass(heads, n, d, G):
+    for window in (1, 30, 64, 97, n):
+        w = W["llama7b_b1"].scaled(name="one_pass", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d,
+                                   r_l=min(1.0, (window + 0.5) / n), seed=900 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+        H.log_report(f"one pass U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
+# Row masses of the one-pass form: as below, 10^5 rows, so within 4 x 1.7e-8 / 300; a shift that moves with every
+# tile and a hardware exponential for every rescaling of it would show as 1e-9 and more.
+@pytest.mark.parametrize("U,n,d", [(64, 333, 128), (300, 400, 64), (128, 1000, 64)])
+def test_one_pass_row_masses_have_no_bias(U, n, d):
+    masses = []
+    for seed in range(4):
+        gen = torch.Generator(device="cuda:0").manual_seed(seed)
+        Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+        cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
+        fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3))
+        _, recovery, _ = fg.fastgen_profile(Q, K, cls)
+        masses.append(float(recovery[:, 0].mean()) - 1.0)
+        fg.close()
+    assert abs(sum(masses) / 4) < 2.3e-10, masses
+
+
+# Logits far beyond what a float32 exponential holds without a shift: a key that outweighs all others by 2^600
+# and more, first in the prompt, in a later block, and in the other wave's fragment.
+@pytest.mark.parametrize("n,at", [(100, 0), (300, 170), (1000, 40)])
+def test_one_pass_with_huge_logits(n, at):
+    U, d = 256, 128
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    Q[:, :, 0], K[:, :, 0], K[:, at, 0] = 64.0, 0.0, 120.0
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    cls[0, at] = 1
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3))
+    policy, recovery, _ = fg.fastgen_profile(Q, K, cls)
+    fg.close()
+    want = (n - at) / n   # every row from `at` on gives the key all its mass, the rows before it give none
+    assert float((recovery[:, 0].cpu() - want).abs().max()) < 1e-6
+
+
 # grouped heads, per-unit step (instantiated for up to 2, 4 and 8 heads; 16-, 8- and 32-lane rows) and
 # split-KV beyond its lines (more heads, more tokens), probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
