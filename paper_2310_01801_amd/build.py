@@ -9,7 +9,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfastgen.so")
-SOURCES = ["fastgen_api.hip", "profile_mfma.hip", "profile_once.hip", "profile_f32.hip", "select.hip", "decode.hip", "decode_unit.hip", "decode_group.hip"]
+SOURCES = ["fastgen_api.hip", "profile_mfma.hip", "profile_once.hip", "profile_f32.hip", "select.hip", "decode.hip", "decode_unit.hip", "decode_group.hip",
+           "decode_group_mfma.hip"]
 # measurement aid of bench.py (micro-benchmarks of the matrix and vector pipes), its own library
 UBENCH_LIB = os.path.join(HERE, "libfgubench.so")
 UBENCH_SOURCES = ["ubench.hip"]

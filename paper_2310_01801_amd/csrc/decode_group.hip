@@ -2,12 +2,12 @@
 // its rows are loaded once and serve all of them. A wave converts a tile of keys to float64 once
 // (units that keep scores) and goes through the heads with it, each head with its own running (max,
 // sum, o). One workgroup of 512 threads per unit, longest units first.
+// Serves two bf16 heads and float32; three to eight bf16 heads have a kernel on the matrix cores
+// (decode_group_mfma.hip).
 //
 // Bound: the float64 logits on the vector ALU (per tile of 16 rows and head 32 multiply-adds and the
-// sums over a row's 16 lanes; four sums at once and a maximum per lane group instead of per wave
-// took 256 units of 2048 tokens, G = 4, from 56 to 47 us; split form: 45 + 21). G = 8 at head
-// dimension 64 spills 24 registers, two float32 heads 8, and all spill some 45 scalars; both are still
-// faster than the split form.
+// sums over a row's 16 lanes, four sums at once). Two float32 heads spill 8 registers, and all spill some 45
+// scalars; both are still faster than the split form.
 #include <type_traits>
 
 #include "fg_common.h"
@@ -359,12 +359,12 @@ __global__ __launch_bounds__(NT, ESIZE == 4 && GM == 2 ? 4 : 2) void fg_decode_g
 template <int GM>
 hipError_t launch(const fg_decode_args& a, hipStream_t s) {
   const dim3 grid((unsigned)a.U), block(NT);
-  if (a.dtype == FG_BF16) {
-    if (a.d == 128) hipLaunchKernelGGL((fg_decode_group_kernel<2, 128, GM>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((fg_decode_group_kernel<2, 64, GM>), grid, block, 0, s, a);
-  } else {
+  if (a.dtype == FG_F32) {
     if (a.d == 128) hipLaunchKernelGGL((fg_decode_group_kernel<4, 128, GM>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((fg_decode_group_kernel<4, 64, GM>), grid, block, 0, s, a);
+  } else {   // two heads
+    if (a.d == 128) hipLaunchKernelGGL((fg_decode_group_kernel<2, 128, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((fg_decode_group_kernel<2, 64, 2>), grid, block, 0, s, a);
   }
   return hipGetLastError();
 }
@@ -372,6 +372,7 @@ hipError_t launch(const fg_decode_args& a, hipStream_t s) {
 }  // namespace
 
 hipError_t fg_launch_decode_group(const fg_decode_args& a, hipStream_t s) {
+  if (a.dtype == FG_BF16 && a.G > 2) return fg_launch_decode_group_mfma(a, s);
   if (a.G <= 2) return launch<2>(a, s);
   if (a.G <= 4) return launch<4>(a, s);
   return launch<8>(a, s);

@@ -86,11 +86,12 @@ constexpr int FG_UNIT_TOKENS = 4608, FG_UNIT_TOKENS_256 = 2048, FG_UPDATE_TOKENS
 //   64 of 1000, float32 (1 MiB per unit)           17.2 / 16.7      and one launch less
 //   128 of 1500 (0.75 MiB per unit)                20.1 / 17.3
 //   32 of 2048 (1.02 MiB per unit)                 14.9 / 19.0
-// Grouped heads (G heads share a unit's rows; bound by the float64 logits of the heads):
-//   256 units of 2048 tokens, G = 4                66 / 47 us;  8 of 300, G = 4: 24 / 15
-//   1024 of 700, G = 2                             71 / 52;  600 of 4000, G = 4: 242 / 180
-//   256 of 3000, G = 8                             159 / 166;  32 of 2000, G = 2: 23 / 31
-//   64 of 3000, G = 8                              80 / 149
+// Grouped heads (G heads share a unit's rows), two heads or float32 (bound by the float64 logits of the heads):
+//   1024 of 700, G = 2                             71 / 52;  32 of 2000, G = 2: 23 / 31
+// Three to eight bf16 heads, whose workgroups contract on the matrix cores:
+//   256 units of 2048 tokens, G = 4                66 / 34 us;  16 of 300, G = 8: 37 / 17
+//   300 of 3000, G = 8                             170 / 60;  64 of 3000, G = 8: 86 / 55, G = 3: 43 / 37
+//   4 of 3000, G = 3                               28 / 33, G = 4: 33 / 34;  16 of 2500, G = 3: 27 / 30
 // So: long units stay split (a few of them decide how long the launch takes), and where there are
 // fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit. The step
 // is a one-dimensional launch: 512 threads per unit only while that stays below 2^32 threads.
@@ -120,12 +121,15 @@ inline int fg_unit_threads(const fg_config& c) {
   if (tokens > FG_UNIT_TOKENS || group > 8) return 0;
   if (group == 1 && U >= 2048 && tokens <= FG_UNIT_TOKENS_256) return 256;
   if (U > (1 << 22)) return 0;
+  const bool matrix = c.dtype == FG_BF16 && group > 2;   // the grouped kernel on the matrix cores
   if (c.forced_policy >= 0) {
     const double held = fg_forced_share(c) * (double)unit_bytes;
-    if (c.forced_policy == 4 && U < 48 && held > 0.4e6 && tokens > 900) return 0;
-    if (U > 256 && U <= 360 && held > 0.8e6 && tokens * group <= 16000) return 0;
+    if (c.forced_policy == 4 && U < 48 && held > 0.4e6 && tokens > 900 && !matrix) return 0;   // 4 of 1000, G = 4: 16 / 15
+    // (280 full caches of 3000 tokens, G = 3: 100 split, 108 per unit; 300 of 2000, G = 4: 81 / 70)
+    if (U > 256 && U <= 360 && held > 0.8e6 && tokens * group <= (matrix && group > 3 ? 0 : 16000)) return 0;
     if (U > 256 && c.forced_policy < 4 && group == 1 && held > 1.2e6) return 0;
   }
+  if (matrix) return U < 32 && group <= 4 && tokens > 2200 ? 0 : 512;
   if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
   if (U < 256) return unit_bytes <= (1 << 20) ? 512 : 0;
   if (U > 256 && row_bytes > 256 && tokens > 1856) return 0;
@@ -274,4 +278,5 @@ hipError_t fg_launch_decode_attn(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_update(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_unit(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_decode_group(const fg_decode_args&, hipStream_t);
+hipError_t fg_launch_decode_group_mfma(const fg_decode_args&, hipStream_t);
 hipError_t fg_launch_export(const fg_export_args&, hipStream_t);

@@ -28,10 +28,10 @@ struct fg_update_smem {
 // The bookkeeping of the held tokens is on its way while `merge` runs (the attention output and the
 // maximum M of the scaled logits, from LDS or memory; it holds the barrier after which the logits
 // and the appended slot of this step may be read). The new token's bookkeeping is known here.
-template <int ESIZE, int D, bool GRP, int NT, int NC, bool LAST, class Merge, class SetLen>
+template <int ESIZE, int D, bool GRP, int NT, int NC, bool LAST, class Merge, class SetLen, class Logit>
 __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, int L, int cap, int64_t off,
                                                int policy, int comp, fg_update_smem& sh, Merge merge,
-                                               SetLen set_len) {
+                                               SetLen set_len, Logit logit) {
   constexpr int RB = D * ESIZE, CPR = RB / 16;
   const int tid = threadIdx.x;
   const int G = GRP ? a.G : 1;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
     for (int i = 0; i < NC; ++i) {
       const int j = tid + NT * i;
       lg[i] = 0.0;
-      if (scored && j < L) lg[i] = a.clogit[(off + j) * G];
+      if (scored && j < L) lg[i] = logit(j);
     }
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -338,15 +338,24 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
 
 // The smallest instantiation whose register slots hold the unit. MAX: the longest unit that the calling
 // kernel can meet (0: any length, the part above the registers from memory).
-template <int ESIZE, int D, bool GRP, int NT, int MAX, class Merge, class SetLen>
+// `logit` gives the logit of a slot that the thread owns (grouped heads: its attention).
+template <int ESIZE, int D, bool GRP, int NT, int MAX, class Merge, class SetLen, class Logit>
 __device__ __forceinline__ void fg_update_unit(const fg_decode_args& a, int u, int L, int cap, int64_t off,
                                                int policy, int comp, fg_update_smem& sh, Merge merge,
-                                               SetLen set_len) {
-#define FG_UPDATE(NC, LAST) fg_update_kept<ESIZE, D, GRP, NT, NC, LAST>(a, u, L, cap, off, policy, comp, sh, merge, set_len)
+                                               SetLen set_len, Logit logit) {
+#define FG_UPDATE(NC, LAST) fg_update_kept<ESIZE, D, GRP, NT, NC, LAST>(a, u, L, cap, off, policy, comp, sh, merge, set_len, logit)
   if (L <= NT * 1) FG_UPDATE(1, false);
   else if (L <= NT * 2) FG_UPDATE(2, false);
   else if (L <= NT * 4) FG_UPDATE(4, false);
   else if ((MAX != 0 && MAX <= NT * 8) || L <= NT * 8) FG_UPDATE(8, false);
   else FG_UPDATE(12, (MAX == 0 || MAX > NT * 12));
 #undef FG_UPDATE
+}
+template <int ESIZE, int D, bool GRP, int NT, int MAX, class Merge, class SetLen>
+__device__ __forceinline__ void fg_update_unit(const fg_decode_args& a, int u, int L, int cap, int64_t off,
+                                               int policy, int comp, fg_update_smem& sh, Merge merge,
+                                               SetLen set_len) {
+  const int G = GRP ? a.G : 1;
+  fg_update_unit<ESIZE, D, GRP, NT, MAX>(a, u, L, cap, off, policy, comp, sh, merge, set_len,
+                                         [&](int j) { return a.clogit[(off + j) * G]; });
 }

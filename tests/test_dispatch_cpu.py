@@ -108,6 +108,18 @@ def test_every_accepted_size_has_a_sweep_form(rules):
                         assert forms[0] == PAIRS, (d, n, U, G)
 
 
+F32, BF16 = binding.torch.float32, binding.torch.bfloat16
+
+
+# Three to eight bf16 heads: one workgroup per unit wherever it holds the unit, but a few long ones
+def test_matrix_core_group_forms(rules):
+    for U, tokens, G, dtype, forced, want in ((64, 3000, 8, BF16, -1, 512), (4, 4608, 8, BF16, -1, 512), (4, 3000, 4, BF16, -1, 0),
+                                              (32, 3000, 3, BF16, -1, 512), (4, 1000, 4, BF16, 4, 512), (300, 2000, 4, BF16, 4, 512),
+                                              (280, 3000, 3, BF16, 4, 0), (256, 4609, 4, BF16, -1, 0), (64, 3000, 9, BF16, -1, 0),
+                                              (64, 3000, 2, BF16, -1, 0), (64, 3000, 8, F32, -1, 0)):
+        assert rules.unit_threads(ctypes.byref(_cfg(U, tokens - 8, 8, 128, dtype, group_size=G, forced_policy=forced))) == want
+
+
 # Both bf16 sweeps in one pass: never longer than its columns (512 with four waves), never more workgroups than a
 # launch holds threads for, and not where the two sweeps were measured faster
 def test_one_pass_profile(rules):
@@ -125,7 +137,6 @@ def test_one_pass_profile(rules):
 
 # Forms of the decode step at shapes whose times were far apart: nearly equal caches just above one unit per
 # CU, long float32 rows, and their neighbours that gain from one workgroup per unit
-F32, BF16 = binding.torch.float32, binding.torch.bfloat16
 
 
 @pytest.mark.parametrize("U,tokens,d,dtype,G,forced,want", [

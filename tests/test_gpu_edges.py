@@ -92,6 +92,41 @@ def test_bf16_sweep_forms(heads, n, d, G):
         H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
+# Three to eight bf16 heads on the matrix cores: tiles of 32 tokens (two sets of 16) over eight waves, four and eight
+# columns, prompts of which some waves have no tile, longest units, every policy, probed steps
+@pytest.mark.parametrize("heads,n,S,d,G,forced", [
+    (3, 1, 3, 128, 3, -1), (3, 15, 4, 64, 4, 2), (3, 16, 4, 128, 4, 3), (3, 31, 4, 128, 8, 2), (3, 32, 4, 64, 5, 3), (5, 33, 40, 128, 4, -1),
+    (5, 255, 4, 128, 3, 2), (5, 257, 12, 64, 8, -1), (40, 480, 6, 128, 6, -1), (33, 2300, 4, 128, 4, 3), (3, 4600, 8, 64, 7, -1),
+    (5, 700, 6, 128, 8, 4), (5, 700, 6, 64, 4, 1), (257, 300, 4, 128, 4, -1),
+])
+def test_matrix_core_group_steps(heads, n, S, d, G, forced):
+    w = W["llama7b_b1"].scaled(name="group_mfma", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=d,
+                               dtype="bf16", seed=1100 + n)
+    run = H.GpuRun(w, range(w.num_units), group_size=G, forced_policy=forced)
+    rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}), probe_steps=(1, 2))
+    H.log_report(f"matrix-core group U={heads} n={n} S={S} d={d} G={G} forced={forced}", rep)
+
+
+# A head whose keys outgrow each other from tile to tile moves its shift in every one of them; weights of 2^-200 and
+# less beside it count nothing
+def test_matrix_core_group_with_rising_logits():
+    U, n, d, G = 8, 600, 128, 4
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    Q, K, V = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U, U))
+    K[:, :, 0] = torch.arange(n, device="cuda:0", dtype=torch.bfloat16) * 0.25
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 2, 0.95, 0.3, 0.3, forced_policy=4, group_size=G))
+    fg.fastgen_profile(Q, K, cls)
+    fg.fastgen_compact(K, V)
+    q, k, v = (torch.randn(x, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U, U))
+    q[:, 0] = torch.tensor([0.0, 4.0, 16.0, -16.0], device="cuda:0", dtype=torch.bfloat16).repeat(U)
+    out = fg.fastgen_decode_step(q, k, v, torch.zeros(1, dtype=torch.uint8, device="cuda:0")).float().view(U, G, d)
+    fg.close()
+    Kf, Vf = torch.cat([K, k[:, None]], 1).double().cpu(), torch.cat([V, v[:, None]], 1).double().cpu()
+    a = torch.softmax(q.view(U, G, d).double().cpu() @ Kf.transpose(1, 2) / d ** 0.5, dim=2)
+    assert float((out.cpu().double() - a @ Vf).abs().max()) < 2e-2   # half a bf16 step below 8 is 2^-6
+
+
 # Both bf16 sweeps in one pass: fragments of 32 columns, blocks of 64 rows, four and eight waves, prompt lengths
 # around each and around a wave's next fragment (128, 256), windows whose edge falls in the first, the second or both
 # row fragments of a block; grouped heads walk the columns on in the other direction
