@@ -16,7 +16,7 @@
 // array lives on every GPU the library runs on, from module load until the process ends. In
 // host code the name `scratch` is only a handle for hipGetSymbolAddress; the device address it
 // yields (one per GPU) is what kernels and copies receive.
-static constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
+static constexpr size_t kStaticScratchBytes = FG_STATIC_SCRATCH;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 static constexpr int kMaxDevices = 64;
 static void* g_scratch_ptr[kMaxDevices];   // device address of `scratch`, per GPU (NULL: not asked yet)
@@ -189,11 +189,12 @@ struct PhaseChain {
 
 // The kernels of stage 1a in launch order, over scratch regions `L` inside `ws`. Shared by
 // fastgen_profile (regions in the caller's workspace) and fastgen_profile_static (regions in
-// the library's own static device array).
+// the library's own static device array). `spare` is memory behind the regions, for partial sums.
 hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws, float scale, int w,
                                const void* Q, const void* K, const uint8_t* token_class,
                                const float* lse_opt, int32_t* policy, double* recovery,
-                               int32_t* kept_count, hipStream_t s, PhaseChain& tm, const char** where) {
+                               int32_t* kept_count, void* spare, size_t spare_bytes, hipStream_t s, PhaseChain& tm,
+                               const char** where) {
   auto at = [&](size_t off) { return ws + off; };
   fg_profile_args pa;
   pa.Q = Q; pa.K = K;
@@ -203,11 +204,16 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c);
   pa.scale = scale;
   hipError_t e;
-  const int once = c.dtype == FG_BF16 && !lse_opt ? fg_once_waves(pa.d, pa.U, pa.n, pa.G) : 0;
+  // waves (bf16) or workgroups (float32) per unit of the one-pass form
+  int once = 0;
+  if (!lse_opt) once = c.dtype == FG_BF16 ? fg_once_waves(pa.d, pa.U, pa.n, pa.G) : fg_once_f32_parts(pa.U, pa.n, pa.G);
+  const size_t part = (size_t)pa.U * pa.n * 16;
+  if (c.dtype == FG_F32 && once > 1 && once > (long long)(spare_bytes / part)) once = 0;   // a cache pool smaller than usual
   if (once) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
-    e = fg_launch_profile_once(pa, once, s);
+    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, s)
+                           : fg_launch_profile_once_f32(pa, once, static_cast<double*>(spare), s);
     tm.end();
     if (e != hipSuccess) return e;
   } else {
@@ -347,7 +353,8 @@ fg_status fastgen_profile(fastgen_ctx* ctx, const void* Q, const void* K, const 
   PhaseChain tm(ctx, s, ctx->timing != 0);
   const char* where = "";
   const hipError_t e = launch_profile_path(ctx->cfg, ctx->lay, ctx->ws, ctx->scale, ctx->w, Q, K, token_class,
-                                           lse_opt, policy, recovery, kept_count, s, tm, &where);
+                                           lse_opt, policy, recovery, kept_count, ctx->ws + ctx->lay.ck,
+                                           ctx->lay.cscore - ctx->lay.ck, s, tm, &where);   // the pool is still empty
   if (e != hipSuccess) return hip_fail(ctx, e, where);
   ctx->stage = 1;
   return FG_OK;
@@ -389,7 +396,8 @@ fg_status fastgen_profile_static(const fg_config* cfg, const void* Q, const void
   // every region the kernels read is written first by an earlier kernel of this call for all
   // U * n entries in use, so nothing left over from the previous call needs clearing
   e = launch_profile_path(*cfg, L, static_cast<char*>(base), scale_of(*cfg), window_of(*cfg), Q, K, token_class,
-                          lse_opt, policy, recovery, kept_count, s, tm, &where);
+                          lse_opt, policy, recovery, kept_count, static_cast<char*>(base) + need,
+                          kStaticScratchBytes - need, s, tm, &where);
   if (e != hipSuccess) return sfail(FG_EHIP, "%s: %s", where, hipGetErrorString(e));
   return FG_OK;
 }

@@ -205,6 +205,30 @@ inline int fg_once_waves(int d, int U, int n, int G) {
   return fill >= least ? waves : 0;
 }
 
+// Scratch of fastgen_profile_static; the profiling regions of a shape take about this much of it.
+constexpr size_t FG_STATIC_SCRATCH = (size_t)32 << 20;
+inline size_t fg_profile_bytes(size_t U, size_t n, size_t G) { return U * n * (8 * G + 21) + 112 * U + 16 * 256; }
+
+// Both float32 sweeps in one pass (profile_f32.hip): workgroups per unit, 0 where the two sweeps serve. Up to 2048
+// workgroups in all, at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
+//   64 units of 1000 tokens, d = 128     428 / 236;  16 of 1000 126 / 73;  8 of 1000, G = 4: 270 / 157
+//   64 of 128, d = 128                   25 / 16, d = 64, G = 4: 40 / 34;  128 of 64, d = 64, G = 2: 17 / 16
+//   32 of 128, G = 4                     42 / 49;  4 of 700, G = 4: 122 / 170;  400 of 40, d = 64, G = 4: 45 / 55
+// Fewer than 256 workgroups leave CUs idle, which the sweeps' workgroups of 16 rows do not. The partial sums of a
+// shape that fastgen_profile_static takes fit its scratch: both entry points then add the same parts.
+inline int fg_once_f32_parts(int U, int n, int G) {
+  if (n < 64 || n > 1024 || U > (1 << 22)) return 0;
+  const long long blocks = (n + 15) / 16;
+  long long parts = 2048 / U < blocks / 2 ? 2048 / U : blocks / 2;
+  const size_t held = fg_profile_bytes((size_t)U, (size_t)n, (size_t)G), part = (size_t)U * n * 16;
+  if (held <= FG_STATIC_SCRATCH) {
+    const long long fit = (long long)((FG_STATIC_SCRATCH - held) / part);
+    if (parts > fit) parts = fit;
+  }
+  if (parts < 2) parts = 1;
+  return U * parts >= 256 ? (int)parts : 0;
+}
+
 // ---------------------------------------------------------------- launch arguments
 struct fg_profile_args {
   const void* Q; const void* K;
@@ -261,6 +285,7 @@ struct fg_export_args {
 hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, hipStream_t);
 hipError_t fg_launch_profile_once(const fg_profile_args&, int waves, hipStream_t);
 hipError_t fg_launch_profile_f32(const fg_profile_args&, int pass, hipStream_t);
+hipError_t fg_launch_profile_once_f32(const fg_profile_args&, int parts, double* part_sums, hipStream_t);
 hipError_t fg_launch_lse_to_rowstat(const float* lse_nat, float2* rowstat, size_t count, hipStream_t);
 constexpr int FG_MAX_CLASS_IDS = 64;  // ids per list of fastgen_classify (passed by value)
 struct fg_classify_args {

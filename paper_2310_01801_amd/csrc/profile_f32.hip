@@ -168,6 +168,173 @@ __global__ __launch_bounds__(256, 2) void fg_profile_f32_kernel(
   }
 }
 
+// Both sweeps in one pass over Q and K, for prompts of up to 64 * S tokens. Part p of a unit's P workgroups walks blocks
+// of 16 query rows, dealt out back and forth from the heaviest down. Its waves take the tiles of 16 columns in turn and keep the
+// exponentials of a block in registers, S tiles of four doubles; the waves exchange (m, l) of the rows, and the column
+// sums take the exponentials from the registers. One contraction and one exponential per score instead of two, and
+// no row statistics rounded to float32. A part's column sums meet in LDS (a column belongs to one wave) and
+// leave as partial sums, which fg_part_sum_kernel adds in order.
+// Bound: the float64 matrix pipe. 64 units of 1000 tokens, d = 128: 470 us in two sweeps, 240 in one pass; 16 of 1000:
+// 137 -> 77. With 1024 columns at d = 128 the row's own elements are read back from LDS and the next keys asked
+// for only behind the products, and still five registers spill; held as doubles the row alone takes 64.
+template <int D, int S>
+__global__ __launch_bounds__(256, 2) void fg_profile_once_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, double* __restrict__ colsum, double* __restrict__ bandcol,
+    int U, int n, int w, float c, int G, int P) {
+  constexpr int PL = D / 4;        // elements of a row per lane
+  constexpr int LV = PL / 4;       // 16-byte loads per row and lane
+  constexpr double kFar = 900.0;   // 2^x stays in range up to here
+  constexpr bool EARLY = S <= 8 || D == 64;   // the next tile on its way during the products, else during the exponentials
+  constexpr bool LDS_OWN = S > 8;  // the row's elements wait in LDS where the exponentials need the registers
+  __shared__ __attribute__((aligned(16))) f32x4 s_own[LDS_OWN ? kWaves : 1][LDS_OWN ? LV : 1][64];
+  __shared__ double s_l[2][kWaves][16], s_m[2][kWaves][16];
+  __shared__ double s_sum[2][S * kWaves * kTile];   // column sums, and their part inside the band
+
+  // parts of one unit on one XCD (its L2 then serves the keys)
+  const int idx = blockIdx.x, xcd = idx & 7, rest = idx >> 3;
+  const int unit = (rest / P) * 8 + xcd, part = rest % P;
+  if (unit >= U) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 15, g = lane >> 4;
+  const int nblk = (n + kTile - 1) / kTile;
+  for (int i = tid; i < 2 * S * kWaves * kTile; i += 256) (&s_sum[0][0])[i] = 0.0;
+  __syncthreads();
+  const float* k_mat = K + (size_t)unit * n * D;
+  const double c_d = (double)c;
+  int buf = 0;
+  for (int h = 0; h < G; ++h) {   // the query heads of the unit, over the same columns
+    const float* q_mat = Q + ((size_t)unit * G + h) * n * D;
+    for (int i = 0;; ++i) {
+      const int place = (i & 1) ? (i + 1) * P - 1 - part : i * P + part;   // by weight: P down, P up, ...
+      if (place >= nblk) break;   // every later one is further on
+      const int blk = nblk - 1 - place;
+      const int r0 = blk * kTile, row = r0 + ln;
+      // rows past the end are clamped: they count nothing
+      f32x4 own[LV], next[LV];
+      {
+        const float* src = q_mat + (size_t)min(row, n - 1) * D + g * PL;
+#pragma unroll
+        for (int v = 0; v < LV; ++v) {
+          own[v] = *reinterpret_cast<const f32x4*>(src + 4 * v);
+          if (LDS_OWN) s_own[LDS_OWN ? wave : 0][LDS_OWN ? v : 0][lane] = own[v];
+        }
+      }
+      auto load = [&](int t) {
+        const float* src = k_mat + (size_t)min(t * kTile + ln, n - 1) * D + g * PL;
+#pragma unroll
+        for (int v = 0; v < LV; ++v) next[v] = *reinterpret_cast<const f32x4*>(src + 4 * v);
+      };
+      if (wave <= blk) load(wave);
+      double e[S][4];
+      double m_run = 0.0, l_run = 0.0;   // of this lane's columns 4 i + g of the wave's tiles
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int t = wave + kWaves * s;
+        if (t > blk) continue;
+        f64x4 x = {0.0, 0.0, 0.0, 0.0};   // x[k] = q.k of column 16 t + 4 k + g with row ln
+        f32x4 cur[LV];
+#pragma unroll
+        for (int v = 0; v < LV; ++v) cur[v] = next[v];
+        if (EARLY && s + 1 < S) load(min(t + kWaves, blk));   // the last round re-reads the block's last tile
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < LV; ++v) {
+          if (LDS_OWN) own[v] = s_own[LDS_OWN ? wave : 0][LDS_OWN ? v : 0][lane];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            asm volatile("" : "+v"(own[v][k]));   // widened here: held as doubles the row takes 64 registers
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64((double)cur[v][k], (double)own[v][k], x, 0, 0, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!EARLY && s + 1 < S) load(min(t + kWaves, blk));
+        bool ok[4];
+        double far = -1.0e30;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          ok[k] = t < blk || 4 * k + g <= ln;   // causal
+          x[k] *= c_d;
+          far = fmax(far, ok[k] ? x[k] : -1.0e30);
+        }
+        // The shift only has to keep the exponentials in float64's range: it starts at 0, or at the first
+        // tile's logit where that is far away, and hardly ever moves.
+        if (__any(far > m_run + kFar) || (s == 0 && __any(far < m_run - kFar && far > -1.0e29))) {
+          const double m_new = far > m_run + kFar || (s == 0 && far < m_run - kFar && far > -1.0e29) ? rint(far) : m_run;
+          const double f = exp2(m_run - m_new);
+          l_run = s == 0 ? 0.0 : l_run * f;
+#pragma unroll
+          for (int b = 0; b < s; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[b][k] *= f;
+          m_run = m_new;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          e[s][k] = exp2(ok[k] ? x[k] - m_run : -2000.0);   // masked: 0
+          l_run += e[s][k];
+        }
+      }
+      // (m, l) of every row: its lane groups, then the waves, in a fixed order. A lane without a column has l = 0
+      // and counts with any shift.
+      double M = l_run > 0.0 ? m_run : -1.0e30;
+      M = fmax(M, fg_shfl_xor_f64(M, 16));
+      M = fmax(M, fg_shfl_xor_f64(M, 32));
+      double L = l_run > 0.0 ? l_run * exp2(m_run - M) : 0.0;
+      L += fg_shfl_xor_f64(L, 16);
+      L += fg_shfl_xor_f64(L, 32);
+      if (g == 0) { s_l[buf][wave][ln] = L; s_m[buf][wave][ln] = M; }
+      __syncthreads();
+      M = fmax(fmax(s_m[buf][0][ln], s_m[buf][1][ln]), fmax(s_m[buf][2][ln], s_m[buf][3][ln]));
+      L = 0.0;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) L += s_l[buf][v][ln] * exp2(fmax(s_m[buf][v][ln] - M, -2000.0));
+      buf ^= 1;
+      const double f = row < n ? exp2(fmax(fmin(m_run - M, 1000.0), -2000.0)) / L : 0.0;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int t = wave + kWaves * s, t0 = t * kTile;
+        if (t > blk) continue;
+        double v[4], sum;
+        float unused[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = e[s][k] * f;
+        const int at = t0 + 4 * fg_sum4_index() + g;
+        const bool inside = r0 + kTile - 1 - t0 < w, outside = r0 - (t0 + kTile - 1) >= w;
+        fg_sum4_16(v, 1.0, &sum, unused);
+        // one wave adds to a column, in the order of the blocks; every second lane of four carries the band
+        if ((lane & 3) == 0 || ((lane & 3) == 1 && inside)) s_sum[lane & 3][at] += sum;
+        if (!inside && !outside) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = row - (t0 + 4 * k + g) < w ? v[k] : 0.0;
+          fg_sum4_16(v, 1.0, &sum, unused);
+          if ((lane & 3) == 1) s_sum[1][at] += sum;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const size_t out = ((size_t)part * U + unit) * n;
+  for (int i = tid; i < n; i += 256) {
+    colsum[out + i] = s_sum[0][i];
+    bandcol[out + i] = s_sum[1][i];
+  }
+}
+
+// Sums of the parts [P, N] in order
+__global__ void fg_part_sum_kernel(const double* __restrict__ pcol, const double* __restrict__ pband,
+                                   double* __restrict__ col, double* __restrict__ band, size_t N, int P) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  double a = pcol[i], b = pband[i];
+  for (int p = 1; p < P; ++p) {
+    a += pcol[p * N + i];
+    b += pband[p * N + i];
+  }
+  col[i] = a;
+  band[i] = b;
+}
+
 template <int D>
 hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   const int nblk = (a.n + 15) / 16;
@@ -190,6 +357,19 @@ hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int D, int S>
+hipError_t launch_once(const fg_profile_args& a, int P, double* parts, hipStream_t s) {
+  const size_t N = (size_t)a.U * a.n;
+  double* col = P > 1 ? parts : a.colsum;
+  double* band = P > 1 ? parts + P * N : a.bandcol;
+  hipLaunchKernelGGL((fg_profile_once_f32_kernel<D, S>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(256), 0, s,
+                     static_cast<const float*>(a.Q), static_cast<const float*>(a.K), col, band, a.U, a.n, a.w,
+                     a.scale * FG_LOG2E, a.G, P);
+  if (P > 1)
+    hipLaunchKernelGGL(fg_part_sum_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, col, band, a.colsum, a.bandcol, N, P);
+  return hipGetLastError();
+}
+
 // A caller-supplied natural-log row log-sum-exp as (m, 1/l): m = the nearest integer to its
 // log2 value, 1/l = 2^(m - log2 value) in [0.70, 1.42], so that no bits are lost to the
 // magnitude of the log-sum-exp itself.
@@ -206,6 +386,13 @@ __global__ void fg_lse_to_rowstat_kernel(const float* __restrict__ in, float2* _
 hipError_t fg_launch_profile_f32(const fg_profile_args& a, int pass, hipStream_t s) {
   if (a.d == 128) return launch<128>(a, pass, s);
   return launch<64>(a, pass, s);
+}
+
+hipError_t fg_launch_profile_once_f32(const fg_profile_args& a, int P, double* parts, hipStream_t s) {
+  if (a.n > 1024) return hipErrorInvalidValue;
+  if (a.n <= 256) return a.d == 128 ? launch_once<128, 4>(a, P, parts, s) : launch_once<64, 4>(a, P, parts, s);
+  if (a.n <= 512) return a.d == 128 ? launch_once<128, 8>(a, P, parts, s) : launch_once<64, 8>(a, P, parts, s);
+  return a.d == 128 ? launch_once<128, 16>(a, P, parts, s) : launch_once<64, 16>(a, P, parts, s);
 }
 
 hipError_t fg_launch_lse_to_rowstat(const float* lse_nat, float2* rowstat, size_t count, hipStream_t s) {

@@ -15,6 +15,7 @@ SOURCE = """
 extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
 extern "C" int sweep_form(int d, int pass, int U, int n, int G) { return fg_sweep_form_of(d, pass, U, n, G); }
 extern "C" int once_waves(int d, int U, int n, int G) { return fg_once_waves(d, U, n, G); }
+extern "C" int once_f32_parts(int U, int n, int G) { return fg_once_f32_parts(U, n, G); }
 extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
 
@@ -109,6 +110,23 @@ def test_every_accepted_size_has_a_sweep_form(rules):
 
 
 F32, BF16 = binding.torch.float32, binding.torch.bfloat16
+
+
+# Both float32 sweeps in one pass: at least two blocks of 16 rows per workgroup, and beside the regions of every
+# shape that the static scratch of 32 MiB takes the partial sums fit as well
+def test_one_pass_f32_parts(rules):
+    for n in (1, 63, 64, 200, 1000, 1024, 1025):
+        for U in (1, 8, 32, 64, 200, 256, 300, 1000, 2048, 1 << 16, 1 << 22, (1 << 22) + 1, 1 << 24):
+            for G in (1, 2, 16):
+                parts = rules.once_f32_parts(U, n, G)
+                regions = sum(-(-x // 256) * 256 for x in (U * G * n * 8, U * n * 8, U * n * 8, U * n, U * n * 4, U * 4, U * 40, U * 20,
+                                                           U * 4, (U + 1) * 8, U * 4, 32))
+                if parts:
+                    assert 64 <= n <= 1024 and U * parts >= 256 and (parts == 1 or parts <= n // 32) and (U + 7) * parts * 256 < 1 << 32
+                if parts > 1 and regions <= 32 << 20:
+                    assert regions + parts * U * n * 16 <= 32 << 20, (U, n, G)
+    for args, want in (((64, 1000, 1), 30), ((4, 128, 1), 0), ((16, 1000, 4), 31), ((300, 300, 1), 6), ((3000, 300, 1), 1)):
+        assert rules.once_f32_parts(*args) == want, (args, rules.once_f32_parts(*args))
 
 
 # Three to eight bf16 heads: one workgroup per unit wherever it holds the unit, but a few long ones

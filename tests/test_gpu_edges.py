@@ -92,6 +92,61 @@ def test_bf16_sweep_forms(heads, n, d, G):
         H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
+# Both float32 sweeps in one pass: tiles of 16, four waves that hold 4, 8 or 16 of them each (256, 512 and 1024 columns),
+# one or several workgroups per unit, windows whose edge falls in, at and across tiles; a pool too small for the
+# partial sums takes the two sweeps
+@pytest.mark.parametrize("heads,n,d,G", [
+    (128, 64, 64, 1), (128, 65, 128, 1), (64, 129, 64, 2), (64, 256, 128, 1), (64, 257, 64, 1), (40, 512, 128, 1), (40, 513, 64, 1),
+    (16, 1000, 128, 1), (12, 1024, 64, 3), (300, 100, 128, 1), (2100, 70, 64, 1),
+])
+def test_f32_one_pass(heads, n, d, G):
+    for window in (1, 16, 17, n // 3):
+        w = W["llama7b_b1"].scaled(name="f32_one_pass", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d, dtype="f32",
+                                   r_l=min(1.0, (window + 0.5) / n), seed=700 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+        H.log_report(f"float32 one pass U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
+# The exponentials' shift starts at 0 and moves only for logits beyond 2^900: one such key early, late, and all of them
+@pytest.mark.parametrize("pattern", ["early", "late", "all", "negative"])
+def test_f32_one_pass_with_huge_logits(pattern):
+    U, n, d = 16, 700, 128
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0") for _ in range(2))
+    Q[:, :, 0], K[:, :, 0] = 200.0, 0.0
+    at = {"early": 3, "late": 650, "all": 40, "negative": 40}[pattern]
+    K[:, at, 0] = 100.0                                     # 2^2551
+    if pattern == "all":
+        K[:, :, 0] += 90.0
+    if pattern == "negative":
+        K[:, :, 0] -= 170.0
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    cls[0, at] = 1
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.float32, n, 4, 0.95, 0.3, 0.3))
+    _, recovery, _ = fg.fastgen_profile(Q, K, cls)
+    fg.close()
+    assert float((recovery[:, 0].cpu() - (n - at) / n).abs().max()) < 1e-6   # rows from `at` on give it all their mass
+
+
+def test_f32_one_pass_needs_the_pool():
+    U, n, d = 16, 700, 128
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0") for _ in range(2))
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    cls[0, 0] = 1
+    got = []
+    for pool in (0, U * 8):
+        fg = binding.FastGen(binding.make_config(U, 1, d, torch.float32, n, 4, 0.95, 0.3, 0.3, cache_tokens=pool))
+        fg.fastgen_enable_timing(1)
+        got.append(fg.fastgen_profile(Q, K, cls))
+        torch.cuda.synchronize()
+        assert fg.fastgen_read_timing()["sweep2"][1] == (1 if pool else 0)
+        fg.close()
+    assert torch.equal(got[0][0], got[1][0])
+    assert float((got[0][1] - got[1][1]).abs().max()) < 1e-7
+
+
 # Three to eight bf16 heads on the matrix cores: tiles of 32 tokens (two sets of 16) over eight waves, four and eight
 # columns, prompts of which some waves have no tile, longest units, every policy, probed steps
 @pytest.mark.parametrize("heads,n,S,d,G,forced", [
