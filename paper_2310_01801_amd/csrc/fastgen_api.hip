@@ -204,16 +204,17 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c);
   pa.scale = scale;
   hipError_t e;
-  // waves (bf16) or workgroups (float32) per unit of the one-pass form
-  int once = 0;
-  if (!lse_opt) once = c.dtype == FG_BF16 ? fg_once_waves(pa.d, pa.U, pa.n, pa.G) : fg_once_f32_parts(pa.U, pa.n, pa.G);
-  const size_t part = (size_t)pa.U * pa.n * 16;
-  if (c.dtype == FG_F32 && once > 1 && once > (long long)(spare_bytes / part)) once = 0;   // a cache pool smaller than usual
-  if (once) {
+  fg_once_form once = {0, 1};   // both sweeps in one pass
+  if (!lse_opt) {
+    if (c.dtype == FG_BF16) once = fg_once_of(pa.d, pa.U, pa.n, pa.G);
+    else if (const int parts = fg_once_f32_parts(pa.U, pa.n, pa.G)) once = {4, parts};
+  }
+  // (a cache pool smaller than usual may not hold the partial sums)
+  if (once.waves && (once.parts == 1 || (size_t)once.parts * pa.U * pa.n * 16 <= spare_bytes)) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
-    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, s)
-                           : fg_launch_profile_once_f32(pa, once, static_cast<double*>(spare), s);
+    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(spare), s)
+                           : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(spare), s);
     tm.end();
     if (e != hipSuccess) return e;
   } else {

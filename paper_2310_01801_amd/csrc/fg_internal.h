@@ -182,49 +182,73 @@ inline fg_sweep_form fg_sweep_form_of(int d, int pass, int U, int n, int G) {
   return single ? FG_SWEEP_BLOCKS : FG_SWEEP_PAIRS;
 }
 
-// Both bf16 sweeps in one pass (profile_once.hip): waves of a unit's workgroup, 0 where the two sweeps serve.
-// A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU; while every CU
-// holds at most one, 8 waves serve the shorter prompts too. Measured, two sweeps / one pass in us (random inputs):
-//   d = 128    4096 units of 1024 tokens 1558 / 1256, 1024 of 512 176 / 109, 256 of 512 75 / 36, 256 of 1024 116 /
-//              79, 64 of 333 28 / 21, 300 of 1024 125 / 118; 32 of 512 24 / 29
-//   d = 64     4096 of 1024 1047 / 988, 512 of 333 51 / 29, 128 of 400 26 / 18; 64 of 700 31 / 35
-//   G = 4      d = 128: 1024 of 512 475 / 321, 200 of 333 91 / 54, 64 of 512 45 / 57, 300 of 900 345 / 401; d = 64:
-//              400 of 600 196 / 156, 128 of 333 32 / 35, 600 of 900 487 / 524
-// One workgroup per unit: too few units leave CUs idle, which the split stream does not, grouped heads
-// (G passes in one workgroup) sooner than single ones; and above one round of places a last round that is mostly
-// empty costs what the pass gains at d = 64 or with several heads. Over 465 measured shapes that this rule takes, 1.44x.
-inline int fg_once_waves(int d, int U, int n, int G) {
-  if (n > 1024 || U > (1 << 22)) return 0;
-  const int waves = n > 512 || (U <= 256 && n > 128) ? 8 : 4, places = waves == 8 ? 256 : 512;
-  if (U <= 256) return U >= (G > 1 ? 192 : d == 64 ? 128 : 64) ? waves : 0;
-  const double fill = (double)U / ((double)((U + places - 1) / places) * places);   // of the rounds' places
-  double least = 0.0;
-  if (n > 512 && d == 128 && G > 1) least = 0.65;
-  if (n > 512 && d == 64) least = n > 896 ? 0.8 : G > 1 ? 0.75 : 0.0;
-  if (n <= 256 && d == 64 && G > 1) least = 0.6;
-  return fill >= least ? waves : 0;
-}
-
 // Scratch of fastgen_profile_static; the profiling regions of a shape take about this much of it.
 constexpr size_t FG_STATIC_SCRATCH = (size_t)32 << 20;
 inline size_t fg_profile_bytes(size_t U, size_t n, size_t G) { return U * n * (8 * G + 21) + 112 * U + 16 * 256; }
+
+// Workgroups per unit that fit beside the profiling regions of a shape that fastgen_profile_static takes (both entry
+// points then add the same partial sums); any number for larger shapes.
+inline long long fg_parts_that_fit(int U, int n, int G) {
+  const size_t held = fg_profile_bytes((size_t)U, (size_t)n, (size_t)G);
+  return held <= FG_STATIC_SCRATCH ? (long long)((FG_STATIC_SCRATCH - held) / ((size_t)U * n * 16)) : 1 << 20;
+}
+
+// Both bf16 sweeps in one pass (profile_once.hip): waves of a workgroup and workgroups per unit, 0 waves where the two
+// sweeps serve. A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU. Measured,
+// two sweeps / one pass in us (random inputs; in brackets the workgroups per unit):
+//   d = 128    4096 units of 1024 tokens 1558 / 1256 (1), 300 of 1000 121 / 84 (3), 64 of 1000 70 / 22 (4), 8 of 1000
+//              35 / 24 (12), 128 of 512 46 / 17 (2), 32 of 333 23 / 14 (6), 64 of 64 15 / 10 (1)
+//   d = 64     4096 of 1024 1047 / 988 (1), 64 of 1000 46 / 21 (4), 32 of 400 20 / 16 (6), 4 of 1000 30 / 27 (12)
+//   G = 4      d = 128: 32 of 512 54 / 26 (8), 200 of 333 91 / 54, 64 of 64 19 / 22; d = 64: 16 of 200 22 / 23, 8 of 333
+//              27 / 28; G = 8: 128 of 64 29 / 38, d = 64: 32 of 256 38 / 39
+// Parts: the more of the places are taken in the last round the better, less 5 % for every further part's
+// prologue and sums; an extra launch adds the sums, so a single pair of blocks stays whole. Above 2048 units nothing is
+// gained. A unit's G heads are one workgroup's work one after the other, where the first sweep alone has a
+// workgroup for each: several heads need enough 64 x 64 tiles in all, and single blocks of them enough units.
+struct fg_once_form { int waves, parts; };
+inline fg_once_form fg_once_of(int d, int U, int n, int G) {
+  if (n > 1024 || U > (1 << 22)) return {0, 1};
+  const int blocks = (n + 63) / 64;
+  const double tiles = (double)U * blocks * (blocks + 1) / 2;
+  if (G > 2 && blocks == 1 && (d == 64 || U < (G > 4 ? 256 : 192))) return {0, 1};
+  if (n < 512 && blocks > 1) {
+    const double least = G > 8 ? 1280 : G > 4 ? (d == 64 ? 640 : 400) : G > 2 ? (d == 64 ? 320 : 200) : G == 2 && d == 64 && blocks > 2 ? 320 : 0;
+    if (tiles < least) return {0, 1};
+  }
+  if (G > 4 && d == 64 && U < 8) return {0, 1};
+  if (G > 8 && U < 32) return {0, 1};
+  const int waves = n > 512 || (U <= 128 && n > 128) ? 8 : 4, places = waves == 8 ? 256 : 512;
+  int parts = 1;
+  if (U <= 2048 && (blocks > 2 || (blocks == 2 && G > 1))) {
+    long long most = fg_parts_that_fit(U, n, G);
+    if (most > 12) most = 12;
+    if (most > blocks) most = blocks;
+    double best = 0.0;
+    for (int p = 1; p <= most; ++p) {
+      const long long groups = (long long)U * p, rounds = (groups + places - 1) / places;
+      const double score = (double)groups / (double)(rounds * places) * (1.05 - 0.05 * p);
+      if (score > best + 1e-9) { best = score; parts = p; }
+    }
+  }
+  // a last round that is mostly empty and cannot be filled: 300 of 1000, d = 64, G = 8: 703 / 951,
+  // 2049 of 1000, d = 64: 610 / 650
+  if (parts == 1 && U > 256 && n > 512 && (d == 64 || G > 1) &&
+      (double)U < (d == 64 && n > 896 ? 0.85 : 0.75) * (double)((U + places - 1) / places) * places)
+    return {0, 1};
+  return {waves, parts};
+}
 
 // Both float32 sweeps in one pass (profile_f32.hip): workgroups per unit, 0 where the two sweeps serve. Up to 2048
 // workgroups in all, at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
 //   64 units of 1000 tokens, d = 128     428 / 236;  16 of 1000 126 / 73;  8 of 1000, G = 4: 270 / 157
 //   64 of 128, d = 128                   25 / 16, d = 64, G = 4: 40 / 34;  128 of 64, d = 64, G = 2: 17 / 16
 //   32 of 128, G = 4                     42 / 49;  4 of 700, G = 4: 122 / 170;  400 of 40, d = 64, G = 4: 45 / 55
-// Fewer than 256 workgroups leave CUs idle, which the sweeps' workgroups of 16 rows do not. The partial sums of a
-// shape that fastgen_profile_static takes fit its scratch: both entry points then add the same parts.
+// Fewer than 256 workgroups leave CUs idle, which the sweeps' workgroups of 16 rows do not.
 inline int fg_once_f32_parts(int U, int n, int G) {
   if (n < 64 || n > 1024 || U > (1 << 22)) return 0;
   const long long blocks = (n + 15) / 16;
   long long parts = 2048 / U < blocks / 2 ? 2048 / U : blocks / 2;
-  const size_t held = fg_profile_bytes((size_t)U, (size_t)n, (size_t)G), part = (size_t)U * n * 16;
-  if (held <= FG_STATIC_SCRATCH) {
-    const long long fit = (long long)((FG_STATIC_SCRATCH - held) / part);
-    if (parts > fit) parts = fit;
-  }
+  if (parts > fg_parts_that_fit(U, n, G)) parts = fg_parts_that_fit(U, n, G);
   if (parts < 2) parts = 1;
   return U * parts >= 256 ? (int)parts : 0;
 }
@@ -283,7 +307,9 @@ struct fg_export_args {
 };
 
 hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, hipStream_t);
-hipError_t fg_launch_profile_once(const fg_profile_args&, int waves, hipStream_t);
+hipError_t fg_launch_profile_once(const fg_profile_args&, fg_once_form, double* part_sums, hipStream_t);
+// sums over [parts, N] in order, of two arrays
+hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, size_t N, int parts, hipStream_t);
 hipError_t fg_launch_profile_f32(const fg_profile_args&, int pass, hipStream_t);
 hipError_t fg_launch_profile_once_f32(const fg_profile_args&, int parts, double* part_sums, hipStream_t);
 hipError_t fg_launch_lse_to_rowstat(const float* lse_nat, float2* rowstat, size_t count, hipStream_t);

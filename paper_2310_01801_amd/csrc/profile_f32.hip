@@ -365,9 +365,8 @@ hipError_t launch_once(const fg_profile_args& a, int P, double* parts, hipStream
   hipLaunchKernelGGL((fg_profile_once_f32_kernel<D, S>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(256), 0, s,
                      static_cast<const float*>(a.Q), static_cast<const float*>(a.K), col, band, a.U, a.n, a.w,
                      a.scale * FG_LOG2E, a.G, P);
-  if (P > 1)
-    hipLaunchKernelGGL(fg_part_sum_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, col, band, a.colsum, a.bandcol, N, P);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return P > 1 && e == hipSuccess ? fg_launch_part_sums(col, band, a.colsum, a.bandcol, N, P, s) : e;
 }
 
 // A caller-supplied natural-log row log-sum-exp as (m, 1/l): m = the nearest integer to its
@@ -382,6 +381,11 @@ __global__ void fg_lse_to_rowstat_kernel(const float* __restrict__ in, float2* _
 }
 
 }  // namespace
+
+hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, size_t N, int parts, hipStream_t s) {
+  hipLaunchKernelGGL(fg_part_sum_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, pcol, pband, col, band, N, parts);
+  return hipGetLastError();
+}
 
 hipError_t fg_launch_profile_f32(const fg_profile_args& a, int pass, hipStream_t s) {
   if (a.d == 128) return launch<128>(a, pass, s);

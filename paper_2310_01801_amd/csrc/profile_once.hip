@@ -1,13 +1,15 @@
 // Both profiling sweeps of a short bf16 prompt in one pass over Q and K (Alg. 1: A = softmax(Q K^T);
 // Sec. 3.4 cumulative attention score; same outputs as the two sweeps of profile_mfma.hip).
 //
-// One workgroup owns a unit and walks its query rows in blocks of 64. Its waves hold the whole block's
-// exponentials in registers: the causal columns are dealt out in fragments of 32, fragment j to wave j mod NW,
-// at most four per wave, so 4 * 32 * NW columns are the longest prompt. A value p~ = 2^(c q.k - m) is
+// A workgroup walks the query rows of a unit in blocks of 64; where units are few, several workgroups share
+// the blocks of each, dealt from the heavy end. The waves hold the whole block's exponentials in registers: the
+// causal columns are dealt out in fragments of 32, fragment j to wave j mod NW, at most four per wave, so
+// 4 * 32 * NW columns are the longest prompt. A value p~ = 2^(c q.k - m) is
 // made once, with the running shift m of its row in this wave (a whole number, so that every later rescaling
 // is a power of two); the waves then exchange (m, l) of the 64 rows through LDS, and the column sums
 // take p~ * 2^(m - M) / l from the registers. One contraction, one exponential per score and one read of
-// Q and K instead of two, and no row statistics in memory.
+// Q and K instead of two, and no row statistics in memory. Workgroups that share a unit leave partial column sums, which
+// are added in order.
 //
 // The row index is the lane index (Q is the B operand of v_mfma_f32_32x32x16_bf16), so row maxima and sums are
 // private to a lane; the column sums cross the lanes once per block, after the block's two row fragments have been
@@ -18,7 +20,8 @@
 // Bound: the vector ALU (56 % busy) with two waves per SIMD, whose waits at the block's barrier and for keys
 // from beyond L2 are the rest. 4096 units of 1024 tokens, d = 128, planted inputs: 870 + 1060 us in two sweeps, 1290 in
 // one pass (the walk back and forth: 1390 without); of 512 tokens 305 + 340 -> 357. Error of the column sums against
-// float64: 1.66e-8 (two sweeps 1.91e-8). Tried without gain: the next fragment's matrix instructions between this
+// float64: 1.66e-8 (two sweeps 1.91e-8), the same when shared. 64 units of 1000 tokens by four workgroups each 22
+// (one each 60, two sweeps 70). Tried without gain: the next fragment's matrix instructions between this
 // one's exponentials by hand (1410: more instructions, the same time), two to eight workgroups per unit that share
 // its keys in L2 (1420, and partial sums), query operands in registers (51 spills).
 #include "fg_common.h"
@@ -77,7 +80,7 @@ constexpr __device__ int fg_acc_item(int i) { return (i >> 2) * 8 + (i & 3); }
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, double* __restrict__ colsum,
-    double* __restrict__ bandcol, int n, int w, float c, int G) {
+    double* __restrict__ bandcol, int U, int n, int w, float c, int G, int P) {
   constexpr int KK = D / 16;
   constexpr int RB = D * 2;           // bytes of a row
   constexpr int PPR = D / 8;          // 16-byte pieces of a row
@@ -93,12 +96,19 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   __shared__ float s_m[2][NW][kRows];
   __shared__ double s_sum[2][COLS];   // column sums, and their part inside the band
 
-  const int unit = blockIdx.x;
+  // parts of one unit on one XCD (its L2 then serves the keys)
+  const int idx = blockIdx.x, xcd = idx & 7, rest = idx >> 3;
+  const int unit = (rest / P) * 8 + xcd, part = rest % P;
+  if (unit >= U) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, lh = lane >> 5;
   const int nblk = (n + kRows - 1) / kRows;
   for (int i = tid; i < 2 * COLS; i += NT) (&s_sum[0][0])[i] = 0.0;
+  // blocks dealt out by weight from the heaviest, to the parts down, up, ...; walked from the lightest
+  auto block = [&](int i) { return nblk - 1 - ((i & 1) ? (i + 1) * P - 1 - part : i * P + part); };
+  int mine = 1;   // at most nblk parts
+  while (block(mine) >= 0) ++mine;
 
   // the loads write LDS in lane order, so a lane picks the piece that belongs to its place; rows past the end of
   // the unit read as zeros (every use of them is masked)
@@ -125,9 +135,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       for (int i = 0; i < QL; ++i)
         fg_load_lds16(q_rsrc, &s_q[to][(wave * QL + i) * 1024], source(wave * QL + i), b * kRows * RB + (wave * QL + i) * 1024);
     };
-    load_q(0, buf);   // the last reads of this buffer lie behind a barrier
+    load_q(block(mine - 1), buf);   // the last reads of this buffer lie behind a barrier
     __syncthreads();
-    for (int b = 0; b < nblk; ++b, buf ^= 1, down = !down) {
+    for (int i = mine - 1; i >= 0; --i, buf ^= 1, down = !down) {
+      const int b = block(i);
       const int r0 = b * kRows;
       const int jl = min(2 * b + 1, (n - 1) / kFrag);   // last column fragment
       const int cnt = jl >= wave ? (jl - wave) / NW + 1 : 0;   // fragments of this wave
@@ -210,7 +221,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         ms[s][0] = m_run[0];
         ms[s][1] = m_run[1];
       }
-      if (b + 1 < nblk) load_q(b + 1, buf ^ 1);
+      if (i > 0) load_q(block(i - 1), buf ^ 1);
       // (m, l) of row `lane` of the block: the halves of the wave (columns), then the waves
       {
         float ma = m_run[0], mb = m_run[1];
@@ -271,23 +282,27 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   }
   __syncthreads();
   for (int i = tid; i < n; i += NT) {
-    colsum[(size_t)unit * n + i] = s_sum[0][i];
-    bandcol[(size_t)unit * n + i] = s_sum[1][i];
+    colsum[((size_t)part * U + unit) * n + i] = s_sum[0][i];
+    bandcol[((size_t)part * U + unit) * n + i] = s_sum[1][i];
   }
 }
 
 template <int D, int NW>
-hipError_t launch(const fg_profile_args& a, hipStream_t s) {
-  hipLaunchKernelGGL((fg_profile_once_kernel<D, NW>), dim3((unsigned)a.U), dim3(NW * 64), 0, s,
-                     static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), a.colsum, a.bandcol, a.n, a.w,
-                     a.scale * FG_LOG2E, a.G);
-  return hipGetLastError();
+hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s) {
+  const size_t N = (size_t)a.U * a.n;
+  double* col = P > 1 ? parts : a.colsum;
+  double* band = P > 1 ? parts + P * N : a.bandcol;
+  hipLaunchKernelGGL((fg_profile_once_kernel<D, NW>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(NW * 64), 0, s,
+                     static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), col, band, a.U, a.n, a.w,
+                     a.scale * FG_LOG2E, a.G, P);
+  const hipError_t e = hipGetLastError();
+  return P > 1 && e == hipSuccess ? fg_launch_part_sums(col, band, a.colsum, a.bandcol, N, P, s) : e;
 }
 
 }  // namespace
 
-hipError_t fg_launch_profile_once(const fg_profile_args& a, int waves, hipStream_t s) {
-  if (a.n > kSlots * kFrag * waves) return hipErrorInvalidValue;
-  if (waves == 8) return a.d == 128 ? launch<128, 8>(a, s) : launch<64, 8>(a, s);
-  return a.d == 128 ? launch<128, 4>(a, s) : launch<64, 4>(a, s);
+hipError_t fg_launch_profile_once(const fg_profile_args& a, fg_once_form f, double* parts, hipStream_t s) {
+  if (a.n > kSlots * kFrag * f.waves || f.parts > (a.n + kRows - 1) / kRows) return hipErrorInvalidValue;
+  if (f.waves == 8) return a.d == 128 ? launch<128, 8>(a, f.parts, parts, s) : launch<64, 8>(a, f.parts, parts, s);
+  return a.d == 128 ? launch<128, 4>(a, f.parts, parts, s) : launch<64, 4>(a, f.parts, parts, s);
 }

@@ -14,7 +14,7 @@ SOURCE = """
 #include "paper_2310_01801_amd/csrc/fg_internal.h"
 extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
 extern "C" int sweep_form(int d, int pass, int U, int n, int G) { return fg_sweep_form_of(d, pass, U, n, G); }
-extern "C" int once_waves(int d, int U, int n, int G) { return fg_once_waves(d, U, n, G); }
+extern "C" int once_form(int d, int U, int n, int G) { const fg_once_form f = fg_once_of(d, U, n, G); return f.waves * 100 + f.parts; }
 extern "C" int once_f32_parts(int U, int n, int G) { return fg_once_f32_parts(U, n, G); }
 extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
@@ -119,12 +119,10 @@ def test_one_pass_f32_parts(rules):
         for U in (1, 8, 32, 64, 200, 256, 300, 1000, 2048, 1 << 16, 1 << 22, (1 << 22) + 1, 1 << 24):
             for G in (1, 2, 16):
                 parts = rules.once_f32_parts(U, n, G)
-                regions = sum(-(-x // 256) * 256 for x in (U * G * n * 8, U * n * 8, U * n * 8, U * n, U * n * 4, U * 4, U * 40, U * 20,
-                                                           U * 4, (U + 1) * 8, U * 4, 32))
                 if parts:
                     assert 64 <= n <= 1024 and U * parts >= 256 and (parts == 1 or parts <= n // 32) and (U + 7) * parts * 256 < 1 << 32
-                if parts > 1 and regions <= 32 << 20:
-                    assert regions + parts * U * n * 16 <= 32 << 20, (U, n, G)
+                if parts > 1 and _profile_regions(U, n, G) <= 32 << 20:
+                    assert _profile_regions(U, n, G) + parts * U * n * 16 <= 32 << 20, (U, n, G)
     for args, want in (((64, 1000, 1), 30), ((4, 128, 1), 0), ((16, 1000, 4), 31), ((300, 300, 1), 6), ((3000, 300, 1), 1)):
         assert rules.once_f32_parts(*args) == want, (args, rules.once_f32_parts(*args))
 
@@ -138,19 +136,28 @@ def test_matrix_core_group_forms(rules):
         assert rules.unit_threads(ctypes.byref(_cfg(U, tokens - 8, 8, 128, dtype, group_size=G, forced_policy=forced))) == want
 
 
-# Both bf16 sweeps in one pass: never longer than its columns (512 with four waves), never more workgroups than a
-# launch holds threads for, and not where the two sweeps were measured faster
+def _profile_regions(U, n, G):
+    return sum(-(-x // 256) * 256 for x in (U * G * n * 8, U * n * 8, U * n * 8, U * n, U * n * 4, U * 4, U * 40, U * 20, U * 4,
+                                            (U + 1) * 8, U * 4, 32))
+
+
+# Both bf16 sweeps in one pass: never longer than a workgroup's columns (512 with four waves), never more parts than
+# blocks of 64 rows or more threads than a launch holds, the partial sums within the static scratch, and not
+# where the two sweeps were measured faster
 def test_one_pass_profile(rules):
     for d in (64, 128):
-        for G in (1, 2, 16):
-            for n in (1, 128, 129, 512, 513, 1024, 1025, 131072):
-                for U in (1, 64, 256, 257, 512, 1000, 1 << 22, (1 << 22) + 1, 1 << 24):
-                    waves = rules.once_waves(d, U, n, G)
-                    assert waves in (0, 4, 8) and (waves == 0 or (n <= 128 * waves and U * waves * 64 < 1 << 32))
-    for args, want in (((128, 4096, 1024, 1), 8), ((128, 4096, 512, 1), 4), ((128, 256, 512, 1), 8), ((128, 32, 333, 1), 0),
-                       ((64, 64, 700, 1), 0), ((128, 64, 512, 4), 0), ((128, 300, 900, 4), 0), ((64, 600, 900, 4), 0),
-                       ((128, 1024, 2048, 1), 0)):
-        assert rules.once_waves(*args) == want, args
+        for G in (1, 2, 4, 8, 16):
+            for n in (1, 64, 65, 128, 129, 512, 513, 1000, 1024, 1025, 131072):
+                for U in (1, 8, 64, 128, 129, 256, 257, 300, 512, 1000, 2048, 2049, 1 << 22, (1 << 22) + 1, 1 << 24):
+                    waves, parts = divmod(rules.once_form(d, U, n, G), 100)
+                    assert waves in (0, 4, 8) and 1 <= parts <= -(-n // 64)
+                    assert waves == 0 or (n <= 128 * waves and (U + 7) * parts * waves * 64 < 1 << 32)
+                    if waves and parts > 1 and _profile_regions(U, n, G) <= 32 << 20:
+                        assert _profile_regions(U, n, G) + parts * U * n * 16 <= 32 << 20, (d, U, n, G)
+    for args, want in (((128, 4096, 1024, 1), 801), ((128, 4096, 512, 1), 401), ((128, 64, 1000, 1), 804), ((128, 32, 333, 1), 806),
+                       ((128, 160, 400, 1), 403), ((128, 8, 1000, 1), 810), ((64, 1, 64, 1), 401), ((128, 64, 64, 4), 1), ((64, 256, 64, 8), 1),
+                       ((64, 32, 256, 8), 1), ((64, 8, 333, 2), 1), ((128, 8, 512, 16), 1), ((64, 300, 1000, 8), 1), ((128, 1024, 2048, 1), 1)):
+        assert rules.once_form(*args) == want, (args, rules.once_form(*args))
 
 
 # Forms of the decode step at shapes whose times were far apart: nearly equal caches just above one unit per

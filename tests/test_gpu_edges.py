@@ -184,11 +184,12 @@ def test_matrix_core_group_with_rising_logits():
 
 # Both bf16 sweeps in one pass: fragments of 32 columns, blocks of 64 rows, four and eight waves, prompt lengths
 # around each and around a wave's next fragment (128, 256), windows whose edge falls in the first, the second or both
-# row fragments of a block; grouped heads walk the columns on in the other direction
+# row fragments of a block; one and several workgroups per unit, even and odd numbers of blocks for them; grouped
+# heads walk the columns on in the other direction
 @pytest.mark.parametrize("heads,n,d,G", [
-    (64, 1, 128, 1), (64, 31, 128, 1), (128, 33, 64, 1), (64, 63, 128, 1), (64, 65, 128, 1), (192, 97, 128, 2), (64, 129, 128, 1),
+    (64, 1, 128, 1), (1, 31, 128, 1), (128, 33, 64, 1), (4, 63, 128, 1), (64, 65, 128, 1), (192, 97, 128, 2), (64, 129, 128, 1),
     (192, 130, 64, 3), (300, 257, 64, 1), (300, 385, 128, 1), (300, 511, 128, 2), (513, 512, 64, 1), (64, 513, 128, 1), (192, 700, 64, 2),
-    (128, 993, 64, 1), (64, 1023, 128, 1), (257, 1024, 128, 1),
+    (128, 993, 64, 1), (3, 1023, 128, 1), (257, 1024, 128, 1), (20, 960, 64, 5), (2100, 130, 64, 1),
 ])
 def test_bf16_one_pass(heads, n, d, G):
     for window in (1, 30, 64, 97, n):
