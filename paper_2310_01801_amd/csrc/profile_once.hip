@@ -18,12 +18,13 @@
 // would touch 32 cache lines per instruction (as fast measured, but 32 registers more).
 //
 // Bound: the vector ALU (56 % busy) with two waves per SIMD, whose waits at the block's barrier and for keys
-// from beyond L2 are the rest. 4096 units of 1024 tokens, d = 128, planted inputs: 870 + 1060 us in two sweeps, 1290 in
-// one pass (the walk back and forth: 1390 without); of 512 tokens 305 + 340 -> 357. Error of the column sums against
+// from beyond L2 are the rest. 4096 units of 1024 tokens, d = 128, planted inputs: 870 + 1060 us in two sweeps, 1250 in
+// one pass (the walk back and forth: 1390 without); of 512 tokens 305 + 340 -> 352. Error of the column sums against
 // float64: 1.66e-8 (two sweeps 1.91e-8), the same when shared. 64 units of 1000 tokens by four workgroups each 22
 // (one each 60, two sweeps 70). Tried without gain: the next fragment's matrix instructions between this
 // one's exponentials by hand (1410: more instructions, the same time), two to eight workgroups per unit that share
-// its keys in L2 (1420, and partial sums), query operands in registers (51 spills).
+// its keys in L2 (1420, and partial sums), query operands in registers (51 spills), the next block's first
+// contraction under this one's column sums (3 % slower, 12 % with many workgroups per unit).
 #include "fg_common.h"
 #include "fg_internal.h"
 
@@ -207,6 +208,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         __builtin_amdgcn_sched_barrier(0);
         held = j;
         if (s + 1 < kSlots && s + 1 < cnt) load_k(fragment(s + 1));   // the keys have been read
+        else if (i > 0) load_q(block(i - 1), buf ^ 1);   // (at the block's barrier, which waits for it: 3 to 5 % slower)
         if (j < 2 * b) {
           full(e[s][0], 0);
           full(e[s][1], 1);
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         ms[s][0] = m_run[0];
         ms[s][1] = m_run[1];
       }
-      if (i > 0) load_q(block(i - 1), buf ^ 1);
+      if (cnt == 0 && i > 0) load_q(block(i - 1), buf ^ 1);
       // (m, l) of row `lane` of the block: the halves of the wave (columns), then the waves
       {
         float ma = m_run[0], mb = m_run[1];
