@@ -38,7 +38,7 @@ MEASURED_TRAFFIC = {
                     "decode_attn": (9838007 * 2 + 274807) * 1024.0},
     "llama7b_b1": {"sweeps": (718457 * 2 + 16384 + 734949 * 2 + 53248) * 1024.0,
                    "decode_attn": (269828 * 2 + 11049) * 1024.0},
-    "llama7b_b16": {"sweeps": (6595921 * 2 + 131072 + 5888382 * 2 + 425984) * 1024.0,
+    "llama7b_b16": {"sweeps": (12024641 * 2 + 262144) * 1024.0,   # one pass
                     "decode_attn": (2147152 * 2 + 96773) * 1024.0},
     "llama13b_b4": {"sweeps": (8411611 * 2 + 204800 + 9088354 * 2 + 665600) * 1024.0,
                     "decode_attn": (4355092 * 2 + 116486) * 1024.0},

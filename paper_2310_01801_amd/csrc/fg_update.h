@@ -1,8 +1,8 @@
 // The kept-set update of one unit after a decode step (Alg. 2: f again, with the head's policy):
 // cumulative scores += this step's attention (policies with `frequent`, or every policy when the
 // step is probed), kept = special | punct | TopK(score, k_f(L)) | window, in-place release of the
-// evicted slots, and the probe's masses. Shared by the forms of a decode step (decode.hip, decode_unit.hip
-// and decode_group.hip). One workgroup of NT threads calls it for its unit.
+// evicted slots, and the probe's masses. Shared by the forms of a decode step (decode.hip, decode_unit.hip,
+// decode_group.hip and decode_group_mfma.hip). One workgroup of NT threads calls it for its unit.
 #pragma once
 #include "fg_common.h"
 #include "fg_internal.h"
