@@ -143,17 +143,18 @@ fg_status fastgen_profile(fastgen_ctx* ctx, const void* Q, const void* K,
 /* Stage 1a for callers that cannot allocate device memory and hold no workspace (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): fastgen_profile without
  * a context. The scratch its kernels need (row statistics, column and band sums, kept flags,
- * per-unit results) lives in a static device array of 32 MiB inside the library, one copy per
- * GPU, held until the process ends; the call allocates nothing, on the host or the device.
+ * per-unit results) lives in a static device array inside the library, 32 MiB and another 64 MiB
+ * for partial sums, one copy per GPU, held until the process ends; the call allocates nothing, on
+ * the host or the device.
  *   cfg          the configuration fastgen_create would take (max_new_tokens and cache_tokens
  *                only size the slot reservation and do not matter here). The shape is limited
- *                by the array: U * n * (8 * G + 21) + 112 * U bytes, each of the twelve regions
+ *                by the 32 MiB: U * n * (8 * G + 21) + 112 * U bytes, each of the twelve regions
  *                rounded up to 256 bytes, must not exceed 32 MiB (e.g. U * n <= 1.1 M tokens at
  *                G = 1); larger shapes return FG_ENOMEM and launch nothing.
  *   Q, K, token_class, lse_opt, policy, recovery, kept_count, stream: as for fastgen_profile;
  *                the caller owns inputs and outputs. The device that owns `stream` must be the
  *                current device.
- * Results are the same as fastgen_profile's for the same inputs. Every call on one GPU uses
+ * Results are the same as fastgen_profile's for the same inputs, bit for bit. Every call on one GPU uses
  * that GPU's one array: calls that overlap on a GPU (two streams, two threads) race; calls on
  * one stream are ordered. Nothing of a previous call is read. There is no context to compact
  * from: follow with fastgen_create / fastgen_profile when the cache is wanted. On failure

@@ -16,8 +16,8 @@
 // array lives on every GPU the library runs on, from module load until the process ends. In
 // host code the name `scratch` is only a handle for hipGetSymbolAddress; the device address it
 // yields (one per GPU) is what kernels and copies receive.
-static constexpr size_t kStaticScratchBytes = FG_STATIC_SCRATCH;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static constexpr size_t kStaticScratchBytes = FG_STATIC_SCRATCH;   // the profiling regions; behind them the partial sums
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + FG_PART_SUMS];
 static constexpr int kMaxDevices = 64;
 static void* g_scratch_ptr[kMaxDevices];   // device address of `scratch`, per GPU (NULL: not asked yet)
 static std::mutex g_scratch_mu;
@@ -128,7 +128,10 @@ fg_layout make_layout(const fg_config& c) {
   L.chunk_off = take((U + 1) * 4);
   L.item_unit = take((size_t)L.max_chunks * 32);
   L.part = take((size_t)L.max_chunks * G * (d + 2) * 4);
-  L.total = o;
+  // all that lies behind the profiling part is still unused while a prompt is profiled: the partial sums of workgroups
+  // that share a unit live there (more than a usual pool holds anyway)
+  const size_t sums = L.ck + align_up(fg_part_bytes(c));
+  L.total = o > sums ? o : sums;
   return L;
 }
 
@@ -189,11 +192,11 @@ struct PhaseChain {
 
 // The kernels of stage 1a in launch order, over scratch regions `L` inside `ws`. Shared by
 // fastgen_profile (regions in the caller's workspace) and fastgen_profile_static (regions in
-// the library's own static device array). `spare` is memory behind the regions, for partial sums.
+// the library's own static device array). `part_sums` holds fg_part_bytes(c).
 hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws, float scale, int w,
                                const void* Q, const void* K, const uint8_t* token_class,
                                const float* lse_opt, int32_t* policy, double* recovery,
-                               int32_t* kept_count, void* spare, size_t spare_bytes, hipStream_t s, PhaseChain& tm,
+                               int32_t* kept_count, void* part_sums, hipStream_t s, PhaseChain& tm,
                                const char** where) {
   auto at = [&](size_t off) { return ws + off; };
   fg_profile_args pa;
@@ -204,17 +207,12 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c);
   pa.scale = scale;
   hipError_t e;
-  fg_once_form once = {0, 1};   // both sweeps in one pass
-  if (!lse_opt) {
-    if (c.dtype == FG_BF16) once = fg_once_of(pa.d, pa.U, pa.n, pa.G);
-    else if (const int parts = fg_once_f32_parts(pa.U, pa.n, pa.G)) once = {4, parts};
-  }
-  // (a cache pool smaller than usual may not hold the partial sums)
-  if (once.waves && (once.parts == 1 || (size_t)once.parts * pa.U * pa.n * 16 <= spare_bytes)) {
+  const fg_once_form once = lse_opt ? fg_once_form{0, 1} : fg_once_form_of(c);   // both sweeps in one pass
+  if (once.waves) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
-    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(spare), s)
-                           : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(spare), s);
+    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
+                           : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
     tm.end();
     if (e != hipSuccess) return e;
   } else {
@@ -354,8 +352,7 @@ fg_status fastgen_profile(fastgen_ctx* ctx, const void* Q, const void* K, const 
   PhaseChain tm(ctx, s, ctx->timing != 0);
   const char* where = "";
   const hipError_t e = launch_profile_path(ctx->cfg, ctx->lay, ctx->ws, ctx->scale, ctx->w, Q, K, token_class,
-                                           lse_opt, policy, recovery, kept_count, ctx->ws + ctx->lay.ck,
-                                           ctx->lay.cscore - ctx->lay.ck, s, tm, &where);   // the pool is still empty
+                                           lse_opt, policy, recovery, kept_count, ctx->ws + ctx->lay.ck, s, tm, &where);
   if (e != hipSuccess) return hip_fail(ctx, e, where);
   ctx->stage = 1;
   return FG_OK;
@@ -397,8 +394,7 @@ fg_status fastgen_profile_static(const fg_config* cfg, const void* Q, const void
   // every region the kernels read is written first by an earlier kernel of this call for all
   // U * n entries in use, so nothing left over from the previous call needs clearing
   e = launch_profile_path(*cfg, L, static_cast<char*>(base), scale_of(*cfg), window_of(*cfg), Q, K, token_class,
-                          lse_opt, policy, recovery, kept_count, static_cast<char*>(base) + need,
-                          kStaticScratchBytes - need, s, tm, &where);
+                          lse_opt, policy, recovery, kept_count, static_cast<char*>(base) + kStaticScratchBytes, s, tm, &where);
   if (e != hipSuccess) return sfail(FG_EHIP, "%s: %s", where, hipGetErrorString(e));
   return FG_OK;
 }

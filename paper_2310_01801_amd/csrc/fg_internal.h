@@ -182,16 +182,13 @@ inline fg_sweep_form fg_sweep_form_of(int d, int pass, int U, int n, int G) {
   return single ? FG_SWEEP_BLOCKS : FG_SWEEP_PAIRS;
 }
 
-// Scratch of fastgen_profile_static; the profiling regions of a shape take about this much of it.
+// Scratch of fastgen_profile_static: the profiling regions of every shape that it takes.
 constexpr size_t FG_STATIC_SCRATCH = (size_t)32 << 20;
-inline size_t fg_profile_bytes(size_t U, size_t n, size_t G) { return U * n * (8 * G + 21) + 112 * U + 16 * 256; }
 
-// Workgroups per unit that fit beside the profiling regions of a shape that fastgen_profile_static takes (both entry
-// points then add the same partial sums); any number for larger shapes.
-inline long long fg_parts_that_fit(int U, int n, int G) {
-  const size_t held = fg_profile_bytes((size_t)U, (size_t)n, (size_t)G);
-  return held <= FG_STATIC_SCRATCH ? (long long)((FG_STATIC_SCRATCH - held) / ((size_t)U * n * 16)) : 1 << 20;
-}
+// Room for the partial sums [parts, U, n] of the one-pass kernels, two doubles each. The rules below choose within it by the
+// shape alone, and a context's workspace as well as the static scratch always hold it, so that a shape gives
+// the same bits with any cache pool and from either entry point. (Most chosen: 60 MiB, 1920 units of 1024 tokens in two parts.)
+constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 
 // Both bf16 sweeps in one pass (profile_once.hip): waves of a workgroup and workgroups per unit, 0 waves where the two
 // sweeps serve. A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU. Measured,
@@ -201,10 +198,14 @@ inline long long fg_parts_that_fit(int U, int n, int G) {
 //   d = 64     4096 of 1024 1047 / 988 (1), 64 of 1000 46 / 21 (4), 32 of 400 20 / 16 (6), 4 of 1000 30 / 27 (12)
 //   G = 4      d = 128: 32 of 512 54 / 26 (8), 200 of 333 91 / 54, 64 of 64 19 / 22; d = 64: 16 of 200 22 / 23, 8 of 333
 //              27 / 28; G = 8: 128 of 64 29 / 38, d = 64: 32 of 256 38 / 39
-// Parts: the more of the places are taken in the last round the better, less 5 % for every further part's
-// prologue and sums; an extra launch adds the sums, so a single pair of blocks stays whole. Above 2048 units nothing is
-// gained. A unit's G heads are one workgroup's work one after the other, where the first sweep alone has a
-// workgroup for each: several heads need enough 64 x 64 tiles in all, and single blocks of them enough units.
+// Parts, at most ten: the more of the places are taken in the last round the better, less 5 % for every further
+// part's prologue and sums; an extra launch adds the sums, so a single pair of blocks stays whole. The parts of a unit run
+// on one XCD and units are dealt out over the eight, so the fullest XCD (eighths of the units, rounded up) counts the rounds: 83
+// units of 519 tokens, d = 64, G = 16, 33 workgroups on 32 CUs with three parts 261, with five 185 (two sweeps
+// 194). Above 512 units a part needs work enough (658 of 159, d = 64, G = 2, one part 31.9, three 36.6; 1746 of 365, d =
+// 64, one 80, two 92; 1099 of 365, G = 16, one 851, three 761); above 2048 nothing is gained. A unit's G heads are one
+// workgroup's work one after the other, where the first sweep alone has a workgroup for each: several heads need
+// enough 64 x 64 tiles in all, and single blocks of them enough units.
 struct fg_once_form { int waves, parts; };
 inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (n > 1024 || U > (1 << 22)) return {0, 1};
@@ -219,19 +220,18 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (G > 8 && U < 32) return {0, 1};
   const int waves = n > 512 || (U <= 128 && n > 128) ? 8 : 4, places = waves == 8 ? 256 : 512;
   int parts = 1;
-  if (U <= 2048 && (blocks > 2 || (blocks == 2 && G > 1))) {
-    long long most = fg_parts_that_fit(U, n, G);
-    if (most > 12) most = 12;
+  if (U <= 2048 && (blocks > 2 || (blocks == 2 && G > 1)) && (U <= 512 || G * blocks >= (U <= 1024 ? 8 : 16))) {
+    long long most = (long long)(FG_PART_SUMS / ((size_t)U * n * 16));
+    if (most > 10) most = 10;
     if (most > blocks) most = blocks;
     double best = 0.0;
     for (int p = 1; p <= most; ++p) {
-      const long long groups = (long long)U * p, rounds = (groups + places - 1) / places;
-      const double score = (double)groups / (double)(rounds * places) * (1.05 - 0.05 * p);
+      const int rounds = ((U + 7) / 8 * p + places / 8 - 1) / (places / 8);
+      const double score = (double)U * p / ((double)rounds * places) * (1.05 - 0.05 * p);
       if (score > best + 1e-9) { best = score; parts = p; }
     }
   }
-  // a last round that is mostly empty and cannot be filled: 300 of 1000, d = 64, G = 8: 703 / 951,
-  // 2049 of 1000, d = 64: 610 / 650
+  // a last round that is mostly empty and not filled: 2049 of 1000, d = 64: 610 / 650
   if (parts == 1 && U > 256 && n > 512 && (d == 64 || G > 1) &&
       (double)U < (d == 64 && n > 896 ? 0.85 : 0.75) * (double)((U + places - 1) / places) * places)
     return {0, 1};
@@ -239,7 +239,7 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
 }
 
 // Both float32 sweeps in one pass (profile_f32.hip): workgroups per unit, 0 where the two sweeps serve. Up to 2048
-// workgroups in all, at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
+// workgroups in all (32 MiB of partial sums at most), at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
 //   64 units of 1000 tokens, d = 128     428 / 236;  16 of 1000 126 / 73;  8 of 1000, G = 4: 270 / 157
 //   64 of 128, d = 128                   25 / 16, d = 64, G = 4: 40 / 34;  128 of 64, d = 64, G = 2: 17 / 16
 //   32 of 128, G = 4                     42 / 49;  4 of 700, G = 4: 122 / 170;  400 of 40, d = 64, G = 4: 45 / 55
@@ -248,9 +248,20 @@ inline int fg_once_f32_parts(int U, int n, int G) {
   if (n < 64 || n > 1024 || U > (1 << 22)) return 0;
   const long long blocks = (n + 15) / 16;
   long long parts = 2048 / U < blocks / 2 ? 2048 / U : blocks / 2;
-  if (parts > fg_parts_that_fit(U, n, G)) parts = fg_parts_that_fit(U, n, G);
   if (parts < 2) parts = 1;
   return U * parts >= 256 ? (int)parts : 0;
+}
+
+// What serves a configuration without a supplied log-sum-exp (0 waves: the two sweeps), and the bytes of its partial sums.
+inline fg_once_form fg_once_form_of(const fg_config& c) {
+  const int G = c.group_size > 1 ? c.group_size : 1;
+  if (c.dtype == FG_BF16) return fg_once_of(c.head_dim, c.num_units, c.prompt_len, G);
+  const int parts = fg_once_f32_parts(c.num_units, c.prompt_len, G);
+  return {parts ? 4 : 0, parts ? parts : 1};
+}
+inline size_t fg_part_bytes(const fg_config& c) {
+  const fg_once_form f = fg_once_form_of(c);
+  return f.waves && f.parts > 1 ? (size_t)f.parts * c.num_units * c.prompt_len * 16 : 0;
 }
 
 // ---------------------------------------------------------------- launch arguments

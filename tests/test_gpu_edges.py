@@ -93,8 +93,7 @@ def test_bf16_sweep_forms(heads, n, d, G):
 
 
 # Both float32 sweeps in one pass: tiles of 16, four waves that hold 4, 8 or 16 of them each (256, 512 and 1024 columns),
-# one or several workgroups per unit, windows whose edge falls in, at and across tiles; a pool too small for the
-# partial sums takes the two sweeps
+# one or several workgroups per unit, windows whose edge falls in, at and across tiles
 @pytest.mark.parametrize("heads,n,d,G", [
     (128, 64, 64, 1), (128, 65, 128, 1), (64, 129, 64, 2), (64, 256, 128, 1), (64, 257, 64, 1), (40, 512, 128, 1), (40, 513, 64, 1),
     (16, 1000, 128, 1), (12, 1024, 64, 3), (300, 100, 128, 1), (2100, 70, 64, 1),
@@ -129,22 +128,29 @@ def test_f32_one_pass_with_huge_logits(pattern):
     assert float((recovery[:, 0].cpu() - (n - at) / n).abs().max()) < 1e-6   # rows from `at` on give it all their mass
 
 
-def test_f32_one_pass_needs_the_pool():
-    U, n, d = 16, 700, 128
+# The form of the pass follows from the shape alone: a pool that holds all, some or none of the partial sums of workgroups
+# that share a unit gives the same bits, and so does the entry point without a context
+@pytest.mark.parametrize("U,n,d,G,dtype", [(16, 700, 128, 1, torch.float32), (64, 1000, 64, 1, torch.float32), (16, 1000, 64, 1, torch.bfloat16),
+                                           (32, 333, 128, 1, torch.bfloat16), (64, 400, 128, 4, torch.bfloat16), (640, 1000, 64, 1, torch.bfloat16)])
+def test_one_pass_with_any_pool(U, n, d, G, dtype):
     gen = torch.Generator(device="cuda:0").manual_seed(4)
-    Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0") for _ in range(2))
+    Q, K = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=dtype) for x in (U * G, U))
     cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
     cls[0, 0] = 1
-    got = []
-    for pool in (0, U * 8):
-        fg = binding.FastGen(binding.make_config(U, 1, d, torch.float32, n, 4, 0.95, 0.3, 0.3, cache_tokens=pool))
+    cfg = binding.make_config(U, 1, d, dtype, n, 4, 0.95, 0.3, 0.3, group_size=G)
+    want = (torch.empty(U, dtype=torch.int32, device="cuda:0"), torch.empty((U, 5), dtype=torch.float64, device="cuda:0"),
+            torch.empty((U, 5), dtype=torch.int32, device="cuda:0"))
+    binding.fastgen_profile_static(cfg, Q, K, cls, *want)
+    for pool in (0, U * 8, U * n * 2 // 5):
+        cfg.cache_tokens = pool
+        fg = binding.FastGen(cfg)
+        fg.workspace.fill_(255)
         fg.fastgen_enable_timing(1)
-        got.append(fg.fastgen_profile(Q, K, cls))
+        got = fg.fastgen_profile(Q, K, cls)
         torch.cuda.synchronize()
-        assert fg.fastgen_read_timing()["sweep2"][1] == (1 if pool else 0)
+        assert fg.fastgen_read_timing()["sweep2"][1] == 0
+        assert all(torch.equal(x, y) for x, y in zip(got, want)), pool
         fg.close()
-    assert torch.equal(got[0][0], got[1][0])
-    assert float((got[0][1] - got[1][1]).abs().max()) < 1e-7
 
 
 # Three to eight bf16 heads on the matrix cores: tiles of 32 tokens (two sets of 16) over eight waves, four and eight
