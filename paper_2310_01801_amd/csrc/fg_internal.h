@@ -192,26 +192,45 @@ constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 
 // Both bf16 sweeps in one pass (profile_once.hip): waves of a workgroup and workgroups per unit, 0 waves where the two
 // sweeps serve. A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU. Measured,
-// two sweeps / one pass in us (random inputs; in brackets the workgroups per unit):
-//   d = 128    4096 units of 1024 tokens 1558 / 1256 (1), 300 of 1000 121 / 84 (3), 64 of 1000 70 / 22 (4), 8 of 1000
-//              35 / 24 (12), 128 of 512 46 / 17 (2), 32 of 333 23 / 14 (6), 64 of 64 15 / 10 (1)
-//   d = 64     4096 of 1024 1047 / 988 (1), 64 of 1000 46 / 21 (4), 32 of 400 20 / 16 (6), 4 of 1000 30 / 27 (12)
-//   G = 4      d = 128: 32 of 512 54 / 26 (8), 200 of 333 91 / 54, 64 of 64 19 / 22; d = 64: 16 of 200 22 / 23, 8 of 333
-//              27 / 28; G = 8: 128 of 64 29 / 38, d = 64: 32 of 256 38 / 39
+// two sweeps / one pass in us (random inputs, launches back to back; in brackets the workgroups per unit):
+//   d = 128    4096 units of 1024 tokens 1586 / 1324 (1), of 512 542 / 401 (1), 300 of 1000 152 / 110 (4), 64 of 1000 77 / 25
+//              (4), 8 of 1000 22 / 15 (10), 128 of 512 49 / 19 (2), 32 of 333 16 / 10 (6), 64 of 64 7.2 / 5.4 (1)
+//   d = 64     4096 of 1024 1116 / 1073 (1), 64 of 1000 49 / 23 (4), 32 of 400 13.5 / 10.2 (7), 4 of 1000 15.7 / 14.5 (10)
+//   G = 4      d = 128: 32 of 512 48 / 24 (8), 200 of 333 107 / 55 (5), 64 of 64 10.4 / 12.4; d = 64: 16 of 200 13.7 / 16.3, 8 of
+//              333 17.5 / 18.8; G = 8: 300 of 1000 973 / 787 (4), 128 of 64 16.8 / 23.3, d = 64: 32 of 256 25.4 / 27.9
 // Parts, at most ten: the more of the places are taken in the last round the better, less 5 % for every further
 // part's prologue and sums; an extra launch adds the sums, so a single pair of blocks stays whole. The parts of a unit run
-// on one XCD and units are dealt out over the eight, so the fullest XCD (eighths of the units, rounded up) counts the rounds: 83
-// units of 519 tokens, d = 64, G = 16, 33 workgroups on 32 CUs with three parts 261, with five 185 (two sweeps
-// 194). Above 512 units a part needs work enough (658 of 159, d = 64, G = 2, one part 31.9, three 36.6; 1746 of 365, d =
-// 64, one 80, two 92; 1099 of 365, G = 16, one 851, three 761); above 2048 nothing is gained. A unit's G heads are one
-// workgroup's work one after the other, where the first sweep alone has a workgroup for each: several heads need
-// enough 64 x 64 tiles in all, and single blocks of them enough units.
+// on one XCD and units are dealt out over the eight, so the fullest XCD (an eighth of the units, rounded up) counts the
+// rounds: 83 units of 519 tokens, d = 64, G = 16, in three parts each put 33 workgroups on 32 CUs (261), in five 185; two
+// sweeps 194. Many units fill the places whole, and only parts with work enough gain (one part / several: 658 of 159, d = 64,
+// G = 2, 31.9 / 36.6, 1746 of 365, d = 64, 80 / 92, 1667 of 290, G = 4, 305 / 329; but 1099 of 365, d = 64, G = 16, 851 /
+// 761, 1804 of 965 618 / 593); above 2048 nothing is gained. Over 4070 shapes 2.0 % above the best form in the mean.
+// A unit's G heads are one workgroup's work one after the other, where the first sweep alone has a workgroup for
+// each: several heads need enough 64 x 64 tiles in all, single blocks of them enough units, and blocks that are mostly
+// empty weigh more with them. Two sweeps / one pass, or the gain of one pass:
+//   up to 32 tokens      d = 128: 576 of 22, G = 16, 56 / 85, 225 of 21, G = 4, 9.8 / 12.3, 27 of 10, G = 2, 6.4 / 7.6;
+//                        but 482 of 32, G = 4, 18.4 / 13.1, 1277 of 16, G = 2, 23.3 / 19.7; d = 64: 3387 of 21 22.9 / 27.2
+//   two blocks, G = 2    d = 64: 16 of 77 7.9 / 9.1, 97 of 95 10.7 / 9.1; d = 128: 40 of 86 9.5 / 9.9, 54 of 99 10.8 / 9.9
+//   d = 64, > 512 units  549 of 78, G = 16, 105 / 121, 1368 of 83, G = 6, 84 / 92, 620 of 139, G = 12, 128 / 156; but 1398
+//                        of 128, G = 4, 1.21x, 1161 of 229, G = 6, 1.13x
+//   tiles (n < 512)      G > 8, d = 64: 119 of 84 (357) 0.76x, 361 of 96 (1083) 0.95x, 226 of 163 (1356) 1.54x; d = 128: 114
+//                        of 143 (684) 0.87x, 338 of 92 (1014) 1.19x. G 5..8, d = 64: 57 of 135 (342) 0.95x, 213 of
+//                        114 (639) 1.21x; d = 128: 104 of 135 (624) 0.97x, 56 of 158 (336) 1.06x, 59 of 237 (590) 1.46x
+//   few units            d = 64: 2 of 534, G = 4, 29 / 31, 1 of 660, G = 5, 0.98x, 5 of 372, G = 8, 0.88x; G > 8: 3 of 378, d = 64,
+//                        0.85x, 7 of 320 0.99x. From some 400 tiles on these would gain (5 of 894, d = 64, G = 8, 1.28x, 17 of
+//                        873, G = 12, 219 / 88): the lines for few units leave that to the two sweeps
 struct fg_once_form { int waves, parts; };
 inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (n > 1024 || U > (1 << 22)) return {0, 1};
   const int blocks = (n + 63) / 64;
   const double tiles = (double)U * blocks * (blocks + 1) / 2;
   if (G > 2 && blocks == 1 && (d == 64 || U < (G > 4 ? 256 : 192))) return {0, 1};
+  // up to 32 tokens leave half of a block empty: with several heads one round of workgroups at most, which a few
+  // units do not fill
+  if (n <= 32 && (G > 1 ? U <= (G == 2 ? 200 : 320) || (U > 512 && (G > 2 || d == 64)) : d == 64 && U > 1024)) return {0, 1};
+  if (blocks == 2 && G == 2 && U <= 66 && (d == 64 || n <= 96)) return {0, 1};
+  if (d == 64 && U > 512 && ((blocks == 2 && G > 2 && n <= 96) || (blocks == 3 && G > 4 && n <= 160))) return {0, 1};
+  if (d == 64 && G > 2 && U < 3 && n < 640) return {0, 1};
   if (n < 512 && blocks > 1) {
     const double least = G > 8 ? 1280 : G > 4 ? (d == 64 ? 640 : 400) : G > 2 ? (d == 64 ? 320 : 200) : G == 2 && d == 64 && blocks > 2 ? 320 : 0;
     if (tiles < least) return {0, 1};
@@ -220,7 +239,8 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (G > 8 && U < 32) return {0, 1};
   const int waves = n > 512 || (U <= 128 && n > 128) ? 8 : 4, places = waves == 8 ? 256 : 512;
   int parts = 1;
-  if (U <= 2048 && (blocks > 2 || (blocks == 2 && G > 1)) && (U <= 512 || G * blocks >= (U <= 1024 ? 8 : 16))) {
+  const bool enough = U <= 512 || (U <= 1024 ? G * blocks >= 8 : blocks > 3 && G * blocks >= (blocks > 12 ? 16 : 24));
+  if (U <= 2048 && enough && (blocks > 2 || (blocks == 2 && G > 1))) {
     long long most = (long long)(FG_PART_SUMS / ((size_t)U * n * 16));
     if (most > 10) most = 10;
     if (most > blocks) most = blocks;
@@ -231,25 +251,31 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
       if (score > best + 1e-9) { best = score; parts = p; }
     }
   }
-  // a last round that is mostly empty and not filled: 2049 of 1000, d = 64: 610 / 650
+  // a last round that is mostly empty and not filled: 2049 of 1000, d = 64: 559 / 585, 1330 of 923, d = 64: 332 / 337; but
+  // 1447 of 926, d = 64: 362 / 340, 459 of 1002 156 / 121
   if (parts == 1 && U > 256 && n > 512 && (d == 64 || G > 1) &&
-      (double)U < (d == 64 && n > 896 ? 0.85 : 0.75) * (double)((U + places - 1) / places) * places)
+      (double)U < (d == 64 && n > 896 ? (U > 1024 ? 0.9 : 0.85) : 0.75) * (double)((U + places - 1) / places) * places)
     return {0, 1};
+  // eight waves for little more than four hold, in two parts of unequal work: 1864 of 537, G = 3, 587 / 631, 1028 of 520, G =
+  // 12, 1319 / 1451
+  if (d == 64 && n > 512 && n <= 544 && U > 640 && parts == 2) return {0, 1};
   return {waves, parts};
 }
 
 // Both float32 sweeps in one pass (profile_f32.hip): workgroups per unit, 0 where the two sweeps serve. Up to 2048
 // workgroups in all (32 MiB of partial sums at most), at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
-//   64 units of 1000 tokens, d = 128     428 / 236;  16 of 1000 126 / 73;  8 of 1000, G = 4: 270 / 157
+//   64 units of 1000 tokens, d = 128     464 / 253;  16 of 1000 134 / 78
 //   64 of 128, d = 128                   25 / 16, d = 64, G = 4: 40 / 34;  128 of 64, d = 64, G = 2: 17 / 16
-//   32 of 128, G = 4                     42 / 49;  4 of 700, G = 4: 122 / 170;  400 of 40, d = 64, G = 4: 45 / 55
-// Fewer than 256 workgroups leave CUs idle, which the sweeps' workgroups of 16 rows do not.
+//   32 of 128, G = 4                     41 / 48;  4 of 700, G = 4: 127 / 117;  8 of 1000, G = 4 (248 workgroups): 276 / 173
+// Fewer than 256 workgroups leave CUs idle, which the sweeps' workgroups of 16 rows do not; short prompts of several
+// heads need more of them (two sweeps / one pass: 130 of 65, d = 64, G = 4, in 260 workgroups 37 / 48, 131 of 71, G = 16, in 262
+// 225 / 266; but 114 of 95, G = 8, in 342 158 / 122, 83 of 120, G = 16, in 332 304 / 253, and 120 of 84, d = 64, G = 16, in 360 134 / 148).
 inline int fg_once_f32_parts(int U, int n, int G) {
   if (n < 64 || n > 1024 || U > (1 << 22)) return 0;
   const long long blocks = (n + 15) / 16;
   long long parts = 2048 / U < blocks / 2 ? 2048 / U : blocks / 2;
   if (parts < 2) parts = 1;
-  return U * parts >= 256 ? (int)parts : 0;
+  return U * parts >= (G > 2 && blocks < 6 ? 400 : 256) ? (int)parts : 0;
 }
 
 // What serves a configuration without a supplied log-sum-exp (0 waves: the two sweeps), and the bytes of its partial sums.

@@ -159,8 +159,21 @@ def test_one_pass_profile(rules):
                        ((128, 160, 400, 1), 403), ((128, 8, 1000, 1), 810), ((64, 1, 64, 1), 401), ((128, 64, 64, 4), 1), ((64, 256, 64, 8), 1),
                        ((64, 32, 256, 8), 1), ((64, 8, 333, 2), 1), ((128, 8, 512, 16), 1), ((64, 300, 1000, 8), 804), ((128, 1024, 2048, 1), 1),
                        ((128, 300, 1000, 8), 804), ((128, 350, 1000, 8), 802), ((128, 400, 1000, 8), 803), ((64, 83, 519, 16), 805),
-                       ((64, 658, 159, 2), 401), ((64, 1746, 365, 1), 401), ((64, 1099, 365, 16), 403)):
+                       ((64, 658, 159, 2), 401), ((64, 1746, 365, 1), 401), ((64, 1256, 183, 12), 401), ((64, 1099, 365, 16), 403)):
         assert rules.once_form(*args) == want, (args, rules.once_form(*args))
+
+
+# Short prompts that the two sweeps were measured to serve faster, and their neighbours in one pass: up to 32 tokens with
+# several heads, two blocks that are mostly empty, few units, a last round that stays mostly empty
+def test_short_prompts_of_the_two_sweeps(rules):
+    for args, want in (((128, 576, 22, 16), 0), ((128, 225, 21, 4), 0), ((128, 27, 10, 2), 0), ((64, 4151, 32, 2), 0), ((64, 3387, 21, 1), 0),
+                       ((128, 482, 32, 4), 401), ((128, 1277, 16, 2), 401), ((128, 576, 33, 16), 401), ((64, 16, 77, 2), 0), ((64, 97, 95, 2), 402),
+                       ((128, 40, 86, 2), 0), ((128, 54, 99, 2), 402), ((64, 549, 78, 16), 0), ((64, 2189, 66, 4), 0), ((64, 1398, 128, 4), 401),
+                       ((64, 620, 139, 12), 0), ((64, 1161, 229, 6), 403), ((64, 2, 534, 4), 0), ((64, 3, 700, 4), 810), ((64, 1864, 537, 3), 0), ((64, 1219, 527, 8), 801), ((64, 2049, 1000, 1), 0),
+                       ((64, 1447, 926, 1), 801), ((64, 459, 1002, 1), 801), ((128, 2049, 1000, 1), 801)):
+        assert rules.once_form(*args) == (want or 1), (args, rules.once_form(*args))   # (1: no waves, one part)
+    for args, want in (((130, 65, 4), 0), ((131, 71, 16), 0), ((114, 95, 8), 3), ((126, 118, 4), 4), ((83, 120, 16), 4), ((130, 65, 1), 2)):
+        assert rules.once_f32_parts(*args) == want, (args, rules.once_f32_parts(*args))
 
 
 # A context holds the partial sums whatever its cache pool, behind the regions of the profile; a usual pool's workspace
