@@ -92,6 +92,14 @@ constexpr int FG_UNIT_TOKENS = 4608, FG_UNIT_TOKENS_256 = 2048, FG_UPDATE_TOKENS
 //   256 units of 2048 tokens, G = 4                66 / 34 us;  16 of 300, G = 8: 37 / 17
 //   300 of 3000, G = 8                             170 / 60;  64 of 3000, G = 8: 86 / 55, G = 3: 43 / 37
 //   4 of 3000, G = 3                               28 / 33, G = 4: 33 / 34;  16 of 2500, G = 3: 27 / 30
+// A few long units of theirs (per unit / split, d = 128; its time goes with the unit's bytes and with the four or eight
+// columns that the heads are padded to, the split form's with the heads; full caches, which have no update, part earlier):
+//   G = 5      1 of 4600 policy 3 66 / 50, full 1.57x; 12 of 3200 1.17x; 24 of 2600 1.11x; 32 of 4000 1.11x; 4 of 1600 1.0x, 64
+//              of 3200 0.95x;  d = 64: 1 of 4600 full 1.10x, 4 of 3200 0.93x
+//   G = 6      4 of 4000 policy 3 1.22x, full 1.21x; 12 of 2600 1.06x, 0.99x; 24 of 4000 1.01x, 0.95x;  G = 7 full 1 of 4600 1.20x,
+//              of 3200 1.01x;  G = 8 full 4 of 4600 1.08x, of 4000 0.98x
+//   G = 3      full 4 of 2000 1.45x, 24 of 1600 1.10x, 48 of 3200 1.12x, 64 of 3200 1.05x, 96 of 4000 0.96x; others 4 of 2000
+//              1.09x, 32 of 3000 1.06x, 48 of 2600 1.02x;  G = 4 full 4 of 2000 1.18x, 24 of 2000 1.05x, 32 of 2600 1.00x
 // So: long units stay split (a few of them decide how long the launch takes), and where there are
 // fewer units than CUs a workgroup's own rate bounds the bytes (tokens times heads) per unit. The step
 // is a one-dimensional launch: 512 threads per unit only while that stays below 2^32 threads.
@@ -129,7 +137,19 @@ inline int fg_unit_threads(const fg_config& c) {
     if (U > 256 && U <= 360 && held > 0.8e6 && tokens * group <= (matrix && group > 3 ? 0 : 16000)) return 0;
     if (U > 256 && c.forced_policy < 4 && group == 1 && held > 1.2e6) return 0;
   }
-  if (matrix) return U < 32 && group <= 4 && tokens > 2200 ? 0 : 512;
+  if (matrix) {
+    // longest tokens at d = 128 for up to so many units, from there on growing with their square (three to eight heads)
+    static const struct { int tokens, units; } line[2][6] = {
+        {{1700, 28}, {FG_UNIT_TOKENS, 1}, {1700, 28}, {2400, 12}, {FG_UNIT_TOKENS, 1}, {FG_UNIT_TOKENS, 1}},
+        {{1200, 40}, {1200, 20}, {1800, 20}, {2400, 20}, {3000, 16}, {4000, 16}}};   // full caches
+    const auto& few = line[c.forced_policy == 4][group - 3];
+    const double over = U > few.units ? (double)U / few.units : 1.0;
+    // what one policy evicts counts less (policy 2, ratio 0.3: 2 of 1819, G = 5, 26 / 31; policy 0: 7 of 4590, G = 5, 8 / 24)
+    const double share = c.forced_policy >= 0 ? fg_forced_share(c) : 1.0;
+    const double held = (double)tokens * row_bytes * (share >= 0.6 ? 1.0 : share > 0.0 ? 0.4 + share : 0.0);
+    if (held > few.tokens * 256.0 * over * over) return 0;
+    return U < 32 && group <= 4 && tokens > 2200 ? 0 : 512;
+  }
   if (group > 1) return tokens * group <= (U < 256 ? 2048 : 20000) ? 512 : 0;
   if (U < 256) return unit_bytes <= (1 << 20) ? 512 : 0;
   if (U > 256 && row_bytes > 256 && tokens > 1856) return 0;

@@ -128,12 +128,18 @@ def test_one_pass_f32_parts(rules):
         assert rules.once_f32_parts(*args) == want, (args, rules.once_f32_parts(*args))
 
 
-# Three to eight bf16 heads: one workgroup per unit wherever it holds the unit, but a few long ones
+# Three to eight bf16 heads: one workgroup per unit wherever it holds the unit, but a few long ones (fewer and longer the
+# more heads share the padded columns, and with full caches earlier)
 def test_matrix_core_group_forms(rules):
     for U, tokens, G, dtype, forced, want in ((64, 3000, 8, BF16, -1, 512), (4, 4608, 8, BF16, -1, 512), (4, 3000, 4, BF16, -1, 0),
-                                              (32, 3000, 3, BF16, -1, 512), (4, 1000, 4, BF16, 4, 512), (300, 2000, 4, BF16, 4, 512),
+                                              (32, 3000, 3, BF16, -1, 0), (48, 3000, 3, BF16, -1, 512), (4, 1000, 4, BF16, 4, 512), (300, 2000, 4, BF16, 4, 512),
                                               (280, 3000, 3, BF16, 4, 0), (256, 4609, 4, BF16, -1, 0), (64, 3000, 9, BF16, -1, 0),
-                                              (64, 3000, 2, BF16, -1, 0), (64, 3000, 8, F32, -1, 0)):
+                                              (64, 3000, 2, BF16, -1, 0), (64, 3000, 8, F32, -1, 0),
+                                              (8, 4506, 5, BF16, -1, 0), (1, 2822, 5, BF16, 3, 0), (24, 2706, 5, BF16, -1, 0), (4, 1600, 5, BF16, 3, 512),
+                                              (64, 3200, 5, BF16, -1, 512), (7, 4264, 6, BF16, 3, 0), (24, 4000, 6, BF16, 3, 512), (8, 4575, 6, BF16, 4, 0),
+                                              (1, 4600, 7, BF16, 4, 0), (1, 4600, 7, BF16, 3, 512), (4, 4600, 8, BF16, 4, 0), (11, 2085, 4, BF16, 4, 0),
+                                              (24, 1600, 3, BF16, 4, 0), (96, 4000, 3, BF16, 4, 512), (2, 1819, 5, BF16, 2, 512), (4, 3974, 5, BF16, 2, 0),
+                                              (7, 4590, 5, BF16, 0, 512)):
         assert rules.unit_threads(ctypes.byref(_cfg(U, tokens - 8, 8, 128, dtype, group_size=G, forced_policy=forced))) == want
 
 
