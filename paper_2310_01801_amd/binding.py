@@ -46,10 +46,11 @@ class FastGenError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
+_classify = None   # fastgen_classify that takes the id lists' addresses, for lists checked in _ids
 
 
 def load_library() -> ctypes.CDLL:
-    global _lib
+    global _lib, _classify
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -67,7 +68,8 @@ def load_library() -> ctypes.CDLL:
     lib.fastgen_profile_static.restype = ctypes.c_int
     lib.fastgen_profile_static.argtypes = [cp] + [vp] * 8
     lib.fastgen_classify.restype = ctypes.c_int
-    lib.fastgen_classify.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int32, vp, ctypes.c_int32, vp, vp]
+    ids = ctypes.POINTER(ctypes.c_int32)
+    lib.fastgen_classify.argtypes = [vp, ctypes.c_int64, ids, ctypes.c_int32, ids, ctypes.c_int32, vp, vp]
     lib.fastgen_compact.restype = ctypes.c_int
     lib.fastgen_compact.argtypes = [vp] * 4
     lib.fastgen_decode_step.restype = ctypes.c_int
@@ -84,7 +86,11 @@ def load_library() -> ctypes.CDLL:
     lib.fastgen_read_timing.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     lib.fastgen_version.restype = ctypes.c_char_p
     lib.fastgen_version.argtypes = []
-    _lib = lib
+    raw = lib["fastgen_classify"]   # a function object of its own (the checked pointers: 0.7 to 1.8 us more per call)
+    raw.restype = ctypes.c_int
+    raw.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int32, vp, ctypes.c_int32, vp, vp]
+    _classify = raw
+    _lib = lib   # last: other threads look at this one
     return lib
 
 
@@ -126,7 +132,7 @@ def fastgen_workspace_bytes(cfg: FgConfig) -> int:
 def _ids(ids):
     """A host sequence of ids as int32 values, and their address."""
     if type(ids) in (list, tuple):
-        try:   # (a ctypes array of 16 ids: 1.0 us more; it is what wraps and truncates other values)
+        try:   # (ctypes arrays of 1 and 16 ids: 3 us more per call; they wrap and truncate other values)
             held = array("i", ids)
             return held, held.buffer_info()[0]
         except (TypeError, OverflowError):
@@ -144,8 +150,8 @@ def fastgen_classify(token_ids: torch.Tensor, special_ids, punct_ids,
     if token_class is None:
         token_class = torch.empty_like(token_ids, dtype=torch.uint8)   # (a sized torch.empty: 1 us more)
     (special, sp), (punct, pu) = _ids(special_ids), _ids(punct_ids)
-    st = lib.fastgen_classify(_ptr(token_ids), token_ids.numel(), sp, len(special_ids), pu, len(punct_ids),
-                              _ptr(token_class), _stream())
+    st = _classify(_ptr(token_ids), token_ids.numel(), sp, len(special_ids), pu, len(punct_ids),
+                   _ptr(token_class), _stream())
     if st != FG_OK:
         raise FastGenError(st, lib.fastgen_last_error(None).decode())
     return token_class

@@ -115,6 +115,21 @@ def test_classify_rejects_bad_arguments_on_the_host(lib):
     assert call(fake, 8, None, 3, None, 0, fake, None) == binding.FG_EINVAL        # a count without a list
 
 
+def test_classify_takes_id_lists_of_32_bit_integers_only(lib):
+    # the declared pointer type refuses other arrays and bare addresses, whose bytes would be read as ids
+    for wrong in ((ctypes.c_int64 * 2)(1, 2), (ctypes.c_uint8 * 8)(1, 2), 0x10000):
+        for args in ((wrong, 2, None, 0), (None, 0, wrong, 2)):
+            with pytest.raises(ctypes.ArgumentError):
+                lib.fastgen_classify(None, 0, *args, None, None)
+    assert lib.fastgen_classify(None, 0, (ctypes.c_int32 * 2)(1, 2), 2, None, 0, None, None) == binding.FG_OK
+    ids = [3, True, -(1 << 31), 1 << 31, -1]
+    for given, want in ((ids[:3], [3, 1, -(1 << 31)]), (tuple(ids), [3, 1, -(1 << 31), -(1 << 31), -1]), (["7", 2.9], [7, 2]),
+                        (binding.torch.tensor([5, 6]), [5, 6]), ((), []), ([], []), (range(3), [0, 1, 2])):
+        held, address = binding._ids(given)
+        assert list(held)[:len(want)] == want
+        assert not want or list((ctypes.c_int32 * len(want)).from_address(address)) == want
+
+
 def test_microbenchmark_library_loads_and_rejects_bad_arguments(lib):
     # the measurement aid of bench.py: built next to the main library, one C entry point
     path = os.path.join(os.path.dirname(binding.LIB_PATH), "libfgubench.so")
