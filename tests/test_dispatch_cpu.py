@@ -109,6 +109,21 @@ def test_every_accepted_size_has_a_sweep_form(rules):
                         assert forms[0] == PAIRS, (d, n, U, G)
 
 
+# The shapes of the two-sweep tests on the GPU do not go in one pass, and reach every form
+def test_forms_of_the_tested_two_sweep_shapes(rules):
+    seen = set()
+    for d, U, n, G, want in ((64, 2, 1033, 1, (SPLIT_32, SPLIT_32)), (128, 1, 1025, 1, (SPLIT_32, SPLIT_32)), (128, 16, 1100, 1, (SPLIT_64, SPLIT_64)),
+                             (64, 16, 1100, 1, (SPLIT_64, SPLIT_64)), (64, 9, 2049, 1, (SPLIT_64, SPLIT_64)), (128, 100, 1032, 1, (BLOCKS, PAIRS)),
+                             (64, 100, 1032, 1, (BLOCKS, BLOCKS)), (64, 120, 1513, 1, (BLOCKS, BLOCKS)), (128, 50, 1513, 2, (BLOCKS, SPLIT_64)),
+                             (128, 200, 1100, 1, (PAIRS, PAIRS)), (128, 4, 300, 8, (SPLIT_64, SPLIT_32)), (64, 8, 333, 2, (SPLIT_32, SPLIT_32)),
+                             (64, 256, 64, 8, (PAIRS, SPLIT_64)), (64, 549, 78, 16, (PAIRS, BLOCKS)), (128, 600, 30, 16, (PAIRS, PAIRS)),
+                             (64, 32, 256, 8, (BLOCKS, SPLIT_32)), (64, 4, 1100, 4, (SPLIT_64, SPLIT_32)), (64, 4, 1500, 1, (SPLIT_32, SPLIT_32)), (64, 260, 1029, 1, (PAIRS, PAIRS))):
+        assert rules.once_form(d, U, n, G) == 1, (d, U, n, G)
+        assert tuple(rules.sweep_form(d, p, U, n, G) for p in (1, 2)) == want, (d, U, n, G)
+        seen |= {(d, p, form) for p, form in enumerate(want)}
+    assert len(seen) == 15   # all but the single blocks of the second sweep at d = 128
+
+
 F32, BF16 = binding.torch.float32, binding.torch.bfloat16
 
 

@@ -75,9 +75,8 @@ def test_selection_sizes(heads, n):
     H.log_report(f"selection U={heads} n={n}", rep)
 
 
-# bf16 sweeps: the split stream with one or two fragments of 32 owners (few units), 256-owner blocks
-# taken singly (first sweep; both at d = 64) or in pairs, by unit count; prompt lengths around tiles
-# and blocks, and local windows whose edge falls inside, at and across tiles
+# bf16 prompts of all lengths around tiles and blocks, and local windows whose edge falls inside, at and across tiles.
+# Most go in one pass; the forms of the two sweeps have the test after this one
 @pytest.mark.parametrize("heads,n,d,G", [
     (2, 31, 128, 1), (2, 32, 64, 1), (3, 33, 128, 1), (3, 63, 64, 2), (3, 65, 128, 1), (5, 129, 128, 2), (4, 300, 128, 8),
     (24, 333, 128, 1), (24, 257, 64, 1), (200, 400, 128, 1), (200, 400, 64, 1), (9, 2049, 64, 1),
@@ -90,6 +89,25 @@ def test_bf16_sweep_forms(heads, n, d, G):
         run = H.GpuRun(w, range(w.num_units), group_size=G)
         rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
         H.log_report(f"sweep forms U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
+# bf16 sweeps: the split stream with one or two fragments of 32 owners (few units), 256-owner blocks taken singly (first
+# sweep; both at d = 64) or in pairs, by unit count: prompts above 1024 tokens, and the short ones of several heads that
+# one pass does not serve (the form of every shape here is asserted in test_dispatch_cpu.py)
+@pytest.mark.parametrize("heads,n,d,G", [
+    (2, 1033, 64, 1), (1, 1025, 128, 1), (16, 1100, 128, 1), (16, 1100, 64, 1), (9, 2049, 64, 1), (100, 1032, 128, 1), (100, 1032, 64, 1),
+    (120, 1513, 64, 1), (50, 1513, 128, 2), (200, 1100, 128, 1), (4, 300, 128, 8), (8, 333, 64, 2), (256, 64, 64, 8), (549, 78, 64, 16),
+    (600, 30, 128, 16), (32, 256, 64, 8), (260, 1029, 64, 1),
+])
+def test_two_sweep_forms(heads, n, d, G):
+    for window in (1, 31, 33, max(1, n // 3)):
+        w = W["llama7b_b1"].scaled(name="two_sweeps", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d,
+                                   r_l=min(1.0, (window + 0.5) / n), seed=600 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        run.fg.fastgen_enable_timing(1)
+        rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+        assert run.fg.fastgen_read_timing()["sweep2"][1] == 1
+        H.log_report(f"two sweeps U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
 # Both float32 sweeps in one pass: tiles of 16, four waves that hold 4, 8 or 16 of them each (256, 512 and 1024 columns),
@@ -188,6 +206,45 @@ def test_matrix_core_group_with_rising_logits():
     assert float((out.cpu().double() - a @ Vf).abs().max()) < 2e-2   # half a bf16 step below 8 is 2^-6
 
 
+# The scores of such heads: every tile keeps its exponentials under the shift of its wave at that moment, the sums are
+# rescaled whenever the shift moves, and the factors of the tiles meet at the end. Logits that rise and fall by half a
+# power of two per token (the shift moves in every tile, or once), and by 32 of them (factors of 2^-4096 and less).
+# Ratios of 1 keep every token, so that the scores grow by the step's attention and the probe sees whole classes. Logits
+# of up to 2e4 powers of two in float64: 2e4 x 2^-53 each, some of them added.
+@pytest.mark.parametrize("d,G", [(128, 4), (64, 4), (128, 8), (64, 8), (128, 3), (64, 6)])
+@pytest.mark.parametrize("forced", [2, 3])
+@pytest.mark.parametrize("slope", [0.25, -0.25, 16.0, -16.0])
+def test_matrix_core_group_scores_with_moving_shifts(d, G, forced, slope):
+    U, n = 6, 611
+    gen = torch.Generator(device="cuda:0").manual_seed(7)
+    Q, K, V = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U, U))
+    ramp = torch.arange(n + 1, device="cuda:0") * abs(slope)
+    ramp = (ramp if slope > 0 else ramp.flip(0)).bfloat16()
+    K[:, :, 0] = ramp[:n]
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    cls[0, ::7], cls[0, 3::11] = 1, 2
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 2, 0.95, 1.0, 1.0, forced_policy=forced, group_size=G))
+    fg.fastgen_profile(Q, K, cls)
+    fg.fastgen_compact(K, V)
+    before = fg.fastgen_export_state()["scores"].view(U, n)
+    q, k, v = (torch.randn(x, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U, U))
+    k[:, 0] = ramp[n]
+    q[:, 0] = torch.tensor([0.0, 4.0, 16.0, -16.0, 8.0, -8.0, 1.0, -2.0], device="cuda:0", dtype=torch.bfloat16)[:G].repeat(U)
+    new_class = torch.ones(1, dtype=torch.uint8, device="cuda:0")
+    out, probe = fg.fastgen_decode_step_probe(q, k, v, new_class)
+    after = fg.fastgen_export_state()["scores"].view(U, n + 1)
+    fg.close()
+    Kd, Vd = torch.cat([K, k[:, None]], 1).double().cpu(), torch.cat([V, v[:, None]], 1).double().cpu()
+    scale = float(torch.tensor(1.0 / math.sqrt(d), dtype=torch.float32))
+    a = torch.softmax(q.view(U, G, d).double().cpu() @ Kd.transpose(1, 2).contiguous() * scale, dim=2)
+    gained = after - torch.cat([before, torch.zeros_like(before[:, :1])], 1)
+    assert float((gained.cpu() - a.sum(1)).abs().max()) < 1e-10
+    held = torch.cat([cls[0], new_class]).cpu()
+    masses = [(a.mean(1) * ((held & bits) != 0)).sum(1) for bits in (1, 3)] + [torch.ones(U, dtype=torch.float64)] * 3
+    assert float((probe.cpu() - torch.stack(masses, 1)).abs().max()) < 1e-10
+    assert float((out.float().view(U, G, d).cpu().double() - a @ Vd).abs().max()) < 2e-2   # half a bf16 step below 8 is 2^-6
+
+
 # Both bf16 sweeps in one pass: fragments of 32 columns, blocks of 64 rows, four and eight waves, prompt lengths
 # around each and around a wave's next fragment (128, 256), windows whose edge falls in the first, the second or both
 # row fragments of a block; one and several workgroups per unit, even and odd numbers of blocks for them; grouped
@@ -239,8 +296,8 @@ def test_one_pass_with_huge_logits(n, at):
     assert float((recovery[:, 0].cpu() - want).abs().max()) < 1e-6
 
 
-# grouped heads, per-unit step (instantiated for up to 2, 4 and 8 heads; 16-, 8- and 32-lane rows) and
-# split-KV beyond its lines (more heads, more tokens), probed steps included
+# grouped heads, per-unit step (vector ALU for two heads and float32, matrix cores for three to eight bf16 heads) and
+# split-KV for more heads, probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
     (3, 1, 3, 128, "bf16", 2), (3, 17, 5, 128, "bf16", 3), (3, 130, 9, 128, "bf16", 4), (3, 130, 9, 64, "bf16", 4),
     (3, 250, 6, 128, "bf16", 5), (3, 250, 6, 128, "bf16", 8), (2, 251, 6, 64, "bf16", 8), (3, 100, 6, 128, "f32", 2),
@@ -254,6 +311,19 @@ def test_grouped_decode_step_forms(heads, n, S, d, dtype, G):
     check = sorted({0, 1, 2, heads // 2, heads - 1} & set(range(heads)))
     rep = H.compare(run, check_units=check, probe_steps=(1,), cover_policies=1)
     H.log_report(f"grouped forms U={heads} n={n} S={S} d={d} {dtype} G={G}", rep)
+
+
+# The split form of three to eight bf16 heads: a few long units, full caches earlier, and more than 4608 tokens
+@pytest.mark.parametrize("heads,n,S,d,G,forced", [(3, 2300, 4, 128, 3, -1), (2, 1900, 4, 128, 5, 3), (2, 1300, 4, 128, 3, 4), (3, 1500, 3, 128, 4, 4),
+                                                  (2, 2600, 4, 128, 6, -1), (2, 4650, 4, 64, 8, -1), (2, 4650, 3, 64, 7, 2)])
+def test_split_grouped_steps(heads, n, S, d, G, forced):
+    w = W["llama7b_b1"].scaled(name="grouped_split", layers=1, heads=heads, batch=1, prompt_len=n, steps=S, head_dim=d,
+                               dtype="bf16", seed=500 + n)
+    run = H.GpuRun(w, range(w.num_units), group_size=G, forced_policy=forced)
+    run.fg.fastgen_enable_timing(1)
+    rep = H.compare(run, probe_steps=(1,))
+    assert run.fg.fastgen_read_timing()["decode_update"][1] == S
+    H.log_report(f"grouped split U={heads} n={n} S={S} d={d} G={G} forced={forced}", rep)
 
 
 # float32 outputs of a grouped step: both forms of the step on the same inputs (which one runs depends
@@ -310,17 +380,22 @@ def test_step_without_a_free_slot_is_reported(G):
 
 
 # A local window over the whole prompt keeps every column in every row, as special tokens everywhere do:
-# the band sums are then the column sums, term by term, and the two recoveries the same number. The
-# split-stream sweeps (few units) and the 256-owner blocks.
-@pytest.mark.parametrize("U,n,d,G", [(2, 33, 64, 1), (32, 333, 128, 1), (4, 300, 64, 4), (3, 300, 128, 2), (300, 400, 128, 1)])
-def test_band_over_the_whole_prompt_is_the_column_sum(U, n, d, G):
+# the band sums are then the column sums, term by term, and the two recoveries the same number. The one
+# pass by one and by several workgroups per unit; in two sweeps the split stream with 32 and 64 owners, and 256-owner
+# blocks singly (d = 64) and in pairs.
+@pytest.mark.parametrize("U,n,d,G,sweeps", [
+    (2, 33, 64, 1, 1), (32, 333, 128, 1, 1), (4, 300, 64, 4, 2), (3, 300, 128, 2, 1), (300, 400, 128, 1, 1), (2, 1033, 64, 1, 2),
+    (16, 1100, 128, 1, 2), (9, 2049, 64, 1, 2), (4, 1100, 64, 4, 2), (100, 1032, 64, 1, 2), (100, 1032, 128, 1, 2), (200, 1100, 128, 1, 2)])
+def test_band_over_the_whole_prompt_is_the_column_sum(U, n, d, G, sweeps):
     gen = torch.Generator(device="cuda:0").manual_seed(n)
     Q, K = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U))
     cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
     cfg = binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 1.0, 0.3, family=(8, 1, 0, 0), group_size=G)
     fg = binding.FastGen(cfg)
+    fg.fastgen_enable_timing(1)
     _, recovery, _ = fg.fastgen_profile(Q, K, cls)
     rec = recovery.cpu()
+    assert fg.fastgen_read_timing()["sweep2"][1] == sweeps - 1
     fg.close()
     assert torch.equal(rec[:, 0], rec[:, 1]), (rec[:, 0] - rec[:, 1]).abs().max()
     assert float((rec[:, 0] - 1.0).abs().max()) < 1e-6
@@ -329,7 +404,7 @@ def test_band_over_the_whole_prompt_is_the_column_sum(U, n, d, G):
 # Rows of the attention map sum to 1. A float32 1/l per row is off by up to half an ulp, 1.7e-8 rms in
 # either direction: over 10^4 rows and more the mean mass is within 4 x 1.7e-8 / 100 of 1 unless merging
 # the waves of the split-stream sweep adds an error of one sign (one hardware exponential per merge: 1.7e-9).
-@pytest.mark.parametrize("U,n,d", [(32, 333, 128), (32, 333, 64), (16, 1000, 64)])
+@pytest.mark.parametrize("U,n,d", [(16, 1100, 128), (16, 1100, 64), (4, 1500, 64)])   # 64, 64 and 32 owners
 def test_split_stream_row_masses_have_no_bias(U, n, d):
     masses = []
     for seed in range(8):
@@ -337,8 +412,10 @@ def test_split_stream_row_masses_have_no_bias(U, n, d):
         Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
         cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
         fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3))
+        fg.fastgen_enable_timing(1)
         _, recovery, _ = fg.fastgen_profile(Q, K, cls)
         masses.append(float(recovery[:, 0].mean()) - 1.0)
+        assert fg.fastgen_read_timing()["sweep2"][1] == 1
         fg.close()
     print(f"[accuracy] row masses U={U} n={n} d={d}: mean {sum(masses) / 8:.2e}", flush=True)
     assert abs(sum(masses) / 8) < 7e-10, masses
