@@ -14,7 +14,8 @@
 // update's chain behind it. Measured per step against the vector-ALU form (decode_group.hip): 256 units of 2048 tokens,
 // G = 4: 48.8 -> 34.3 us (that form's score sums over memory kept: 39.4; each head's partials reduced by plain
 // shuffles: 37.0); 256 of 1500, G = 8: 66 -> 38; 2048 of 64, G = 4: 75 -> 67; 4 of 64, G = 4: 10.2 -> 9.3. Two heads leave
-// half of the columns idle and gain nothing (1024 of 700: 52 / 59).
+// half of the columns idle and gain nothing (1024 of 700: 52 / 59); a few long units stay in the split form
+// (fg_unit_threads), three and five heads first, which pay for four and eight columns.
 #include <type_traits>
 
 #include "fg_common.h"

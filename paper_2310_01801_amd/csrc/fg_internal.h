@@ -33,8 +33,9 @@ struct fg_layout {
   size_t cscore;    // [pool] double
   size_t cpos;      // [pool] int32
   size_t ccls;      // [pool] uint8
-  size_t clogit;    // [pool, G] double  this step's scaled logit of every held token, per query head (written
-                    //                   for the units whose cumulative scores are kept)
+  size_t clogit;    // [pool, G] double  of every held token and query head, for the units whose cumulative scores are kept:
+                    //                   this step's scaled logit; three to eight bf16 heads in one workgroup per unit:
+                    //                   2^(logit - shift of its tile), a factor per tile and head turns it into attention
   // decode scratch
   size_t chunk_off; // [U + 1] int32  first chunk of each unit in the flat work list (per-unit form: its place by size)
   size_t item_unit; // [max_chunks, 8] int32  work-item records: unit, chunk, cap, tokens held, pool offset lo/hi, policy word, 0

@@ -23,8 +23,9 @@ struct fg_update_smem {
 // instruction fetch: it is instantiated for a few sizes and the smallest one that fits is taken.
 // Score path in float64 (Sec. 3.4, cumulative attention score): this step's attention on held slot
 // j is a_j = 2^(x_j - M) / Z with the float64 logits x_j the attention kept and Z = sum_j 2^(x_j - M)
-// summed here in float64 (M is only a shift: the float maximum). Grouped heads: clogit[j, 0]
-// already holds the attention summed over the heads.
+// summed here in float64 (M is only a shift: the float maximum). Grouped heads: `logit` gives the attention
+// summed over the heads, from clogit[j, 0] or (three to eight bf16 heads in one workgroup per unit) as the sum of
+// the slot's kept exponentials times its tile's factors, which it leaves in clogit[j, 0] for the probe.
 // The bookkeeping of the held tokens is on its way while `merge` runs (the attention output and the
 // maximum M of the scaled logits, from LDS or memory; it holds the barrier after which the logits
 // and the appended slot of this step may be read). The new token's bookkeeping is known here.

@@ -174,8 +174,8 @@ __global__ __launch_bounds__(256, 2) void fg_profile_f32_kernel(
 // sums take the exponentials from the registers. One contraction and one exponential per score instead of two, and
 // no row statistics rounded to float32. A part's column sums meet in LDS (a column belongs to one wave) and
 // leave as partial sums, which fg_part_sum_kernel adds in order.
-// Bound: the float64 matrix pipe. 64 units of 1000 tokens, d = 128: 470 us in two sweeps, 240 in one pass; 16 of 1000:
-// 137 -> 77. With 1024 columns at d = 128 the row's own elements are read back from LDS and the next keys asked
+// Bound: the float64 matrix pipe (52 % busy there). 64 units of 1000 tokens, d = 128: 464 us in two sweeps, 253 in one
+// pass and the part sums; 16 of 1000: 134 -> 78. With 1024 columns at d = 128 the row's own elements are read back from LDS and the next keys asked
 // for only behind the products, and still five registers spill; held as doubles the row alone takes 64.
 template <int D, int S>
 __global__ __launch_bounds__(256, 2) void fg_profile_once_f32_kernel(

@@ -7,9 +7,9 @@
 // 4 * 32 * NW columns are the longest prompt. A value p~ = 2^(c q.k - m) is
 // made once, with the running shift m of its row in this wave (a whole number, so that every later rescaling
 // is a power of two); the waves then exchange (m, l) of the 64 rows through LDS, and the column sums
-// take p~ * 2^(m - M) / l from the registers. One contraction, one exponential per score and one read of
-// Q and K instead of two, and no row statistics in memory. Workgroups that share a unit leave partial column sums, which
-// are added in order.
+// take p~ * 2^(m - M) / l from the registers. One contraction and one exponential per score instead of two, and
+// no row statistics in memory. Q is read once, the causal keys once per block of rows but for the fragment that each wave
+// still holds. Workgroups that share a unit leave partial column sums, which are added in order.
 //
 // The row index is the lane index (Q is the B operand of v_mfma_f32_32x32x16_bf16), so row maxima and sums are
 // private to a lane; the column sums cross the lanes once per block, after the block's two row fragments have been
@@ -17,11 +17,13 @@
 // wave shares its keys with no other wave and waits for nobody's. Straight from memory into operand registers they
 // would touch 32 cache lines per instruction (as fast measured, but 32 registers more).
 //
-// Bound: the vector ALU (56 % busy) with two waves per SIMD, whose waits at the block's barrier and for keys
-// from beyond L2 are the rest. 4096 units of 1024 tokens, d = 128, planted inputs: 870 + 1060 us in two sweeps, 1250 in
-// one pass (the walk back and forth: 1390 without); of 512 tokens 305 + 340 -> 352. Error of the column sums against
-// float64: 1.66e-8 (two sweeps 1.91e-8), the same when shared. 64 units of 1000 tokens by four workgroups each 22
-// (one each 60, two sweeps 70). Tried without gain: the next fragment's matrix instructions between this
+// Bound: two waves per SIMD, whose waits (41 % of their cycles: the block's barrier, and keys from beyond L2) neither
+// the vector ALU (about half busy: 282 instructions per wave-step, the two sweeps 141 + 132) nor the matrix pipe covers.
+// 16384 units of 1024 tokens, d = 128, fetch 24.6 GB for 8.6 GB of Q and K (two sweeps 25.6), 4.4 to 4.8 TB/s:
+// the traffic is part of the bound. 4096 units of 1024 tokens, d = 128, 1586 us in two sweeps, 1324 in one pass
+// (the walk back and forth: 100 us more without); of 512 tokens 542 -> 401. Error of the column sums against
+// float64: 1.66e-8 (two sweeps 1.91e-8), the same when shared. 64 units of 1000 tokens by four workgroups each 25
+// (one each 66, two sweeps 77). Tried without gain: the next fragment's matrix instructions between this
 // one's exponentials by hand (1410: more instructions, the same time), two to eight workgroups per unit that share
 // its keys in L2 (1420, and partial sums), query operands in registers (51 spills), the next block's first
 // contraction under this one's column sums (3 % slower, 12 % with many workgroups per unit).
