@@ -171,6 +171,32 @@ def test_one_pass_with_any_pool(U, n, d, G, dtype):
         fg.close()
 
 
+# In a small pool the partial sums lie over everything behind the profile's regions, the step's scratch included: what
+# follows reads none of it
+@pytest.mark.parametrize("U,n,d,G,dtype,forced", [(16, 1000, 64, 1, torch.float32, 0), (16, 1000, 64, 1, torch.bfloat16, 2), (64, 400, 128, 4, torch.bfloat16, 0),
+                                                  (24, 900, 64, 9, torch.float32, 2)])
+def test_session_in_a_small_pool_after_one_pass(U, n, d, G, dtype, forced):
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    Q, K, V = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=dtype) for x in (U * G, U, U))
+    q, k, v = (torch.randn(3, x, d, generator=gen, device="cuda:0", dtype=dtype) for x in (U * G, U, U))
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    cls[0, :3] = 1
+    seen = []
+    for pool in (0, U * 64):
+        cfg = binding.make_config(U, 1, d, dtype, n, 3, 0.95, 0.03, 0.03, forced_policy=forced, cache_tokens=pool, group_size=G)
+        fg = binding.FastGen(cfg)
+        fg.workspace.fill_(255)
+        fg.fastgen_profile(Q, K, cls)
+        fg.fastgen_compact(K, V)
+        outs = [fg.fastgen_decode_step(q[t], k[t], v[t], cls[:, 5].contiguous()) for t in range(2)]
+        outs += fg.fastgen_decode_step_probe(q[2], k[2], v[2], cls[:, 5].contiguous())
+        st = fg.fastgen_export_state(rows=True)
+        assert int(st["status"].item()) == 0
+        seen.append(outs + [st[x] for x in ("lengths", "positions", "scores", "keys", "values")])
+        fg.close()
+    assert all(torch.equal(x, y) for x, y in zip(*seen))
+
+
 # Three to eight bf16 heads on the matrix cores: tiles of 32 tokens (two sets of 16) over eight waves, four and eight
 # columns, prompts of which some waves have no tile, longest units, every policy, probed steps
 @pytest.mark.parametrize("heads,n,S,d,G,forced", [
