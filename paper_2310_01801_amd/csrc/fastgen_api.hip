@@ -208,11 +208,16 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.scale = scale;
   hipError_t e;
   const fg_once_form once = lse_opt ? fg_once_form{0, 1} : fg_once_form_of(c);   // both sweeps in one pass
+  const size_t sums = (size_t)pa.U * pa.n;
+  const double* part_col = static_cast<const double*>(part_sums);
+  const double* part_band = part_col + (size_t)once.parts * sums;
   if (once.waves) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
     e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
                            : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
+    if (e == hipSuccess && once.parts > FG_SELECT_PARTS)
+      e = fg_launch_part_sums(part_col, part_band, pa.colsum, pa.bandcol, sums, once.parts, s);
     tm.end();
     if (e != hipSuccess) return e;
   } else {
@@ -231,6 +236,8 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
 
   fg_select_args sa;
   sa.colsum = pa.colsum; sa.bandcol = pa.bandcol; sa.token_class = token_class;
+  sa.part_col = part_col; sa.part_band = part_band;
+  sa.parts = once.parts <= FG_SELECT_PARTS ? once.parts : 1;
   sa.keep = reinterpret_cast<uint8_t*>(at(L.keep)); sa.slot = reinterpret_cast<int32_t*>(at(L.slot));
   sa.policy = reinterpret_cast<int32_t*>(at(L.policy)); sa.recov = reinterpret_cast<double*>(at(L.recov));
   sa.kcount = reinterpret_cast<int32_t*>(at(L.kcount)); sa.cap = reinterpret_cast<int32_t*>(at(L.cap));

@@ -299,6 +299,10 @@ inline int fg_once_f32_parts(int U, int n, int G) {
   return U * parts >= (G > 2 && blocks < 6 ? 400 : 256) ? (int)parts : 0;
 }
 
+// Up to so many parts the selection adds them itself; more of them (float32) keep the card busy in a launch of their own
+// (64 units of 1000 tokens in 31 parts: 32 MB, in the 64 workgroups of the selection 20 us, in all CUs 10).
+constexpr int FG_SELECT_PARTS = 10;
+
 // What serves a configuration without a supplied log-sum-exp (0 waves: the two sweeps), and the bytes of its partial sums.
 inline fg_once_form fg_once_form_of(const fg_config& c) {
   const int G = c.group_size > 1 ? c.group_size : 1;
@@ -321,7 +325,8 @@ struct fg_profile_args {
 };
 
 struct fg_select_args {
-  const double* colsum; const double* bandcol; const uint8_t* token_class;  // [B, n]
+  double* colsum; const double* bandcol; const uint8_t* token_class;  // [B, n]
+  const double* part_col; const double* part_band; int parts;   // parts > 1: both sums still lie in parts [parts, U, n]
   uint8_t* keep; int32_t* slot;
   int32_t* policy; double* recov; int32_t* kcount; int32_t* cap; int32_t* len;
   int32_t* policy_out; double* recov_out; int32_t* kcount_out;  // optional caller copies
@@ -365,6 +370,7 @@ struct fg_export_args {
 };
 
 hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, hipStream_t);
+// (several workgroups per unit leave their sums in `part_sums`: columns [parts, U, n], then band)
 hipError_t fg_launch_profile_once(const fg_profile_args&, fg_once_form, double* part_sums, hipStream_t);
 // sums over [parts, N] in order, of two arrays
 hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, size_t N, int parts, hipStream_t);

@@ -365,8 +365,7 @@ hipError_t launch_once(const fg_profile_args& a, int P, double* parts, hipStream
   hipLaunchKernelGGL((fg_profile_once_f32_kernel<D, S>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(256), 0, s,
                      static_cast<const float*>(a.Q), static_cast<const float*>(a.K), col, band, a.U, a.n, a.w,
                      a.scale * FG_LOG2E, a.G, P);
-  const hipError_t e = hipGetLastError();
-  return P > 1 && e == hipSuccess ? fg_launch_part_sums(col, band, a.colsum, a.bandcol, N, P, s) : e;
+  return hipGetLastError();
 }
 
 // A caller-supplied natural-log row log-sum-exp as (m, 1/l): m = the nearest integer to its

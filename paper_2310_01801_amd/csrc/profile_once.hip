@@ -299,8 +299,7 @@ hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s)
   hipLaunchKernelGGL((fg_profile_once_kernel<D, NW>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(NW * 64), 0, s,
                      static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), col, band, a.U, a.n, a.w,
                      a.scale * FG_LOG2E, a.G, P);
-  const hipError_t e = hipGetLastError();
-  return P > 1 && e == hipSuccess ? fg_launch_part_sums(col, band, a.colsum, a.bandcol, N, P, s) : e;
+  return hipGetLastError();
 }
 
 }  // namespace
