@@ -4,29 +4,33 @@
 // A workgroup walks the query rows of a unit in blocks of 64; where units are few, several workgroups share
 // the blocks of each, dealt from the heavy end. The waves hold the whole block's exponentials in registers: the
 // causal columns are dealt out in fragments of 32, fragment j to wave j mod NW, at most four per wave, so
-// 4 * 32 * NW columns are the longest prompt. A value p~ = 2^(c q.k - m) is
-// made once, with the running shift m of its row in this wave (a whole number, so that every later rescaling
-// is a power of two); the waves then exchange (m, l) of the 64 rows through LDS, and the column sums
-// take p~ * 2^(m - M) / l from the registers. One contraction and one exponential per score instead of two, and
-// no row statistics in memory. Q is read once, the causal keys once per block of rows but for the fragment that each wave
-// still holds. Workgroups that share a unit leave partial column sums, which are added in order.
+// 4 * 32 * NW columns are the longest prompt. A value 2^(c q.k - m) is made once, with a shift m of its row that all
+// waves share: what the sum of the row 64 before came to, as a whole number. No maximum is looked for, so a
+// fragment's exponentials start with its last matrix instruction; whether the shift fits shows in the row's sum, and a
+// block where one does not (or a workgroup's only block, which has none before it) is done again with each wave's own
+// maximum as its shift. The waves exchange the sums of the 64 rows through LDS, and the column sums take
+// value / sum from the registers. One contraction and one exponential per score instead of two, and no row statistics
+// in memory. Workgroups that share a unit leave partial column sums, which are added in order.
 //
-// The row index is the lane index (Q is the B operand of v_mfma_f32_32x32x16_bf16), so row maxima and sums are
+// The row index is the lane index (Q is the B operand of v_mfma_f32_32x32x16_bf16), so row sums are
 // private to a lane; the column sums cross the lanes once per block, after the block's two row fragments have been
-// added (fg_cols_over_rows). The fragments of K arrive by loads that write LDS directly, one ahead: a
-// wave shares its keys with no other wave and waits for nobody's. Straight from memory into operand registers they
-// would touch 32 cache lines per instruction (as fast measured, but 32 registers more).
+// added (fg_cols_over_rows). A wave shares its keys with no other wave and waits for nobody's. Of its four fragments one
+// stays in registers for the whole unit and one in LDS as the last one of a block and the first of the next; the other two
+// take its place in LDS in turn, one ahead (d = 64: two in registers, two in LDS, each read once). The first two go
+// through the matrix pipe together and share the reads of the query rows.
 //
-// Bound: two waves per SIMD, whose waits (41 % of their cycles: the block's barrier, and keys from beyond L2) neither
-// the vector ALU (about half busy: 282 instructions per wave-step, the two sweeps 141 + 132) nor the matrix pipe covers.
-// 16384 units of 1024 tokens, d = 128, fetch 24.6 GB for 8.6 GB of Q and K (two sweeps 25.6), 4.4 to 4.8 TB/s:
-// the traffic is part of the bound. 4096 units of 1024 tokens, d = 128, 1586 us in two sweeps, 1324 in one pass
-// (the walk back and forth: 100 us more without); of 512 tokens 542 -> 401. Error of the column sums against
-// float64: 1.66e-8 (two sweeps 1.91e-8), the same when shared. 64 units of 1000 tokens by four workgroups each 25
-// (one each 66, two sweeps 77). Tried without gain: the next fragment's matrix instructions between this
-// one's exponentials by hand (1410: more instructions, the same time), two to eight workgroups per unit that share
-// its keys in L2 (1420, and partial sums), query operands in registers (51 spills), the next block's first
-// contraction under this one's column sums (3 % slower, 12 % with many workgroups per unit).
+// Bound: two waves per SIMD in step. Per piece of 64 x 32 and wave, cycles, 16384 units of 1024 tokens, d = 128: 1010 of
+// matrix instructions (512 alone), 885 of exponentials, 780 of column sums, and per block 680 for the exchange and 1500 at
+// its barrier, where waves with a fragment less wait. 4096 units of 1024 tokens, d = 128, 1270 us with running maxima
+// and all keys through LDS, 1154 now (two sweeps 1586); of 512 385 -> 346, of 500, d = 64, 291 -> 254, 1024 of 1000, d =
+// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Error of the column sums against float64 as before (1.67e-8 / 1.69e-8,
+// inside the band 2.69e-8 / 2.72e-8, 1024 units of 1000 tokens); without a shift 4 % more. Tried without gain: all keys in registers with 32
+// rows a block (1325) or 16 and the exchange under the next rows' products (1810), higher priority for half of the
+// waves or for the matrix instructions (1115 to 1186 where 1114 without), keys for the registers straight from memory
+// (1204 where 1154, and short prompts 0.6 us more), the first two fragments one by one in a first block (8 spills), the
+// next block's first contraction under this one's column sums.
+#include <type_traits>
+
 #include "fg_common.h"
 #include "fg_internal.h"
 
@@ -35,12 +39,23 @@ namespace {
 constexpr int kFrag = 32;    // columns of a fragment
 constexpr int kRows = 64;    // query rows of a block: two fragments
 constexpr int kSlots = 4;    // fragments of a wave in one block: 128 registers
+// Row sums in which every term that counts is a normal number and none overflows. A head whose rows differ by more from one
+// block to the next, 20 and 100 powers of two, goes through every block twice.
+constexpr double kLeastSum = 0x1p-20, kMostSum = 0x1p100;
 
-// 16 bytes per lane from memory straight into LDS, to `lds` + 16 * lane
-__device__ __forceinline__ void fg_load_lds16(__amdgpu_buffer_rsrc_t r, void* lds, int voff, int soff) {
-#ifdef __HIP_DEVICE_COMPILE__   // the host pass does not know the 16-byte form
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+// 16 bytes per lane from memory straight into LDS, to `lds` + 16 * lane. Written out, because behind the builtin the
+// compiler waits for the data at the next read of any LDS; here the waits below do, which every reader stands behind.
+__device__ __forceinline__ void fg_load_lds16(__amdgpu_buffer_rsrc_t r, const void* lds, int voff, int soff) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)lds;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(at)), "v"(voff), "s"(r), "s"(soff) : "memory");   // (m0 holds nothing of the compiler's)
 #endif
+}
+__device__ __forceinline__ void fg_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }        // this wave's loads
+__device__ __forceinline__ void fg_have_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }   // its LDS reads
+__device__ __forceinline__ void fg_barrier() {   // all waves' loads and LDS accesses
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // a: the lower halves of both, b: the upper halves
@@ -90,11 +105,14 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   constexpr int RPL = 1024 / RB;      // rows of one load of the wave (1 KiB)
   constexpr int NT = NW * 64;
   constexpr int QL = kRows * RB / 1024 / NW;   // loads of a row block per wave
-  constexpr int KL = kFrag * RB / 1024;        // loads of a fragment
+  constexpr int KL = kFrag * RB / 1024;        // loads of a fragment of keys
   constexpr int COLS = kSlots * kFrag * NW;
+  constexpr int HELD = 128 / D;       // fragments of a wave in registers, and as many in LDS
+  constexpr auto in_registers = [](int p) { return p == 1 || (HELD == 2 && p == 2); };
+  constexpr auto register_of = [](int p) { return HELD == 2 && p == 2 ? 1 : 0; };
   // Piece p of row r lies at place p ^ (r mod PPR): the lanes of a fragment, one row each, read different banks.
   __shared__ __attribute__((aligned(16))) unsigned char s_q[2][kRows * RB];
-  __shared__ __attribute__((aligned(16))) unsigned char s_k[NW][kFrag * RB];
+  __shared__ __attribute__((aligned(16))) unsigned char s_k[NW][HELD][kFrag * RB];
   __shared__ double s_l[2][NW][kRows];
   __shared__ float s_m[2][NW][kRows];
   __shared__ double s_sum[2][COLS];   // column sums, and their part inside the band
@@ -119,17 +137,19 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       const_cast<__bf16*>(K + (size_t)unit * n * D), 0, n * RB, 0x00020000);
   const int lrow = lane / PPR, lplace = lane % PPR;
   auto source = [&](int load) { return lrow * RB + ((lplace ^ lrow ^ (load * RPL)) & (PPR - 1)) * 16; };
-  auto load_k = [&](int j) {
+  auto load_k = [&](int slot, int to) {
 #pragma unroll
-    for (int i = 0; i < KL; ++i) fg_load_lds16(k_rsrc, &s_k[wave][i * 1024], source(i), j * kFrag * RB + i * 1024);
+    for (int i = 0; i < KL; ++i)
+      fg_load_lds16(k_rsrc, &s_k[wave][to][i * 1024], source(i), (wave + NW * slot) * kFrag * RB + i * 1024);
   };
   const int frag = ln * RB + ((lh ^ ln) & (PPR - 1)) * 16;   // piece 2 kk + lh of row ln: frag ^ (32 kk)
   const int item = ((lane >> 4) & 1) * 16 + ((lane >> 3) & 1) * 8 + lh * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
-
-  // The columns are walked upwards in one block and downwards in the next: a block begins with the keys that the one
-  // before has read last. The first fragment is then still in LDS, and more of the others in the XCD's L2.
-  int buf = 0, held = -1;   // the fragment in s_k
-  bool down = false;
+  bf16x8 kf[HELD][KK];
+  // (by LDS: from memory into the operands' registers, 32 cache lines an instruction, cost a short prompt 0.6 us)
+#pragma unroll
+  for (int s = 0; s < HELD; ++s) load_k(s, s);
+  const int most = min(kSlots, ((n - 1) / kFrag - wave) / NW + 1);   // fragments of this wave in the last block (or below 1)
+  int buf = 0, held = 1;   // the fragment in s_k (d = 128)
   for (int h = 0; h < G; ++h) {   // the query heads of the unit, one after the other over the same columns
     const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<__bf16*>(Q + ((size_t)unit * G + h) * n * D), 0, n * RB, 0x00020000);
@@ -139,147 +159,237 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         fg_load_lds16(q_rsrc, &s_q[to][(wave * QL + i) * 1024], source(wave * QL + i), b * kRows * RB + (wave * QL + i) * 1024);
     };
     load_q(block(mine - 1), buf);   // the last reads of this buffer lie behind a barrier
-    __syncthreads();
-    for (int i = mine - 1; i >= 0; --i, buf ^= 1, down = !down) {
+    fg_barrier();
+    if (h == 0) {
+#pragma unroll
+      for (int s = 0; s < HELD; ++s)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) kf[s][kk] = *reinterpret_cast<const bf16x8*>(&s_k[wave][s][frag ^ (32 * kk)]);
+      fg_have_read();
+      if (most > HELD) load_k(HELD, 0);
+      if (most > 3 && HELD == 2) load_k(3, 1);
+    }
+    float m_run[2] = {0.f, 0.f};   // the shifts of this lane's rows, the same in all waves
+    for (int i = mine - 1; i >= 0; --i, buf ^= 1) {
       const int b = block(i);
       const int r0 = b * kRows;
       const int jl = min(2 * b + 1, (n - 1) / kFrag);   // last column fragment
       const int cnt = jl >= wave ? (jl - wave) / NW + 1 : 0;   // fragments of this wave
-      auto fragment = [&](int s) { return wave + NW * (down ? cnt - 1 - s : s); };
-      if (cnt > 0 && fragment(0) != held) load_k(fragment(0));
+      if (i > 0) load_q(block(i - 1), buf ^ 1);
       f32x16 e[kSlots][2];
-      float ms[kSlots][2];   // the shifts that e holds
-      float m_run[2] = {FG_NEG_BIG, FG_NEG_BIG};
-      double l_run[2] = {0.0, 0.0};
-      // exponentials of 16 dot products in place, row statistics carried on
-      auto full = [&](f32x16& ac, int f) __attribute__((always_inline)) {
-        const float x0 = fmaxf(fmaxf(ac[0], ac[1]), ac[2]), x1 = fmaxf(fmaxf(ac[3], ac[4]), ac[5]);
-        const float x2 = fmaxf(fmaxf(ac[6], ac[7]), ac[8]), x3 = fmaxf(fmaxf(ac[9], ac[10]), ac[11]);
-        const float x4 = fmaxf(fmaxf(ac[12], ac[13]), ac[14]);
-        const float y0 = fmaxf(fmaxf(x0, x1), x2), y1 = fmaxf(fmaxf(x3, x4), ac[15]);
-        const float m_new = fmaxf(rintf(fmaxf(y0, y1) * c), m_run[f]);
-        float s[2];
+      int at[kSlots];        // the fragments' slots
+      double l_run[2];
+      auto active = [&](int p) { return HELD == 1 ? cnt > (p == 0 ? 1 : p == 1 ? 0 : p) : cnt > at[p]; };
+      // a fragment's products: MODE 0 become exponentials, with their sums over the row; MODE 1 give the rows' largest values
+      auto rows = [&](auto md, int p) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(md)::value;
+        auto half = [&](f32x16& ac, int f, bool diagonal) __attribute__((always_inline)) {
+          const int lim = diagonal ? ln - lh * 4 : 32;   // column <= row
+          float s[4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          ac[i] = fg_exp2(fmaf(ac[i], c, -m_new));
-          s[i & 1] = i < 2 ? ac[i] : s[i & 1] + ac[i];
-        }
-        l_run[f] = fma(l_run[f], (double)fg_exp2(m_run[f] - m_new), (double)(s[0] + s[1]));
-        m_run[f] = m_new;
-      };
-      auto diagonal = [&](f32x16& ac, int f) __attribute__((always_inline)) {   // column <= row
-        const int lim = ln - lh * 4;
-        float tmax = FG_NEG_BIG;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, fg_acc_item(i) <= lim ? ac[i] * c : FG_NEG_BIG);
-        const float m_new = fmaxf(m_run[f], rintf(tmax));
-        float s[2] = {0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float p = fg_exp2(fmaf(ac[i], c, -m_new));
-          ac[i] = fg_acc_item(i) <= lim ? p : 0.f;
-          s[i & 1] += ac[i];
-        }
-        l_run[f] = fma(l_run[f], (double)fg_exp2(m_run[f] - m_new), (double)(s[0] + s[1]));
-        m_run[f] = m_new;
-      };
-#pragma unroll
-      for (int s = 0; s < kSlots; ++s) {
-        if (s >= cnt) continue;
-        const int j = fragment(s);
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) e[s][f][i] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(&s_k[wave][frag ^ (32 * kk)]);
-          const bf16x8 q0 = *reinterpret_cast<const bf16x8*>(&s_q[buf][frag ^ (32 * kk)]);
-          const bf16x8 q1 = *reinterpret_cast<const bf16x8*>(&s_q[buf][32 * RB + (frag ^ (32 * kk))]);
-          e[s][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q0, e[s][0], 0, 0, 0);
-          e[s][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q1, e[s][1], 0, 0, 0);
-        }
-        // operand reads three steps ahead of the matrix instructions
-        constexpr int AHEAD = 3;
-        __builtin_amdgcn_sched_group_barrier(0x100, 3 * AHEAD, 0);
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
-          if (kk + AHEAD < KK) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        held = j;
-        if (s + 1 < kSlots && s + 1 < cnt) load_k(fragment(s + 1));   // the keys have been read
-        else if (i > 0) load_q(block(i - 1), buf ^ 1);   // (at the block's barrier, which waits for it: 3 to 5 % slower)
+          for (int i = 0; i < 16; ++i) {
+            const bool ok = !diagonal || fg_acc_item(i) <= lim;
+            if (MODE == 1) m_run[f] = fmaxf(m_run[f], ok ? ac[i] * c : FG_NEG_BIG);
+            else {
+              const float v = fg_exp2(fmaf(ac[i], c, -m_run[f]));
+              ac[i] = ok ? v : 0.f;
+              s[i & 3] = i < 4 ? ac[i] : s[i & 3] + ac[i];
+            }
+          }
+          if (MODE == 0) l_run[f] += (double)((s[0] + s[1]) + (s[2] + s[3]));
+        };
+        const int j = wave + NW * at[p];
         if (j < 2 * b) {
-          full(e[s][0], 0);
-          full(e[s][1], 1);
+          half(e[p][0], 0, false);
+          half(e[p][1], 1, false);
         } else if (j == 2 * b) {
-          diagonal(e[s][0], 0);
-          full(e[s][1], 1);
+          half(e[p][0], 0, true);
+          half(e[p][1], 1, false);
         } else {   // above the diagonal for the first row fragment
 #pragma unroll
-          for (int i = 0; i < 16; ++i) e[s][0][i] = 0.f;
-          diagonal(e[s][1], 1);
+          for (int i = 0; i < 16; ++i) e[p][0][i] = 0.f;
+          half(e[p][1], 1, true);
         }
-        ms[s][0] = m_run[0];
-        ms[s][1] = m_run[1];
-      }
-      if (cnt == 0 && i > 0) load_q(block(i - 1), buf ^ 1);
-      // (m, l) of row `lane` of the block: the halves of the wave (columns), then the waves
-      {
-        float ma = m_run[0], mb = m_run[1];
+      };
+      // the fragments' contractions, each followed by its rows
+      auto sweep = [&](auto md) __attribute__((always_inline)) {
+        // d = 128: the fragment in LDS, the one in registers, the others through LDS in turn; d = 64: all are at hand
+        auto next = [&](int s) { return s >= cnt - 1 ? 1 : s + 1; };
+        at[0] = HELD == 1 ? (held < cnt ? held : 1) : 2;
+        at[1] = 0;
+        at[2] = HELD == 1 ? next(at[0]) : 1;
+        at[3] = HELD == 1 ? next(at[2]) : 3;
+        // matrix instructions of one or two fragments, the operand reads three steps ahead of them
+        auto contract = [&](auto first, auto second) __attribute__((always_inline)) {
+          constexpr int pa = decltype(first)::value, pb = decltype(second)::value;   // second: none below 0
+          constexpr bool ra = in_registers(pa), rb = pb < 0 || in_registers(pb);
+          constexpr int reads = 2 + (ra ? 0 : 1) + (rb ? 0 : 1), AHEAD = 3;
+          const unsigned char* ka = s_k[wave][HELD == 2 && pa == 3 ? 1 : 0];
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              e[pa][f][i] = 0.f;
+              if (pb >= 0) e[pb & 3][f][i] = 0.f;
+            }
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            const bf16x8 a = ra ? kf[register_of(pa)][kk] : *reinterpret_cast<const bf16x8*>(ka + (frag ^ (32 * kk)));
+            const bf16x8 q0 = *reinterpret_cast<const bf16x8*>(&s_q[buf][frag ^ (32 * kk)]);
+            const bf16x8 q1 = *reinterpret_cast<const bf16x8*>(&s_q[buf][32 * RB + (frag ^ (32 * kk))]);
+            e[pa][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q0, e[pa][0], 0, 0, 0);
+            e[pa][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q1, e[pa][1], 0, 0, 0);
+            if (pb >= 0) {
+              const bf16x8 o = kf[register_of(pb & 3)][kk];
+              e[pb & 3][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o, q0, e[pb & 3][0], 0, 0, 0);
+              e[pb & 3][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o, q1, e[pb & 3][1], 0, 0, 0);
+            }
+          }
+          __builtin_amdgcn_sched_group_barrier(0x100, reads * AHEAD, 0);
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            __builtin_amdgcn_sched_group_barrier(0x8, pb < 0 ? 2 : 4, 0);
+            if (kk + AHEAD < KK) __builtin_amdgcn_sched_group_barrier(0x100, reads, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        const std::integral_constant<int, -1> none;
+        const std::integral_constant<int, 0> p0;
+        const std::integral_constant<int, 1> p1;
+        const std::integral_constant<int, 2> p2;
+        const std::integral_constant<int, 3> p3;
+        if (HELD == 1) {
+          if (cnt > 1) {
+            if (held != at[0]) load_k(at[0], 0);
+            if (held != at[0] || i == mine - 1) fg_landed();   // (else it has landed before the last barrier)
+            contract(p0, p1);
+            held = at[0];
+            if (cnt > 2) load_k(at[2], 0);   // the keys have been read: the next fragment takes their place
+            rows(md, 0);
+            rows(md, 1);
+          } else if (cnt > 0) {
+            contract(p1, none);
+            rows(md, 1);
+          }
+          if (cnt > 2) {
+            fg_landed();
+            contract(p2, none);
+            held = at[2];
+            if (cnt > 3) load_k(at[3], 0);
+            rows(md, 2);
+          }
+          if (cnt > 3) {
+            fg_landed();
+            contract(p3, none);
+            held = at[3];
+            rows(md, 3);
+          }
+        } else {
+          if (cnt > 1) {
+            contract(p2, p1);
+            rows(md, 2);
+            rows(md, 1);
+          } else if (cnt > 0) {
+            contract(p1, none);
+            rows(md, 1);
+          }
+          if (cnt > 2) {
+            if (i == mine - 1) fg_landed();
+            contract(p0, none);
+            rows(md, 0);
+          }
+          if (cnt > 3) {
+            contract(p3, none);
+            rows(md, 3);
+          }
+        }
+      };
+      // sums of row `lane` of the block: the halves of the wave (columns), then the waves
+      auto put_sums = [&]() __attribute__((always_inline)) {
         double la = l_run[0], lb = l_run[1];
-        fg_swap_halves(ma, mb);
         fg_swap_halves(la, lb);
-        const float mm = fmaxf(ma, mb);
-        s_m[buf][wave][lane] = mm;
-        s_l[buf][wave][lane] = fma(la, (double)fg_exp2(ma - mm), lb * (double)fg_exp2(mb - mm));
-      }
-      __syncthreads();
-      float mv[NW], M = FG_NEG_BIG;
-#pragma unroll
-      for (int i = 0; i < NW; ++i) {
-        mv[i] = s_m[buf][i][lane];
-        M = fmaxf(M, mv[i]);
-      }
+        s_l[buf][wave][lane] = la + lb;
+      };
       double L = 0.0;
+      float M = lh ? m_run[1] : m_run[0], share = 1.f;
+      l_run[0] = l_run[1] = 0.0;
+      bool again = mine == 1;
+      if (!again) {
+        sweep(std::integral_constant<int, 0>());
+        put_sums();
+        fg_barrier();
 #pragma unroll
-      for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
+        for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
+        again = __any(r0 + lane < n && !(L >= kLeastSum && L <= kMostSum));   // the same in all waves
+        if (again) fg_barrier();   // s_l has been read
+      }
+      if (again) {   // the shifts do not fit, or there are none: this wave's own
+        m_run[0] = m_run[1] = FG_NEG_BIG;
+        sweep(std::integral_constant<int, 1>());
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          float o = m_run[f];
+          fg_swap_halves(m_run[f], o);
+          m_run[f] = rintf(fmaxf(m_run[f], o));
+        }
+        l_run[0] = l_run[1] = 0.0;
+#pragma unroll
+        for (int p = 0; p < kSlots; ++p)
+          if (active(p)) rows(std::integral_constant<int, 0>(), p);
+        put_sums();
+        const float own = lh ? m_run[1] : m_run[0];
+        s_m[buf][wave][lane] = own;
+        fg_barrier();
+        float mv[NW];
+        M = FG_NEG_BIG;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          mv[i] = s_m[buf][i][lane];
+          M = fmaxf(M, mv[i]);
+        }
+        L = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
+        share = fg_exp2(own - M);
+      }
+      if (i > 0) {   // the shifts of the next block: what these rows' sums came to (its rows past the end stay at products of 0)
+        float ma = block(i - 1) * kRows + lane < n ? M + rintf(__builtin_amdgcn_logf((float)L)) : 0.f, mb = ma;
+        fg_swap_halves(ma, mb);
+        m_run[0] = ma;
+        m_run[1] = mb;
+      }
       double inv = __builtin_amdgcn_rcp(L);
       inv = fma(inv, fma(-L, inv, 1.0), inv);
-      float M0 = M, M1 = M, i0 = r0 + lane < n ? (float)inv : 0.f, i1 = i0;   // rows past the end count nothing
-      fg_swap_halves(M0, M1);
-      fg_swap_halves(i0, i1);
+      float f0 = r0 + lane < n ? (float)inv * share : 0.f, f1 = f0;   // rows past the end count nothing
+      fg_swap_halves(f0, f1);
 #pragma unroll
-      for (int s = 0; s < kSlots; ++s) {
-        if (s >= cnt) continue;
-        const int j = fragment(s);
-        const float f0 = fg_exp2(ms[s][0] - M0) * i0, f1 = fg_exp2(ms[s][1] - M1) * i1;
+      for (int p = 0; p < kSlots; ++p) {
+        if (!active(p)) continue;
+        const int j = wave + NW * at[p];
         const int d0 = r0 - j * kFrag;   // row - column of the fragment's corner
-        const int at = j * kFrag + item;
+        const int to = j * kFrag + item;
         float t[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t[i] = fmaf(e[s][1][i], f1, e[s][0][i] * f0);
+        for (int i = 0; i < 16; ++i) t[i] = fmaf(e[p][1][i], f1, e[p][0][i] * f0);
         // one wave adds to a column, in the order of the blocks; odd lanes carry the band
         const bool inside = d0 + 63 < w, outside = d0 - 31 >= w;
         const double v = fg_cols_over_rows(t, lane);
-        if (!(lane & 1) || inside) unsafeAtomicAdd(&s_sum[lane & 1][at], v);
+        if (!(lane & 1) || inside) unsafeAtomicAdd(&s_sum[lane & 1][to], v);
         if (!inside && !outside) {
           const int o0 = d0 + ln - lh * 4 - w;   // in the band: row - column < w, so the item's offset is above o0
           if (d0 + 1 >= w) {          // the second row fragment lies outside
 #pragma unroll
-            for (int i = 0; i < 16; ++i) t[i] = (fg_acc_item(i) > o0 ? e[s][0][i] : 0.f) * f0;
+            for (int i = 0; i < 16; ++i) t[i] = (fg_acc_item(i) > o0 ? e[p][0][i] : 0.f) * f0;
           } else if (d0 + 31 < w) {   // the first one inside
 #pragma unroll
-            for (int i = 0; i < 16; ++i) t[i] = fmaf(fg_acc_item(i) > o0 + 32 ? e[s][1][i] : 0.f, f1, e[s][0][i] * f0);
+            for (int i = 0; i < 16; ++i) t[i] = fmaf(fg_acc_item(i) > o0 + 32 ? e[p][1][i] : 0.f, f1, e[p][0][i] * f0);
           } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-              t[i] = fmaf(fg_acc_item(i) > o0 + 32 ? e[s][1][i] : 0.f, f1, (fg_acc_item(i) > o0 ? e[s][0][i] : 0.f) * f0);
+              t[i] = fmaf(fg_acc_item(i) > o0 + 32 ? e[p][1][i] : 0.f, f1, (fg_acc_item(i) > o0 ? e[p][0][i] : 0.f) * f0);
           }
           const double vb = fg_cols_over_rows(t, lane);
-          if (lane & 1) unsafeAtomicAdd(&s_sum[1][at], vb);
+          if (lane & 1) unsafeAtomicAdd(&s_sum[1][to], vb);
         }
       }
     }

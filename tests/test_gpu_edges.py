@@ -322,6 +322,32 @@ def test_one_pass_with_huge_logits(n, at):
     assert float((recovery[:, 0].cpu() - want).abs().max()) < 1e-6
 
 
+# A row's shift is what the row 64 before came to. Logits whose rows lie up to 130 powers of two higher or lower than that
+# one, in the first and later blocks, in whole blocks, single rows and the last row, with one and several workgroups per
+# unit and with heads after one another. All keys share the offset, so the probabilities keep the size of a plain
+# prompt's; a dot product of up to 600 over eight rounded steps in float32 is good to 8 x 2^-24 x 600 / sqrt(d), so the masses to
+# 3.6e-5 (d = 64).
+@pytest.mark.parametrize("U,n,d,G", [(2, 1, 128, 1), (300, 64, 128, 1), (300, 130, 64, 1), (20, 333, 128, 1), (300, 700, 128, 1), (64, 1000, 64, 1), (200, 500, 64, 2)])
+@pytest.mark.parametrize("rows", ["high", "low", "alternate", "single", "last"])
+def test_one_pass_with_rows_far_from_the_ones_before(U, n, d, G, rows):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + d)
+    Q, K = (torch.randn(x, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for x in (U * G, U))
+    i = torch.arange(n, device="cuda:0")
+    step = {"high": 0 * i + 1, "low": 0 * i - 1, "alternate": torch.where((i // 40) % 2 == 0, 1, -1),
+            "single": (i % 97 == 50).int() - (i % 89 == 70).int(), "last": (i == n - 1).int()}[rows]
+    Q[:, :, 0], K[:, :, 0] = (step * 64).bfloat16(), 8.0
+    cls = (i % 3 == 0).to(torch.uint8)[None].contiguous()
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3, group_size=G))
+    _, recovery, _ = fg.fastgen_profile(Q, K, cls)
+    fg.close()
+    scale = float(torch.tensor(1.0 / math.sqrt(d), dtype=torch.float32))
+    some = sorted({0, U // 2, U - 1})
+    x = Q.view(U, G, n, d)[some].double().cpu().matmul(K[some].double().cpu().transpose(1, 2).contiguous()[:, None]) * scale
+    x = x.masked_fill(torch.ones(n, n).triu(1).bool(), -math.inf)
+    want = torch.softmax(x, dim=3)[:, :, :, cls[0].cpu() != 0].sum(3).mean((1, 2))
+    assert float((recovery[some, 0].cpu() - want).abs().max()) < 3.6e-5
+
+
 # grouped heads, per-unit step (vector ALU for two heads and float32, matrix cores for three to eight bf16 heads) and
 # split-KV for more heads, probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
