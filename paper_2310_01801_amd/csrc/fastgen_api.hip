@@ -204,32 +204,42 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   pa.rowstat = reinterpret_cast<float2*>(at(L.rowstat));
   pa.colsum = reinterpret_cast<double*>(at(L.colsum));
   pa.bandcol = reinterpret_cast<double*>(at(L.bandcol));
-  pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c);
+  pa.U = c.num_units; pa.n = c.prompt_len; pa.d = c.head_dim; pa.w = w; pa.G = group_of(c); pa.stride = pa.n;
   pa.scale = scale;
   hipError_t e;
   const fg_once_form once = lse_opt ? fg_once_form{0, 1} : fg_once_form_of(c);   // both sweeps in one pass
-  const size_t sums = (size_t)pa.U * pa.n;
+  const int cols = pa.n < FG_ONCE_TOKENS ? pa.n : FG_ONCE_TOKENS;   // of the one pass
+  const bool beyond = pa.n > cols;                                  // columns that two sweeps take
   const double* part_col = static_cast<const double*>(part_sums);
-  const double* part_band = part_col + (size_t)once.parts * sums;
+  const double* part_band = part_col + (size_t)once.parts * pa.U * cols;
+  const bool select_adds = !beyond && once.parts <= FG_SELECT_PARTS;
   if (once.waves) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
-    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
-                           : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
-    if (e == hipSuccess && once.parts > FG_SELECT_PARTS)
-      e = fg_launch_part_sums(part_col, part_band, pa.colsum, pa.bandcol, sums, once.parts, s);
+    e = beyond ? fg_launch_profile_bf16(pa, 1, cols, s) : hipSuccess;
+    if (e == hipSuccess)
+      e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
+                             : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
+    if (e == hipSuccess && once.parts > 1 && !select_adds)
+      e = fg_launch_part_sums(part_col, part_band, pa.colsum, pa.bandcol, pa.U, cols, pa.n, once.parts, s);
     tm.end();
     if (e != hipSuccess) return e;
+    if (beyond) {
+      tm.begin(FG_PHASE_SWEEP2);
+      e = fg_launch_profile_bf16(pa, 2, cols, s);
+      tm.end();
+      if (e != hipSuccess) return e;
+    }
   } else {
     *where = "fastgen_profile(row log-sum-exp sweep)";
     tm.begin(FG_PHASE_SWEEP1);
     if (lse_opt) e = fg_launch_lse_to_rowstat(lse_opt, pa.rowstat, (size_t)c.num_units * pa.G * c.prompt_len, s);
-    else e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 1, s) : fg_launch_profile_f32(pa, 1, s);
+    else e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 1, 0, s) : fg_launch_profile_f32(pa, 1, s);
     tm.end();
     if (e != hipSuccess) return e;
     *where = "fastgen_profile(column sweep)";
     tm.begin(FG_PHASE_SWEEP2);
-    e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 2, s) : fg_launch_profile_f32(pa, 2, s);
+    e = (c.dtype == FG_BF16) ? fg_launch_profile_bf16(pa, 2, 0, s) : fg_launch_profile_f32(pa, 2, s);
     tm.end();
     if (e != hipSuccess) return e;
   }
@@ -237,7 +247,7 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   fg_select_args sa;
   sa.colsum = pa.colsum; sa.bandcol = pa.bandcol; sa.token_class = token_class;
   sa.part_col = part_col; sa.part_band = part_band;
-  sa.parts = once.parts <= FG_SELECT_PARTS ? once.parts : 1;
+  sa.parts = select_adds ? once.parts : 1;
   sa.keep = reinterpret_cast<uint8_t*>(at(L.keep)); sa.slot = reinterpret_cast<int32_t*>(at(L.slot));
   sa.policy = reinterpret_cast<int32_t*>(at(L.policy)); sa.recov = reinterpret_cast<double*>(at(L.recov));
   sa.kcount = reinterpret_cast<int32_t*>(at(L.kcount)); sa.cap = reinterpret_cast<int32_t*>(at(L.cap));

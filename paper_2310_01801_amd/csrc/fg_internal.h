@@ -240,6 +240,7 @@ constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 //   few units            d = 64: 2 of 534, G = 4, 29 / 31, 1 of 660, G = 5, 0.98x, 5 of 372, G = 8, 0.88x; G > 8: 3 of 378, d = 64,
 //                        0.85x, 7 of 320 0.99x. From some 400 tiles on these would gain (5 of 894, d = 64, G = 8, 1.28x, 17 of
 //                        873, G = 12, 219 / 88): the lines for few units leave that to the two sweeps
+constexpr int FG_ONCE_TOKENS = 1024;   // columns that the one-pass kernels hold
 struct fg_once_form { int waves, parts; };
 inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (n > 1024 || U > (1 << 22)) return {0, 1};
@@ -283,6 +284,37 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   return {waves, parts};
 }
 
+// Longer bf16 prompts: workgroups per unit that take the first 1024 columns of all rows in one pass, 0 where the two sweeps
+// serve the whole prompt. The triangle of rows and columns from 1024 on stays with the two sweeps: the first one leaves its
+// rows' sums, which join the one pass, and the second one takes the rows' normalisers from there. Two sweeps / so, in us (in
+// brackets the workgroups per unit):
+//   d = 128    1024 units of 2048 tokens 1330 / 1159 (1), of 1337 688 / 554 (1), 256 of 3000 666 / 617 (4), 1024 of 4096 4654 / 4090 (3),
+//              512 of 8192 8773 / 8430 (2), 64 of 1060 90 / 42 (4), 32 of 2048 130 / 85 (8), 16 of 2048 88 / 60 (16), 64 of 4096 343 / 343 (4)
+//   d = 64     1024 of 2048 868 / 811 (1), 432 of 1337 254 / 206 (1), 700 of 2048 613 / 612 (1), 32 of 3000 142 / 120 (8), 180 of 2048 201 / 200 (4)
+//   G > 1      256 of 2048, G = 4, 1370 / 1138 (1), 400 of 4000, G = 2, 3602 / 3240 (3), 64 of 4000, G = 8, 2491 / 2230 (4), 16 of 2048, G = 8, 391 / 303 (9)
+// Parts: as above, the fullest XCD counts the rounds. A part's prologue and sums cost 5 % of a prompt of 1060 tokens (7 % at
+// d = 64), 1 % of one of 2048; several workgroups that read a unit's keys from one L2 gain 2 to 3 % at d = 128 (1024 units of
+// 4096 in one, two, three parts: 1.10x, 1.11x, 1.14x; of 1060 1.40x, 1.31x, 1.27x). Few units of long prompts stay: their
+// sweeps spread over the card as well, and the share of the first columns falls (32 units of 4096 0.98x, 100 of 6000 0.94x, 67 of 3469 0.96x, 8 of
+// 3000 1.09x, 0.94x at d = 64, 4 of 1060, d = 64, 0.80x; 8 of 1500 1.14x, 1.07x). From 8192 tokens on, 1.03x, nothing was measured.
+inline int fg_once_long_parts(int d, int U, int n, int G) {
+  (void)G;   // (heads only lengthen a part)
+  if (n <= FG_ONCE_TOKENS || n > 8192 || U > (1 << 22)) return 0;
+  if (n > (U >= 180 ? 8192 : U >= 96 ? 5000 : U >= 12 ? 3200 : U >= 8 ? 1600 : 0)) return 0;
+  long long most = (long long)(FG_PART_SUMS / ((size_t)U * FG_ONCE_TOKENS * 16));
+  if (most > 16) most = 16;   // (a prompt of more than 1024 tokens has 17 blocks)
+  const double part = (d == 64 ? 0.075 : 0.05) * (1024.0 / n) * (1024.0 / n);
+  int parts = 1;
+  double best = 0.0;
+  for (int p = 1; p == 1 || p <= most; ++p) {
+    const long long rounds = ((long long)(U + 7) / 8 * p + 31) / 32;
+    const double shared = d == 128 && n >= 1700 ? (p > 2 ? 1.03 : p > 1 ? 1.02 : 1.0) : 1.0;
+    const double score = (double)U * p / (256.0 * (double)rounds) * (1.0 - part * (p - 1)) * shared;
+    if (score > best + 1e-9) { best = score; parts = p; }
+  }
+  return parts;
+}
+
 // Both float32 sweeps in one pass (profile_f32.hip): workgroups per unit, 0 where the two sweeps serve. Up to 2048
 // workgroups in all (32 MiB of partial sums at most), at least two blocks of 16 rows each. Measured, two sweeps / one pass in us:
 //   64 units of 1000 tokens, d = 128     464 / 253;  16 of 1000 134 / 78
@@ -306,13 +338,18 @@ constexpr int FG_SELECT_PARTS = 10;
 // What serves a configuration without a supplied log-sum-exp (0 waves: the two sweeps), and the bytes of its partial sums.
 inline fg_once_form fg_once_form_of(const fg_config& c) {
   const int G = c.group_size > 1 ? c.group_size : 1;
-  if (c.dtype == FG_BF16) return fg_once_of(c.head_dim, c.num_units, c.prompt_len, G);
+  if (c.dtype == FG_BF16) {
+    if (c.prompt_len <= FG_ONCE_TOKENS) return fg_once_of(c.head_dim, c.num_units, c.prompt_len, G);
+    const int parts = fg_once_long_parts(c.head_dim, c.num_units, c.prompt_len, G);
+    return {parts ? 8 : 0, parts ? parts : 1};
+  }
   const int parts = fg_once_f32_parts(c.num_units, c.prompt_len, G);
   return {parts ? 4 : 0, parts ? parts : 1};
 }
 inline size_t fg_part_bytes(const fg_config& c) {
   const fg_once_form f = fg_once_form_of(c);
-  return f.waves && f.parts > 1 ? (size_t)f.parts * c.num_units * c.prompt_len * 16 : 0;
+  const int cols = c.prompt_len < FG_ONCE_TOKENS ? c.prompt_len : FG_ONCE_TOKENS;
+  return f.waves && f.parts > 1 ? (size_t)f.parts * c.num_units * cols * 16 : 0;
 }
 
 // ---------------------------------------------------------------- launch arguments
@@ -320,6 +357,7 @@ struct fg_profile_args {
   const void* Q; const void* K;
   float2* rowstat; double* colsum; double* bandcol;
   int U, n, d, w;
+  int stride;  // tokens from one unit to the next (of Q, K and all sums)
   int G;  // query heads per K/V unit: Q and rowstat hold U * G units
   float scale;
 };
@@ -369,11 +407,11 @@ struct fg_export_args {
   int U, d, esize, max_pos;  // max_pos = n + S
 };
 
-hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, hipStream_t);
+hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, int from, hipStream_t);
 // (several workgroups per unit leave their sums in `part_sums`: columns [parts, U, n], then band)
 hipError_t fg_launch_profile_once(const fg_profile_args&, fg_once_form, double* part_sums, hipStream_t);
-// sums over [parts, N] in order, of two arrays
-hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, size_t N, int parts, hipStream_t);
+// sums over [parts, U, cols] in order, of two arrays, into [U, stride]
+hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, int U, int cols, int stride, int parts, hipStream_t);
 hipError_t fg_launch_profile_f32(const fg_profile_args&, int pass, hipStream_t);
 hipError_t fg_launch_profile_once_f32(const fg_profile_args&, int parts, double* part_sums, hipStream_t);
 hipError_t fg_launch_lse_to_rowstat(const float* lse_nat, float2* rowstat, size_t count, hipStream_t);

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256, 2) void fg_profile_once_f32_kernel(
 
 // Sums of the parts [P, N] in order
 __global__ void fg_part_sum_kernel(const double* __restrict__ pcol, const double* __restrict__ pband,
-                                   double* __restrict__ col, double* __restrict__ band, size_t N, int P) {
+                                   double* __restrict__ col, double* __restrict__ band, int cols, int stride, size_t N, int P) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
   double a = pcol[i], b = pband[i];
@@ -331,8 +331,9 @@ __global__ void fg_part_sum_kernel(const double* __restrict__ pcol, const double
     a += pcol[p * N + i];
     b += pband[p * N + i];
   }
-  col[i] = a;
-  band[i] = b;
+  const size_t to = i / cols * stride + i % cols;
+  col[to] = a;
+  band[to] = b;
 }
 
 template <int D>
@@ -381,8 +382,9 @@ __global__ void fg_lse_to_rowstat_kernel(const float* __restrict__ in, float2* _
 
 }  // namespace
 
-hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, size_t N, int parts, hipStream_t s) {
-  hipLaunchKernelGGL(fg_part_sum_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, pcol, pband, col, band, N, parts);
+hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, int U, int cols, int stride, int parts, hipStream_t s) {
+  const size_t N = (size_t)U * cols;
+  hipLaunchKernelGGL(fg_part_sum_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, pcol, pband, col, band, cols, stride, N, parts);
   return hipGetLastError();
 }
 

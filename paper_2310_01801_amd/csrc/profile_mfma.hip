@@ -35,10 +35,18 @@ struct Lds {
   static constexpr int kTileBytes = kTile * kRowBytes;
 };
 
+// What a row of the first sweep leaves: shift and 1 / sum; where the columns before are still to come, a whole number for the
+// shift and the sum itself (whatever their shift, bringing it there is then exact).
+__device__ __forceinline__ float2 fg_row_result(float m, double l, bool more) {
+  if (!more) return make_float2(m, (float)(1.0 / l));
+  const float whole = rintf(m);
+  return make_float2(whole, (float)(l * exp2((double)m - (double)whole)));
+}
+
 template <int D, int PASS, bool PAIRED>
 __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
-    double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int w, float c,
+    double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int ns, int w, float c,
     int nblk, int G) {
   constexpr int KK = D / 16;
   constexpr int RS = Lds<D>::kRowBytes;
@@ -70,10 +78,10 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   // G query heads share a K/V unit. Sweep 1 runs per query head (U counts query heads, unit =
   // u * G + g) against the keys of u; sweep 2 runs per K/V unit and streams the query rows of
   // its G heads one after the other (heads are contiguous: one buffer covers them all).
-  const size_t mat = (size_t)n * D;
+  const size_t mat = (size_t)ns * D;
   const __bf16* own_mat = (PASS == 1 ? Q : K) + (size_t)unit * mat;
   const __bf16* str_mat = (PASS == 1) ? K + (size_t)(unit / G) * mat : Q + (size_t)unit * G * mat;
-  const float2* stat_row = rowstat + (size_t)unit * (PASS == 1 ? 1 : G) * n;
+  const float2* stat_row = rowstat + (size_t)unit * (PASS == 1 ? 1 : G) * ns;
   const int heads = (PASS == 1) ? 1 : G;
 
   const int WG0 = blk * kOwnPerBlock;       // first owner item of the workgroup
@@ -112,9 +120,9 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   constexpr bool DMA = (D == 128) && (PASS == 1);
   typedef __attribute__((address_space(3))) void* lds_ptr;
   const __amdgpu_buffer_rsrc_t str_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(str_mat), 0, heads * n * D * 2, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(str_mat), 0, (heads * ns - (ns - n)) * D * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t stat_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(stat_row), 0, heads * n * 8, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(stat_row), 0, (heads * ns - (ns - n)) * 8, 0x00020000);
   int voff[LOADS];
 #pragma unroll
   for (int r = 0; r < LOADS; ++r) {
@@ -179,8 +187,8 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
     int t_next = t + 1, head_next = head_row0;
     if (PASS == 2) {
       t_next = t - 1;
-      if (t_next < t_begin) { t_next = t_end - 1; head_next += n; }
-    } else if (t_next == t_end) { t_next = t_begin; head_next += n; }
+      if (t_next < t_begin) { t_next = t_end - 1; head_next += ns; }
+    } else if (t_next == t_end) { t_next = t_begin; head_next += ns; }
     // unconditional (the load count per iteration is static); the last iteration re-reads its own tile
     gload(it + 1 < n_it ? head_next + t_next * kTile : head_row0 + t0, buf ^ 1);
 
@@ -334,7 +342,7 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
       const float M = fmaxf(m_run[f], m_o);
       const double L = l_run[f] * (double)fg_exp2(m_run[f] - M) + l_o * (double)fg_exp2(m_o - M);
       const int row = O0 + 32 * f + ln;
-      if (lh == 0 && row < n) rowstat[(size_t)unit * n + row] = make_float2(M, (float)(1.0 / L));
+      if (lh == 0 && row < n) rowstat[(size_t)unit * ns + row] = fg_row_result(M, L, ns != n);
     }
   } else {
 #pragma unroll
@@ -343,8 +351,8 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
       const double bs = band_acc[f] + fg_shfl_xor_f64(band_acc[f], 32);
       const int col = O0 + 32 * f + ln;
       if (lh == 0 && col < n) {
-        colsum[(size_t)unit * n + col] = cs;
-        bandcol[(size_t)unit * n + col] = bs;
+        colsum[(size_t)unit * ns + col] = cs;
+        bandcol[(size_t)unit * ns + col] = bs;
       }
     }
   }
@@ -394,7 +402,7 @@ __device__ __forceinline__ void fg_col_tile(const f32x16& ac, const float (&ms)[
 template <int D, int PASS, int F>
 __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
-    double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int w, float c,
+    double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int ns, int w, float c,
     int nblk, int G) {
   constexpr int KK = D / 16;
   __shared__ double s_a[4][F][32], s_b[4][F][32];
@@ -408,10 +416,10 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, lh = lane >> 5;
-  const size_t mat = (size_t)n * D;
+  const size_t mat = (size_t)ns * D;
   const __bf16* own_mat = (PASS == 1 ? Q : K) + (size_t)unit * mat;
   const __bf16* str_mat = (PASS == 1) ? K + (size_t)(unit / G) * mat : Q + (size_t)unit * G * mat;
-  const float2* stat_row = rowstat + (size_t)unit * (PASS == 1 ? 1 : G) * n;
+  const float2* stat_row = rowstat + (size_t)unit * (PASS == 1 ? 1 : G) * ns;
   const int heads = (PASS == 1) ? 1 : G;
   const int O0 = blk * (32 * F);
 
@@ -427,7 +435,7 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
   const int t_end = (PASS == 1) ? (min(n, O0 + 32 * F) + kTile - 1) / kTile : (n + kTile - 1) / kTile;
   const int nt = t_end - t_begin, n_it = nt * heads;
   const __amdgpu_buffer_rsrc_t stat_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(stat_row), 0, heads * n * 8, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(stat_row), 0, (heads * ns - (ns - n)) * 8, 0x00020000);
 
   float m_run[F];
   double acc_a[F], acc_b[F];   // pass 1: l (acc_b unused); pass 2: column sum and its part in the band
@@ -437,7 +445,7 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
   u32x4 next[KK];
   auto load = [&](int it) {   // rows past the end of the unit are clamped: masked wherever they are used
     const int h = it / nt, row = min((t_begin + it - h * nt) * kTile + ln, n - 1);
-    const __bf16* src = str_mat + ((size_t)h * n + row) * D + lh * 8;
+    const __bf16* src = str_mat + ((size_t)h * ns + row) * D + lh * 8;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) next[kk] = *reinterpret_cast<const u32x4*>(src + 16 * kk);
   };
@@ -449,7 +457,7 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
     if (PASS == 2) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {   // rows past the last head's end read as zeros
-        const int at = (h * n + sbase + g * 8) * 8;
+        const int at = (h * ns + sbase + g * 8) * 8;
         const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at, 0, 0));
         const f32x4 u = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at + 16, 0, 0));
         ms[g * 4 + 0] = v[0]; ms[g * 4 + 1] = v[2]; ms[g * 4 + 2] = u[0]; ms[g * 4 + 3] = u[2];
@@ -493,13 +501,13 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
   __syncthreads();
   if (tid < 32 * F && O0 + tid < n) {
     const int f = tid >> 5, o = tid & 31;
-    const size_t at = (size_t)unit * n + O0 + tid;
+    const size_t at = (size_t)unit * ns + O0 + tid;
     if (PASS == 1) {
       const double M = fmax(fmax(s_b[0][f][o], s_b[1][f][o]), fmax(s_b[2][f][o], s_b[3][f][o]));
       double L = 0.0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) L += s_a[i][f][o] * (double)fg_exp2((float)(s_b[i][f][o] - M));
-      rowstat[at] = make_float2((float)M, (float)(1.0 / L));
+      rowstat[at] = fg_row_result((float)M, L, ns != n);
     } else {
       colsum[at] = (s_a[0][f][o] + s_a[1][f][o]) + (s_a[2][f][o] + s_a[3][f][o]);
       bandcol[at] = (s_b[0][f][o] + s_b[1][f][o]) + (s_b[2][f][o] + s_b[3][f][o]);
@@ -517,10 +525,10 @@ hipError_t launch_small(const fg_profile_args& a, int pass, hipStream_t s) {
   const __bf16* K = static_cast<const __bf16*>(a.K);
   if (pass == 1)
     hipLaunchKernelGGL((fg_profile_small_kernel<D, 1, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
   else
     hipLaunchKernelGGL((fg_profile_small_kernel<D, 2, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
   return hipGetLastError();
 }
 
@@ -535,10 +543,10 @@ hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   const __bf16* K = static_cast<const __bf16*>(a.K);
   if (pass == 1)
     hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 1, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
   else   // (single blocks do not serve the second sweep at d = 128)
     hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2, PAIRED || D == 128>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
   return hipGetLastError();
 }
 
@@ -554,6 +562,15 @@ hipError_t launch_sized(const fg_profile_args& a, int pass, hipStream_t s) {
 
 }  // namespace
 
-hipError_t fg_launch_profile_bf16(const fg_profile_args& a, int pass, hipStream_t s) {
+// `from` > 0: of the rows and columns from that token on, the triangle below the diagonal
+hipError_t fg_launch_profile_bf16(const fg_profile_args& whole, int pass, int from, hipStream_t s) {
+  fg_profile_args a = whole;
+  const size_t skip = (size_t)from * a.d;
+  a.Q = static_cast<const __bf16*>(a.Q) + skip;
+  a.K = static_cast<const __bf16*>(a.K) + skip;
+  a.rowstat += from;
+  a.colsum += from;
+  a.bandcol += from;
+  a.n -= from;
   return a.d == 128 ? launch_sized<128>(a, pass, s) : launch_sized<64>(a, pass, s);
 }

@@ -52,6 +52,13 @@ __device__ __forceinline__ void fg_load_lds16(__amdgpu_buffer_rsrc_t r, const vo
                :: "s"(__builtin_amdgcn_readfirstlane(at)), "v"(voff), "s"(r), "s"(soff) : "memory");   // (m0 holds nothing of the compiler's)
 #endif
 }
+__device__ __forceinline__ void fg_load_lds4(__amdgpu_buffer_rsrc_t r, const void* lds, int voff, int soff) {   // 4 bytes per lane
+#ifdef __HIP_DEVICE_COMPILE__
+  const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)lds;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(at)), "v"(voff), "s"(r), "s"(soff) : "memory");
+#endif
+}
 __device__ __forceinline__ void fg_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }        // this wave's loads
 __device__ __forceinline__ void fg_have_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }   // its LDS reads
 __device__ __forceinline__ void fg_barrier() {   // all waves' loads and LDS accesses
@@ -95,10 +102,10 @@ __device__ __forceinline__ double fg_cols_over_rows(const float (&t)[16], int la
 // offset of accumulator i of a lane within its 32 items (matrix instruction layout, without the half's 4)
 constexpr __device__ int fg_acc_item(int i) { return (i >> 2) * 8 + (i & 3); }
 
-template <int D, int NW>
+template <int D, int NW, bool LONG>
 __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
-    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, double* __restrict__ colsum,
-    double* __restrict__ bandcol, int U, int n, int w, float c, int G, int P) {
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* rowstat, double* __restrict__ colsum,
+    double* __restrict__ bandcol, int U, int n, int stride, int w, float c, int G, int P) {
   constexpr int KK = D / 16;
   constexpr int RB = D * 2;           // bytes of a row
   constexpr int PPR = D / 8;          // 16-byte pieces of a row
@@ -115,6 +122,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   __shared__ __attribute__((aligned(16))) unsigned char s_k[NW][HELD][kFrag * RB];
   __shared__ double s_l[2][NW][kRows];
   __shared__ float s_m[2][NW][kRows];
+  __shared__ float2 s_x[2][LONG ? kRows : 1];   // of the columns beyond, per row: a whole number for its shift, and its sum
   __shared__ double s_sum[2][COLS];   // column sums, and their part inside the band
 
   // parts of one unit on one XCD (its L2 then serves the keys)
@@ -153,10 +161,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   for (int h = 0; h < G; ++h) {   // the query heads of the unit, one after the other over the same columns
     const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<__bf16*>(Q + ((size_t)unit * G + h) * n * D), 0, n * RB, 0x00020000);
+    float2* stat = rowstat + ((size_t)unit * G + h) * n;
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(stat, 0, n * 8, 0x00020000);
     auto load_q = [&](int b, int to) {
 #pragma unroll
       for (int i = 0; i < QL; ++i)
         fg_load_lds16(q_rsrc, &s_q[to][(wave * QL + i) * 1024], source(wave * QL + i), b * kRows * RB + (wave * QL + i) * 1024);
+      if (LONG && wave < 2) fg_load_lds4(x_rsrc, &s_x[to][wave * kRows / 2], lane * 4, b * kRows * 8 + wave * kRows * 4);
     };
     load_q(block(mine - 1), buf);   // the last reads of this buffer lie behind a barrier
     fg_barrier();
@@ -174,7 +185,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       const int b = block(i);
       const int r0 = b * kRows;
       const int jl = min(2 * b + 1, (n - 1) / kFrag);   // last column fragment
-      const int cnt = jl >= wave ? (jl - wave) / NW + 1 : 0;   // fragments of this wave
+      const int cnt = jl >= wave ? min((jl - wave) / NW + 1, kSlots) : 0;   // fragments of this wave
+      auto beyond = [&]() { return LONG && r0 >= COLS && r0 + lane < n ? s_x[buf][lane] : make_float2(FG_NEG_BIG, 0.f); };
       if (i > 0) load_q(block(i - 1), buf ^ 1);
       f32x16 e[kSlots][2];
       int at[kSlots];        // the fragments' slots
@@ -320,6 +332,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         fg_barrier();
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
+        if (LONG) {
+          const float2 x = beyond();
+          L = fma((double)x.y, (double)fg_exp2(x.x - M), L);
+        }
         again = __any(r0 + lane < n && !(L >= kLeastSum && L <= kMostSum));   // the same in all waves
         if (again) fg_barrier();   // s_l has been read
       }
@@ -341,13 +357,14 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         s_m[buf][wave][lane] = own;
         fg_barrier();
         float mv[NW];
-        M = FG_NEG_BIG;
+        const float2 x = beyond();
+        M = x.x;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
           mv[i] = s_m[buf][i][lane];
           M = fmaxf(M, mv[i]);
         }
-        L = 0.0;
+        L = LONG ? (double)x.y * (double)fg_exp2(x.x - M) : 0.0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
         share = fg_exp2(own - M);
@@ -360,6 +377,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       }
       double inv = __builtin_amdgcn_rcp(L);
       inv = fma(inv, fma(-L, inv, 1.0), inv);
+      if (LONG && wave == 0 && r0 >= COLS && r0 + lane < n) stat[r0 + lane] = make_float2(M, (float)inv);
       float f0 = r0 + lane < n ? (float)inv * share : 0.f, f1 = f0;   // rows past the end count nothing
       fg_swap_halves(f0, f1);
 #pragma unroll
@@ -395,27 +413,29 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
     }
   }
   __syncthreads();
-  for (int i = tid; i < n; i += NT) {
-    colsum[((size_t)part * U + unit) * n + i] = s_sum[0][i];
-    bandcol[((size_t)part * U + unit) * n + i] = s_sum[1][i];
+  for (int i = tid; i < min(n, COLS); i += NT) {
+    colsum[((size_t)part * U + unit) * stride + i] = s_sum[0][i];
+    bandcol[((size_t)part * U + unit) * stride + i] = s_sum[1][i];
   }
 }
 
-template <int D, int NW>
+template <int D, int NW, bool LONG>
 hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s) {
-  const size_t N = (size_t)a.U * a.n;
+  const int cols = a.n < FG_ONCE_TOKENS ? a.n : FG_ONCE_TOKENS;
+  const size_t N = (size_t)a.U * cols;
   double* col = P > 1 ? parts : a.colsum;
   double* band = P > 1 ? parts + P * N : a.bandcol;
-  hipLaunchKernelGGL((fg_profile_once_kernel<D, NW>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(NW * 64), 0, s,
-                     static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), col, band, a.U, a.n, a.w,
-                     a.scale * FG_LOG2E, a.G, P);
+  hipLaunchKernelGGL((fg_profile_once_kernel<D, NW, LONG>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(NW * 64), 0, s,
+                     static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), a.rowstat, col, band, a.U, a.n,
+                     P > 1 ? cols : a.n, a.w, a.scale * FG_LOG2E, a.G, P);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t fg_launch_profile_once(const fg_profile_args& a, fg_once_form f, double* parts, hipStream_t s) {
-  if (a.n > kSlots * kFrag * f.waves || f.parts > (a.n + kRows - 1) / kRows) return hipErrorInvalidValue;
-  if (f.waves == 8) return a.d == 128 ? launch<128, 8>(a, f.parts, parts, s) : launch<64, 8>(a, f.parts, parts, s);
-  return a.d == 128 ? launch<128, 4>(a, f.parts, parts, s) : launch<64, 4>(a, f.parts, parts, s);
+  if ((a.n > kSlots * kFrag * f.waves && f.waves != 8) || f.parts > (a.n + kRows - 1) / kRows) return hipErrorInvalidValue;
+  if (a.n > FG_ONCE_TOKENS) return a.d == 128 ? launch<128, 8, true>(a, f.parts, parts, s) : launch<64, 8, true>(a, f.parts, parts, s);
+  if (f.waves == 8) return a.d == 128 ? launch<128, 8, false>(a, f.parts, parts, s) : launch<64, 8, false>(a, f.parts, parts, s);
+  return a.d == 128 ? launch<128, 4, false>(a, f.parts, parts, s) : launch<64, 4, false>(a, f.parts, parts, s);
 }

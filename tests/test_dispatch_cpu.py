@@ -16,6 +16,7 @@ extern "C" int unit_threads(const fg_config* c) { return fg_unit_threads(*c); }
 extern "C" int sweep_form(int d, int pass, int U, int n, int G) { return fg_sweep_form_of(d, pass, U, n, G); }
 extern "C" int once_form(int d, int U, int n, int G) { const fg_once_form f = fg_once_of(d, U, n, G); return f.waves * 100 + f.parts; }
 extern "C" int once_f32_parts(int U, int n, int G) { return fg_once_f32_parts(U, n, G); }
+extern "C" int once_long_parts(int d, int U, int n, int G) { return fg_once_long_parts(d, U, n, G); }
 extern "C" int update_threads(const fg_config* c) { return fg_update_threads(*c); }
 """
 
@@ -182,6 +183,21 @@ def test_one_pass_profile(rules):
                        ((128, 300, 1000, 8), 804), ((128, 350, 1000, 8), 802), ((128, 400, 1000, 8), 803), ((64, 83, 519, 16), 805),
                        ((64, 658, 159, 2), 401), ((64, 1746, 365, 1), 401), ((64, 1256, 183, 12), 401), ((64, 1099, 365, 16), 403)):
         assert rules.once_form(*args) == want, (args, rules.once_form(*args))
+
+
+# The first 1024 columns of longer bf16 prompts in one pass: parts as above, at most the 17 blocks of the shortest such
+# prompt and the room for their sums; few units of long prompts stay with the two sweeps, whose measured gain would be below 1
+def test_first_columns_of_long_prompts(rules):
+    for d in (64, 128):
+        for n in (1, 1024, 1025, 1500, 2048, 3201, 5001, 8192, 8193, 131072):
+            for U in (1, 8, 12, 95, 96, 179, 180, 1024, 4096, 1 << 22, (1 << 22) + 1):
+                parts = rules.once_long_parts(d, U, n, 1)
+                assert 0 <= parts <= 16 and (not parts or 1024 < n <= 8192)
+                assert parts < 2 or parts * U * 1024 * 16 <= PART_SUMS
+                assert (U + 7) * parts * 512 < 1 << 32
+    for args, want in (((128, 1024, 2048), 2), ((128, 1024, 1337), 1), ((128, 1024, 4096), 3), ((128, 64, 1060), 4), ((128, 32, 2048), 8), ((128, 16, 2048), 16), ((64, 432, 1337), 1),
+                       ((128, 640, 2048), 2), ((128, 150, 1060), 3), ((128, 32, 4096), 0), ((128, 100, 6000), 0), ((64, 4, 1060), 0), ((128, 8, 3000), 0)):
+        assert rules.once_long_parts(*args, 1) == want, (args, rules.once_long_parts(*args, 1))
 
 
 # Short prompts that the two sweeps were measured to serve faster, and their neighbours in one pass: up to 32 tokens with

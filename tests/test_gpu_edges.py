@@ -289,6 +289,21 @@ def test_bf16_one_pass(heads, n, d, G):
         H.log_report(f"one pass U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
+# The first 1024 columns of longer prompts in one pass, the triangle behind them in two sweeps that leave and take row
+# sums: triangles of one row, of a tile and of a block more or less, one and several workgroups per unit, grouped heads,
+# windows inside a block, up to the seam at column 1024 and beyond it
+@pytest.mark.parametrize("heads,n,d,G", [
+    (8, 1025, 128, 1), (16, 1056, 64, 1), (64, 1087, 128, 2), (300, 1088, 64, 1), (256, 1313, 128, 1), (13, 1500, 128, 4), (200, 2111, 64, 1),
+])
+def test_long_prompts_in_one_pass_and_two_sweeps(heads, n, d, G):
+    for window in (1, 64, 1024, n - 30, n):
+        w = W["llama7b_b1"].scaled(name="long_pass", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d,
+                                   r_l=min(1.0, (window + 0.5) / n), seed=700 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        rep = H.compare(run, check_units=sorted({0, heads - 1}))
+        H.log_report(f"long pass U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
 # Row masses of the one-pass form: as below, 10^5 rows, so within 4 x 1.7e-8 / 300; a shift that moves with every
 # tile and a hardware exponential for every rescaling of it would show as 1e-9 and more.
 @pytest.mark.parametrize("U,n,d", [(64, 333, 128), (300, 400, 64), (128, 1000, 64)])
@@ -327,7 +342,7 @@ def test_one_pass_with_huge_logits(n, at):
 # unit and with heads after one another. All keys share the offset, so the probabilities keep the size of a plain
 # prompt's; a dot product of up to 600 over eight rounded steps in float32 is good to 8 x 2^-24 x 600 / sqrt(d), so the masses to
 # 3.6e-5 (d = 64).
-@pytest.mark.parametrize("U,n,d,G", [(2, 1, 128, 1), (300, 64, 128, 1), (300, 130, 64, 1), (20, 333, 128, 1), (300, 700, 128, 1), (64, 1000, 64, 1), (200, 500, 64, 2)])
+@pytest.mark.parametrize("U,n,d,G", [(2, 1, 128, 1), (300, 64, 128, 1), (300, 130, 64, 1), (256, 1200, 128, 1), (16, 1100, 64, 2), (20, 333, 128, 1), (300, 700, 128, 1), (64, 1000, 64, 1), (200, 500, 64, 2)])
 @pytest.mark.parametrize("rows", ["high", "low", "alternate", "single", "last"])
 def test_one_pass_with_rows_far_from_the_ones_before(U, n, d, G, rows):
     gen = torch.Generator(device="cuda:0").manual_seed(n + d)
