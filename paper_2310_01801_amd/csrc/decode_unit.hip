@@ -7,11 +7,16 @@
 //
 // Bound: HBM in the streaming part, the update's chain of latencies at the end of a launch.
 // Measured against the split form (attention + update launch): 1024 units of 2048 tokens, d = 128
-// bf16: 101 + 20 -> 112 us per step; 16384 of 1024: 804 + 144 -> 845; 432 of 1337, d = 64:
-// 15 + 14 -> 20; 4 of 128, float32: 12 -> 6.6. Four loads of K and of V per lane and tile, the
-// next tile's K on its way during the sums and its V during the logits, keep 109 to 118 vector
+// bf16: 101 + 20 -> 104 us per step; 16384 of 1024: 804 + 144 -> 820; 432 of 1337, d = 64:
+// 15 + 14 -> 18; 4 of 128, float32: 12 -> 5.9. The logits of the units that keep scores stay in LDS for the update
+// (through memory their stores held up the merge's barrier and their loads the update), and the new token comes
+// first: with both, and fewer barriers in the update, 110 -> 104, 19.4 -> 18.2, 6.4 -> 5.9, 4096 units of 1024
+// tokens 217 -> 209, 1600 of 4096 424 -> 407. Four loads of K and of V per lane and tile, the
+// next tile's K on its way during the sums and its V during the logits, keep 109 to 126 vector
 // registers (and spill 55 to 73 scalars into lanes of one): eight loads spill vectors (199 us at the first
-// shape), 1024 threads are slower everywhere.
+// shape), 96 registers for five waves per SIMD too (190), 1024 threads are slower everywhere. By a clock trace
+// of the first shape a scored unit of 1212 tokens streams for 62 us and holds its place for 23 more: 11 until its
+// last wave is through, 12 in the update, while only two workgroups fit a CU.
 #include <type_traits>
 
 #include "fg_common.h"
@@ -33,6 +38,7 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
   __shared__ fg_update_smem sh;
   __shared__ float s_m[NW + 1], s_l[NW + 1];   // partials of the waves, then of the new token
   __shared__ float s_o[NW + 1][D];
+  __shared__ double s_x[NT == 256 ? FG_UNIT_TOKENS_256 : FG_UNIT_TOKENS];   // logits of the units that keep scores
 
   // header: one 32-byte record per unit carries everything, the current length included
   int32_t* rec_p = a.item_unit + (size_t)blockIdx.x * 8;
@@ -106,7 +112,6 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
   float oacc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) oacc[e] = 0.f;
-  double* const clogit = a.clogit + off;
   auto stream = [&](auto keep) __attribute__((always_inline)) {
     for (int tile = wave; tile < ntile; tile += NW) {
       const int slot0 = tile * TW + sub;
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
         const bool ok = slot < Lold;
         if (decltype(keep)::value) {
           const double dd = logit64(kv[it]);
-          if (ok && g == 0) clogit[slot] = dd;
+          if (ok && g == 0) s_x[slot] = dd;
           x[it] = (float)dd;
         } else {
           x[it] = logit32(kv[it]);
@@ -149,10 +154,8 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
       if (more) load(v_rsrc, vv, tile + NW);
     }
   };
-  if (keep_logits) stream(std::true_type{});
-  else stream(std::false_type{});
-
-  // the new token: a partial of its own, and its row appended in the first free slot
+  // the new token: a partial of its own, and its row appended in the first free slot (at the start: behind the stream
+  // its loads would keep the other waves waiting)
   if (wave == NW - 1) {
     const u32x4 knew = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.k_new) + (size_t)u * RB + g * 16);
     const u32x4 vnew = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.v_new) + (size_t)u * RB + g * 16);
@@ -169,11 +172,14 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
       a.cpos[off + Lold] = a.n + a.step;
       a.ccls[off + Lold] = a.class_new[u / a.units_per_seq];
       a.cscore[off + Lold] = 0.0;
-      if (keep_logits) clogit[Lold] = dd;
+      if (keep_logits) s_x[Lold] = dd;
       s_m[NW] = (float)dd;
       s_l[NW] = 1.f;
     }
   }
+  if (keep_logits) stream(std::true_type{});
+  else stream(std::false_type{});
+
   // the row groups of the wave (lanes with equal g), then the waves
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) {
@@ -187,7 +193,7 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
   }
   if (lane == 0) { s_m[wave] = mw; s_l[wave] = lsum; }
   auto merge = [&]() -> float {
-  __syncthreads();   // also orders the appended slot and the kept logits before the update
+  __syncthreads();   // also orders the appended slot and the logits before the update
   float M = s_m[0];
 #pragma unroll
   for (int i = 1; i <= NW; ++i) M = fmaxf(M, s_m[i]);
@@ -212,7 +218,8 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
     set_len(L);
     return;
   }
-  fg_update_unit<ESIZE, D, false, NT, NT == 256 ? FG_UNIT_TOKENS_256 : FG_UNIT_TOKENS>(a, u, L, cap, off, policy, comp, sh, merge, set_len);
+  fg_update_unit<ESIZE, D, false, NT, NT == 256 ? FG_UNIT_TOKENS_256 : FG_UNIT_TOKENS>(a, u, L, cap, off, policy, comp, sh, merge, set_len,
+      [&](int j) { return s_x[j]; });
 }
 
 template <int NT>

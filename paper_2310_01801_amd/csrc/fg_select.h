@@ -180,10 +180,17 @@ __device__ __forceinline__ fg_topk fg_select_topk_regs(const uint64_t (&kc)[NC],
 // On success every unprotected token with key >= out->thr is in the top k (mode 2, no position
 // tie-break needed); left[0, *left_count) (shared memory, visible after the next barrier) are the
 // slots of the tokens that leave. Keys of slot tid + NT i are kc[i] (valid while < m).
+// Two barriers per test: the buffers of odd and even tests take turns, so that two barriers lie between a read and the next
+// write (with one buffer four barriers, 256 units of 2048 tokens with four heads 37.3 us per step, 33.7 so; 4 units of 128,
+// float32, 6.4 and 5.9). Two values per round, for half of the rounds, gained nothing: their minima cost as much.
 #define FG_EVICT_TRIES 6
+struct fg_evict_smem {
+  double low[2][16];
+  int count[2][16];
+};
 template <int NT, int NC>
 __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint32_t prot, int m, int k,
-                                                  double* red_d, int* red_i, int* left, int* left_count,
+                                                  fg_evict_smem& sh, int* left, int* left_count,
                                                   fg_topk* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double inf = __longlong_as_double(0x7ff0000000000000ll);
@@ -197,12 +204,11 @@ __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint
       if (j < m && !((prot >> i) & 1u) && v > last) loc = fmin(loc, v);
     }
     loc = fg_wave_min_f64(loc);
+    if (lane == 0) sh.low[it & 1][wave] = loc;
     __syncthreads();
-    if (lane == 0) red_d[wave] = loc;
-    __syncthreads();
-    double kmin = red_d[0];
+    double kmin = sh.low[it & 1][0];
 #pragma unroll
-    for (int i = 1; i < NT / 64; ++i) kmin = fmin(kmin, red_d[i]);
+    for (int i = 1; i < NT / 64; ++i) kmin = fmin(kmin, sh.low[it & 1][i]);
     out->mode = 2; out->pthr = 0xffffffffu;
     if (kmin == inf) {  // no unprotected token is left: none of them is in the top k
       *left_count = it;
@@ -216,7 +222,12 @@ __device__ __forceinline__ bool fg_evict_cut_regs(const uint64_t (&kc)[NC], uint
       const double v = __longlong_as_double((long long)kc[i]);
       if (j < m) cnt += (v > kmin ? 1 : 0) + (v == kmin ? (1 << 16) : 0);
     }
-    const int tot = fg_block_sum_i32(cnt, red_i);
+    cnt = fg_wave_sum_i32(cnt);
+    if (lane == 0) sh.count[it & 1][wave] = cnt;
+    __syncthreads();
+    int tot = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) tot += sh.count[it & 1][i];
     if ((tot >> 16) != 1) return false;       // a tie at the tested value: needs the position rule
     if ((tot & 0xffff) < k) {                  // fewer than k larger scores: it stays, and so do all above it
       *left_count = it;

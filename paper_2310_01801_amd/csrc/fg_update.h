@@ -14,6 +14,8 @@ struct fg_update_smem {
   fg_select_smem sm;
   double dred[16];
   int ired[20];
+  double zred[16];       // used once per step: no barrier in front of the write
+  fg_evict_smem cut;
   int move[2 * FG_MOVE_LDS];
 };
 
@@ -96,7 +98,13 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
             z += lg[i];
           }
         }
-        inv_d = 1.0 / fg_block_sum_f64(z, sh.dred);
+        z = fg_wave_sum_f64(z);
+        if ((tid & 63) == 0) sh.zred[tid >> 6] = z;
+        __syncthreads();
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) t += sh.zred[i];
+        inv_d = 1.0 / t;
       }
 #pragma unroll
       for (int i = 0; i < NC; ++i) {
@@ -114,7 +122,7 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
       // without the probe only the unprotected tokens' membership matters: try the lowest ones
       bool done = false;
       if (!probing && k_f > 0 && k_f < L && L <= 0xffff)
-        done = fg_evict_cut_regs<NT, NC>(kc, prot, L, k_f, sh.dred, sh.ired, sh.move, &evicted, &tk);
+        done = fg_evict_cut_regs<NT, NC>(kc, prot, L, k_f, sh.cut, sh.move, &evicted, &tk);
       if (!done) {
         evicted = -1;
         __syncthreads();  // score[] is re-read by other threads only if the boundary value is tied
@@ -146,7 +154,7 @@ __device__ __forceinline__ void fg_update_kept(const fg_decode_args& a, int u, i
     for (int j = tid; j < L; j += NT) {
       // the mean of the G heads' rows
       const double aj = GRP ? a.clogit[(off + j) * G] / (double)G
-                            : exp2(a.clogit[off + j] - (double)M) * inv_d;
+                            : exp2(logit(j) - (double)M) * inv_d;
       const int c = cls[j];
       const bool top = fg_in_topk(tk, score[j], (uint32_t)pos[j]), recent = pos[j] > p_new - a.w;
 #pragma unroll
