@@ -7,16 +7,17 @@
 //
 // Bound: HBM in the streaming part, the update's chain of latencies at the end of a launch.
 // Measured against the split form (attention + update launch): 1024 units of 2048 tokens, d = 128
-// bf16: 101 + 20 -> 104 us per step; 16384 of 1024: 804 + 144 -> 820; 432 of 1337, d = 64:
+// bf16: 101 + 20 -> 102 us per step; 16384 of 1024: 804 + 144 -> 820; 432 of 1337, d = 64:
 // 15 + 14 -> 18; 4 of 128, float32: 12 -> 5.9. The logits of the units that keep scores stay in LDS for the update
-// (through memory their stores held up the merge's barrier and their loads the update), and the new token comes
-// first: with both, and fewer barriers in the update, 110 -> 104, 19.4 -> 18.2, 6.4 -> 5.9, 4096 units of 1024
-// tokens 217 -> 209, 1600 of 4096 424 -> 407. Four loads of K and of V per lane and tile, the
+// (through memory their stores held up the merge's barrier and their loads the update), and the new token falls to
+// a wave that ends early (the last one, behind its rows, kept the others waiting for 7 us): with both, and fewer barriers
+// in the update, 110 -> 102, 19.4 -> 17.8, 6.4 -> 5.9, 4096 units of 1024 tokens 217 -> 205, 1600 of 4096 424 -> 403. Four loads of K and of V per lane and tile, the
 // next tile's K on its way during the sums and its V during the logits, keep 109 to 126 vector
 // registers (and spill 55 to 73 scalars into lanes of one): eight loads spill vectors (199 us at the first
 // shape), 96 registers for five waves per SIMD too (190), 1024 threads are slower everywhere. By a clock trace
-// of the first shape a scored unit of 1212 tokens streams for 62 us and holds its place for 23 more: 11 until its
-// last wave is through, 12 in the update, while only two workgroups fit a CU.
+// of the first shape a scored unit of 1212 tokens streams for 54 to 62 us and holds its place for the update's 5, while
+// only two workgroups fit a CU. Tried without gain: the last round's rows shared alike (104 -> 108), higher
+// priority for the later waves (with this order 106) or for the update.
 #include <type_traits>
 
 #include "fg_common.h"
@@ -154,9 +155,12 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
       if (more) load(v_rsrc, vv, tile + NW);
     }
   };
-  // the new token: a partial of its own, and its row appended in the first free slot (at the start: behind the stream
-  // its loads would keep the other waves waiting)
-  if (wave == NW - 1) {
+  if (keep_logits) stream(std::true_type{});
+  else stream(std::false_type{});
+
+  // The new token: a partial of its own, and its row appended in the first free slot. By one of the waves that are through
+  // first: the later half of them shares its SIMDs with older ones and ends 8 of 62 us after those.
+  if (wave == NW / 2 - 1) {
     const u32x4 knew = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.k_new) + (size_t)u * RB + g * 16);
     const u32x4 vnew = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.v_new) + (size_t)u * RB + g * 16);
     const double dd = keep_logits ? logit64(knew) : (double)logit32(knew);
@@ -177,9 +181,6 @@ __global__ __launch_bounds__(NT, 4) void fg_decode_unit_kernel(fg_decode_args a)
       s_l[NW] = 1.f;
     }
   }
-  if (keep_logits) stream(std::true_type{});
-  else stream(std::false_type{});
-
   // the row groups of the wave (lanes with equal g), then the waves
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) {
