@@ -155,13 +155,18 @@ def run_workload(w, args, steps, warmup, dev="cuda:0"):
     # ---- roofline of the profiling sweeps (matrix-core bound)
     flop_sweep = float(d) * n * (n + 1) * U * G   # causal QK^T, one sweep
     sweeps_ms = phase["sweep1"] + phase["sweep2"]
-    contractions = max(1, launches["sweep1"] + launches["sweep2"])   # 1: both sweeps in one pass
-    mfma_achieved = contractions * flop_sweep / (sweeps_ms * 1e-3)
-    roof_profile = dict(kernel="fg_profile_once_kernel (both sweeps in one pass)" if contractions == 1 else
-                        "fg_profile_mfma_kernel (both sweeps)", bound="mfma",
+    sweep_launches = max(1, launches["sweep1"] + launches["sweep2"])   # 1: both sweeps in one pass
+    flops = sweep_launches * flop_sweep
+    kernel = ("fg_profile_once_kernel (both sweeps in one pass)", "fg_profile_mfma_kernel (both sweeps)")[sweep_launches > 1]
+    if sweep_launches == 3:   # the first 1024 columns in one pass, the triangle of rows and columns from there on in two sweeps
+        m = n - 1024
+        flops = float(d) * (n * (n + 1) + m * (m + 1)) * U * G
+        kernel = "fg_profile_once_kernel (the first 1024 columns) and fg_profile_mfma_kernel (both sweeps, the rest)"
+    mfma_achieved = flops / (sweeps_ms * 1e-3)
+    roof_profile = dict(kernel=kernel, bound="mfma",
                         achieved=mfma_achieved / 1e12, peak=PEAK_BF16_MFMA / 1e12, unit="TFLOP/s",
                         frac=mfma_achieved / PEAK_BF16_MFMA, traffic=traffic.get("sweeps"),
-                        avg_launch_ms=sweeps_ms / contractions, flop_per_launch=flop_sweep)
+                        avg_launch_ms=sweeps_ms / sweep_launches, flop_per_launch=flops / sweep_launches)
 
     # ---- roofline of the decode attention kernel (HBM bound): one untimed replay logs lengths
     roof_decode = None

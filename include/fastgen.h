@@ -222,7 +222,8 @@ fg_status fastgen_export_state(fastgen_ctx* ctx, int32_t* lengths, int64_t* offs
 enum {
   FG_PHASE_SWEEP1 = 0,      /* QK^T -> row log-sum-exp (most prompts of up to 1024 tokens, float32 from 64:
                                both sweeps in one pass, SWEEP2 then stays empty;
-                               longer bf16 ones: with the one pass of the first 1024 columns) */
+                               longer bf16 ones: with the one pass of the first 1024
+                               columns, then two kernel groups)            */
   FG_PHASE_SWEEP2 = 1,      /* QK^T -> softmax -> column / band sums         */
   FG_PHASE_SELECT = 2,      /* top-k, recoveries, policy, kept flags + scan  */
   FG_PHASE_COMPACT = 3,     /* pool offsets + gather of kept rows            */

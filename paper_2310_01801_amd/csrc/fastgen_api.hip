@@ -216,10 +216,14 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   if (once.waves) {
     *where = "fastgen_profile(sweeps in one pass)";
     tm.begin(FG_PHASE_SWEEP1);
-    e = beyond ? fg_launch_profile_bf16(pa, 1, cols, s) : hipSuccess;
-    if (e == hipSuccess)
-      e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
-                             : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
+    if (beyond) {
+      e = fg_launch_profile_bf16(pa, 1, cols, s);
+      tm.end();
+      if (e != hipSuccess) return e;
+      tm.begin(FG_PHASE_SWEEP1);
+    }
+    e = c.dtype == FG_BF16 ? fg_launch_profile_once(pa, once, static_cast<double*>(part_sums), s)
+                           : fg_launch_profile_once_f32(pa, once.parts, static_cast<double*>(part_sums), s);
     if (e == hipSuccess && once.parts > 1 && !select_adds)
       e = fg_launch_part_sums(part_col, part_band, pa.colsum, pa.bandcol, pa.U, cols, pa.n, once.parts, s);
     tm.end();
