@@ -7,7 +7,7 @@
 //
 // Bound: HBM in the streaming part, the update's chain of latencies at the end of a launch.
 // Measured against the split form (attention + update launch): 1024 units of 2048 tokens, d = 128
-// bf16: 101 + 20 -> 102 us per step; 16384 of 1024: 804 + 144 -> 820; 432 of 1337, d = 64:
+// bf16: 101 + 20 -> 102 us per step; 16384 of 1024: 835 -> 801 in this form; 432 of 1337, d = 64:
 // 15 + 14 -> 18; 4 of 128, float32: 12 -> 5.9. The logits of the units that keep scores stay in LDS for the update
 // (through memory their stores held up the merge's barrier and their loads the update), and the new token falls to
 // a wave that ends early (the last one, behind its rows, kept the others waiting for 7 us): with both, and fewer barriers

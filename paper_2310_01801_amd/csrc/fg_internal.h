@@ -79,7 +79,8 @@ inline int fg_decode_chunk(int prompt_len, int max_new_tokens) {
 constexpr int FG_UNIT_TOKENS = 4608, FG_UNIT_TOKENS_256 = 2048, FG_UPDATE_TOKENS_256 = 3072;
 
 // Form of the decode step: 0 = split-KV attention and a second launch for merge and update; else one
-// workgroup of that many threads per unit. Measured per step, split / per unit:
+// workgroup of that many threads per unit. Measured per step, split / per unit (before the logits of the per-unit form stayed in
+// LDS, which took 4 to 8 % off it: 1024 of 2048 tokens 102 us, 16384 of 1024 801):
 //   1024 units of 2048 tokens, d = 128 bf16        120 / 112 us     (256 threads: 118)
 //   4096 of 4096                                   831 / 790        (256 threads: 799)
 //   16384 of 1024, 256 threads                     948 / 845        (512 threads: 857)
@@ -208,19 +209,21 @@ constexpr size_t FG_STATIC_SCRATCH = (size_t)32 << 20;
 
 // Room for the partial sums [parts, U, n] of the one-pass kernels, two doubles each. The rules below choose within it by the
 // shape alone, and a context's workspace as well as the static scratch always hold it, so that a shape gives
-// the same bits with any cache pool and from either entry point. (Most chosen: 60 MiB, 1920 units of 1024 tokens in two parts.)
+// the same bits with any cache pool and from either entry point. (Most chosen: all of it, 2048 units of 1792 tokens in two parts.)
 constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 
 // Both bf16 sweeps in one pass (profile_once.hip): waves of a workgroup and workgroups per unit, 0 waves where the two
 // sweeps serve. A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU. Measured,
-// two sweeps / one pass in us (random inputs, launches back to back; in brackets the workgroups per unit):
+// two sweeps / one pass in us (random inputs, launches back to back; in brackets the workgroups per unit; the one pass
+// before its shifts came from the rows before, which took another 5 to 15 % off it, 4096 units of 1024 tokens 1154, so
+// every line still lies on its safe side):
 //   d = 128    4096 units of 1024 tokens 1586 / 1324 (1), of 512 542 / 401 (1), 300 of 1000 152 / 110 (4), 64 of 1000 77 / 25
 //              (4), 8 of 1000 22 / 15 (10), 128 of 512 49 / 19 (2), 32 of 333 16 / 10 (6), 64 of 64 7.2 / 5.4 (1)
 //   d = 64     4096 of 1024 1116 / 1073 (1), 64 of 1000 49 / 23 (4), 32 of 400 13.5 / 10.2 (7), 4 of 1000 15.7 / 14.5 (10)
 //   G = 4      d = 128: 32 of 512 48 / 24 (8), 200 of 333 107 / 55 (5), 64 of 64 10.4 / 12.4; d = 64: 16 of 200 13.7 / 16.3, 8 of
 //              333 17.5 / 18.8; G = 8: 300 of 1000 973 / 787 (4), 128 of 64 16.8 / 23.3, d = 64: 32 of 256 25.4 / 27.9
 // Parts, at most ten: the more of the places are taken in the last round the better, less 5 % for every further
-// part's prologue and sums; an extra launch adds the sums, so a single pair of blocks stays whole. The parts of a unit run
+// part's prologue and sums, which the selection adds; a single pair of blocks stays whole. The parts of a unit run
 // on one XCD and units are dealt out over the eight, so the fullest XCD (an eighth of the units, rounded up) counts the
 // rounds: 83 units of 519 tokens, d = 64, G = 16, in three parts each put 33 workgroups on 32 CUs (261), in five 185; two
 // sweeps 194. Many units fill the places whole, and only parts with work enough gain (one part / several: 658 of 159, d = 64,
