@@ -32,16 +32,17 @@ TIMING_SAMPLE = 8         # decode steps between two timed ones (an event record
 # a timed run. "sweeps" = both sweeps together, "decode_attn" = per launch over the first 16
 # decode steps.
 MEASURED_TRAFFIC = {
-    # (FETCH_SIZE KiB x 2 + WRITE_SIZE KiB) x 1024 of sweep 1 + sweep 2; of the decode attention launch
-    # (fg_decode_partial_kernel at llama65b_b2, else fg_decode_unit_kernel, which holds the update too)
-    "llama65b_b2": {"sweeps": (26387765 * 2 + 655360 + 32396615 * 2 + 2129920) * 1024.0,
-                    "decode_attn": (9838007 * 2 + 274807) * 1024.0},
-    "llama7b_b1": {"sweeps": (718457 * 2 + 16384 + 734949 * 2 + 53248) * 1024.0,
-                   "decode_attn": (269828 * 2 + 11049) * 1024.0},
-    "llama7b_b16": {"sweeps": (12024641 * 2 + 262144) * 1024.0,   # one pass
-                    "decode_attn": (2147152 * 2 + 96773) * 1024.0},
-    "llama13b_b4": {"sweeps": (8411611 * 2 + 204800 + 9088354 * 2 + 665600) * 1024.0,
-                    "decode_attn": (4355092 * 2 + 116486) * 1024.0},
+    # (FETCH_SIZE KiB x 2 + WRITE_SIZE KiB) x 1024 of the profiling kernels (sweep 1, one pass and its part sums, sweep 2; at
+    # llama7b_b16 the one pass); of the decode attention launch (fg_decode_partial_kernel at llama65b_b2, else
+    # fg_decode_unit_kernel, which holds the update too)
+    "llama65b_b2": {"sweeps": (26303810 * 2 + 573440 + 87079825 * 2 + 778240 + 26806676 * 2 + 1863680) * 1024.0,
+                    "decode_attn": (9838040 * 2 + 274802) * 1024.0},
+    "llama7b_b1": {"sweeps": (353872 * 2 + 8192 + 453669 * 2 + 49152 + 16396 * 2 + 16384 + 369847 * 2 + 26624) * 1024.0,
+                   "decode_attn": (267632 * 2 + 5737) * 1024.0},
+    "llama7b_b16": {"sweeps": (7141986 * 2 + 262144) * 1024.0,
+                    "decode_attn": (2130738 * 2 + 54638) * 1024.0},
+    "llama13b_b4": {"sweeps": (6682646 * 2 + 153600 + 25073054 * 2 + 281600 + 6864444 * 2 + 499200) * 1024.0,
+                    "decode_attn": (4329658 * 2 + 57598) * 1024.0},
 }
 
 BASELINE_INDEX = {"tiny": 0, "llama7b_b1": 1, "llama7b_b16": 2, "llama13b_b4": 3, "llama65b_b2": 4}

@@ -290,7 +290,7 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
 // Longer bf16 prompts: workgroups per unit that take the first 1024 columns of all rows in one pass, 0 where the two sweeps
 // serve the whole prompt. The triangle of rows and columns from 1024 on stays with the two sweeps: the first one leaves its
 // rows' sums, which join the one pass, and the second one takes the rows' normalisers from there. Two sweeps / so, in us (in
-// brackets the workgroups per unit):
+// brackets the workgroups per unit of that run; for some the rule, fitted afterwards, picks more, 256 of 3000 one less):
 //   d = 128    1024 units of 2048 tokens 1330 / 1159 (1), of 1337 688 / 554 (1), 256 of 3000 666 / 617 (4), 1024 of 4096 4654 / 4090 (3),
 //              512 of 8192 8773 / 8430 (2), 64 of 1060 90 / 42 (4), 32 of 2048 130 / 85 (8), 16 of 2048 88 / 60 (16), 64 of 4096 343 / 343 (4)
 //   d = 64     1024 of 2048 868 / 811 (1), 432 of 1337 254 / 206 (1), 700 of 2048 613 / 612 (1), 32 of 3000 142 / 120 (8), 180 of 2048 201 / 200 (4)
