@@ -186,6 +186,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       const int r0 = b * kRows;
       const int jl = min(2 * b + 1, (n - 1) / kFrag);   // last column fragment
       const int cnt = jl >= wave ? min((jl - wave) / NW + 1, kSlots) : 0;   // fragments of this wave
+      // (read before a barrier of the block: behind the last one the next block's load_q writes there)
       auto beyond = [&]() { return LONG && r0 >= COLS && r0 + lane < n ? s_x[buf][lane] : make_float2(FG_NEG_BIG, 0.f); };
       if (i > 0) load_q(block(i - 1), buf ^ 1);
       f32x16 e[kSlots][2];
@@ -329,13 +330,11 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       if (!again) {
         sweep(std::integral_constant<int, 0>());
         put_sums();
+        const float2 x = beyond();
         fg_barrier();
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
-        if (LONG) {
-          const float2 x = beyond();
-          L = fma((double)x.y, (double)fg_exp2(x.x - M), L);
-        }
+        if (LONG) L = fma((double)x.y, (double)fg_exp2(x.x - M), L);
         again = __any(r0 + lane < n && !(L >= kLeastSum && L <= kMostSum));   // the same in all waves
         if (again) fg_barrier();   // s_l has been read
       }
@@ -355,9 +354,9 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         put_sums();
         const float own = lh ? m_run[1] : m_run[0];
         s_m[buf][wave][lane] = own;
+        const float2 x = beyond();
         fg_barrier();
         float mv[NW];
-        const float2 x = beyond();
         M = x.x;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
