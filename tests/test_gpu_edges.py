@@ -558,10 +558,14 @@ def test_read_back_by_several_workgroups(heads, n):
     assert torch.equal(keys, run.K[unit, pos]) and torch.equal(values, run.V[unit, pos])
 
 
-# Nothing of what the workspace held before is read, rows behind the end of a unit in a partly filled tile
-# included: a workspace of NaN patterns gives what a cleared one gives
+# Nothing of what the workspace held before counts, rows behind the end of a unit or of a head in a partly filled
+# tile included: a workspace of NaN patterns gives what a cleared one gives. The last six take the first 1024 columns in one
+# pass, which leaves the statistics of the first 1024 rows unwritten, and the triangle behind them in the split stream with 32
+# (two) and 64 owners, in blocks and in pairs (two).
 @pytest.mark.parametrize("U,n,d,dtype,G", [(3, 5, 64, "bf16", 1), (3, 37, 128, "f32", 1), (2, 21, 64, "bf16", 3), (2, 1100, 128, "bf16", 2),
-                                           (40, 333, 128, "bf16", 1), (2, 5000, 64, "bf16", 1)])
+                                           (40, 333, 128, "bf16", 1), (2, 5000, 64, "bf16", 1),
+                                           (16, 1100, 64, "bf16", 2), (13, 1500, 128, "bf16", 4), (64, 1313, 64, "bf16", 2),
+                                           (300, 1313, 64, "bf16", 2), (200, 1999, 64, "bf16", 3), (128, 1999, 128, "bf16", 2)])
 def test_previous_contents_of_the_workspace_are_not_read(U, n, d, dtype, G):
     w = W["llama7b_b1"].scaled(name="stale", layers=1, heads=U, batch=1, prompt_len=n, steps=3, head_dim=d, dtype=dtype, seed=n)
     seen = []

@@ -49,6 +49,9 @@ def test_static_scratch_profile_twice_second_call_smaller():
     _both(W["tiny"])
     _both(W["llama7b_b1"].scaled(name="static_gqa", layers=1, heads=4, batch=1, prompt_len=200, steps=2, seed=303),
           group_size=2)
+    # grouped heads of a longer prompt: the row statistics of the first 1024 rows are left unwritten
+    _both(W["llama7b_b1"].scaled(name="static_long", layers=1, heads=13, batch=1, prompt_len=1500, steps=2, seed=304),
+          group_size=4)
 
 
 def test_static_scratch_rejects_what_does_not_fit():
