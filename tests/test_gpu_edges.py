@@ -304,12 +304,15 @@ def test_long_prompts_in_one_pass_and_two_sweeps(heads, n, d, G):
         H.log_report(f"long pass U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
-# Row masses of the one-pass form: as below, 10^5 rows, so within 4 x 1.7e-8 / 300; a shift that moves with every
-# tile and a hardware exponential for every rescaling of it would show as 1e-9 and more.
+# Row masses of the one-pass form. A float32 normaliser is off by up to 2^-24, 2.5e-8 in the root mean square over its
+# mantissas; with the rounding of a row's partial sums and of its probabilities, all without a preference, 3.5e-8 a row (40 runs of
+# 21312 rows scatter by 2.4e-10, with running maxima as with shifts from the rows before). Over 16 runs of that size the mean
+# is within 4 x 3.5e-8 / 584; over four it was not, for no fault. A shift that moves with every tile and a hardware
+# exponential for every rescaling of it would show as 1e-9 and more.
 @pytest.mark.parametrize("U,n,d", [(64, 333, 128), (300, 400, 64), (128, 1000, 64)])
 def test_one_pass_row_masses_have_no_bias(U, n, d):
     masses = []
-    for seed in range(4):
+    for seed in range(16):
         gen = torch.Generator(device="cuda:0").manual_seed(seed)
         Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
         cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
@@ -317,7 +320,7 @@ def test_one_pass_row_masses_have_no_bias(U, n, d):
         _, recovery, _ = fg.fastgen_profile(Q, K, cls)
         masses.append(float(recovery[:, 0].mean()) - 1.0)
         fg.close()
-    assert abs(sum(masses) / 4) < 2.3e-10, masses
+    assert abs(sum(masses) / 16) < 2.3e-10, masses
 
 
 # Logits far beyond what a float32 exponential holds without a shift: a key that outweighs all others by 2^600
