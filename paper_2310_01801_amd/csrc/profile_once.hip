@@ -5,7 +5,7 @@
 // the blocks of each, dealt from the heavy end. The waves hold the whole block's exponentials in registers: the
 // causal columns are dealt out in fragments of 32, fragment j to wave j mod NW, at most four per wave, so
 // 4 * 32 * NW columns are the longest prompt. A value 2^(c q.k - m) is made once, with a shift m of its row that all
-// waves share: what the sum of the row 64 before came to, as a whole number. No maximum is looked for, so a
+// waves share: from what the sum of the row 64 before came to, a whole number. No maximum is looked for, so a
 // fragment's exponentials start with its last matrix instruction; whether the shift fits shows in the row's sum, and a
 // block where one does not (or a workgroup's only block, which has none before it) is done again with each wave's own
 // maximum as its shift. The waves exchange the sums of the 64 rows through LDS, and the column sums take
@@ -23,8 +23,10 @@
 // matrix instructions (512 alone), 885 of exponentials, 780 of column sums, and per block 680 for the exchange and 1500 at
 // its barrier, where waves with a fragment less wait. 4096 units of 1024 tokens, d = 128, 1270 us with running maxima
 // and all keys through LDS, 1154 now (two sweeps 1586); of 512 385 -> 346, of 500, d = 64, 291 -> 254, 1024 of 1000, d =
-// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Error of the column sums against float64 as before (1.67e-8 / 1.69e-8,
-// inside the band 2.69e-8 / 2.72e-8, 1024 units of 1000 tokens); without a shift 4 % more. Tried without gain: all keys in registers with 32
+// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Error of the column sums against float64, with
+// running maxima / so: 512 units of 1000 tokens 1.28e-8 / 1.19e-8, with queries three times as large 8.16e-8 / 8.15e-8, a tenth
+// 8.0e-9 / 6.4e-9; rows 6 to 24 powers of two apart and 1000 units of 512 in d = 64 alike. (With the row sum itself for a shift 1.10, 1.01 and 1.19 times the
+// first; a third float64 step in the column sums, 1 to 3 % of the time, makes up for the rest.) Tried without gain: all keys in registers with 32
 // rows a block (1325) or 16 and the exchange under the next rows' products (1810), higher priority for half of the
 // waves or for the matrix instructions (1115 to 1186 where 1114 without), keys for the registers straight from memory
 // (1204 where 1154, and short prompts 0.6 us more), the first two fragments one by one in a first block (8 spills), the
@@ -39,9 +41,11 @@ namespace {
 constexpr int kFrag = 32;    // columns of a fragment
 constexpr int kRows = 64;    // query rows of a block: two fragments
 constexpr int kSlots = 4;    // fragments of a wave in one block: 128 registers
-// Row sums in which every term that counts is a normal number and none overflows. A head whose rows differ by more from one
-// block to the next, 20 and 100 powers of two, goes through every block twice.
-constexpr double kLeastSum = 0x1p-20, kMostSum = 0x1p100;
+// Sums that a row may come to under the shift of the row 64 before, whose shift would have left the square root of its
+// length (up to 2^6.5). An exponential's argument is rounded at its own size, beyond 16 by 2^-20 and more, which rows with a
+// shift of their own do not pay (300 units of 500 tokens, exact products, rows 24 powers of two above the ones 64 before:
+// accepted, column sums are 3.5e-7 off float64; redone, 4.2e-8).
+constexpr double kLeastSum = 0x1p-8, kMostSum = 0x1p14;
 
 // 16 bytes per lane from memory straight into LDS, to `lds` + 16 * lane. Written out, because behind the builtin the
 // compiler waits for the data at the next read of any LDS; here the waits below do, which every reader stands behind.
@@ -82,9 +86,10 @@ __device__ __forceinline__ void fg_swap_halves(double& a, double& b) {
 
 // 16 values per lane (columns) summed over the 32 lanes of its half (rows), in a fixed order. Every step
 // halves the values a lane still carries: it ends with the sum of column number b4 b3 b2 b1 (bits of the lane).
-// The last two steps run in float64: they would otherwise hold three quarters of the rounding of a 64-row sum.
+// The last three steps run in float64: they would otherwise hold nine tenths of the rounding of a 64-row sum.
 __device__ __forceinline__ double fg_cols_over_rows(const float (&t)[16], int lane) {
-  float a[8], b[4], c[2];
+  float a[8], b[4];
+  double c[2];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(t[i]), __float_as_uint(t[i + 8]), false, false);
@@ -94,8 +99,8 @@ __device__ __forceinline__ double fg_cols_over_rows(const float (&t)[16], int la
 #pragma unroll
   for (int i = 0; i < 4; ++i) b[i] = (b3 ? a[i + 4] : a[i]) + fg_dpp<FG_DPP_MIRROR>(b3 ? a[i] : a[i + 4]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) c[i] = (b2 ? b[i + 2] : b[i]) + fg_dpp<FG_DPP_HALF_MIRROR>(b2 ? b[i] : b[i + 2]);
-  const double d = (double)(b1 ? c[1] : c[0]) + (double)fg_dpp<FG_DPP_XOR2>(b1 ? c[0] : c[1]);
+  for (int i = 0; i < 2; ++i) c[i] = (double)(b2 ? b[i + 2] : b[i]) + (double)fg_dpp<FG_DPP_HALF_MIRROR>(b2 ? b[i] : b[i + 2]);
+  const double d = (b1 ? c[1] : c[0]) + fg_dpp_f64<FG_DPP_XOR2>(b1 ? c[0] : c[1]);
   return d + fg_dpp_f64<FG_DPP_XOR1>(d);
 }
 
@@ -180,7 +185,9 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       if (most > HELD) load_k(HELD, 0);
       if (most > 3 && HELD == 2) load_k(3, 1);
     }
-    float m_run[2] = {0.f, 0.f};   // the shifts of this lane's rows, the same in all waves
+    // the shifts of this lane's rows, the same in all waves; at first what products of 0 would leave the block's first row
+    const float first = (float)((31 - __builtin_clz(block(mine - 1) * kRows + 1)) / 2);
+    float m_run[2] = {first, first};
     for (int i = mine - 1; i >= 0; --i, buf ^= 1) {
       const int b = block(i);
       const int r0 = b * kRows;
@@ -368,8 +375,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
         share = fg_exp2(own - M);
       }
-      if (i > 0) {   // the shifts of the next block: what these rows' sums came to (its rows past the end stay at products of 0)
-        float ma = block(i - 1) * kRows + lane < n ? M + rintf(__builtin_amdgcn_logf((float)L)) : 0.f, mb = ma;
+      // The shifts of the next block: where these rows' sums would have been the square root of their length. What counts in
+      // a row then lies on both sides of 0, be the row even (its terms would lie at -log2 n under the sum itself) or held
+      // by few columns. (Its rows past the end stay at products of 0.)
+      if (i > 0) {
+        const float sum = (float)L * __builtin_amdgcn_rsqf((float)(r0 + lane + 1));
+        float ma = block(i - 1) * kRows + lane < n ? M + rintf(__builtin_amdgcn_logf(sum)) : 0.f, mb = ma;
         fg_swap_halves(ma, mb);
         m_run[0] = ma;
         m_run[1] = mb;

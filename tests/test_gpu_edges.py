@@ -366,6 +366,36 @@ def test_one_pass_with_rows_far_from_the_ones_before(U, n, d, G, rows):
     assert float((recovery[some, 0].cpu() - want).abs().max()) < 3.6e-5
 
 
+# Rows that lie a given number of powers of two above the rows 64 before, with products that are exact in float32 (an offset
+# per block of rows and a number per column), against float64 with the factor that the device takes. What is left
+# is the rounding of the exponential's argument at its own size: within 8 where a row's maximum is its shift (logits within 4
+# of their middle), uniformly 2^-22, 9.5e-8 of the value in the root mean square; within 16 where a sum of up to 2^14 is accepted, twice that;
+# the hardware exponential, the normaliser and the sums add less than 5e-8. A column's relative error so stays
+# below 1.1e-7 (redone) and 2e-7 (accepted) in the root mean square. Sums of up to 2^100, accepted, made 1.2e-7 to 3.5e-7.
+@pytest.mark.parametrize("U,n,d", [(64, 1000, 128), (300, 1024, 64), (300, 500, 128), (64, 1500, 128), (300, 1100, 64)])
+@pytest.mark.parametrize("step", [64, 24, 6, -6, -24, -64])
+def test_one_pass_keeps_its_precision_where_rows_lie_apart(U, n, d, step):
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    Q, K = (torch.zeros(U, n, d, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    c = torch.tensor(1.0 / math.sqrt(d), dtype=torch.float32) * torch.tensor(math.log2(math.e), dtype=torch.float32)
+    block = torch.arange(n, device="cuda:0") // 64
+    Q[:, :, 0] = block.float() if step > 0 else block.max() - block.float()   # times K's: raw products of a step
+    K[:, :, 0] = round(abs(step) / float(c))
+    K[:, :, 1] = torch.randint(-120, 121, (U, n), generator=gen, device="cuda:0") / (4.0 if d == 128 else 8.0)
+    Q[:, :, 1] = 1.0
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 1.0, 0.5, forced_policy=3))
+    fg.fastgen_profile(Q, K, cls)
+    fg.fastgen_compact(K, K)
+    got = fg.fastgen_export_state()["scores"][:U * n].view(U, n).cpu()
+    fg.close()
+    x = torch.matmul(Q[:8].double().cpu(), K[:8].double().cpu().transpose(1, 2).contiguous()) * float(c) * math.log(2.0)
+    want = torch.softmax(x.masked_fill(torch.ones(n, n).triu(1).bool(), -math.inf), dim=2).sum(1)
+    error = ((got[:8] - want) / want).pow(2).mean().sqrt()
+    print(f"rows {step} apart, U={U} n={n} d={d}: {float(error):.2e}")
+    assert float(error) < (1.1e-7 if abs(step) > 10 else 2e-7)
+
+
 # grouped heads, per-unit step (vector ALU for two heads and float32, matrix cores for three to eight bf16 heads) and
 # split-KV for more heads, probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
