@@ -7,8 +7,9 @@
 // 4 * 32 * NW columns are the longest prompt. A value 2^(c q.k - m) is made once, with a shift m of its row that all
 // waves share: from what the sum of the row 64 before came to, a whole number. No maximum is looked for, so a
 // fragment's exponentials start with its last matrix instruction; whether the shift fits shows in the row's sum, and a
-// block where one does not (or a workgroup's only block, which has none before it) is done again with each wave's own
-// maximum as its shift. The waves exchange the sums of the 64 rows through LDS, and the column sums take
+// block where one does not is done again with each wave's own maximum as its shift. The next block then starts with its own
+// maxima if the shifts from before would not have fitted here either, and so does a workgroup's only block, which has
+// none before it. The waves exchange the sums of the 64 rows through LDS, and the column sums take
 // value / sum from the registers. One contraction and one exponential per score instead of two, and no row statistics
 // in memory. Workgroups that share a unit leave partial column sums, which are added in order.
 //
@@ -23,7 +24,8 @@
 // matrix instructions (512 alone), 885 of exponentials, 780 of column sums, and per block 680 for the exchange and 1500 at
 // its barrier, where waves with a fragment less wait. 4096 units of 1024 tokens, d = 128, 1270 us with running maxima
 // and all keys through LDS, 1154 now (two sweeps 1586); of 512 385 -> 346, of 500, d = 64, 291 -> 254, 1024 of 1000, d =
-// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Error of the column sums against float64, with
+// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Heads whose rows never fit (60 powers of two up or down every 40 rows), with
+// running maxima / so: 1024 of 1000 322 / 339, d = 64, 700 of 1000 191 / 207 (each block twice: 443 and 266), 256 of 2048 354 / 325. Error of the column sums against float64, with
 // running maxima / so: 512 units of 1000 tokens 1.28e-8 / 1.19e-8, with queries three times as large 8.16e-8 / 8.15e-8, a tenth
 // 8.0e-9 / 6.4e-9; rows 6 to 24 powers of two apart and 1000 units of 512 in d = 64 alike. (With the row sum itself for a shift 1.10, 1.01 and 1.19 times the
 // first; a third float64 step in the column sums, 1 to 3 % of the time, makes up for the rest.) Tried without gain: all keys in registers with 32
@@ -46,6 +48,7 @@ constexpr int kSlots = 4;    // fragments of a wave in one block: 128 registers
 // shift of their own do not pay (300 units of 500 tokens, exact products, rows 24 powers of two above the ones 64 before:
 // accepted, column sums are 3.5e-7 off float64; redone, 4.2e-8).
 constexpr double kLeastSum = 0x1p-8, kMostSum = 0x1p14;
+__device__ __forceinline__ bool fg_fits(double sum) { return sum >= kLeastSum && sum <= kMostSum; }
 
 // 16 bytes per lane from memory straight into LDS, to `lds` + 16 * lane. Written out, because behind the builtin the
 // compiler waits for the data at the next read of any LDS; here the waits below do, which every reader stands behind.
@@ -188,6 +191,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
     // the shifts of this lane's rows, the same in all waves; at first what products of 0 would leave the block's first row
     const float first = (float)((31 - __builtin_clz(block(mine - 1) * kRows + 1)) / 2);
     float m_run[2] = {first, first};
+    bool own = mine == 1;          // the next block starts with each wave's own maxima
     for (int i = mine - 1; i >= 0; --i, buf ^= 1) {
       const int b = block(i);
       const int r0 = b * kRows;
@@ -209,14 +213,17 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const bool ok = !diagonal || fg_acc_item(i) <= lim;
-            if (MODE == 1) m_run[f] = fmaxf(m_run[f], ok ? ac[i] * c : FG_NEG_BIG);
-            else {
+            if (MODE == 1) {   // (c > 0: the largest product gives the largest logit)
+              const float x = ok ? ac[i] : FG_NEG_BIG;
+              s[i & 3] = i < 4 ? x : fmaxf(s[i & 3], x);
+            } else {
               const float v = fg_exp2(fmaf(ac[i], c, -m_run[f]));
               ac[i] = ok ? v : 0.f;
               s[i & 3] = i < 4 ? ac[i] : s[i & 3] + ac[i];
             }
           }
-          if (MODE == 0) l_run[f] += (double)((s[0] + s[1]) + (s[2] + s[3]));
+          if (MODE == 1) m_run[f] = fmaxf(m_run[f], fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c);
+          else l_run[f] += (double)((s[0] + s[1]) + (s[2] + s[3]));
         };
         const int j = wave + NW * at[p];
         if (j < 2 * b) {
@@ -331,9 +338,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         s_l[buf][wave][lane] = la + lb;
       };
       double L = 0.0;
-      float M = lh ? m_run[1] : m_run[0], share = 1.f;
+      const float given = lh ? m_run[1] : m_run[0];
+      float M = given, share = 1.f;
       l_run[0] = l_run[1] = 0.0;
-      bool again = mine == 1;
+      bool again = own;
       if (!again) {
         sweep(std::integral_constant<int, 0>());
         put_sums();
@@ -342,10 +350,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
         if (LONG) L = fma((double)x.y, (double)fg_exp2(x.x - M), L);
-        again = __any(r0 + lane < n && !(L >= kLeastSum && L <= kMostSum));   // the same in all waves
+        again = __any(r0 + lane < n && !fg_fits(L));   // the same in all waves
         if (again) fg_barrier();   // s_l has been read
       }
-      if (again) {   // the shifts do not fit, or there are none: this wave's own
+      if (again) {   // the shifts do not fit, or hardly will, or there are none: this wave's own
         m_run[0] = m_run[1] = FG_NEG_BIG;
         sweep(std::integral_constant<int, 1>());
 #pragma unroll
@@ -359,8 +367,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         for (int p = 0; p < kSlots; ++p)
           if (active(p)) rows(std::integral_constant<int, 0>(), p);
         put_sums();
-        const float own = lh ? m_run[1] : m_run[0];
-        s_m[buf][wave][lane] = own;
+        const float wave_m = lh ? m_run[1] : m_run[0];
+        s_m[buf][wave][lane] = wave_m;
         const float2 x = beyond();
         fg_barrier();
         float mv[NW];
@@ -373,7 +381,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         L = LONG ? (double)x.y * (double)fg_exp2(x.x - M) : 0.0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
-        share = fg_exp2(own - M);
+        share = fg_exp2(wave_m - M);
+        own = mine == 1 || __any(r0 + lane < n && !fg_fits(L * (double)fg_exp2(M - given)));   // as far as this block tells
       }
       // The shifts of the next block: where these rows' sums would have been the square root of their length. What counts in
       // a row then lies on both sides of 0, be the row even (its terms would lie at -log2 n under the sum itself) or held

@@ -396,6 +396,34 @@ def test_one_pass_keeps_its_precision_where_rows_lie_apart(U, n, d, step):
     assert float(error) < (1.1e-7 if abs(step) > 10 else 2e-7)
 
 
+# A head none of whose rows fit the shifts of the rows 64 before costs no more than the maxima of its rows: each block is
+# contracted once. Going through every block twice took 1.5 times an ordinary head's time at d = 128 and 1.6 at 64, so 1.15.
+@pytest.mark.parametrize("U,n,d", [(700, 1000, 64), (1024, 1000, 128)])
+def test_one_pass_of_rows_that_never_fit_costs_their_maxima(U, n, d):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + d)
+    Q, K = (torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
+    cfg = binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3)
+    space = torch.empty(binding.fastgen_workspace_bytes(cfg), dtype=torch.uint8, device="cuda:0")
+    K[:, :, 0] = 8.0
+    apart = torch.where((torch.arange(n, device="cuda:0") // 40) % 2 == 0, 32.0, -32.0).bfloat16()
+    times = {0: [], 1: []}
+    for _ in range(12):
+        for jump in (0, 1):   # in turn: the clock is shared
+            Q[:, :, 0] = apart * jump
+            fg = binding.FastGen(cfg, "cuda:0", workspace=space)
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            fg.fastgen_profile(Q, K, cls)
+            end.record()
+            end.synchronize()
+            times[jump].append(start.elapsed_time(end))
+            fg.close()
+    ratio = sorted(times[1])[4] / sorted(times[0])[4]
+    print(f"rows that never fit, U={U} n={n} d={d}: {ratio:.2f}")
+    assert ratio < 1.35
+
+
 # grouped heads, per-unit step (vector ALU for two heads and float32, matrix cores for three to eight bf16 heads) and
 # split-KV for more heads, probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
