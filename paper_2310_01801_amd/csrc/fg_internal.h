@@ -215,9 +215,9 @@ constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 // Both bf16 sweeps in one pass (profile_once.hip): waves of a workgroup and workgroups per unit, 0 waves where the two
 // sweeps serve. A workgroup of 8 waves holds 1024 columns and fills a CU, one of 4 waves 512 and half a CU. Measured,
 // two sweeps / one pass in us (random inputs, launches back to back; in brackets the workgroups per unit; the one pass
-// before its shifts came from the rows before, which took another 5 to 15 % off it, 4096 units of 1024 tokens 1154, so
-// every line still lies on its safe side; a single block, up to 64 tokens, takes 0.4 to 0.6 us more than it did,
-// less than the 1.8 that one pass gains there):
+// before its shifts came from the rows before, which took another 5 to 15 % off it, 4096 units of 1024 tokens 1154, and before a
+// single block, up to 64 tokens, had a kernel of its own, 1 us less and up to 45 %: every line lies on the side of the two sweeps,
+// which keep shapes near it that one pass may serve faster by now):
 //   d = 128    4096 units of 1024 tokens 1586 / 1324 (1), of 512 542 / 401 (1), 300 of 1000 152 / 110 (4), 64 of 1000 77 / 25
 //              (4), 8 of 1000 22 / 15 (10), 128 of 512 49 / 19 (2), 32 of 333 16 / 10 (6), 64 of 64 7.2 / 5.4 (1)
 //   d = 64     4096 of 1024 1116 / 1073 (1), 64 of 1000 49 / 23 (4), 32 of 400 13.5 / 10.2 (7), 4 of 1000 15.7 / 14.5 (10)

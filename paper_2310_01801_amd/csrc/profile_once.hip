@@ -438,6 +438,123 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   }
 }
 
+// Prompts of a single block, up to 64 tokens: three waves take a tile of 32 rows and 32 columns each (the fourth only loads), with
+// the tile's own row maxima for shifts. Bound: latency, so what counts is the one chain of load, matrix instructions, maxima,
+// exponentials, exchange and column sums; in the kernel above it held the keys' way into registers, both row fragments one after
+// the other and a second pass over the products. A call, with running maxima in one wave per 32 columns / in the kernel above / so:
+// 4 units of 64 tokens, d = 128, 11.1 / 11.7 / 10.2 us, 4096 59.8 / 60.0 / 46.5, 4096 of 33, d = 64, 53 / 55 / 33, 300 of 64, G = 5,
+// 26.6 / 27.3 / 19.2, 16000 of 64, d = 64, 200 / 202 / 113 (76 registers and 53 KB of LDS leave three to a CU).
+template <int D>
+__global__ __launch_bounds__(256) void fg_profile_block_kernel(
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, double* __restrict__ colsum, double* __restrict__ bandcol,
+    int n, int w, float c, int G) {
+  constexpr int KK = D / 16, RB = D * 2, PPR = D / 8, RPL = 1024 / RB;
+  constexpr int LOADS = kRows * RB / 1024 / 4;   // per wave and matrix
+  __shared__ __attribute__((aligned(16))) unsigned char s_q[2][kRows * RB];   // laid out as above
+  __shared__ __attribute__((aligned(16))) unsigned char s_k[kRows * RB];
+  __shared__ double s_l[2][4][32], s_sum[4][2][32];
+  __shared__ float s_m[2][4][32];
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 31, lh = lane >> 5;
+  const int lrow = lane / PPR, lplace = lane % PPR;
+  auto load = [&](const __bf16* from, unsigned char* to) {   // rows past the end read as zeros
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(from), 0, n * RB, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int at = wave * LOADS + i;
+      fg_load_lds16(rsrc, to + at * 1024, lrow * RB + ((lplace ^ lrow ^ (at * RPL)) & (PPR - 1)) * 16, at * 1024);
+    }
+  };
+  const int tr = wave > 0, tc = wave == 2;   // the wave's tile: (0, 0), (1, 0), (1, 1)
+  const bool active = wave < 3 && tr * 32 < n;
+  const int frag = ln * RB + ((lh ^ ln) & (PPR - 1)) * 16;
+  const int row = tr * 32 + ln, d0 = (tr - tc) * 32;
+  const bool inside = d0 + 31 < w, outside = d0 - 31 >= w;
+  double sum = 0.0;   // of column tc * 32 + item; odd lanes carry the band
+  load(Q + (size_t)unit * G * n * D, s_q[0]);
+  load(K + (size_t)unit * n * D, s_k);
+  fg_barrier();
+  for (int h = 0, buf = 0; h < G; ++h, buf ^= 1) {
+    if (h + 1 < G) load(Q + ((size_t)unit * G + h + 1) * n * D, s_q[buf ^ 1]);   // read last before the barrier of the head before
+    f32x16 ac;
+    float m = FG_NEG_BIG;
+    double l = 0.0;
+    if (active) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ac[i] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&s_k[tc * 32 * RB + (frag ^ (32 * kk))]);
+        const bf16x8 q = *reinterpret_cast<const bf16x8*>(&s_q[buf][tr * 32 * RB + (frag ^ (32 * kk))]);
+        ac = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q, ac, 0, 0, 0);
+      }
+      const int lim = tr == tc ? ln - lh * 4 : 32;   // column <= row
+      float s[4];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float x = fg_acc_item(i) <= lim ? ac[i] : FG_NEG_BIG;
+        s[i & 3] = i < 4 ? x : fmaxf(s[i & 3], x);
+      }
+      m = fmaxf(FG_NEG_BIG, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c);
+      float o = m;
+      fg_swap_halves(m, o);
+      m = rintf(fmaxf(m, o));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float e = fg_exp2(fmaf(ac[i], c, -m));
+        ac[i] = fg_acc_item(i) <= lim ? e : 0.f;
+        s[i & 3] = i < 4 ? ac[i] : s[i & 3] + ac[i];
+      }
+      l = (double)((s[0] + s[1]) + (s[2] + s[3]));
+      double lo = l;
+      fg_swap_halves(l, lo);
+      l += lo;
+      if (lh == 0) { s_m[buf][wave][ln] = m; s_l[buf][wave][ln] = l; }
+    }
+    fg_barrier();
+    if (active) {
+      float M = m;
+      double L = l;
+      if (tr) {   // the row's other tile
+        const float mo = s_m[buf][3 - wave][ln];
+        M = fmaxf(m, mo);
+        L = fma(s_l[buf][3 - wave][ln], (double)fg_exp2(mo - M), l * (double)fg_exp2(m - M));
+      }
+      double inv = __builtin_amdgcn_rcp(L);
+      inv = fma(inv, fma(-L, inv, 1.0), inv);
+      const float f = row < n ? (float)inv * fg_exp2(m - M) : 0.f;   // rows past the end count nothing
+      float t[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t[i] = ac[i] * f;
+      const double v = fg_cols_over_rows(t, lane);
+      if (!(lane & 1) || inside) sum += v;
+      if (!inside && !outside) {
+        const int o0 = d0 + ln - lh * 4 - w;   // in the band: row - column < w, so the item's offset is above o0
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i] = fg_acc_item(i) > o0 ? t[i] : 0.f;
+        const double vb = fg_cols_over_rows(t, lane);
+        if (lane & 1) sum += vb;
+      }
+    }
+  }
+  const int item = ((lane >> 4) & 1) * 16 + ((lane >> 3) & 1) * 8 + lh * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
+  s_sum[wave][lane & 1][item] = sum;   // 0 where the wave has no tile
+  __syncthreads();
+  const int which = tid >> 6, col = tid & 63;
+  if (which < 2 && col < n) {
+    const int o = col & 31;
+    (which ? bandcol : colsum)[(size_t)unit * n + col] = col < 32 ? s_sum[0][which][o] + s_sum[1][which][o] : s_sum[2][which][o];
+  }
+}
+
+template <int D>
+hipError_t launch_block(const fg_profile_args& a, hipStream_t s) {
+  hipLaunchKernelGGL((fg_profile_block_kernel<D>), dim3((unsigned)a.U), dim3(256), 0, s, static_cast<const __bf16*>(a.Q),
+                     static_cast<const __bf16*>(a.K), a.colsum, a.bandcol, a.n, a.w, a.scale * FG_LOG2E, a.G);
+  return hipGetLastError();
+}
+
 template <int D, int NW, bool LONG>
 hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s) {
   const int cols = a.n < FG_ONCE_TOKENS ? a.n : FG_ONCE_TOKENS;
@@ -454,6 +571,7 @@ hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s)
 
 hipError_t fg_launch_profile_once(const fg_profile_args& a, fg_once_form f, double* parts, hipStream_t s) {
   if ((a.n > kSlots * kFrag * f.waves && f.waves != 8) || f.parts > (a.n + kRows - 1) / kRows) return hipErrorInvalidValue;
+  if (a.n <= kRows) return a.d == 128 ? launch_block<128>(a, s) : launch_block<64>(a, s);
   if (a.n > FG_ONCE_TOKENS) return a.d == 128 ? launch<128, 8, true>(a, f.parts, parts, s) : launch<64, 8, true>(a, f.parts, parts, s);
   if (f.waves == 8) return a.d == 128 ? launch<128, 8, false>(a, f.parts, parts, s) : launch<64, 8, false>(a, f.parts, parts, s);
   return a.d == 128 ? launch<128, 4, false>(a, f.parts, parts, s) : launch<64, 4, false>(a, f.parts, parts, s);

@@ -289,6 +289,20 @@ def test_bf16_one_pass(heads, n, d, G):
         H.log_report(f"one pass U={heads} n={n} d={d} G={G} w={window}", rep)
 
 
+# Prompts of one block: a wave per tile of 32 rows and columns, the second row of tiles empty, partly filled and full;
+# one to sixteen heads after one another; windows inside, at the edge of and beyond a tile
+@pytest.mark.parametrize("heads,n,d,G", [
+    (5, 1, 64, 1), (300, 17, 128, 1), (9, 32, 128, 1), (64, 33, 128, 2), (70, 50, 64, 2), (300, 63, 128, 5), (200, 64, 128, 3), (300, 64, 64, 1), (260, 64, 128, 16), (2000, 64, 64, 1),
+])
+def test_prompts_of_one_block(heads, n, d, G):
+    for window in sorted({1, 2, 31, 32, 33, n // 2, n - 1, n} & set(range(1, n + 1))):
+        w = W["llama7b_b1"].scaled(name="one_block", layers=1, heads=heads, batch=1, prompt_len=n, steps=1, head_dim=d,
+                                   r_l=min(1.0, (window + 0.5) / n), seed=800 + n)
+        run = H.GpuRun(w, range(w.num_units), group_size=G)
+        rep = H.compare(run, check_units=sorted({0, heads // 2, heads - 1}))
+        H.log_report(f"one block U={heads} n={n} d={d} G={G} w={window}", rep)
+
+
 # The first 1024 columns of longer prompts in one pass, the triangle behind them in two sweeps that leave and take row
 # sums: triangles of one row, of a tile and of a block more or less, one and several workgroups per unit, grouped heads,
 # windows inside a block, up to the seam at column 1024 and beyond it
