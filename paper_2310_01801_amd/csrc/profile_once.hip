@@ -223,7 +223,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
           for (int i = 0; i < 16; ++i) {
             const bool ok = !diagonal || fg_acc_item(i) <= lim;
             if (MODE == 1) {   // (c > 0: the largest product gives the largest logit)
-              const float x = ok ? ac[i] : FG_NEG_BIG;
+              const float x = ok ? ac[i] : -INFINITY;
               s[i & 3] = i < 4 ? x : fmaxf(s[i & 3], x);
             } else {
               const float v = fg_exp2(fmaf(ac[i], c, -m_run[f]));
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void fg_profile_block_kernel(
       float s[4];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float x = fg_acc_item(i) <= lim ? ac[i] : FG_NEG_BIG;
+        const float x = fg_acc_item(i) <= lim ? ac[i] : -INFINITY;
         s[i & 3] = i < 4 ? x : fmaxf(s[i & 3], x);
       }
       m = fmaxf(FG_NEG_BIG, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c);
