@@ -412,9 +412,9 @@ fg_status fastgen_profile_static(const fg_config* cfg, const void* Q, const void
   hipStream_t s = static_cast<hipStream_t>(stream);
   PhaseChain tm(nullptr, s, false);
   const char* where = "";
-  // every entry that counts is written first by an earlier kernel of this call, and what is read along with
-  // them (row statistics of a tile's rows past its head's end) is selected away, so nothing left over from the
-  // previous call needs clearing
+  // every entry that the kernels use is written first by an earlier kernel of this call (of the row statistics of longer
+  // bf16 prompts only the first 64 rows of a head and those from 1024 on), so nothing left over from the previous
+  // call needs clearing
   e = launch_profile_path(*cfg, L, static_cast<char*>(base), scale_of(*cfg), window_of(*cfg), Q, K, token_class,
                           lse_opt, policy, recovery, kept_count, static_cast<char*>(base) + kStaticScratchBytes, s, tm, &where);
   if (e != hipSuccess) return sfail(FG_EHIP, "%s: %s", where, hipGetErrorString(e));

@@ -134,9 +134,10 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   u32x4 stage[LOADS];
   float2 stage_stat = make_float2(0.f, 0.f);
   // `row0` = first streamed row of the tile counted over all heads (head * ns + t * 32); a tile
-  // that runs past its head's last row reads the next head's rows (or zeros after the last
-  // head): those rows are masked wherever they are used, and their statistics, which nothing may have written, selected
-  // away. `buf` is the LDS buffer the tile is for.
+  // that runs past its head's last row reads the next head's first rows (or zeros after the last
+  // head): their exponentials are masked wherever they are used, and their statistics are numbers, written for every head (by the
+  // one pass where that takes the columns before: selecting them away in the split stream cost 2 to 7 % of short sweeps).
+  // `buf` is the LDS buffer the tile is for.
   auto gload = [&](int row0, int buf) {
     if (DMA) {
 #pragma unroll
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
               const int o = (i >> 2) * 8 + (i & 3);
               const bool ok = (dbase + o >= 0) && (o < rlim);
               const float e = fg_exp2(fmaf(acc[f][i], c, -ms[i]));   // may be huge where masked: select, do not scale
-              s = fmaf(ok ? e : 0.f, o < rlim ? il[i] : 0.f, s);
+              s = fmaf(ok ? e : 0.f, il[i], s);
             }
             col_acc[f] += (double)s;
             band_acc[f] += (double)s;
@@ -458,16 +459,12 @@ __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
     float ms[16], il[16];
     if (PASS == 2) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {   // rows past the last head's end read as zeros
+      for (int g = 0; g < 4; ++g) {   // rows past a head's end: the next head's first ones, zeros after the last head
         const int at = (h * ns + sbase + g * 8) * 8;
         const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at, 0, 0));
         const f32x4 u = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, at + 16, 0, 0));
         ms[g * 4 + 0] = v[0]; ms[g * 4 + 1] = v[2]; ms[g * 4 + 2] = u[0]; ms[g * 4 + 3] = u[2];
         il[g * 4 + 0] = v[1]; il[g * 4 + 1] = v[3]; il[g * 4 + 2] = u[1]; il[g * 4 + 3] = u[3];
-      }
-      if (t0 + kTile > n) {   // rows past this head's end: the next head's, which nothing may have written
-#pragma unroll
-        for (int i = 0; i < 16; ++i) il[i] = (i >> 2) * 8 + (i & 3) < n - sbase ? il[i] : 0.f;
       }
     }
     f32x16 acc[F];

@@ -405,7 +405,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       }
       double inv = __builtin_amdgcn_rcp(L);
       inv = fma(inv, fma(-L, inv, 1.0), inv);
-      if (LONG && wave == 0 && r0 >= COLS && r0 + lane < n) stat[r0 + lane] = make_float2(M, (float)inv);
+      // for the second sweep behind the columns held here, whose last tile of a head runs on into the next head's first rows
+      if (LONG && wave == 0 && (r0 >= COLS || r0 == 0) && r0 + lane < n) stat[r0 + lane] = make_float2(M, (float)inv);
       float f0 = r0 + lane < n ? (float)inv * share : 0.f, f1 = f0;   // rows past the end count nothing
       fg_swap_halves(f0, f1);
 #pragma unroll

@@ -635,7 +635,7 @@ def test_read_back_by_several_workgroups(heads, n):
 
 # Nothing of what the workspace held before counts, rows behind the end of a unit or of a head in a partly filled
 # tile included: a workspace of NaN patterns gives what a cleared one gives. The last six take the first 1024 columns in one
-# pass, which leaves the statistics of the first 1024 rows unwritten, and the triangle behind them in the split stream with 32
+# pass, which leaves most statistics of the first 1024 rows unwritten, and the triangle behind them in the split stream with 32
 # (two) and 64 owners, in blocks and in pairs (two).
 @pytest.mark.parametrize("U,n,d,dtype,G", [(3, 5, 64, "bf16", 1), (3, 37, 128, "f32", 1), (2, 21, 64, "bf16", 3), (2, 1100, 128, "bf16", 2),
                                            (40, 333, 128, "bf16", 1), (2, 5000, 64, "bf16", 1),
