@@ -44,11 +44,12 @@ __device__ __forceinline__ float2 fg_row_result(float m, double l, bool more) {
   return make_float2(whole, (float)(l * exp2((double)m - (double)whole)));
 }
 
+// (The arguments fill 64 bytes: one line to wait for. With one more integer a call of few units took 0.2 to 0.4 us longer.)
 template <int D, int PASS, bool PAIRED>
 __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
     double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int ns, int w, float c,
-    int nblk, int G) {
+    int G) {
   constexpr int KK = D / 16;
   constexpr int RS = Lds<D>::kRowBytes;
   constexpr int CHUNKS_PER_ROW = D / 8;                    // 16-byte chunks per item
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256, 3) void fg_profile_mfma_kernel(
   // ---- which (unit, owner block): units of one XCD walk one unit's blocks back to back
   const int idx = blockIdx.x;
   const int xcd = idx & 7, rest = idx >> 3;
-  const int npair = PAIRED ? (nblk + 1) / 2 : nblk;
+  const int nblk = (n + kOwnPerBlock - 1) / kOwnPerBlock, npair = PAIRED ? (nblk + 1) / 2 : nblk;
   const int pair_ord = rest % npair;
   const int unit = (rest / npair) * 8 + xcd;
   if (unit >= U) return;
@@ -406,12 +407,13 @@ template <int D, int PASS, int F>
 __global__ __launch_bounds__(256, 2) void fg_profile_small_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* __restrict__ rowstat,
     double* __restrict__ colsum, double* __restrict__ bandcol, int U, int n, int ns, int w, float c,
-    int nblk, int G) {
+    int G) {
   constexpr int KK = D / 16;
   __shared__ double s_a[4][F][32], s_b[4][F][32];
 
   const int idx = blockIdx.x;
   const int xcd = idx & 7, rest = idx >> 3;
+  const int nblk = (n + 32 * F - 1) / (32 * F);
   const int ord = rest % nblk;
   const int unit = (rest / nblk) * 8 + xcd;
   if (unit >= U) return;
@@ -528,10 +530,10 @@ hipError_t launch_small(const fg_profile_args& a, int pass, hipStream_t s) {
   const __bf16* K = static_cast<const __bf16*>(a.K);
   if (pass == 1)
     hipLaunchKernelGGL((fg_profile_small_kernel<D, 1, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, a.G);
   else
     hipLaunchKernelGGL((fg_profile_small_kernel<D, 2, F>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, a.G);
   return hipGetLastError();
 }
 
@@ -546,10 +548,10 @@ hipError_t launch(const fg_profile_args& a, int pass, hipStream_t s) {
   const __bf16* K = static_cast<const __bf16*>(a.K);
   if (pass == 1)
     hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 1, PAIRED>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, a.G);
   else   // (single blocks do not serve the second sweep at d = 128)
     hipLaunchKernelGGL((fg_profile_mfma_kernel<D, 2, PAIRED || D == 128>), grid, block, 0, s, Q, K, a.rowstat, a.colsum,
-                       a.bandcol, units, a.n, a.stride, a.w, c, nblk, a.G);
+                       a.bandcol, units, a.n, a.stride, a.w, c, a.G);
   return hipGetLastError();
 }
 

@@ -122,7 +122,7 @@ constexpr __device__ int fg_acc_item(int i) { return (i >> 2) * 8 + (i & 3); }
 template <int D, int NW, bool LONG>
 __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, float2* rowstat, double* __restrict__ colsum,
-    double* __restrict__ bandcol, int U, int n, int stride, int w, float c, int G, int P) {
+    double* __restrict__ bandcol, int U, int n, int w, float c, int G, int P) {   // (64 bytes of arguments, one line)
   constexpr int KK = D / 16;
   constexpr int RB = D * 2;           // bytes of a row
   constexpr int PPR = D / 8;          // 16-byte pieces of a row
@@ -442,6 +442,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
     }
   }
   __syncthreads();
+  const int stride = P > 1 ? min(n, FG_ONCE_TOKENS) : n;   // part sums are dense
   for (int i = tid; i < min(n, COLS); i += NT) {
     colsum[((size_t)part * U + unit) * stride + i] = s_sum[0][i];
     bandcol[((size_t)part * U + unit) * stride + i] = s_sum[1][i];
@@ -573,7 +574,7 @@ hipError_t launch(const fg_profile_args& a, int P, double* parts, hipStream_t s)
   double* band = P > 1 ? parts + P * N : a.bandcol;
   hipLaunchKernelGGL((fg_profile_once_kernel<D, NW, LONG>), dim3((unsigned)(8 * P * ((a.U + 7) / 8))), dim3(NW * 64), 0, s,
                      static_cast<const __bf16*>(a.Q), static_cast<const __bf16*>(a.K), a.rowstat, col, band, a.U, a.n,
-                     P > 1 ? cols : a.n, a.w, a.scale * FG_LOG2E, a.G, P);
+                     a.w, a.scale * FG_LOG2E, a.G, P);
   return hipGetLastError();
 }
 
