@@ -250,8 +250,6 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
 
   fg_select_args sa;
   sa.colsum = pa.colsum; sa.bandcol = pa.bandcol; sa.token_class = token_class;
-  sa.part_col = part_col; sa.part_band = part_band;
-  sa.parts = select_adds ? once.parts : 1;
   sa.keep = reinterpret_cast<uint8_t*>(at(L.keep)); sa.slot = reinterpret_cast<int32_t*>(at(L.slot));
   sa.policy = reinterpret_cast<int32_t*>(at(L.policy)); sa.recov = reinterpret_cast<double*>(at(L.recov));
   sa.kcount = reinterpret_cast<int32_t*>(at(L.kcount)); sa.cap = reinterpret_cast<int32_t*>(at(L.cap));
@@ -263,7 +261,7 @@ hipError_t launch_profile_path(const fg_config& c, const fg_layout& L, char* ws,
   family_of(c, sa.family);
   *where = "fastgen_profile(select)";
   tm.begin(FG_PHASE_SELECT);
-  e = fg_launch_select(sa, s);
+  e = fg_launch_select(sa, {part_col, part_band, select_adds ? once.parts : 1}, s);
   tm.end();
   return e;
 }

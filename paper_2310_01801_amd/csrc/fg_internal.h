@@ -375,10 +375,11 @@ struct fg_select_args {
   double T, r_f;
   int forced_policy;
   int family[4];  // FG_COMP_* mask of policy ids 0..3 (0 = unused id)
-  // parts > 1: both sums still lie in parts [parts, U, n]. (At the end: in front they cost the other kernels 0.4 of 7 us,
-  // whose first loads wait for one more line of arguments.)
-  const double* part_col; const double* part_band; int parts;
 };
+// Where both sums still lie in parts [parts, U, n], of the selection that adds them alone: in fg_select_args they cost the others
+// 0.2 of 7 us (in its middle 0.4), whose block size lies behind the arguments and then on one line more of them.
+struct fg_part_sums { const double* col; const double* band; int parts; };
+static_assert(sizeof(fg_select_args) + 8 + 16 <= 3 * 64, "a fourth line of arguments");
 
 struct fg_compact_args {
   const void* K; const void* V;
@@ -428,7 +429,7 @@ struct fg_classify_args {
   int32_t special[FG_MAX_CLASS_IDS], punct[FG_MAX_CLASS_IDS];
 };
 hipError_t fg_launch_classify(const fg_classify_args&, hipStream_t);
-hipError_t fg_launch_select(const fg_select_args&, hipStream_t);
+hipError_t fg_launch_select(const fg_select_args&, const fg_part_sums&, hipStream_t);   // parts = 1: the sums are whole
 hipError_t fg_launch_compact(const fg_compact_args&, hipStream_t);
 hipError_t fg_launch_offsets(const int32_t* cap, const int32_t* len, const int32_t* policy, int64_t* off,
                              int32_t* chunk_off, int32_t* item_unit, int32_t* flags, int U, int64_t pool_tokens,

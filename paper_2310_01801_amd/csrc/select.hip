@@ -11,6 +11,8 @@
 //                      units by size).
 //   fg_gather_kernel   copies the kept rows of K, V with score, position, class.
 //   fg_export_kernel   cache state read-back in ascending position order.
+#include <type_traits>
+
 #include "fg_common.h"
 #include "fg_internal.h"
 #include "fg_select.h"
@@ -32,10 +34,11 @@ __global__ __launch_bounds__(256) void fg_classify_kernel(fg_classify_args a) {
 // Latency-bound: one workgroup's chain of loads and block reductions per unit. With NC > 0 (n <= NT *
 // NC) every token's column sum, band sum and class stay in registers (token tid + NT i in slot i),
 // loaded once and all at once, and the prefix scan of the kept flags takes two barriers. Sums that several
-// workgroups of a short prompt left in parts (a.parts > 1) are added here, in order, three parts' loads in flight: a launch
+// workgroups of a short prompt left in parts are added here, in order, three parts' loads in flight: a launch
 // of their own, fg_part_sum_kernel, took 3.4 us of 32 units of 333 tokens in six parts.
-template <int NT, int NC, bool PARTS>
-__global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
+struct fg_no_parts {};
+template <int NT, int NC, class Parts>
+__global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a, Parts ps) {
   __shared__ fg_select_smem sm;
   __shared__ double part_r[NT / 64][4], sum_r[4];
   __shared__ int part_n[NT / 64][8], sum_n[8];
@@ -52,32 +55,32 @@ __global__ __launch_bounds__(NT) void fg_select_kernel(fg_select_args a) {
   uint64_t key[NR];
   double band[NR];
   int cl[NR];
-  if (REGS && PARTS) {
+  if constexpr (REGS && std::is_same<Parts, fg_part_sums>::value) {
     const size_t N = (size_t)a.U * n, at = (size_t)u * n;
     double sum[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int j = min(tid + NT * i, n - 1);
-      sum[i] = a.part_col[at + j];
-      band[i] = a.part_band[at + j];
+      sum[i] = ps.col[at + j];
+      band[i] = ps.band[at + j];
       cl[i] = cls[j];
     }
-    for (int p = 1; p < a.parts; p += 3) {
+    for (int p = 1; p < ps.parts; p += 3) {
       double s[3][NR], b[3][NR];
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-          const size_t from = min(p + q, a.parts - 1) * N + at + min(tid + NT * i, n - 1);
-          s[q][i] = a.part_col[from];
-          b[q][i] = a.part_band[from];
+          const size_t from = min(p + q, ps.parts - 1) * N + at + min(tid + NT * i, n - 1);
+          s[q][i] = ps.col[from];
+          b[q][i] = ps.band[from];
         }
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-          sum[i] = p + q < a.parts ? sum[i] + s[q][i] : sum[i];
-          band[i] = p + q < a.parts ? band[i] + b[q][i] : band[i];
+          sum[i] = p + q < ps.parts ? sum[i] + s[q][i] : sum[i];
+          band[i] = p + q < ps.parts ? band[i] + b[q][i] : band[i];
         }
     }
 #pragma unroll
@@ -563,7 +566,7 @@ hipError_t fg_launch_classify(const fg_classify_args& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t fg_launch_select(const fg_select_args& a, hipStream_t s) {
+hipError_t fg_launch_select(const fg_select_args& a, const fg_part_sums& ps, hipStream_t s) {
   // More threads shorten a unit's chain while the card has room for them: 512 of them for few units,
   // 256 where many units of few tokens are bound by the workgroups in flight (512 / 256 threads
   // before the tokens stayed in registers: 256 units of 3000 tokens 27 / 38 us, 1024 of 2048
@@ -574,26 +577,27 @@ hipError_t fg_launch_select(const fg_select_args& a, hipStream_t s) {
   // so many units take fewer slots or smaller workgroups where that is enough: 1024 x 8 / 512 x 12 slots,
   // 513 units of 4400 52 / 41, 1600 of 4400 125 / 83 (re-read 115), 1600 of 6000 139 / 91; 256 x 12 / x 10,
   // 1024 of 2100 39 / 28, 8192 of 2500 220 / 174 (re-read 213); 4096 of 3000 with twelve 134 (138).
-#define FG_SELECT(NT, NC, PARTS) hipLaunchKernelGGL((fg_select_kernel<NT, NC, PARTS>), dim3((unsigned)a.U), dim3(NT), 0, s, a)
-  if (a.parts > 1) {   // (a kernel of its own: the parts' loads take 20 registers more)
+  const fg_no_parts whole;
+#define FG_SELECT(NT, NC, P) hipLaunchKernelGGL((fg_select_kernel<NT, NC, std::decay_t<decltype(P)>>), dim3((unsigned)a.U), dim3(NT), 0, s, a, P)
+  if (ps.parts > 1) {   // (a kernel of its own: the parts' loads take 20 registers more)
     if (a.n > 1024) return hipErrorInvalidValue;
-    if (a.U <= 512) { if (a.n <= 512) FG_SELECT(512, 1, true); else FG_SELECT(512, 2, true); }
-    else if (a.n <= 512) FG_SELECT(256, 2, true);
-    else FG_SELECT(256, 4, true);
+    if (a.U <= 512) { if (a.n <= 512) FG_SELECT(512, 1, ps); else FG_SELECT(512, 2, ps); }
+    else if (a.n <= 512) FG_SELECT(256, 2, ps);
+    else FG_SELECT(256, 4, ps);
   } else if (a.U <= 512 || a.n > 3072) {
-    if (a.n <= 512) FG_SELECT(512, 1, false);
-    else if (a.n <= 1024) FG_SELECT(512, 2, false);
-    else if (a.n <= 2048) FG_SELECT(512, 4, false);
-    else if (a.n <= 4096) FG_SELECT(512, 8, false);
-    else if (a.n <= 6144 && a.U > 512) FG_SELECT(512, 12, false);
-    else if (a.n <= 8192) FG_SELECT(1024, 8, false);
-    else FG_SELECT(512, 0, false);
+    if (a.n <= 512) FG_SELECT(512, 1, whole);
+    else if (a.n <= 1024) FG_SELECT(512, 2, whole);
+    else if (a.n <= 2048) FG_SELECT(512, 4, whole);
+    else if (a.n <= 4096) FG_SELECT(512, 8, whole);
+    else if (a.n <= 6144 && a.U > 512) FG_SELECT(512, 12, whole);
+    else if (a.n <= 8192) FG_SELECT(1024, 8, whole);
+    else FG_SELECT(512, 0, whole);
   } else {
-    if (a.n <= 512) FG_SELECT(256, 2, false);
-    else if (a.n <= 1024) FG_SELECT(256, 4, false);
-    else if (a.n <= 2048) FG_SELECT(256, 8, false);
-    else if (a.n <= 2560) FG_SELECT(256, 10, false);
-    else FG_SELECT(256, 12, false);
+    if (a.n <= 512) FG_SELECT(256, 2, whole);
+    else if (a.n <= 1024) FG_SELECT(256, 4, whole);
+    else if (a.n <= 2048) FG_SELECT(256, 8, whole);
+    else if (a.n <= 2560) FG_SELECT(256, 10, whole);
+    else FG_SELECT(256, 12, whole);
   }
 #undef FG_SELECT
   return hipGetLastError();
