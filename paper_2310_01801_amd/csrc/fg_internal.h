@@ -245,6 +245,7 @@ constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
 //                        0.85x, 7 of 320 0.99x. From some 400 tiles on these would gain (5 of 894, d = 64, G = 8, 1.28x, 17 of
 //                        873, G = 12, 219 / 88): the lines for few units leave that to the two sweeps
 constexpr int FG_ONCE_TOKENS = 1024;   // columns that the one-pass kernels hold
+constexpr double FG_ROW_SUM_LESS = 1.5;   // what a row sum of the columns behind them, between 1 and 2, is handed on less by
 struct fg_once_form { int waves, parts; };
 inline fg_once_form fg_once_of(int d, int U, int n, int G) {
   if (n > 1024 || U > (1 << 22)) return {0, 1};

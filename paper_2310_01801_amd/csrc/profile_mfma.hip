@@ -36,12 +36,14 @@ struct Lds {
 };
 
 // What a row of the first sweep leaves: shift and 1 / sum; where the columns before are still to come, a whole number for the
-// shift and the sum itself (whatever their shift, bringing it there is then exact). The sum rounded to 24 bits weighs no more
-// than the normaliser, which is: with the rest carried along, no error of the column sums changed in its second digit.
+// shift and the sum itself (whatever their shift, bringing it there is then exact): between 1 and 2, less 1.5, which rounds
+// it by no more than 2^-27.
 __device__ __forceinline__ float2 fg_row_result(float m, double l, bool more) {
   if (!more) return make_float2(m, (float)(1.0 / l));
   const float whole = rintf(m);
-  return make_float2(whole, (float)(l * exp2((double)m - (double)whole)));
+  const double sum = l * exp2((double)m - (double)whole);
+  const int up = ilogb(sum);
+  return make_float2(whole + (float)up, (float)(ldexp(sum, -up) - FG_ROW_SUM_LESS));
 }
 
 // (The arguments fill 64 bytes: one line to wait for. With one more integer a call of few units took 0.2 to 0.4 us longer.)

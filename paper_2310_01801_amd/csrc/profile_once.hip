@@ -139,7 +139,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
   __shared__ __attribute__((aligned(16))) unsigned char s_k[NW][HELD][kFrag * RB];
   __shared__ double s_l[2][NW][kRows];
   __shared__ float s_m[2][NW][kRows];
-  __shared__ float2 s_x[2][LONG ? kRows : 1];   // of the columns beyond, per row: a whole number for its shift, and its sum
+  __shared__ float2 s_x[2][LONG ? kRows : 1];   // of the columns beyond, per row: a whole number for its shift, and its sum less FG_ROW_SUM_LESS
   __shared__ double s_sum[2][COLS];   // column sums, and their part inside the band
 
   // parts of one unit on one XCD (its L2 then serves the keys)
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
         fg_barrier();
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
-        if (LONG) L = fma((double)x.y, (double)fg_exp2(x.x - M), L);
+        if (LONG) L = fma((double)x.y + FG_ROW_SUM_LESS, (double)fg_exp2(x.x - M), L);
         again = __any(r0 + lane < n && !fg_fits(L));   // the same in all waves
         if (again) fg_barrier();   // s_l has been read
       }
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
           mv[i] = s_m[buf][i][lane];
           M = fmaxf(M, mv[i]);
         }
-        L = LONG ? (double)x.y * (double)fg_exp2(x.x - M) : 0.0;
+        L = LONG ? ((double)x.y + FG_ROW_SUM_LESS) * (double)fg_exp2(x.x - M) : 0.0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
         share = fg_exp2(wave_m - M);

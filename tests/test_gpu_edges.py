@@ -410,6 +410,36 @@ def test_one_pass_keeps_its_precision_where_rows_lie_apart(U, n, d, step):
     assert float(error) < (1.1e-7 if abs(step) > 10 else 2e-7)
 
 
+# The rows' sums behind column 1024 reach the one pass with more than 24 bits: 1 + 2^-24 of the columns there (in tiles of
+# their own), which 24 bits make 1 or 1 + 2^-23, and one column before them of a random weight A per unit. Column 1024 is the sum of 1 / (A + 1)
+# over 64 rows and of 1 / (A + 1 + 2^-24) over 192. What is left is the rounding of the normalisers and of their sums, 4e-8 a unit
+# at most in the root mean square and without a preference, four times that over 512 units 7e-9, and A's, whose hardware exponential counts
+# for a fifth or less (1.3e-9 and 3.0e-9 measured); sums of 24 bits are 2.8e-8 and 3.6e-8 off.
+@pytest.mark.parametrize("U,d", [(512, 64), (512, 128)])
+def test_row_sums_behind_the_one_pass_keep_their_bits(U, d):
+    n = 1280
+    gen = torch.Generator(device="cuda:0").manual_seed(d)
+    Q, K = (torch.zeros(U, n, d, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    c = float(torch.tensor(1.0 / math.sqrt(d), dtype=torch.float32) * torch.tensor(math.log2(math.e), dtype=torch.float32))
+    Q[:, :, 0] = 1.0
+    K[:, :, 0] = -300.0 / c
+    K[:, 0, 0] = (-3.0 + 2.0 * torch.rand(U, generator=gen, device="cuda:0")) / c
+    K[:, 1024, 0] = 0.0
+    K[:, 1088, 0] = -int(24.0 / c)
+    cls = torch.zeros((1, n), dtype=torch.uint8, device="cuda:0")
+    fg = binding.FastGen(binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 1.0, 0.5, forced_policy=3))
+    fg.fastgen_profile(Q, K, cls)
+    fg.fastgen_compact(K, K)
+    got = fg.fastgen_export_state()["scores"][:U * n].view(U, n)[:, 1024].cpu()
+    fg.close()
+    weight = torch.exp2(K[:, :, 0].double().cpu() * c)
+    start = weight[:, 0] + weight[:, 1024]
+    want = 64.0 / start + 192.0 / (start + weight[:, 1088])
+    error = float(((got - want) / want).mean())
+    print(f"row sums behind the one pass, U={U} d={d}: {error:.2e}")
+    assert abs(error) < 1e-8
+
+
 # A head none of whose rows fit the shifts of the rows 64 before costs no more than the maxima of its rows: each block is
 # contracted once. Going through every block twice took 1.5 times an ordinary head's time at d = 128 and 1.6 at 64, so 1.15.
 @pytest.mark.parametrize("U,n,d", [(700, 1000, 64), (1024, 1000, 128)])
