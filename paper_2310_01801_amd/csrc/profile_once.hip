@@ -43,12 +43,16 @@ namespace {
 constexpr int kFrag = 32;    // columns of a fragment
 constexpr int kRows = 64;    // query rows of a block: two fragments
 constexpr int kSlots = 4;    // fragments of a wave in one block: 128 registers
-// Sums that a row may come to under the shift of the row 64 before, whose shift would have left the square root of its
+// Sums that row `row` may come to under the shift of the row 64 before, whose shift would have left the square root of its
 // length (up to 2^6.5). An exponential's argument is rounded at its own size, beyond 16 by 2^-20 and more, which rows with a
 // shift of their own do not pay (300 units of 500 tokens, exact products, rows 24 powers of two above the ones 64 before:
-// accepted, column sums are 3.5e-7 off float64; redone, 4.2e-8).
-constexpr double kLeastSum = 0x1p-8, kMostSum = 0x1p14;
-__device__ __forceinline__ bool fg_fits(double sum) { return sum >= kLeastSum && sum <= kMostSum; }
+// accepted, column sums are 3.5e-7 off float64; redone, 4.2e-8). No argument is above its sum's power of two, and those of an even row
+// lie below it by that of its length. A block done again costs 2 us, which few units cannot hide: with 2^-8 to 2^14 for all rows,
+// products of 0 for a head's first shifts and each row's own sum for the next ones, one in three heads with favoured columns was
+// (static calls of 50 units of 435 tokens 19.9 -> 22.1 us, 81 of 1023, d = 64, 38.0 -> 41.2; of 1110 such heads none is now, and the calls take 20.0 and 38.8).
+__device__ __forceinline__ bool fg_fits(float sum, int row) { return sum >= (float)min(row + 1, 1024) * 0x1p-18f && sum <= 0x1p16f; }
+constexpr float kFirstShift = 6.f;   // of a head's first block: a sum of 2^-12 (of one product) to 2^22 fits
+constexpr float kBelowMost = 6.f;    // of the next one: no further below the largest, since a head's first rows are short
 
 // 16 bytes per lane from memory straight into LDS, to `lds` + 16 * lane. Written out, because behind the builtin the
 // compiler waits for the data at the next read of any LDS; here the waits below do, which every reader stands behind.
@@ -197,9 +201,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
       if (most > HELD) load_k(HELD, 0);
       if (most > 3 && HELD == 2) load_k(3, 1);
     }
-    // the shifts of this lane's rows, the same in all waves; at first what products of 0 would leave the block's first row
-    const float first = (float)((31 - __builtin_clz(block(mine - 1) * kRows + 1)) / 2);
-    float m_run[2] = {first, first};
+    float m_run[2] = {kFirstShift, kFirstShift};   // the shifts of this lane's rows, the same in all waves
     bool own = mine == 1;          // the next block starts with each wave's own maxima
     for (int i = mine - 1; i >= 0; --i, buf ^= 1) {
       const int b = block(i);
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += s_l[buf][i][lane];
         if (LONG) L = fma((double)x.y + FG_ROW_SUM_LESS, (double)fg_exp2(x.x - M), L);
-        again = __any(r0 + lane < n && !fg_fits(L));   // the same in all waves
+        again = __any(r0 + lane < n && !fg_fits((float)L, r0 + lane));   // the same in all waves
         if (again) fg_barrier();   // s_l has been read
       }
       if (again) {   // the shifts do not fit, or hardly will, or there are none: this wave's own
@@ -391,14 +393,18 @@ __global__ __launch_bounds__(NW * 64, 2) void fg_profile_once_kernel(
 #pragma unroll
         for (int i = 0; i < NW; ++i) L = fma(s_l[buf][i][lane], (double)fg_exp2(mv[i] - M), L);
         share = fg_exp2(wave_m - M);
-        own = mine == 1 || __any(r0 + lane < n && !fg_fits(L * (double)fg_exp2(M - given)));   // as far as this block tells
+        // as far as this block tells; a head's first block, whose shifts are no row's, tells nothing
+        own = mine == 1 || (i < mine - 1 && __any(r0 + lane < n && !fg_fits((float)(L * (double)fg_exp2(M - given)), r0 + lane)));
       }
       // The shifts of the next block: where these rows' sums would have been the square root of their length. What counts in
       // a row then lies on both sides of 0, be the row even (its terms would lie at -log2 n under the sum itself) or held
       // by few columns. (Its rows past the end stay at products of 0.)
       if (i > 0) {
         const float sum = (float)L * __builtin_amdgcn_rsqf((float)(r0 + lane + 1));
-        float ma = block(i - 1) * kRows + lane < n ? M + rintf(__builtin_amdgcn_logf(sum)) : 0.f, mb = ma;
+        float ma = M + rintf(__builtin_amdgcn_logf(sum));
+        if (i == mine - 1) ma = fmaxf(ma, fg_wave_max(ma) - kBelowMost);
+        if (block(i - 1) * kRows + lane >= n) ma = 0.f;
+        float mb = ma;
         fg_swap_halves(ma, mb);
         m_run[0] = ma;
         m_run[1] = mb;

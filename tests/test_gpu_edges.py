@@ -468,6 +468,36 @@ def test_one_pass_of_rows_that_never_fit_costs_their_maxima(U, n, d):
     assert ratio < 1.35
 
 
+# Few heads with favoured columns (about 2^13 over the others, one in 16) are contracted once as heads without any are: a block
+# done again costs 2 us of a call of 15 to 22 (1.08 to 1.14 times; without, 0.98 to 1.00).
+@pytest.mark.parametrize("U,n,d", [(50, 435, 128), (64, 700, 128), (100, 200, 128)])
+def test_one_pass_of_favoured_columns_costs_as_others(U, n, d):
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    plain = [torch.randn(U, n, d, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2)]
+    favoured = [x.clone() for x in plain]
+    size = math.sqrt(9.0 * math.sqrt(d))
+    favoured[0][:, :, 0] = size
+    favoured[1][:, :, 0] = size * (torch.arange(n, device="cuda:0") % 16 == 5)
+    cls = torch.ones((1, n), dtype=torch.uint8, device="cuda:0")
+    cfg = binding.make_config(U, 1, d, torch.bfloat16, n, 0, 0.95, 0.3, 0.3)
+    policy, kept = (torch.empty((U, k), dtype=torch.int32, device="cuda:0") for k in (1, 5))
+    recovery = torch.empty((U, 5), dtype=torch.float64, device="cuda:0")
+    times = {0: [], 1: []}
+    for _ in range(8):
+        for which, (Q, K) in enumerate((plain, favoured)):   # in turn: the clock is shared
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            start.record()
+            for _ in range(200):
+                binding.fastgen_profile_static(cfg, Q, K, cls, policy, recovery, kept)
+            end.record()
+            end.synchronize()
+            times[which].append(start.elapsed_time(end))
+    ratio = min(times[1]) / min(times[0])
+    print(f"favoured columns, U={U} n={n} d={d}: {ratio:.3f}")
+    assert ratio < 1.06
+
+
 # grouped heads, per-unit step (vector ALU for two heads and float32, matrix cores for three to eight bf16 heads) and
 # split-KV for more heads, probed steps included
 @pytest.mark.parametrize("heads,n,S,d,dtype,G", [
