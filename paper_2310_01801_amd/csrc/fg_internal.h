@@ -207,7 +207,7 @@ inline fg_sweep_form fg_sweep_form_of(int d, int pass, int U, int n, int G) {
 // Scratch of fastgen_profile_static: the profiling regions of every shape that it takes.
 constexpr size_t FG_STATIC_SCRATCH = (size_t)32 << 20;
 
-// Room for the partial sums [parts, U, n] of the one-pass kernels, two doubles each. The rules below choose within it by the
+// Room for the partial sums [parts, U, columns] of the one-pass kernels (a prompt's columns, up to 1024), two doubles each. The rules below choose within it by the
 // shape alone, and a context's workspace as well as the static scratch always hold it, so that a shape gives
 // the same bits with any cache pool and from either entry point. (Most chosen: all of it, 2048 units of 1792 tokens in two parts.)
 constexpr size_t FG_PART_SUMS = (size_t)64 << 20;
@@ -292,7 +292,8 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
 // Longer bf16 prompts: workgroups per unit that take the first 1024 columns of all rows in one pass, 0 where the two sweeps
 // serve the whole prompt. The triangle of rows and columns from 1024 on stays with the two sweeps: the first one leaves its
 // rows' sums, which join the one pass, and the second one takes the rows' normalisers from there. Two sweeps / so, in us (in
-// brackets the workgroups per unit of that run; for some the rule, fitted afterwards, picks more, 256 of 3000 one less):
+// brackets the workgroups per unit of that run; for some the rule, fitted afterwards, picks more, 256 of 3000 one less: with its parts and the
+// present kernels 1024 of 2048 1106, of 1337 497, 256 of 3000 610, 64 of 1060 43, 32 of 2048 86, d = 64, 1024 of 2048 801, 256 of 2048, G = 4, 1033):
 //   d = 128    1024 units of 2048 tokens 1330 / 1159 (1), of 1337 688 / 554 (1), 256 of 3000 666 / 617 (4), 1024 of 4096 4654 / 4090 (3),
 //              512 of 8192 8773 / 8430 (2), 64 of 1060 90 / 42 (4), 32 of 2048 130 / 85 (8), 16 of 2048 88 / 60 (16), 64 of 4096 343 / 343 (4)
 //   d = 64     1024 of 2048 868 / 811 (1), 432 of 1337 254 / 206 (1), 700 of 2048 613 / 612 (1), 32 of 3000 142 / 120 (8), 180 of 2048 201 / 200 (4)
@@ -301,9 +302,9 @@ inline fg_once_form fg_once_of(int d, int U, int n, int G) {
 // d = 64), 1 % of one of 2048; several workgroups that read a unit's keys from one L2 gain 2 to 3 % at d = 128 (1024 units of
 // 4096 in one, two, three parts: 1.10x, 1.11x, 1.14x; of 1060 1.40x, 1.31x, 1.27x). Few units of long prompts stay: their
 // sweeps spread over the card as well, and the share of the first columns falls (32 units of 4096 0.98x, 100 of 6000 0.94x, 67 of 3469 0.96x, 8 of
-// 3000 1.09x, 0.94x at d = 64, 4 of 1060, d = 64, 0.80x; 8 of 1500 1.14x, 1.07x). From 8192 tokens on, 1.03x, nothing was measured.
+// 3000 1.09x, 0.94x at d = 64, 4 of 1060, d = 64, 0.80x; 8 of 1500 1.14x, 1.07x). At 8192 tokens 1.03x; beyond, nothing was measured.
 inline int fg_once_long_parts(int d, int U, int n, int G) {
-  (void)G;   // (heads only lengthen a part)
+  (void)G;   // (heads lengthen a part; few units of many heads have not been measured and count as few)
   if (n <= FG_ONCE_TOKENS || n > 8192 || U > (1 << 22)) return 0;
   if (n > (U >= 180 ? 8192 : U >= 96 ? 5000 : U >= 12 ? 3200 : U >= 8 ? 1600 : 0)) return 0;
   long long most = (long long)(FG_PART_SUMS / ((size_t)U * FG_ONCE_TOKENS * 16));
@@ -416,7 +417,7 @@ struct fg_export_args {
 };
 
 hipError_t fg_launch_profile_bf16(const fg_profile_args&, int pass, int from, hipStream_t);
-// (several workgroups per unit leave their sums in `part_sums`: columns [parts, U, n], then band)
+// (several workgroups per unit leave their sums in `part_sums`: of the columns [parts, U, n or 1024], then of the band)
 hipError_t fg_launch_profile_once(const fg_profile_args&, fg_once_form, double* part_sums, hipStream_t);
 // sums over [parts, U, cols] in order, of two arrays, into [U, stride]
 hipError_t fg_launch_part_sums(const double* pcol, const double* pband, double* col, double* band, int U, int cols, int stride, int parts, hipStream_t);

@@ -5,13 +5,14 @@
 // the blocks of each, dealt from the heavy end. The waves hold the whole block's exponentials in registers: the
 // causal columns are dealt out in fragments of 32, fragment j to wave j mod NW, at most four per wave, so
 // 4 * 32 * NW columns are the longest prompt. A value 2^(c q.k - m) is made once, with a shift m of its row that all
-// waves share: from what the sum of the row 64 before came to, a whole number. No maximum is looked for, so a
+// waves share: from what the sum of the row 64 before came to, a whole number (fg_fits and below). No maximum is looked for, so a
 // fragment's exponentials start with its last matrix instruction; whether the shift fits shows in the row's sum, and a
 // block where one does not is done again with each wave's own maximum as its shift. The next block then starts with its own
 // maxima if the shifts from before would not have fitted here either, and so does a workgroup's only block, which has
 // none before it. The waves exchange the sums of the 64 rows through LDS, and the column sums take
-// value / sum from the registers. One contraction and one exponential per score instead of two, and no row statistics
-// in memory. Workgroups that share a unit leave partial column sums, which are added in order.
+// value / sum from the registers. One contraction and one exponential per score instead of two. Of the row statistics only
+// those of longer prompts pass through memory: the sums of the columns behind the ones held here come from there, and the normalisers of
+// the rows behind them and of a head's first 64 go back (for the second sweep over those columns). Workgroups that share a unit leave partial column sums, which are added in order.
 //
 // The row index is the lane index (Q is the B operand of v_mfma_f32_32x32x16_bf16), so row sums are
 // private to a lane; the column sums cross the lanes once per block, after the block's two row fragments have been
@@ -23,12 +24,13 @@
 // Bound: two waves per SIMD in step. Per piece of 64 x 32 and wave, cycles, 16384 units of 1024 tokens, d = 128: 1010 of
 // matrix instructions (512 alone), 885 of exponentials, 780 of column sums, and per block 680 for the exchange and 1500 at
 // its barrier, where waves with a fragment less wait. 4096 units of 1024 tokens, d = 128, 1270 us with running maxima
-// and all keys through LDS, 1154 now (two sweeps 1586); of 512 385 -> 346, of 500, d = 64, 291 -> 254, 1024 of 1000, d =
-// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. Heads whose rows never fit (60 powers of two up or down every 40 rows), with
-// running maxima / so: 1024 of 1000 322 / 339, d = 64, 700 of 1000 191 / 207 (each block twice: 443 and 266), 256 of 2048 354 / 325. Error of the column sums against float64, with
-// running maxima / so: 512 units of 1000 tokens 1.28e-8 / 1.19e-8, with queries three times as large 8.16e-8 / 8.15e-8, a tenth
-// 8.0e-9 / 6.4e-9; rows 6 to 24 powers of two apart and 1000 units of 512 in d = 64 alike. (With the row sum itself for a shift 1.10, 1.01 and 1.19 times the
-// first; a third float64 step in the column sums, 1 to 3 % of the time, makes up for the rest.) Tried without gain: all keys in registers with 32
+// and all keys through LDS, 1154 with the row sums themselves for shifts (two sweeps 1586); of 512 385 -> 346, of 500, d = 64, 291 -> 254, 1024 of 1000, d =
+// 64, 274 -> 241, 256 of 700, G = 4, 183 -> 157. The present shifts and a third float64 step take 1 to 3 % more than those (in turn, 1101 -> 1128,
+// 308 -> 315, 229 -> 237, 217 -> 223, 137 -> 139). Heads whose rows never fit (60 powers of two up or down every 40 rows), with
+// running maxima / so: 1024 of 1000 322 / 339, d = 64, 700 of 1000 191 / 207 (each block twice: 443 and 266), 256 of 2048 354 / 325. Relative error of a column sum against
+// float64, running maxima / row sums for shifts / so: 512 units of 1000 tokens 1.85e-8 / 2.63e-8 / 1.92e-8, with queries a tenth as large 1.05e-8 / 1.97e-8 /
+// 1.15e-8, three times 1.55e-7 / 1.59e-7 / 1.56e-7, 1000 of 512 in d = 64 2.01e-8 / 2.82e-8 / 1.96e-8, 50 of 435 2.42e-8 / 2.51e-8 / 2.31e-8; two
+// float64 steps 2.03e-8, 1.34e-8, 1.56e-7, 2.15e-8, 2.47e-8. Tried without gain: all keys in registers with 32
 // rows a block (1325) or 16 and the exchange under the next rows' products (1810), higher priority for half of the
 // waves or for the matrix instructions (1115 to 1186 where 1114 without), keys for the registers straight from memory
 // (1204 where 1154, and short prompts 0.6 us more), the first two fragments one by one in a first block (8 spills), the

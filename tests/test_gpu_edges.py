@@ -274,7 +274,7 @@ def test_matrix_core_group_scores_with_moving_shifts(d, G, forced, slope):
 # Both bf16 sweeps in one pass: fragments of 32 columns, blocks of 64 rows, four and eight waves, prompt lengths
 # around each and around a wave's next fragment (128, 256), windows whose edge falls in the first, the second or both
 # row fragments of a block; one and several workgroups per unit, even and odd numbers of blocks for them; grouped
-# heads walk the columns on in the other direction
+# heads go through the columns anew one after the other
 @pytest.mark.parametrize("heads,n,d,G", [
     (64, 1, 128, 1), (1, 31, 128, 1), (128, 33, 64, 1), (4, 63, 128, 1), (64, 65, 128, 1), (192, 97, 128, 2), (64, 129, 128, 1),
     (192, 130, 64, 3), (300, 257, 64, 1), (300, 385, 128, 1), (300, 511, 128, 2), (513, 512, 64, 1), (64, 513, 128, 1), (192, 700, 64, 2),
@@ -358,7 +358,7 @@ def test_one_pass_with_huge_logits(n, at):
 # one, in the first and later blocks, in whole blocks, single rows and the last row, with one and several workgroups per
 # unit and with heads after one another. All keys share the offset, so the probabilities keep the size of a plain
 # prompt's; a dot product of up to 600 over eight rounded steps in float32 is good to 8 x 2^-24 x 600 / sqrt(d), so the masses to
-# 3.6e-5 (d = 64).
+# 3.6e-5 (d = 64). So these are of the ways that a block can take; what they cost in precision is tested with exact products below.
 @pytest.mark.parametrize("U,n,d,G", [(2, 1, 128, 1), (300, 64, 128, 1), (300, 130, 64, 1), (256, 1200, 128, 1), (16, 1100, 64, 2), (20, 333, 128, 1), (300, 700, 128, 1), (64, 1000, 64, 1), (200, 500, 64, 2)])
 @pytest.mark.parametrize("rows", ["high", "low", "alternate", "single", "last"])
 def test_one_pass_with_rows_far_from_the_ones_before(U, n, d, G, rows):
